@@ -1,0 +1,403 @@
+"""Workloads of the rotation-convolution library, as a training or serving program issues them.
+
+A case is one layer call (or a few that belong together) through `paper_2512_08888_amd.binding`, or one whole
+training step of the UNet-shaped stack through `paper_2512_08888_amd.unet`.  Kinds of layer calls:
+
+  infer      rotconv_pool_fwd: pooled responses and arg-max
+  plain      rotconv_fwd: every orientation's response (R = 1: an ordinary convolution)
+  backward   rotconv_pool_bwd_weight and rotconv_pool_bwd_data on a stored arg-max map
+  step       infer, then backward on the arg-max map stored with the state (a layer's share of a training step)
+  first      step without the input gradient (a network's first layer: the image needs none)
+
+Layers carry the fused ReLU of the stacks where they pool (arg-max 255 marks a dead element), activations are
+post-ReLU (half of them zero), weights He-normal, images uniform in [0, 1).
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_2512_08888_amd import binding as rc
+from paper_2512_08888_amd import unet
+
+_DT = {"f32": torch.float32, "bf16": torch.bfloat16}
+
+
+def _layer(kind, N, Cin, Cout, H, W, R=4, mode="exact90", G=0, k=3, stride=1, pad=1, dtype="f32"):
+    return dict(kind=kind, N=N, Cin=Cin, Cout=Cout, H=H, W=W, R=R, mode=mode, G=G, k=k, stride=stride, pad=pad,
+                dtype=dtype)
+
+
+def listed():
+    return [
+        # the smallest layer anybody runs: one RGB tile, eight filters; launches and latency count
+        dict(_layer("step", 1, 3, 8, 64, 64), name="tiny_rgb_step_f32"),
+        # an image network's first layer at full resolution (no input gradient)
+        dict(_layer("first", 2, 3, 64, 512, 512), name="first_layer_f32"),
+        # the benchmark layer, 64 -> 64 channels at 256 x 256, four quarter turns: forward and backward apart
+        dict(_layer("infer", 8, 64, 64, 256, 256), name="r4_256_infer_f32"),
+        dict(_layer("backward", 8, 64, 64, 256, 256), name="r4_256_backward_f32"),
+        # a UNet bottleneck layer: small map, deep channels
+        dict(_layer("step", 4, 512, 512, 32, 32), name="r4_deep_step_f32"),
+        # the sixteen-orientation layer of the benchmark (22.5 degree steps, bilinear resampling)
+        dict(_layer("step", 4, 128, 128, 128, 128, R=16, mode="bilinear"), name="r16_128_step_f32"),
+        # a steerable layer on a cropped image: odd rows, ragged channels, pooled over each four quarter turns
+        dict(_layer("step", 3, 40, 24, 101, 75, R=8, mode="steerable", G=4), name="ragged_steer_step_f32"),
+        # an ordinary convolution on a small deep map (single-orientation sweep), forward only: serving
+        dict(_layer("plain", 1, 512, 128, 16, 16, R=1), name="plain_16_f32"),
+        # a filter size outside the 3 x 3 kernels
+        dict(_layer("step", 2, 32, 32, 96, 96, k=5, pad=2), name="k5_step_f32"),
+        # mixed precision: the benchmark layer and a deep sixteen-orientation layer in bfloat16
+        dict(_layer("step", 8, 64, 64, 256, 256, dtype="bf16"), name="r4_256_step_bf16"),
+        dict(_layer("step", 2, 256, 256, 64, 64, R=16, mode="bilinear", dtype="bf16"), name="r16_deep_step_bf16"),
+        # a whole training step of the stack (encoder, bottleneck, decoder, head, loss)
+        dict(kind="unet", N=2, Cin=3, H=128, W=128, w0=64, depth=2, classes=6, R=4, mode="exact90", dtype="f32",
+             name="unet_step_f32"),
+    ]
+
+
+_CAP = 1.25e11          # flop of the largest listed case: 2 passes over 64 -> 64 at 256 x 256, batch 8, in three calls
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    while True:
+        what = rng.choice(["r4", "r4", "r4", "r16", "r16", "bf16", "bf16", "steer", "plain", "first", "other", "unet"])
+        if what == "unet":
+            c = dict(kind="unet", N=rng.randint(1, 3), Cin=3, H=16 * rng.randint(4, 12), W=16 * rng.randint(4, 12),
+                     w0=rng.choice([32, 48, 64]), depth=rng.randint(1, 3), classes=rng.randint(2, 8), R=4,
+                     mode="exact90", dtype="f32")
+        else:
+            kind = rng.choice(["infer", "backward", "step", "step"])
+            N, H, W = rng.randint(1, 8), _log(rng, 12, 300), _log(rng, 12, 300)
+            if rng.random() < 0.6:        # images and their halvings; otherwise any width
+                W = max(16, W // 16 * 16)
+            Ci, Co = _log(rng, 12, 600), _log(rng, 12, 600)
+            if rng.random() < 0.5:
+                Ci, Co = max(16, Ci // 16 * 16), max(16, Co // 16 * 16)
+            c = _layer(kind, N, Ci, Co, H, W)
+            if what == "r16":
+                c.update(R=rng.choice([8, 16]), mode="bilinear")
+            elif what == "bf16":
+                c.update(dtype="bf16", **rng.choice([dict(), dict(R=16, mode="bilinear")]))
+            elif what == "steer":
+                c.update(R=8, mode="steerable", G=rng.choice([0, 4]))
+            elif what == "plain":
+                c.update(kind="plain", R=1, N=rng.randint(1, 4))
+            elif what == "first":
+                c.update(kind="first", Cin=rng.randint(1, 4), dtype=rng.choice(["f32", "f32", "bf16"]))
+            elif what == "other":
+                k = rng.choice([2, 5, 7])
+                c.update(k=k, pad=k // 2, stride=rng.choice([1, 1, 2]), N=rng.randint(1, 2), H=max(16, H // 2),
+                         W=max(16, W // 2), Cin=min(Ci, 64), Cout=min(Co, 64))
+        cap = _CAP if what not in ("other", "steer") else _CAP / 20      # the general kernels run at a lower rate
+        if what != "unet" or c["H"] % 2 ** c["depth"] == 0 and c["W"] % 2 ** c["depth"] == 0:
+            if work(c)["flops"] <= cap:
+                return c
+
+
+# ---- a layer's shapes ---------------------------------------------------------------------------------------
+
+def _out_hw(c):
+    return ((c["H"] + 2 * c["pad"] - c["k"]) // c["stride"] + 1, (c["W"] + 2 * c["pad"] - c["k"]) // c["stride"] + 1)
+
+
+def _banks(c):
+    return 2 if c["mode"] == "steerable" else 1
+
+
+def _group(c):
+    return c["G"] or c["R"]
+
+
+def _unet_config(c):
+    return unet.UNetConfig("case", c["N"], c["Cin"], c["H"], c["W"], tuple(c["w0"] << i for i in range(c["depth"] + 1)),
+                           c["classes"], R=c["R"], mode=c["mode"])
+
+
+def _relu(c):
+    return c["kind"] != "plain"
+
+
+def _inputs(c, seed):
+    """The layer's tensors in 32 bits, drawn on the GPU, rounded to the storage type."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    Ho, Wo = _out_hw(c)
+    ng = c["R"] // _group(c)
+    t = _DT[c["dtype"]]
+
+    def normal(*shape):
+        return torch.randn(shape, generator=g, device="cuda")
+
+    xs = (c["N"], c["Cin"], c["H"], c["W"])
+    x = torch.rand(xs, generator=g, device="cuda") if c["Cin"] <= 4 else normal(*xs).clamp_(min=0)
+    w = normal(_banks(c), c["Cout"], c["Cin"], c["k"], c["k"]) * math.sqrt(2.0 / (c["Cin"] * c["k"] ** 2))
+    out = dict(x=x.to(t), w=w.to(t))
+    if c["kind"] in ("backward", "step", "first"):
+        ys = (c["N"], c["Cout"] * ng, Ho, Wo)
+        out["g"] = (normal(*ys) * 0.05).to(t)
+        # the winners of an earlier forward: any member of the channel's pool group, half of the elements dead
+        member = torch.randint(0, _group(c), ys, generator=g, device="cuda", dtype=torch.int32) * ng
+        member += (torch.arange(ys[1], device="cuda", dtype=torch.int32) % ng).view(1, -1, 1, 1)
+        dead = torch.rand(ys, generator=g, device="cuda") < 0.5
+        out["idx"] = member.masked_fill_(dead, 255).to(torch.uint8)
+    return out
+
+
+def _unet_inputs(c, seed):
+    cfg = _unet_config(c)
+    r = np.random.default_rng(seed)
+    params = {}
+    for n, s in sorted(unet.param_shapes(cfg).items()):
+        fan = s[1] if n == "head" else s[0] if n.startswith("up") else s[2] * 9
+        params[n] = (r.standard_normal(s) * math.sqrt(2.0 / fan)).astype(np.float32)
+    images = r.random((c["N"], c["Cin"], c["H"], c["W"]), dtype=np.float32)
+    labels = r.integers(0, c["classes"], (c["N"], c["H"], c["W"])).astype(np.int32)
+    return cfg, params, images, labels
+
+
+# ---- what a program keeps, and one pass ---------------------------------------------------------------------
+
+def prepare(case, seed):
+    c = case
+    if c["kind"] == "unet":
+        cfg, params, images, labels = _unet_inputs(c, seed)
+        net = unet.UNet(cfg, params, dtype=c["dtype"])
+        net.load_batch(images, labels)
+        return dict(net=net)
+    s = _inputs(c, seed)
+    p = rc.Plan(c["N"], c["Cin"], c["H"], c["W"], c["Cout"], k=c["k"], R=c["R"], mode=c["mode"], stride=c["stride"],
+                pad=c["pad"], pool_group=c["G"], dtype=rc.BF16 if c["dtype"] == "bf16" else rc.F32, relu=_relu(c))
+    p.workspace()
+    t = _DT[c["dtype"]]
+    s.update(kind=c["kind"], plan=p)
+    if c["kind"] in ("infer", "step", "first"):
+        s["y"] = torch.empty((c["N"], p.Cpooled, p.Ho, p.Wo), dtype=t, device="cuda")
+        s["won"] = torch.empty((c["N"], p.Cpooled, p.Ho, p.Wo), dtype=torch.uint8, device="cuda")
+    if c["kind"] == "plain":
+        s["y"] = torch.empty((c["N"], p.Cunpooled, p.Ho, p.Wo), dtype=t, device="cuda")
+    if c["kind"] in ("backward", "step", "first"):
+        s["dw"] = torch.empty(s["w"].shape, dtype=torch.float32, device="cuda")
+        if c["kind"] != "first":
+            s["dx"] = torch.empty_like(s["x"])
+    return s
+
+
+def run(state):
+    s = state
+    if "net" in s:
+        loss = s["net"].step()
+        return dict(loss=loss, logits=s["net"].act["head"]["y"], **{"d_" + n: t for n, t in s["net"].grads.items()})
+    p, kind = s["plan"], s["kind"]
+    if kind == "plain":
+        rc.rotconv_fwd(p, s["x"], s["w"], s["y"])
+    if kind in ("infer", "step", "first"):
+        rc.rotconv_pool_fwd(p, s["x"], s["w"], s["y"], s["won"])
+    if kind in ("backward", "step", "first"):
+        rc.rotconv_pool_bwd_weight(p, s["x"], s["g"], s["idx"], s["dw"])
+    if kind in ("backward", "step"):
+        rc.rotconv_pool_bwd_data(p, s["g"], s["idx"], s["w"], s["dx"])
+    return {n: s[n] for n in ("y", "won", "dw", "dx") if n in s}
+
+
+# ---- what a pass cannot do without --------------------------------------------------------------------------
+
+def _layer_work(kind, N, Cin, Cout, H, W, Ho, Wo, k, R, ng, B, es):
+    """One contraction of the base bank(s) per call and one addition per (tap, orientation, output) or its adjoint:
+    quarter turns and interpolated angles are linear in the base taps.  The idx map is one byte per pooled value."""
+    P = N * Ho * Wo
+    conv = 2.0 * P * Cin * Cout * k * k * B
+    place = 1.0 * P * Cout * k * k * R
+    x, w = N * Cin * H * W * es, B * Cout * Cin * k * k * es
+    y = P * Cout * ng * es + P * Cout * ng
+    out = [0.0, 0.0]
+
+    def add(flops, nbytes):
+        out[0] += flops
+        out[1] += nbytes
+
+    if kind == "plain":
+        add(conv * (R if R > 4 else 1) + place, x + w + P * Cout * R * es)
+    if kind in ("infer", "step", "first"):
+        add(conv + place, x + w + y)
+    if kind in ("backward", "step", "first"):
+        add(conv + 1.0 * P * Cout * ng * k * k, x + y + B * Cout * Cin * k * k * 4)
+    if kind in ("backward", "step"):
+        add(conv + 1.0 * P * Cout * ng * k * k, y + w + x)
+    return out
+
+
+def work(case):
+    c = case
+    es = 2 if c["dtype"] == "bf16" else 4
+    if c["kind"] != "unet":
+        Ho, Wo = _out_hw(c)
+        f, b = _layer_work(c["kind"], c["N"], c["Cin"], c["Cout"], c["H"], c["W"], Ho, Wo, c["k"], c["R"],
+                           c["R"] // _group(c), _banks(c), es)
+        return {"bytes": b, "flops": f}
+    f = b = 0.0
+    cfg = _unet_config(c)
+    for i, (_, ci, co, h, w) in enumerate(unet.rot_layers(cfg)):
+        df, db = _layer_work("first" if i == 0 else "step", c["N"], ci, co, h, w, h, w, 3, c["R"], 1, 1, es)
+        f, b = f + df, b + db
+    for lvl in range(cfg.depth):
+        h, w, co, ci = c["H"] >> (lvl + 1), c["W"] >> (lvl + 1), cfg.widths[lvl], cfg.widths[lvl + 1]
+        P = c["N"] * h * w
+        f += 3 * 2.0 * P * ci * co * 4                                   # transposed convolution, three passes
+        b += 3.0 * es * (P * ci + 4 * P * co) + 2 * es * 10 * P * co      # ... and pooling, concatenation, both ways
+    P = c["N"] * c["H"] * c["W"]
+    f += 3 * 2.0 * P * cfg.widths[0] * c["classes"]
+    b += 3.0 * es * P * (cfg.widths[0] + c["classes"])
+    return {"bytes": b, "flops": f}
+
+
+def tolerance(case):
+    c = case
+    if c["kind"] == "unet":
+        # the arg-max routing is discontinuous: a few decisions per million turn with the order of a sum
+        return {"rel": 1e-2, "max": 0.5, "differ": 1e-3}
+    if c["dtype"] == "bf16":
+        return {"rel": 1e-2, "max": 0.2, "differ": 1e-4}
+    return {"rel": 1e-5, "max": 1e-4, "differ": 1e-4}
+
+
+# ---- the same in 64 bits ------------------------------------------------------------------------------------
+
+def _expansion(c):
+    """E [R][k*k][B][k*k] in 64 bits: bank r's tap t = sum over (b, u) of E[r, t, b, u] w[b, ..., u]."""
+    k, R, B = c["k"], c["R"], _banks(c)
+    kk, mid = k * k, 0.5 * (k - 1)
+    E = np.zeros((R, kk, B, kk))
+    for r in range(R):
+        theta = 360.0 * r / R
+        s, phi = int(theta // 90), math.radians(theta % 90)
+        F = np.zeros((B, kk, k, k))                       # the filter that each base tap alone turns into
+        for b in range(B):
+            for u in range(kk):
+                base = np.zeros((k, k))
+                base[u // k, u % k] = 1.0
+                if c["mode"] == "steerable":
+                    f = base * (math.sin(phi) if b == 0 else math.cos(phi))
+                elif phi == 0.0:
+                    f = base
+                else:
+                    f = np.zeros((k, k))
+                    for i in range(k):
+                        for j in range(k):
+                            xx, yy = j - mid, mid - i
+                            row = mid - (-math.sin(phi) * xx + math.cos(phi) * yy)
+                            col = mid + (math.cos(phi) * xx + math.sin(phi) * yy)
+                            for a in (math.floor(row), math.floor(row) + 1):
+                                for d in (math.floor(col), math.floor(col) + 1):
+                                    if 0 <= a < k and 0 <= d < k:
+                                        f[i, j] += (1 - abs(row - a)) * (1 - abs(col - d)) * base[a, d]
+                F[b, u] = np.rot90(f, s)
+        E[r] = F.reshape(B, kk, kk).transpose(2, 0, 1)
+    return torch.from_numpy(E).cuda()
+
+
+def _shifted(xp, t, c, Ho, Wo):
+    """Input values that tap t of every output pixel meets: [N, Cin, Ho * Wo] out of the zero-padded input."""
+    k, st = c["k"], c["stride"]
+    i, j = t // k, t % k
+    v = xp[:, :, i:i + st * (Ho - 1) + 1:st, j:j + st * (Wo - 1) + 1:st]
+    return v.reshape(xp.shape[0], xp.shape[1], -1)
+
+
+def _conv64(xp, w, c, Ho, Wo):
+    """w [Cout, Cin, k*k] on the padded input: [N, Cout, Ho, Wo]."""
+    y = 0
+    for t in range(c["k"] ** 2):
+        y = y + torch.matmul(w[:, :, t].contiguous(), _shifted(xp, t, c, Ho, Wo))
+    return y.view(xp.shape[0], w.shape[0], Ho, Wo)
+
+
+def _exact_layer(c, seed):
+    s = _inputs(c, seed)
+    Ho, Wo = _out_hw(c)
+    kk, R, ng, B, pad = c["k"] ** 2, c["R"], c["R"] // _group(c), _banks(c), c["pad"]
+    E = _expansion(c)
+    x = s["x"].double()
+    w = s["w"].double().view(B, c["Cout"], c["Cin"], kk)
+    bank = torch.matmul(w.permute(1, 2, 0, 3).reshape(c["Cout"] * c["Cin"], B * kk), E.view(R * kk, B * kk).t().contiguous())
+    bank = bank.view(c["Cout"], c["Cin"], R, kk)
+    if c["dtype"] == "bf16":
+        bank = bank.float().bfloat16().double()
+    xp = torch.nn.functional.pad(x, (pad, pad, pad, pad))
+    out = {}
+    if c["kind"] == "plain":
+        y = torch.stack([_conv64(xp, bank[:, :, r], c, Ho, Wo) for r in range(R)], 2)
+        out["y"] = y.view(c["N"], c["Cout"] * R, Ho, Wo)
+    if c["kind"] in ("infer", "step", "first"):
+        groups = []
+        for g in range(ng):
+            best = None
+            for r in range(g, R, ng):
+                y = _conv64(xp, bank[:, :, r], c, Ho, Wo)
+                best = y if best is None else torch.maximum(best, y)
+            groups.append(best)
+        out["y"] = torch.stack(groups, 2).view(c["N"], c["Cout"] * ng, Ho, Wo).clamp_(min=0)
+        out["won"] = None
+    if c["kind"] in ("backward", "step", "first"):
+        up = s["g"].double().view(c["N"], c["Cout"], ng, Ho * Wo)
+        idx = s["idx"].view(c["N"], c["Cout"], ng, Ho * Wo)
+        dbank = torch.zeros(c["Cout"], c["Cin"], R, kk, dtype=torch.float64, device="cuda")
+        dxp = torch.zeros_like(xp) if c["kind"] != "first" else None
+        st, k = c["stride"], c["k"]
+        for r in range(R):
+            d = torch.where(idx[:, :, r % ng] == r, up[:, :, r % ng], torch.zeros((), dtype=torch.float64, device="cuda"))
+            for t in range(kk):
+                i, j = t // k, t % k
+                for n in range(c["N"]):
+                    dbank[:, :, r, t] += torch.matmul(d[n], _shifted(xp[n:n + 1], t, c, Ho, Wo)[0].t().contiguous())
+                if dxp is not None:
+                    v = torch.matmul(bank[:, :, r, t].t().contiguous(), d).view(c["N"], c["Cin"], Ho, Wo)
+                    dxp[:, :, i:i + st * (Ho - 1) + 1:st, j:j + st * (Wo - 1) + 1:st] += v
+        dw = torch.matmul(dbank.view(c["Cout"] * c["Cin"], R * kk), E.view(R * kk, B * kk))
+        out["dw"] = dw.view(c["Cout"], c["Cin"], B, kk).permute(2, 0, 1, 3).reshape(s["w"].shape)
+        if dxp is not None:
+            out["dx"] = dxp[:, :, pad:pad + c["H"], pad:pad + c["W"]].contiguous()
+    return out
+
+
+def _exact_unet(c, seed):
+    """Loss and logits of the stack; its gradients follow arg-max decisions that a rounding can turn."""
+    cfg, params, images, labels = _unet_inputs(c, seed)
+    P = {n: torch.from_numpy(v).double().cuda() for n, v in params.items()}
+    one = dict(c, k=3, stride=1, pad=1, G=0)
+    E = _expansion(one)
+
+    def rot(name, x):
+        w = P[name][0]
+        bank = torch.matmul(w.reshape(-1, 9), E.view(c["R"] * 9, 9).t().contiguous()).view(w.shape[0], w.shape[1], c["R"], 9)
+        xp = torch.nn.functional.pad(x, (1, 1, 1, 1))
+        best = _conv64(xp, bank[:, :, 0], one, x.shape[2], x.shape[3])
+        for r in range(1, c["R"]):
+            best = torch.maximum(best, _conv64(xp, bank[:, :, r], one, x.shape[2], x.shape[3]))
+        return best.clamp_(min=0)
+
+    x, skips = torch.from_numpy(images).double().cuda(), []
+    for lvl in range(cfg.depth):
+        x = rot(f"enc{lvl}b", rot(f"enc{lvl}a", x))
+        skips.append(x)
+        n, ch, h, w = x.shape
+        x = x.view(n, ch, h // 2, 2, w // 2, 2).amax((3, 5))
+    x = rot("botb", rot("bota", x))
+    for lvl in reversed(range(cfg.depth)):
+        u = P[f"up{lvl}"]
+        n, ci, h, w = x.shape
+        up = torch.matmul(u.reshape(ci, -1).t().contiguous(), x.reshape(n, ci, h * w)).view(n, u.shape[1], 2, 2, h, w)
+        up = up.permute(0, 1, 4, 2, 5, 3).reshape(n, u.shape[1], 2 * h, 2 * w)
+        x = rot(f"dec{lvl}b", rot(f"dec{lvl}a", torch.cat([skips[lvl], up], 1)))
+    n, ch, h, w = x.shape
+    logits = torch.matmul(P["head"], x.reshape(n, ch, h * w))
+    want = torch.from_numpy(labels).long().cuda().view(n, 1, h * w)
+    loss = (torch.logsumexp(logits, 1) - logits.gather(1, want)[:, 0]).mean().view(1)
+    return dict(loss=loss, logits=logits.view(n, -1, h, w), **{"d_" + name: None for name in P})
+
+
+def exact(case, seed):
+    return _exact_unet(case, seed) if case["kind"] == "unet" else _exact_layer(case, seed)
