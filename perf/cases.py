@@ -257,11 +257,14 @@ def work(case):
 def tolerance(case):
     c = case
     if c["kind"] == "unet":
-        # the arg-max routing is discontinuous: a few decisions per million turn with the order of a sum
-        return {"rel": 1e-2, "max": 0.5, "differ": 1e-3}
+        # gradients follow arg-max decisions, a few per million of which turn with the order of a sum: images moved by
+        # 1.5e-7 move the gradients by 3e-5 in norm and 6e-4 at the most
+        return {"rel": 3e-4, "max": 1e-2, "differ": 1e-4}
     if c["dtype"] == "bf16":
-        return {"rel": 1e-2, "max": 0.2, "differ": 1e-4}
-    return {"rel": 1e-5, "max": 1e-4, "differ": 1e-4}
+        # results and the summed routed gradients are rounded to eight bits: 2.5e-3 off in norm
+        return {"rel": 1e-2, "max": 0.1, "differ": 1e-4}
+    # 1e-7 to 5e-7 off 64-bit sums in norm; about 1e-7 of the arg-max map turns (one element of a small map)
+    return {"rel": 4e-6, "max": 4e-5, "differ": 1e-4}
 
 
 # ---- the same in 64 bits ------------------------------------------------------------------------------------
