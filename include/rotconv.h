@@ -50,6 +50,9 @@
  *   - `ws` is a DEVICE scratch buffer of at least rotconv_workspace_bytes(plan)
  *     bytes, 256-byte aligned; its contents are undefined between calls, and
  *     two calls sharing one ws must not overlap in time.
+ *   - NaN and infinite inputs: every pooled value they reach is non-finite (an
+ *     infinity may come out as NaN: fp32 products are formed from the operands'
+ *     parts), and NaN passes the fused ReLU.  idx is then some orientation.
  *   - Return value: a rotconv_status.  Argument errors are found on the host
  *     before anything is launched and leave the outputs untouched.
  */

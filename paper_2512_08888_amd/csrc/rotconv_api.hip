@@ -89,26 +89,40 @@ size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
 bool aligned(const void* p, size_t a) { return reinterpret_cast<uintptr_t>(p) % a == 0; }
 
-// Bytes reserved for the packed banks of the fast forward (the larger of the fp32 and, for bf16 plans, the bf16 image).
+// Bytes reserved for the packed banks of the fast forward: the larger of the fp32 kernels' image and, for bf16 plans, the
+// bf16 kernel's.
 size_t fwd_pack_region(const rotconv_plan* p) {
   size_t b = p4_fwd_pack_floats(p) * sizeof(float);
   if (p->d.dtype == ROTCONV_BF16) b = std::max(b, p4_fwd_bf16_pack_bytes(p));
   return align256(b);
 }
 
-// Scratch of the fast forward: packed banks, then per-bank candidates or the unpooled map.
-size_t fwd_fast_ws_bytes(const rotconv_plan* p) {
-  const size_t pack = fwd_pack_region(p);
+// Scratch of the fast forward beside the packed banks: per-bank candidates or the unpooled map.
+size_t fwd_extra_bytes(const rotconv_plan* p) {
   const size_t hw = (size_t)p->d.H * p->d.W;
   const int mode = p4_fwd_pool_mode(p);
-  size_t extra = 0;
-  if (mode == kOutPartial) extra = align256((size_t)p->host.Q * p->d.N * p->d.Cout * hw * 4) +
-                                   align256((size_t)p->host.Q * p->d.N * p->d.Cout * hw);
-  if (mode == kOutUnpooled) extra = align256((size_t)p->d.N * p->d.Cout * p->d.R * hw * 4);
-  // channel split: one unpooled part per split
+  if (mode == kOutPartial) return align256((size_t)p->host.Q * p->d.N * p->d.Cout * hw * 4) +
+                                  align256((size_t)p->host.Q * p->d.N * p->d.Cout * hw);
+  if (mode == kOutUnpooled) return align256((size_t)p->d.N * p->d.Cout * p->d.R * hw * 4);
+  return 0;
+}
+
+// One unpooled part per channel split.
+size_t fwd_part_bytes(const rotconv_plan* p, int cs) {
+  return cs > 1 ? align256((size_t)cs * p->d.N * p->d.Cout * p->d.R * p->d.H * p->d.W * 4) : 0;
+}
+
+size_t fwd_fast_ws_bytes(const rotconv_plan* p) {
   const int cs = std::max(p->fwd_csplit[0], p->fwd_csplit[1]);
-  if (cs > 1) extra = std::max(extra, align256((size_t)cs * p->d.N * p->d.Cout * p->d.R * hw * 4));
-  return pack + extra;
+  return fwd_pack_region(p) + std::max(fwd_extra_bytes(p), fwd_part_bytes(p, cs));
+}
+
+// What the pooled forward can make do with: banks of four bytes a weight (a larger image is packed and multiplied in
+// slices of filter blocks) and no channel split.
+size_t fwd_fast_least_bytes(const rotconv_plan* p) {
+  size_t b = p4_fwd_weights(p) * sizeof(float);
+  if (p->d.dtype == ROTCONV_BF16) b = std::max(b, p4_fwd_bf16_pack_bytes(p));
+  return align256(b) + fwd_extra_bytes(p);
 }
 
 // the fp32 path's own need (a bf16 plan adds its staging areas in front, see carve())
@@ -367,18 +381,11 @@ static int f32_rotconv_fwd(const rotconv_plan* plan, const void* x, const void* 
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int cs = p->fwd_csplit[0];
   if (p->fast[0] && aligned(x, 8) && aligned(ws, cs > 1 ? 256 : 16) && aligned(y, 16)) {
-    const float* wt = static_cast<const float*>(w);      // the kernel takes w itself, or the bank packed into ws
-    if (!p4_fwd_raw_weights(p, 1, cs)) {
-      launch_p4_pack_fwd(p, static_cast<const float*>(w), static_cast<float*>(ws), st);
-      wt = static_cast<const float*>(ws);
-    }
-    if (cs > 1) {     // small map, deep input: the channels are split over workgroups
-      float* part = reinterpret_cast<float*>(static_cast<char*>(ws) + fwd_pack_region(p));
-      launch_p4_fwd(p, kOutUnpooled, static_cast<const float*>(x), wt, part, nullptr, st, 1, cs);
-      launch_p4_sum_parts(p, part, cs, static_cast<float*>(y), st);
-      return finish();
-    }
-    launch_p4_fwd(p, kOutUnpooled, static_cast<const float*>(x), wt, static_cast<float*>(y), nullptr, st);
+    const size_t parts = fwd_part_bytes(p, cs);       // small map, deep input: the channels are split over workgroups
+    float* out = cs > 1 ? static_cast<float*>(ws) : static_cast<float*>(y);
+    launch_p4_fwd(p, kOutUnpooled, static_cast<const float*>(x), static_cast<const float*>(w),
+                  reinterpret_cast<float*>(static_cast<char*>(ws) + parts), ws_bytes - parts, out, nullptr, st, 1, cs);
+    if (cs > 1) launch_p4_sum_parts(p, out, cs, static_cast<float*>(y), st);
     return finish();
   }
   if (p->gs) {
@@ -458,11 +465,11 @@ static bool f32_pool_fwd_is_fast(const rotconv_plan* p, const void* x, const voi
   return !p->avg_child && p->fast[0] && aligned(x, 8) && aligned(ws, 256) && aligned(ypool, 16) && aligned(idx, 8);
 }
 
-// Scratch the pooled forward of an fp32 plan touches: the packed banks (+ candidates / parts) of the register-resident
-// kernel; every other route is sized by the plan's largest call.
+// Scratch the pooled forward of an fp32 plan needs: the packed banks (+ candidates) of the register-resident kernel;
+// every other route is sized by the plan's largest call.
 static size_t f32_pool_fwd_need(const rotconv_plan* p, const void* x, const void* ypool, const uint8_t* idx,
                                 const void* ws) {
-  return f32_pool_fwd_is_fast(p, x, ypool, idx, ws) ? std::min(p->ws_inner, fwd_fast_ws_bytes(p)) : p->ws_inner;
+  return f32_pool_fwd_is_fast(p, x, ypool, idx, ws) ? std::min(p->ws_inner, fwd_fast_least_bytes(p)) : p->ws_inner;
 }
 
 // no_upload: the caller may not allocate, so a plan whose tables are not on this device yet is refused
@@ -487,43 +494,46 @@ static int f32_rotconv_pool_fwd(const rotconv_plan* plan, const void* x, const v
     return rotconv_fwd(p->avg_child, x, wavg, ypool, c + L.child, p->avg_child->ws_bytes, stream);
   }
   if (f32_pool_fwd_is_fast(p, x, ypool, idx, ws)) {
-    float* wt = static_cast<float*>(ws);
-    char* extra = static_cast<char*>(ws) + fwd_pack_region(p);
     const int mode = p4_fwd_pool_mode(p);
     const size_t hw = (size_t)p->d.H * p->d.W;
-    const int cs = p->fwd_csplit[1];
-    // the bank the kernel multiplies with: w itself where the kernel can re-lay its block on its own, else packed into ws
-    auto bank = [&](int nq_, int cs_) -> const float* {
-      if (p4_fwd_raw_weights(p, nq_, cs_)) return static_cast<const float*>(w);
-      launch_p4_pack_fwd(p, static_cast<const float*>(w), wt, st, nq_);
-      return wt;
+    const float *xf = static_cast<const float*>(x), *wf = static_cast<const float*>(w);
+    float* yf = static_cast<float*>(ypool);
+    char* front = static_cast<char*>(ws);      // candidates / parts; the packed banks behind them
+    auto run = [&](int m, size_t used, float* out, uint8_t* oi, int nq, int cs) {
+      launch_p4_fwd(p, m, xf, wf, reinterpret_cast<float*>(front + used), ws_bytes - used, out, oi, st, nq, cs);
     };
-    if (cs > 1) {     // small map, deep input: the channels are split over workgroups, summed and pooled afterwards
-      float* part = reinterpret_cast<float*>(extra);
-      launch_p4_fwd(p, kOutUnpooled, static_cast<const float*>(x), bank(1, cs), part, nullptr, st, 1, cs);
-      launch_p4_sum_pool(p, part, cs, static_cast<float*>(ypool), idx, st);
+    // small map, deep input: the channels are split over workgroups, summed and pooled afterwards (kept whole where
+    // a caller without a full workspace has no room for the parts and a slice of the banks)
+    const int cs = p->fwd_csplit[1];
+    const size_t parts = fwd_part_bytes(p, cs);
+    if (cs > 1 && parts + p4_fwd_least_pack_bytes(p, 1, cs) <= ws_bytes) {
+      float* part = reinterpret_cast<float*>(front);
+      run(kOutUnpooled, parts, part, nullptr, 1, cs);
+      launch_p4_sum_pool(p, part, cs, yf, idx, st);
       return finish();
     }
     if (p->fwd_base) {     // the pool group spans all banks: products of the base bank, banks combined in the kernel
-      launch_p4_pack_base(p, static_cast<const float*>(w), wt, st);
-      launch_p4_fwd_base(p, static_cast<const float*>(x), wt, static_cast<float*>(ypool), idx, st);
+      launch_p4_pack_base(p, wf, static_cast<float*>(ws), st);
+      launch_p4_fwd_base(p, xf, static_cast<float*>(ws), yf, idx, st);
       return finish();
     }
     const int nq = mode == kOutPartial ? p4_fwd_fold(p) : 1;
-    const float* wb = bank(nq, 1);
+    // a full workspace holds all of this; the static scratch may not hold one filter block of thousands of channels
+    const size_t beside = mode == kOutPooled || nq > 1 ? 0 : fwd_extra_bytes(p);
+    if (beside + p4_fwd_least_pack_bytes(p, nq, 1) > ws_bytes) return ROTCONV_ERR_WORKSPACE;
     if (mode == kOutPooled) {
-      launch_p4_fwd(p, mode, static_cast<const float*>(x), wb, static_cast<float*>(ypool), idx, st);
+      run(mode, 0, yf, idx, 1, 1);
     } else if (nq > 1) {     // the pool group spans all banks: pooled across them inside the kernel
-      launch_p4_fwd(p, kOutPooled, static_cast<const float*>(x), wb, static_cast<float*>(ypool), idx, st, nq);
+      run(kOutPooled, 0, yf, idx, nq, 1);
     } else if (mode == kOutPartial) {
-      float* pv = reinterpret_cast<float*>(extra);
-      uint8_t* pi = reinterpret_cast<uint8_t*>(extra + align256((size_t)p->host.Q * p->d.N * p->d.Cout * hw * 4));
-      launch_p4_fwd(p, mode, static_cast<const float*>(x), wb, pv, pi, st);
-      launch_p4_combine(p, pv, pi, static_cast<float*>(ypool), idx, st);
+      float* pv = reinterpret_cast<float*>(front);
+      uint8_t* pi = reinterpret_cast<uint8_t*>(front + align256((size_t)p->host.Q * p->d.N * p->d.Cout * hw * 4));
+      run(mode, fwd_extra_bytes(p), pv, pi, 1, 1);
+      launch_p4_combine(p, pv, pi, yf, idx, st);
     } else {
-      float* yu = reinterpret_cast<float*>(extra);
-      launch_p4_fwd(p, mode, static_cast<const float*>(x), wb, yu, nullptr, st);
-      launch_maxpool_fwd(p, yu, static_cast<float*>(ypool), idx, st, true);
+      float* yu = reinterpret_cast<float*>(front);
+      run(mode, fwd_extra_bytes(p), yu, nullptr, 1, 1);
+      launch_maxpool_fwd(p, yu, yf, idx, st, true);
     }
     return finish();
   }
@@ -776,7 +786,7 @@ size_t pool_fwd_need(const rotconv_plan* plan, const void* x, const void* w, con
   if (pool_fwd_is_px16(plan, x, ypool, ws)) return align256(px_fwd_bf16_pack_bytes(plan));
   if (pool_fwd_is_direct(plan, x, ypool, ws)) return align256(direct_fwd_pack_floats(plan) * sizeof(float));
   if (!is_bf16(plan)) return f32_pool_fwd_need(plan, x, ypool, idx, ws);
-  if (bf16_pool_fwd_is_native(plan, x, w, ypool, idx, ws)) return std::min(plan->ws_bytes, fwd_fast_ws_bytes(plan));
+  if (bf16_pool_fwd_is_native(plan, x, w, ypool, idx, ws)) return std::min(plan->ws_bytes, fwd_fast_least_bytes(plan));
   return plan->ws_bytes;                                                      // fp32 staging areas in front
 }
 
@@ -831,7 +841,7 @@ int pool_fwd_impl(const rotconv_plan* plan, const void* x, const void* w, void* 
     const int rc = ensure_device_tables(p);
     if (rc) return rc;
     uint16_t* wt = static_cast<uint16_t*>(ws);
-    char* extra = static_cast<char*>(ws) + fwd_pack_region(p);
+    char* extra = static_cast<char*>(ws) + align256(p4_fwd_bf16_pack_bytes(p));
     const size_t hw = (size_t)p->d.H * p->d.W;
     const int nq = pmode == kOutPartial ? p4_fwd_bf16_fold(p) : 1;
     launch_p4_pack_fwd_bf16(p, nq, h16(w), wt, st);

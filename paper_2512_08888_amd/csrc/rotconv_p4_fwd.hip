@@ -1,10 +1,12 @@
 // Fast forward kernel for 3x3, stride 1, pad 1 (fp32): shared-product rotation
-// convolution on the fp32 matrix cores (paper Eq. 8, re-designed for CDNA4).
+// convolution on the matrix cores (paper Eq. 8, re-designed for CDNA4).
 //
 // For one first-quadrant bank the nine per-tap channel contractions
 //     P_u[co, h, x] = sum_ci F[co,ci,u] * X[ci,h,x]           (u = base tap)
-// are formed ONCE with v_mfma_f32_16x16x4_f32 (M = 16 pixels, N = 16 filters,
-// K = 4 input channels) and then placed at the four quarter-turn positions
+// are formed ONCE (M = 16 pixels, N = 16 filters, K = 32 input channels: six
+// v_mfma_f32_16x16x32_bf16 on the operands' bf16 parts, rotconv_split3.h; layers
+// with at most four channels: one v_mfma_f32_16x16x4_f32) and then placed at the
+// four quarter-turn positions
 //     Y_s[co, y, x] = sum_u P_u[co, y + i_s(u) - 1, x + j_s(u) - 1],  (i_s,j_s) = R_s(u)
 // entirely in registers: a wave owns 16 filters x 32 consecutive pixels of one
 // image row and walks down the rows of its band, so a row of P feeds the output
@@ -15,9 +17,16 @@
 // the bank's rotations and its arg-max are taken in registers and stored once.
 // Nothing R-fold ever reaches memory, and the input row is read once per bank.
 //
-// The filter block (16 filters x all input channels x 9 taps) stays resident in
-// LDS for the life of the workgroup when it fits (Cin <= 224); deeper inputs
-// stream it through two 32-channel LDS buffers, one barrier per chunk.  Input
+// What bounds it: 108 matrix instructions (16 clk) per 32-channel chunk, row and
+// wave, and some 100 vector instructions for splitting the pixel operands beside
+// about 500 per row for the placement; eight waves of a workgroup share a row and
+// meet at its barrier, so the two add up.  8 x 64 -> 64 channels at 256 x 256, four
+// quarter turns: 0.369 ms with fp32 instructions (32 clk each, 288 per chunk pair
+// and row), 0.218 ms so; 512 -> 512 at 32 x 32, batch 4: 0.246 -> 0.187 ms.
+//
+// The filter block (16 filters x all input channels x 9 taps x 3 parts) stays
+// resident in LDS for the life of the workgroup when it fits (Cin <= 160); deeper
+// inputs stream it through two 32-channel LDS buffers, one barrier per chunk.  Input
 // rows go straight from global memory into the A-operand registers (8-byte
 // loads, 128 B contiguous per 16 lanes), each slot refilled one chunk ahead;
 // scheduling fences keep those loads and the LDS reads of the B operand where
@@ -36,6 +45,7 @@
 #include "rotconv_kernels.h"
 #include "rotconv_p4.h"
 #include "rotconv_p4_taps.h"
+#include "rotconv_split3.h"
 
 namespace rotconv {
 namespace {
@@ -45,6 +55,11 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 // KC (template parameter): K-steps (of 4 channels) per prefetch chunk: 8 (channels padded to 32), or 1 for layers
 // with at most 4 input channels (a network's first layer: channels padded to 4, an eighth of the matrix work)
 int cin_pad_f32(int Cin) { return Cin <= 4 ? 4 : (Cin + 31) / 32 * 32; }
+
+// 4-byte words of one 32-channel chunk of a 16-filter block as matrix operands: [tap][part][lane][8 bf16]
+constexpr int kChunkS3 = 9 * 3 * 256;
+constexpr int kMaxCper = 5;      // chunks of a block that stay in LDS beside the edge arrays
+constexpr int chunk_words(int CinPad) { return CinPad == 4 ? 576 : kChunkS3; }
 
 // UNPOOLED: write every orientation (rotconv_fwd); else max + arg-max over the bank's rotations.
 // FASTW:    W % 8 == 0 and no wave chain reaches beyond the row: no load masks, vector stores.
@@ -60,7 +75,8 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
                                                            P4Geom g) {
   constexpr int NW = NWX * NWY;
   constexpr int NT = 64 * NW;
-  constexpr int CHF = KC * 4 * 144;      // floats of one 32-channel chunk of the filter block
+  constexpr bool S3 = KC == 8;           // bf16 parts of the operands (rotconv_split3.h); else fp32 instructions
+  constexpr int CHF = S3 ? kChunkS3 : KC * 4 * 144;      // floats of one chunk of the filter block
   extern __shared__ float smem[];
   float* Wl = smem;                      // resident: [CinPad][9][16]; streamed: [2][32][9][16]
   float* EL = smem + (STREAM ? 2 * CHF : g.cper * CHF);    // [2][NW][8][16] left-edge values of every wave
@@ -77,45 +93,77 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
   const int nchunk = g.CinPad / (4 * KC);
   const int c_lo = sp * g.cper, c_hi = min(nchunk, c_lo + g.cper);
   const int cb = v % g.CB; v /= g.CB;
+  const int cbo = g.cb0 + cb;            // the block among the layer's
   const int q = v % g.Q; v /= g.Q;
   const int seg = v % g.nseg; v /= g.nseg;
   const int bg = v % g.nbg;
   const int n = v / g.nbg;
 
   const int tid = threadIdx.x;
-  const float* wsrc = wt + ((size_t)(q * g.CB + cb) * g.CinPad) * 144;
-  constexpr int WPT = (CHF / 4 + NT - 1) / NT;   // float4 per thread and chunk when streaming
+  const float* wsrc = wt + (size_t)(q * g.CB + cb) * nchunk * CHF;
+  // A streamed chunk goes through registers in two halves (at most two 16-byte pieces per thread in flight): one is
+  // loaded at the chunk's first tap and written at its fifth, the other from there to the chunk's end.
+  constexpr int WPT = ((CHF / 4 + NT - 1) / NT + 1) / 2;
   f4 wreg[STREAM ? WPT : 1];
-  auto wload = [&](int c) {
+  auto wload = [&](int c, int half) {
 #pragma unroll
     for (int k = 0; k < WPT; ++k) {
-      const int e = tid + k * NT;
+      const unsigned e = threadIdx.x + (half * WPT + k) * NT;
       if (e < CHF / 4) wreg[k] = reinterpret_cast<const f4*>(wsrc + (size_t)c * CHF)[e];
     }
   };
-  auto wstore = [&](int buf) {
+  auto wstore = [&](int buf, int half) {
 #pragma unroll
     for (int k = 0; k < WPT; ++k) {
-      const int e = tid + k * NT;
+      const unsigned e = threadIdx.x + (half * WPT + k) * NT;
       if (e < CHF / 4) reinterpret_cast<f4*>(Wl + buf * CHF)[e] = wreg[k];
     }
   };
+  auto wstage = [&](int c, int buf) {      // both halves at once
+    for (int half = 0; half < 2; ++half) {
+      wload(c, half);
+      wstore(buf, half);
+    }
+  };
   if (STREAM) {
-    wload(0);
-    wstore(0);
+    wstage(0, 0);
   } else if (g.raw_w) {
-    // wt is the caller's w[Cout][Cin][9]: the block's sixteen filters at one (channel, tap) are sixteen loads 9 Cin
-    // floats apart (consecutive lanes: consecutive addresses) and one 64-byte row of the block; zeros beyond Cout / Cin
-    const int pairs = (c_hi - c_lo) * (CHF / 16), e_lo = c_lo * (CHF / 16), e_end = g.Cin * 9;
-    const float* wrow = wt + (size_t)cb * 16 * e_end;
-    for (int i = tid; i < pairs; i += NT) {
-      const int e = e_lo + i;                    // ci * 9 + u
-      f4 v[4];
+    // wt is the caller's w[Cout][Cin][9]; zeros beyond Cout / Cin
+    if constexpr (S3) {
+      // a thread splits the nine taps of two channels of a filter (72 contiguous bytes); the four channel pairs and
+      // sixteen filters of a wave's threads fill 256 contiguous bytes of each (tap, part)
+      const int n = (c_hi - c_lo) * 256;
+      uint32_t* Wu = reinterpret_cast<uint32_t*>(Wl);
+      for (int i = tid; i < n; i += NT) {
+        const int f = (i / 4) % 16, ci = c_lo * 32 + (i / 64) * 8 + (i % 4) * 2;
+        const bool okf = cbo * 16 + f < g.Cout, ok0 = okf && ci < g.Cin, ok1 = okf && ci + 1 < g.Cin;
+        const float* w0 = wt + ((size_t)(ok0 ? cbo * 16 + f : 0) * g.Cin + (ok0 ? ci : 0)) * 9;
+        float v0[9], v1[9];
 #pragma unroll
-      for (int f = 0; f < 16; ++f)
-        v[f / 4][f % 4] = (e < e_end && cb * 16 + f < g.Cout) ? wrow[(size_t)f * e_end + e] : 0.f;
+        for (int u = 0; u < 9; ++u) { v0[u] = ok0 ? w0[u] : 0.f; v1[u] = ok1 ? w0[9 + u] : 0.f; }
+        uint32_t* dst = Wu + (i / 256) * kChunkS3 + i % 256;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) reinterpret_cast<f4*>(Wl)[i * 4 + k] = v[k];
+        for (int u = 0; u < 9; ++u) {
+          uint16_t a[3], b[3];
+          s3_split_weight(v0[u], a[0], a[1], a[2]);
+          s3_split_weight(v1[u], b[0], b[1], b[2]);
+#pragma unroll
+          for (int k = 0; k < 3; ++k) dst[(u * 3 + k) * 256] = (uint32_t)a[k] | (uint32_t)b[k] << 16;
+        }
+      }
+    } else {
+      // sixteen loads 9 Cin floats apart per (channel, tap) and one 64-byte row of the block
+      const int pairs = (c_hi - c_lo) * (CHF / 16), e_lo = c_lo * (CHF / 16), e_end = g.Cin * 9;
+      const float* wrow = wt + (size_t)cbo * 16 * e_end;
+      for (int i = tid; i < pairs; i += NT) {
+        const int e = e_lo + i;                    // ci * 9 + u
+        f4 v[4];
+#pragma unroll
+        for (int f = 0; f < 16; ++f)
+          v[f / 4][f % 4] = (e < e_end && cbo * 16 + f < g.Cout) ? wrow[(size_t)f * e_end + e] : 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) reinterpret_cast<f4*>(Wl)[i * 4 + k] = v[k];
+      }
     }
   } else {
     const f4* src = reinterpret_cast<const f4*>(wsrc + (size_t)c_lo * CHF);
@@ -143,22 +191,23 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
 #pragma unroll
   for (int s = 0; s < 4; ++s) rot[s] = rot_of[qi * 4 + s];
 
-  // A-operand loads: lane (lc, lg) reads X[ci = 4*kstep + lg][h][x0 + 2*lc .. +1].  The address is a
+  // A-operand loads: lane (lc, lg) reads X[ci][h][x0 + 2*lc .. +1], ci = 8*lg + i of a chunk (bf16 parts: its slice of
+  // the 32-channel contraction) or 4*kstep + lg.  The address is a
   // per-row lane pointer plus a 32-bit channel offset.  Products of rows outside the image are discarded,
   // channels beyond Cin meet zero filter taps, so both only need a valid address; pixels beyond W must
   // read as zero (only possible when W % 32 != 0).
   const int pxa = x0 + 2 * lc;
   const bool px_ok = pxa < g.W;
   const float* xn = x + (size_t)n * g.Cin * HW + (px_ok ? pxa : 0);
-  uint32_t lgoff = (uint32_t)lg * (uint32_t)HW;
+  uint32_t lgoff = (uint32_t)(S3 ? lg * 8 : lg) * (uint32_t)HW;
   asm volatile("" : "+v"(lgoff));   // opaque: keeps the K-step part of the offset scalar (no per-load vector multiply)
   const uint32_t off_last = (uint32_t)(g.Cin - 1) * (uint32_t)HW;   // channels beyond Cin read channel Cin-1
   auto row_ptr = [&](int t) -> const float* {
     const int h = min(max(y0 - 1 + t, 0), g.H - 1);
     return xn + (size_t)h * g.W;
   };
-  auto load_a = [&](const float* rp, int kstep) -> float2 {
-    const uint32_t off = min((uint32_t)(kstep * 4) * (uint32_t)HW + lgoff, off_last);
+  auto load_a = [&](const float* rp, int c, int k) -> float2 {      // k-th load of chunk c
+    const uint32_t off = min((uint32_t)(S3 ? c * 32 + k : (c * KC + k) * 4) * (uint32_t)HW + lgoff, off_last);
     const float2 v2 = *reinterpret_cast<const float2*>(rp + off);
     if (FASTW) return v2;
     return px_ok ? v2 : make_float2(0.f, 0.f);
@@ -176,10 +225,10 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
   {
     const float* rp = row_ptr(0);
 #pragma unroll
-    for (int ks = 0; ks < KC; ++ks) a_cur[ks] = load_a(rp, c_lo * KC + ks);
+    for (int ks = 0; ks < KC; ++ks) a_cur[ks] = load_a(rp, c_lo, ks);
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
-  const float* wl_lane = Wl + lg * 144 + lc;
+  const float* wl_lane = S3 ? Wl + lane * 4 : Wl + lg * 144 + lc;
   int seq = 0;                           // chunk steps done (streaming: LDS buffer parity)
 
   for (int t = 0; t < nsteps; ++t) {
@@ -193,32 +242,72 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
     // after its MFMAs, B read from LDS one K-step ahead.  The scheduling fences keep loads and LDS reads
     // where they are issued; left alone the compiler sinks them next to their first use and waits there.
     auto chunk = [&](int c, bool first) {
+      if (STREAM) asm volatile("" : "+s"(c));      // opaque: addresses are formed where they are used, not kept (and spilled) per chunk
       const bool last = c + 1 == c_hi;
       const float* rp = last ? rp_nxt : rp_cur;
-      const int kn = (last ? c_lo : c + 1) * KC;
-      if (STREAM) wload(last ? 0 : c + 1);         // streamed blocks are never split: c_lo = 0
+      const int cn = last ? c_lo : c + 1;
+      if (STREAM) wload(last ? 0 : c + 1, 0);      // streamed blocks are never split: c_lo = 0
       const float* wc = STREAM ? wl_lane + (seq & 1) * CHF : wl_lane + (size_t)(c - c_lo) * CHF;
-      float bw[2][9];
+      if constexpr (S3) {
+        // the chunk's sixteen values of this lane (eight channels x two pixels) as packed parts
+        u32x4 ap[2][3];
 #pragma unroll
-      for (int u = 0; u < 9; ++u) bw[0][u] = wc[u * 16];
+        for (int i = 0; i < 4; ++i) {
+          const S3Pair lo = s3_split2(a_cur[2 * i].x, a_cur[2 * i + 1].x), hi = s3_split2(a_cur[2 * i].y, a_cur[2 * i + 1].y);
 #pragma unroll
-      for (int ks = 0; ks < KC; ++ks) {
-        if (ks + 1 < KC) {
-#pragma unroll
-          for (int u = 0; u < 9; ++u) bw[(ks + 1) & 1][u] = wc[(ks + 1) * 4 * 144 + u * 16];
+          for (int k = 0; k < 3; ++k) { ap[0][k][i] = lo.p[k]; ap[1][k][i] = hi.p[k]; }
         }
-        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < KC; ++k) a_cur[k] = load_a(rp, cn, k);
+        const u32x4* wu = reinterpret_cast<const u32x4*>(wc);
+        u32x4 bw[2][3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) bw[0][k] = wu[k * 64];
 #pragma unroll
         for (int u = 0; u < 9; ++u) {
-          const f4 zero = f4{0.f, 0.f, 0.f, 0.f};
-          P[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a_cur[ks].x, bw[ks & 1][u], first && ks == 0 ? zero : P[u][0], 0, 0, 0);
-          P[u][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a_cur[ks].y, bw[ks & 1][u], first && ks == 0 ? zero : P[u][1], 0, 0, 0);
+          if (u + 1 < 9) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) bw[(u + 1) & 1][k] = wu[((u + 1) * 3 + k) * 64];
+          }
+          if (STREAM && u == 4) {
+            wstore((seq + 1) & 1, 0);
+            wload(last ? 0 : c + 1, 1);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          const u32x4* b = bw[u & 1];
+          f4 s0 = first ? f4{0.f, 0.f, 0.f, 0.f} : P[u][0], s1 = first ? f4{0.f, 0.f, 0.f, 0.f} : P[u][1];
+          // the smallest products first
+          s0 = s3_mfma(ap[0][2], b[0], s0); s1 = s3_mfma(ap[1][2], b[0], s1);
+          s0 = s3_mfma(ap[0][0], b[2], s0); s1 = s3_mfma(ap[1][0], b[2], s1);
+          s0 = s3_mfma(ap[0][1], b[1], s0); s1 = s3_mfma(ap[1][1], b[1], s1);
+          s0 = s3_mfma(ap[0][1], b[0], s0); s1 = s3_mfma(ap[1][1], b[0], s1);
+          s0 = s3_mfma(ap[0][0], b[1], s0); s1 = s3_mfma(ap[1][0], b[1], s1);
+          P[u][0] = s3_mfma(ap[0][0], b[0], s0); P[u][1] = s3_mfma(ap[1][0], b[0], s1);
         }
-        a_cur[ks] = load_a(rp, kn + ks);
         __builtin_amdgcn_sched_barrier(0);
+      } else {
+        float bw[2][9];
+#pragma unroll
+        for (int u = 0; u < 9; ++u) bw[0][u] = wc[u * 16];
+#pragma unroll
+        for (int ks = 0; ks < KC; ++ks) {
+          if (ks + 1 < KC) {
+#pragma unroll
+            for (int u = 0; u < 9; ++u) bw[(ks + 1) & 1][u] = wc[(ks + 1) * 4 * 144 + u * 16];
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int u = 0; u < 9; ++u) {
+            const f4 zero = f4{0.f, 0.f, 0.f, 0.f};
+            P[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a_cur[ks].x, bw[ks & 1][u], first && ks == 0 ? zero : P[u][0], 0, 0, 0);
+            P[u][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a_cur[ks].y, bw[ks & 1][u], first && ks == 0 ? zero : P[u][1], 0, 0, 0);
+          }
+          a_cur[ks] = load_a(rp, cn, ks);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
       if (STREAM) {
-        wstore((seq + 1) & 1);
+        wstore((seq + 1) & 1, 1);
         __syncthreads();
       }
       ++seq;
@@ -232,8 +321,7 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
       for (int c = c_lo + 1; c < c_hi; ++c) chunk(c, false);
     } else if (STREAM) {
       for (int c = 0; c < nchunk; ++c) {
-        wload(c + 1 == nchunk ? 0 : c + 1);
-        wstore((seq + 1) & 1);
+        wstage(c + 1 == nchunk ? 0 : c + 1, (seq + 1) & 1);
         __syncthreads();
         ++seq;
       }
@@ -298,7 +386,7 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
     // ---- place the row of products at the rotated positions (Eq. 8) --------------
     const int y = h - 1;                       // output row completed by this step
     const int px0 = x0 + 8 * lg;               // first of this lane's 8 pixels
-    const int co = NQ > 1 ? cb * FPB + lc % FPB : cb * 16 + lc;
+    const int co = NQ > 1 ? cbo * FPB + lc % FPB : cbo * 16 + lc;
     const bool fin = t >= 2 && y < g.H && co < g.Cout && px0 >= out_lo && px0 < out_hi && (NQ == 1 || lc < FPB);
     float best[8];
     uint32_t pk[2] = {0u, 0u};                 // arg-max bytes of the lane's 8 pixels
@@ -399,7 +487,7 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
     if (!UNPOOLED && g.relu) {      // fused ReLU (pooled output only): dead elements get idx 255
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const bool dead = !(best[j] > 0.f);
+        const bool dead = best[j] <= 0.f;      // a NaN stays one
         best[j] = dead ? 0.f : best[j];
         pk[j >> 2] |= dead ? 0xffu << (8 * (j & 3)) : 0u;
       }
@@ -453,7 +541,7 @@ __global__ __launch_bounds__(256) void k_p4_combine(const float* __restrict__ pv
     if (bi == 255 || vq > best || (vq == best && iq < bi)) { best = vq; bi = iq; }
   }
   const size_t o = ((size_t)n * Cout * ng + chan) * HW + p;
-  const bool dead = relu && !(best > 0.f);
+  const bool dead = relu && best <= 0.f;
   ypool[o] = dead ? 0.f : best;
   idx[o] = dead ? (uint8_t)255 : (uint8_t)bi;
 }
@@ -493,58 +581,61 @@ __global__ __launch_bounds__(256) void k_p4_sum_pool(const float* __restrict__ p
     for (int k = 1; k < nparts; ++k) v += yb[(size_t)k * n_elem + (size_t)r * HW];
     if (bi < 0 || v > best) { best = v; bi = r; }
   }
-  const bool dead = relu && !(best > 0.f);
+  const bool dead = relu && best <= 0.f;
   ypool[e] = dead ? 0.f : best;
   idx[e] = dead ? (uint8_t)255 : (uint8_t)bi;
 }
 
-// base bank(s) -> Q first-quadrant banks in the LDS image layout [Q][CB][CinPad][9][16]
-// (zero for padded filters / channels).
+// base bank(s) -> Q first-quadrant banks in the LDS image layout: [Q][CB][4][9][16] fp32 (at most four channels), or
+// [Q][CB][chunk][tap][part][lane][8] bf16 parts; zero for padded filters / channels.
+// nq > 1: the banks are folded into the 16 columns (column n = bank n / (16/nq), filter n % (16/nq)): [CB']...
+// One thread per (bank, filter, channel or pair of channels): its taps read the same 36 or 72 bytes of w.
+template <bool S3>
 __global__ __launch_bounds__(256) void k_p4_pack_fwd(const float* __restrict__ w, float* __restrict__ wt,
                                                      const int32_t* __restrict__ fq_src,
                                                      const float* __restrict__ fq_coef,
                                                      const double* __restrict__ fq_coef64, int Q, int CB, int CinPad,
-                                                     int Cin, int Cout, int round16, int nq) {
-  // nq > 1: the banks are folded into the 16 columns (column n = bank n / (16/nq), filter n % (16/nq)): [CB'][CinPad]...
-  // One thread per (bank, filter, channel): its nine taps read the same 36 bytes of w.
-  const int total = (nq > 1 ? 1 : Q) * CB * CinPad * 16;
+                                                     int Cin, int Cout, int round16, int nq, int cb0) {
+  constexpr int CPT = S3 ? 2 : 1;                   // channels per thread
+  const int per = CinPad * 16 / CPT;                // threads per block of sixteen filters
+  const int total = (nq > 1 ? 1 : Q) * CB * per;
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= total) return;
-  const int c16 = e % 16;
-  const int ci = (e / 16) % CinPad;
-  const int cb = (e / (16 * CinPad)) % CB;
+  const int blk = e / per, i = e % per;
+  const int c16 = S3 ? (i / 4) % 16 : i % 16;
+  const int ci = S3 ? (i / 64) * 8 + (i % 4) * 2 : i / 16;
+  const int cb = cb0 + blk % CB;
   const int fpb = 16 / nq;
-  const int q = nq > 1 ? c16 / fpb : e / (16 * CinPad * CB);
+  const int q = nq > 1 ? c16 / fpb : blk / CB;
   const int co = nq > 1 ? cb * fpb + c16 % fpb : cb * 16 + c16;
-  const bool in = co < Cout && ci < Cin;
-  const int slices = Cout * Cin;
-  const float* src = w + (size_t)(in ? co * Cin + ci : 0) * 9;
-  float* dst = wt + (size_t)(e / 16) * 144 + c16;
+  const size_t bank_stride = (size_t)Cout * Cin * 9;
+  if constexpr (S3) {
+    const bool in0 = co < Cout && ci < Cin, in1 = co < Cout && ci + 1 < Cin;
+    const float* src = w + ((size_t)(in0 ? co : 0) * Cin + (in0 ? ci : 0)) * 9;
+    uint32_t* dst = reinterpret_cast<uint32_t*>(wt) + ((size_t)blk * (CinPad / 32) + i / 256) * kChunkS3 + i % 256;
 #pragma unroll
-  for (int u = 0; u < 9; ++u) {
-    float acc = 0.f;
-    if (round16) {    // bf16 plans: the combination in fp64, rounded to fp32 and to bf16 once each
-      double a64 = 0.0;
-      for (int z = 0; z < kMaxNnz; ++z) {
-        const int s = fq_src[(q * 9 + u) * kMaxNnz + z];
-        if (in && s >= 0) a64 += fq_coef64[(q * 9 + u) * kMaxNnz + z] * (double)src[(size_t)(s / 9) * slices * 9 + s % 9];
-      }
-      acc = bf16_to_f32(f32_to_bf16((float)a64));
-    } else {
+    for (int u = 0; u < 9; ++u) {
+      uint16_t a[3], b[3];
+      s3_split_weight(s3_expand_tap(src, bank_stride, q * 9 + u, in0, fq_src, fq_coef, fq_coef64, round16), a[0], a[1], a[2]);
+      s3_split_weight(s3_expand_tap(src + 9, bank_stride, q * 9 + u, in1, fq_src, fq_coef, fq_coef64, round16), b[0], b[1],
+                      b[2]);
 #pragma unroll
-      for (int z = 0; z < kMaxNnz; ++z) {
-        const int s = fq_src[(q * 9 + u) * kMaxNnz + z];
-        if (in && s >= 0) acc += fq_coef[(q * 9 + u) * kMaxNnz + z] * src[(size_t)(s / 9) * slices * 9 + s % 9];
-      }
+      for (int k = 0; k < 3; ++k) dst[(u * 3 + k) * 256] = (uint32_t)a[k] | (uint32_t)b[k] << 16;
     }
-    dst[u * 16] = acc;
+  } else {
+    const bool in = co < Cout && ci < Cin;
+    const float* src = w + (size_t)(in ? co * Cin + ci : 0) * 9;
+    float* dst = wt + (size_t)(e / 16) * 144 + c16;
+#pragma unroll
+    for (int u = 0; u < 9; ++u)
+      dst[u * 16] = s3_expand_tap(src, bank_stride, q * 9 + u, in, fq_src, fq_coef, fq_coef64, round16);
   }
 }
 
 template <int NWX, int NWY, bool UNPOOLED, bool FASTW, bool STREAM, int KC = 8, int NQ = 1>
 void launch_i(const P4Geom& g, const float* x, const float* wt, const int32_t* rot_of, float* ov, uint8_t* oi,
               hipStream_t st) {
-  const size_t wfl = STREAM ? (size_t)2 * KC * 4 * 144 : (size_t)g.cper * KC * 4 * 144;
+  const size_t wfl = (size_t)(STREAM ? 2 : g.cper) * chunk_words(g.CinPad);
   const size_t lds = (wfl + 4 * NWX * NWY * 128) * sizeof(float);
   const int grid = (g.units + 7) / 8 * 8;
   auto kern = k_p4_fwd<NWX, NWY, UNPOOLED, FASTW, STREAM, KC, NQ>;
@@ -592,7 +683,8 @@ void launch_t(const P4Geom& g, bool fastw, bool stream, const float* x, const fl
 
 // Is the filter block of 16 filters too large to stay in LDS next to the edge arrays?
 bool needs_stream(int Cin) {
-  return (size_t)cin_pad_f32(Cin) * 576 + 16384 > 160 * 1024;
+  const int CinPad = cin_pad_f32(Cin);
+  return (size_t)(CinPad == 4 ? 1 : CinPad / 32) * chunk_words(CinPad) * 4 + 16384 > 160 * 1024;
 }
 
 }  // namespace
@@ -602,14 +694,12 @@ bool p4_fwd_supported(const rotconv_plan* p) {
   if (d.k != 3 || d.stride != 1 || d.pad != 1) return false;   // bf16 plans run these kernels on widened copies
   if (d.W & 1) return false;
   if (d.W > 256 && (d.W & 31)) return false;          // segmented rows need whole-lane validity
-  // the streaming variant is built for W % 32 == 0; narrower maps split the channels instead
-  if (needs_stream(d.Cin) && (d.W & 31) && p4_fwd_csplit(p, false) < 2) return false;
   return true;
 }
 
 namespace {
-// Cost of a launch plan in quarter row steps (a wave's 144 matrix instructions of one 32-channel chunk and row,
-// about 2 us, count 4): the sum of its launches' band costs.
+// Cost of a launch plan in units of 0.3 us: a wave's row step counts four per 32-channel chunk (108 matrix instructions
+// and the split of their operands) and three for placing the row; the sum of its launches' band costs.
 long plan_cost(const rotconv_plan* p, int out_mode, int csplit, int nq) {
   P4Geom gs[4];
   const int n = p4_fwd_geoms(p, out_mode, gs, 4, csplit, nq);
@@ -622,7 +712,7 @@ long plan_cost(const rotconv_plan* p, int out_mode, int csplit, int nq) {
 
 // Parts the channel contraction is split into (1: no split).  Small maps with deep inputs give the (filter block,
 // band) decomposition too few workgroups, each with a long serial contraction; splitting the 32-channel chunks over
-// workgroups (at most 7 chunks each, so the filter share stays LDS-resident) costs one unpooled fp32 part per split
+// workgroups (at most kMaxCper chunks each, so the filter share stays LDS-resident) costs one unpooled fp32 part per split
 // and an ordered sum.  `pooled`: the caller wants the pooled output (the alternative is the fused pooled kernel,
 // with the banks folded where the plan allows it).
 int p4_fwd_csplit(const rotconv_plan* p, bool pooled) {
@@ -631,29 +721,28 @@ int p4_fwd_csplit(const rotconv_plan* p, bool pooled) {
   if (CinPad == 4 || d.W > 256) return 1;
   const int nchunk = CinPad / 32;
   if (nchunk < 2) return 1;
-  const bool must = needs_stream(d.Cin) && (d.W & 31);          // no unsplit instance for this shape
-  // Plan option fwd_csplit: 1 keeps the contraction whole where an unsplit instance exists, n >= 2 asks for n parts
-  // (rounded so that a part holds at most 7 chunks); 0: the model.
+  // Plan option fwd_csplit: 1 keeps the contraction whole, n >= 2 asks for n parts (rounded so that a part holds at
+  // most kMaxCper chunks); 0: the model.
   const int forced = p->opt.fwd_csplit;
-  if (forced == 1 && !must) return 1;
+  if (forced == 1) return 1;
   if (forced >= 2) {
     const int cper = std::max((nchunk + forced - 1) / forced, (nchunk + 31) / 32);
-    if (cper <= 7) return (nchunk + cper - 1) / cper;
+    if (cper <= kMaxCper) return (nchunk + cper - 1) / cper;
   }
   const int mode = pooled ? p4_fwd_pool_mode(p) : kOutUnpooled;
   const int nq = pooled && mode == kOutPartial ? p4_fwd_fold(p) : 1;
-  long best = must ? -1 : plan_cost(p, nq > 1 ? kOutPooled : mode, 1, nq);
+  long best = plan_cost(p, nq > 1 ? kOutPooled : mode, 1, nq);
   int best_s = 1;
   const double part_bytes = (double)d.N * d.Cout * d.R * d.H * d.W * 4.0;
   for (int s = 2; s <= 32; s *= 2) {
     const int cper = (nchunk + s - 1) / s;
-    if (cper > 7) continue;
+    if (cper > kMaxCper) continue;
     const int s_eff = (nchunk + cper - 1) / cper;
     if (s_eff < 2) break;
-    // parts written and read once at about 4 TB/s, two small launches
-    const long over = 24 + (long)(2.0 * s_eff * part_bytes / 2.0e6);
+    // parts written and read once at about 4 TB/s, and a dependent launch
+    const long over = 28 + (long)(2.0 * s_eff * part_bytes / 1.2e6);
     const long c = plan_cost(p, kOutUnpooled, s_eff, 1) + over;
-    if (best < 0 || c < best) { best = c; best_s = s_eff; }
+    if (c < best) { best = c; best_s = s_eff; }
     if (cper == 1) break;
   }
   return best_s;
@@ -723,7 +812,7 @@ int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, 
       const long cost = ((units + 255) / 256) * (ty + 2) * std::max(4, g.nwx * bands);
       if (best_cost < 0 || cost <= best_cost) { best_cost = cost; g.TY = ty; g.nbg = nbg; g.units = (int)units; }
     }
-    g.cost = (int)std::min<long>(best_cost * g.cper, 1L << 30);
+    g.cost = (int)std::min<long>(best_cost * (4 * g.cper + 3) / 4, 1L << 30);
     if (nq > 1) {
       g.CB = ublk;
       g.Q = 1;
@@ -747,8 +836,23 @@ int p4_fwd_fold(const rotconv_plan* p) {
   return Q;
 }
 
-size_t p4_fwd_pack_floats(const rotconv_plan* p) {
-  return (size_t)p->host.Q * ((p->d.Cout + 15) / 16) * cin_pad_f32(p->d.Cin) * 144;
+namespace {
+int fwd_blocks(const rotconv_plan* p, int nq) { return nq > 1 ? (p->d.Cout * nq + 15) / 16 : (p->d.Cout + 15) / 16; }
+// words of the packed image of one filter block (of every bank, unless they are folded into its columns)
+size_t block_words(const rotconv_plan* p, int nq) {
+  const int CinPad = cin_pad_f32(p->d.Cin);
+  return (size_t)(nq > 1 ? 1 : p->host.Q) * (CinPad == 4 ? 1 : CinPad / 32) * chunk_words(CinPad);
+}
+}  // namespace
+
+size_t p4_fwd_weights(const rotconv_plan* p) {
+  return (size_t)p->host.Q * fwd_blocks(p, 1) * cin_pad_f32(p->d.Cin) * 144;
+}
+
+size_t p4_fwd_pack_floats(const rotconv_plan* p) { return block_words(p, 1) * fwd_blocks(p, 1); }
+
+size_t p4_fwd_least_pack_bytes(const rotconv_plan* p, int nq, int csplit) {
+  return p4_fwd_raw_weights(p, nq, csplit) ? 0 : block_words(p, nq) * sizeof(float);
 }
 
 // How the bank kernel delivers its result for this plan's pooling.
@@ -767,14 +871,6 @@ int p4_fwd_pool_mode(const rotconv_plan* p) {
   return (p->host.Q > p->ng) ? kOutPartial : kOutPooled;
 }
 
-void launch_p4_pack_fwd(const rotconv_plan* p, const float* w, float* wt, hipStream_t st, int nq) {
-  const int CinPad = cin_pad_f32(p->d.Cin), CB = nq > 1 ? (p->d.Cout * nq + 15) / 16 : (p->d.Cout + 15) / 16;
-  const int total = (nq > 1 ? 1 : p->host.Q) * CB * CinPad * 16;
-  hipLaunchKernelGGL(k_p4_pack_fwd, dim3((total + 255) / 256), dim3(256), 0, st, w, wt, p->dev.fq_src, p->dev.fq_coef,
-                     p->dev.fq_coef64,
-                     p->host.Q, CB, CinPad, p->d.Cin, p->d.Cout, p->d.dtype == ROTCONV_BF16 ? 1 : 0, nq);
-}
-
 bool p4_fwd_raw_weights(const rotconv_plan* p, int nq, int csplit) {
   if (p->d.dtype != ROTCONV_F32 || p->host.Q != 1 || p->B != 1 || nq > 1) return false;
   if (csplit < 2 && needs_stream(p->d.Cin)) return false;
@@ -786,21 +882,38 @@ bool p4_fwd_raw_weights(const rotconv_plan* p, int nq, int csplit) {
   return true;
 }
 
-void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const float* wt, float* out_val,
-                   uint8_t* out_idx, hipStream_t st, int nq, int csplit) {
+void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const float* w, float* pack, size_t pack_bytes,
+                   float* out_val, uint8_t* out_idx, hipStream_t st, int nq, int csplit) {
   P4Geom gs[4];
   const int ng = p4_fwd_geoms(p, out_mode, gs, 4, csplit, nq);
   const bool stream = csplit < 2 && needs_stream(p->d.Cin);
   const int raw = p4_fwd_raw_weights(p, nq, csplit) ? 1 : 0;
-  for (int i = 0; i < ng; ++i) {
-    P4Geom& g = gs[i];
-    g.raw_w = raw;
-    const bool fastw = (p->d.W & 7) == 0 && g.inside;   // no lane reaches beyond the row: no masks, vector stores
-    switch (g.nwx) {
-      case 1: launch_t<1, 8>(g, fastw, stream, x, wt, p->dev.rot_of, out_val, out_idx, st); break;
-      case 2: launch_t<2, 4>(g, fastw, stream, x, wt, p->dev.rot_of, out_val, out_idx, st); break;
-      case 4: launch_t<4, 2>(g, fastw, stream, x, wt, p->dev.rot_of, out_val, out_idx, st); break;
-      default: launch_t<8, 1>(g, fastw, stream, x, wt, p->dev.rot_of, out_val, out_idx, st); break;
+  const int blocks = fwd_blocks(p, nq), CinPad = cin_pad_f32(p->d.Cin);
+  const size_t fit = raw ? blocks : pack_bytes / (block_words(p, nq) * sizeof(float));
+  const int slice = (int)std::max<size_t>(1, std::min<size_t>(blocks, fit));
+  for (int cb0 = 0; cb0 < blocks; cb0 += slice) {
+    const int ncb = std::min(slice, blocks - cb0);
+    if (!raw) {
+      const int total = (nq > 1 ? 1 : p->host.Q) * ncb * CinPad * (CinPad == 4 ? 16 : 8);
+      auto kern = CinPad == 4 ? k_p4_pack_fwd<false> : k_p4_pack_fwd<true>;
+      hipLaunchKernelGGL(kern, dim3((total + 255) / 256), dim3(256), 0, st, w, pack, p->dev.fq_src, p->dev.fq_coef,
+                         p->dev.fq_coef64, p->host.Q, ncb, CinPad, p->d.Cin, p->d.Cout,
+                         p->d.dtype == ROTCONV_BF16 ? 1 : 0, nq, cb0);
+    }
+    for (int i = 0; i < ng; ++i) {
+      P4Geom g = gs[i];
+      g.raw_w = raw;
+      g.units = g.units / g.CB * ncb;
+      g.CB = ncb;
+      g.cb0 = cb0;
+      const bool fastw = (p->d.W & 7) == 0 && g.inside;   // no lane reaches beyond the row: no masks, vector stores
+      const float* wt = raw ? w : pack;
+      switch (g.nwx) {
+        case 1: launch_t<1, 8>(g, fastw, stream, x, wt, p->dev.rot_of, out_val, out_idx, st); break;
+        case 2: launch_t<2, 4>(g, fastw, stream, x, wt, p->dev.rot_of, out_val, out_idx, st); break;
+        case 4: launch_t<4, 2>(g, fastw, stream, x, wt, p->dev.rot_of, out_val, out_idx, st); break;
+        default: launch_t<8, 1>(g, fastw, stream, x, wt, p->dev.rot_of, out_val, out_idx, st); break;
+      }
     }
   }
 }

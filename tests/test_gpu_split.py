@@ -1,0 +1,84 @@
+"""The fp32 kernels that multiply bf16 parts of their operands: edges of their tiles and of their dispatch against the
+oracle, exact scaling by powers of two (the parts of a value scale with it, whatever its magnitude), non-finite inputs,
+and banks that the static scratch holds a slice of at a time.
+
+Error bar: a 32-term instruction rounds six sums per 32 channels, each to half an ulp of the running sum, so a sum over
+K channels and nine taps is within about sqrt(6 K / 32) * 2^-24 of its value in norm; the bar is 1e-6, four times that
+for the deepest case (K = 600).
+"""
+import numpy as np
+import pytest
+import torch
+
+import parity_util as pu
+from paper_2512_08888_amd import binding as rc
+from paper_2512_08888_amd import synth
+
+pytestmark = pytest.mark.gpu
+L = synth.LayerConfig
+
+
+def _rel(got, ref):
+    return float(np.linalg.norm(np.asarray(got, np.float64) - ref) / np.linalg.norm(ref))
+
+
+FWD = [
+    L("s_c5", N=2, Cin=5, H=6, W=10, Cout=17, R=4, x_dist="normal", seed=811),                # ragged chunk, second filter block
+    L("s_c33", N=1, Cin=33, H=9, W=34, Cout=16, R=4, x_dist="normal", seed=812),              # a chunk with one channel
+    L("s_c160", N=1, Cin=160, H=5, W=32, Cout=16, R=1, x_dist="absnormal", seed=813),         # the largest resident block
+    L("s_c161", N=1, Cin=161, H=5, W=32, Cout=20, R=4, x_dist="absnormal", seed=814),         # the smallest streamed block
+    L("s_c200m", N=1, Cin=200, H=4, W=30, Cout=16, R=4, x_dist="normal", seed=815),           # streamed, rows with masks
+    L("s_fold", N=1, Cin=192, H=4, W=32, Cout=8, R=8, mode="steerable", x_dist="normal", seed=816),   # folded banks, streamed
+    L("s_c600", N=1, Cin=600, H=4, W=8, Cout=16, R=4, x_dist="absnormal", seed=817),
+]
+
+
+@pytest.mark.parametrize("csplit", [1, 3])
+@pytest.mark.parametrize("cfg", FWD, ids=[c.name for c in FWD])
+def test_forward_edges(cfg, csplit):
+    x, w, g = synth.make_x(cfg), synth.make_w(cfg), synth.make_g(cfg)
+    ref = pu.oracle_layer(cfg, x, w, g)
+    lay = pu.GpuLayer(cfg, x, w, options=dict(fwd_csplit=csplit))
+    yp, idx = lay.pool_fwd()
+    assert _rel(yp, ref["ypool"]) < 1e-6
+    pu.check_idx(idx, ref["y"], ref["abs_terms"], cfg.G, cfg.name)
+    yu = lay.nan(lay.U)
+    rc.rotconv_fwd(lay.plan, lay.x, lay.w, yu)
+    assert _rel(yu.cpu().numpy(), ref["y"].reshape(yu.shape)) < 1e-6
+
+
+def test_forward_scales_by_powers_of_two():
+    cfg = L("s_scale", N=1, Cin=40, H=6, W=32, Cout=16, R=4, x_dist="normal", seed=821)
+    x, w = synth.make_x(cfg), synth.make_w(cfg)
+    y0, i0 = pu.GpuLayer(cfg, x, w).pool_fwd()
+    for ex, ew in ((60, 0), (-60, 0), (50, 30), (-40, -30)):
+        y, i = pu.GpuLayer(cfg, np.ldexp(x, ex), np.ldexp(w, ew)).pool_fwd()
+        assert np.array_equal(y, np.ldexp(y0, ex + ew)) and np.array_equal(i, i0)
+
+
+def test_forward_shows_non_finite_inputs():
+    """An infinite or NaN input makes every pooled value it reaches non-finite, through the fused ReLU too."""
+    cfg = L("s_inf", N=1, Cin=16, H=9, W=32, Cout=16, R=4, x_dist="absnormal", seed=822)
+    x, w = synth.make_x(cfg), synth.make_w(cfg)
+    for bad in (np.inf, -np.inf, np.nan):
+        xb = x.copy()
+        xb[0, 3, 4, 10] = bad
+        for relu in (False, True):
+            yp, _ = pu.GpuLayer(cfg, xb, w, relu=relu).pool_fwd()
+            reached = np.zeros((9, 32), bool)
+            reached[3:6, 9:12] = True
+            assert not np.isfinite(yp[0][:, reached]).any() and np.isfinite(yp[0][:, ~reached]).all()
+
+
+def test_static_scratch_takes_a_slice_of_the_banks_at_a_time():
+    cfg = L("s_slice", N=1, Cin=640, H=6, W=32, Cout=640, R=4, x_dist="absnormal", seed=823)     # 14.7 MB at 4 bytes a weight
+    plan = rc.Plan.from_config(cfg)
+    x, w = pu.dev(synth.make_x(cfg)), pu.dev(synth.make_w(cfg))
+    out = []
+    for call in (rc.rotconv_pool_fwd, rc.rotconv_pool_fwd_static):
+        yp = torch.full((1, plan.Cpooled, 6, 32), float("nan"), device="cuda")
+        idx = torch.full(yp.shape, 254, dtype=torch.uint8, device="cuda")
+        call(plan, x, w, yp, idx)
+        out.append((yp, idx))
+    torch.cuda.synchronize()
+    assert torch.equal(out[0][1], out[1][1]) and torch.equal(out[0][0], out[1][0])
