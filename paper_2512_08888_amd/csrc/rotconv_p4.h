@@ -148,6 +148,11 @@ P4BwdWGeom p4_bwd_weight_geom(const rotconv_plan* p, bool lut = false, bool shar
 size_t p4_bwd_weight_ws_floats(const rotconv_plan* p);
 void launch_p4_bwd_weight(const rotconv_plan* p, const float* x, const float* gpool, const uint8_t* idx,
                           float* partial, float* dw, hipStream_t st);
+// the weight gradient on bf16 parts of the operands: the partial sums of s3_bwd_weight_geom
+bool s3_bwd_weight_supported(const rotconv_plan* p);
+P4BwdWGeom s3_bwd_weight_geom(const rotconv_plan* p);
+void launch_s3_bwd_weight(const rotconv_plan* p, const P4BwdWGeom& g, const float* x, const float* gpool, const uint8_t* idx,
+                          float* partial, hipStream_t st);
 // bfloat16 x and gpool (bf16 matrix cores, fp32 partial sums and result); same workspace
 bool p4_bwd_weight_bf16_supported(const rotconv_plan* p);
 void launch_p4_bwd_weight_bf16(const rotconv_plan* p, const uint16_t* x, const uint16_t* gpool, const uint8_t* idx,

@@ -1446,6 +1446,10 @@ size_t p4_bwd_weight_ws_floats(const rotconv_plan* p) {
     const P4BwdWGeom g = p4_bwd_weight_geom(p, lut != 0, lut == 2);
     need = std::max(need, (size_t)(g.splits + 1) * g.Q * 9 * g.CoutPad * g.CinPad);  // partial sums + their total
   }
+  if (s3_bwd_weight_supported(p)) {
+    const P4BwdWGeom g = s3_bwd_weight_geom(p);
+    need = std::max(need, (size_t)(g.splits + 1) * g.Q * 9 * g.CoutPad * g.CinPad);
+  }
   return need;
 }
 
@@ -1484,6 +1488,12 @@ static void finish_dw(const rotconv_plan* p, const P4BwdWGeom& g, float* partial
 
 void launch_p4_bwd_weight(const rotconv_plan* p, const float* x, const float* gpool, const uint8_t* idx,
                           float* partial, float* dw, hipStream_t st) {
+  if (s3_bwd_weight_supported(p)) {
+    const P4BwdWGeom g = s3_bwd_weight_geom(p);
+    launch_s3_bwd_weight(p, g, x, gpool, idx, partial, st);
+    finish_dw(p, g, partial, dw, st);
+    return;
+  }
   const P4BwdWGeom g = p4_bwd_weight_geom(p, p4_bwd_lut(p), true);
   const int grid = g.splits * g.ncigw * g.ncog;
   if (g.ncg > 1) {          // table variant, the channel groups of a filter block build its D together
