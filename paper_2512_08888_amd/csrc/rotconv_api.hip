@@ -234,6 +234,8 @@ int rotconv_plan_create_opt(const rotconv_desc* desc, const rotconv_plan_options
   if (p->fast[1])
     p->ws_bytes = std::max(p->ws_bytes, align256(p4_bwd_data_pack_floats(p) * sizeof(float)) +
                                             p4_bwd_data_part_floats(p) * sizeof(float));
+  if (s3_bwd_data_supported(p))
+    p->ws_bytes = std::max(p->ws_bytes, align256(s3_bwd_data_pack_bytes(p)) + s3_bwd_data_part_floats(p) * sizeof(float));
   p->fast[2] = p4_bwd_weight_supported(p) ? 1 : 0;
   if (p->fast[2]) p->ws_bytes = std::max(p->ws_bytes, p4_bwd_weight_ws_floats(p) * sizeof(float));
   if (p->d.dtype == ROTCONV_BF16) {     // scratch of the kernels that take bf16 tensors directly
@@ -568,6 +570,11 @@ static int f32_rotconv_pool_bwd_data(const rotconv_plan* plan, const void* gpool
     return rotconv_pool_bwd_data(p->avg_child, gpool, idx0, wavg, dx, c + L.child, p->avg_child->ws_bytes, stream);
   }
   if (p->fast[1] && aligned(gpool, 8) && aligned(idx, 2) && aligned(dx, 16) && aligned(ws, 16)) {
+    if (s3_bwd_data_supported(p)) {
+      float* part = reinterpret_cast<float*>(static_cast<char*>(ws) + align256(s3_bwd_data_pack_bytes(p)));
+      launch_s3_bwd_data(p, static_cast<const float*>(gpool), idx, static_cast<const float*>(w), ws, static_cast<float*>(dx), part, st);
+      return finish();
+    }
     const bool raw = p4_bwd_data_raw_weights(p) && aligned(w, 16);   // the kernel takes w itself, 16 bytes at a time
     const float* wd = static_cast<const float*>(w);
     if (!raw) {                                                       // ... or the banks packed into ws

@@ -100,6 +100,14 @@ size_t p4_bwd_data_pack_floats(const rotconv_plan* p);
 void launch_p4_pack_bwd(const rotconv_plan* p, const float* w, float* wd, hipStream_t st);
 // scratch behind the packed bank: the fp32 partial dX of a bank split (0 floats without one)
 size_t p4_bwd_data_part_floats(const rotconv_plan* p);
+// the input gradient on bf16 parts of the operands; `pack` (16-byte aligned): the weights' parts
+bool s3_bwd_data_supported(const rotconv_plan* p);
+size_t s3_bwd_data_pack_bytes(const rotconv_plan* p);
+size_t s3_bwd_data_part_floats(const rotconv_plan* p);
+void launch_s3_bwd_data(const rotconv_plan* p, const float* gpool, const uint8_t* idx, const float* w, void* pack, float* dx,
+                        float* part, hipStream_t st);
+// dx = the sum of `splits` partial results of n elements each
+void launch_p4_sum_dx(const float* part, float* dx, size_t n, int splits, hipStream_t st);
 void launch_p4_bwd_data(const rotconv_plan* p, const float* gpool, const uint8_t* idx, const float* wd, float* dx,
                         float* part, hipStream_t st, bool raw_w = false);
 

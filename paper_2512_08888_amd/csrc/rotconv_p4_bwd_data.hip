@@ -948,6 +948,11 @@ void launch_p4_pack_bwd(const rotconv_plan* p, const float* w, float* wd, hipStr
                      g.Q, g.CoutPad, g.CinPad, g.Cin, g.Cout, p->d.dtype == ROTCONV_BF16 ? 1 : 0, g.lut);
 }
 
+void launch_p4_sum_dx(const float* part, float* dx, size_t n, int splits, hipStream_t st) {
+  const unsigned blocks = (unsigned)std::max<size_t>(1, std::min<size_t>((n / 4 + 255) / 256, 1u << 16));
+  hipLaunchKernelGGL(k_p4_sum_dx, dim3(blocks), dim3(256), 0, st, part, dx, n, splits);
+}
+
 void launch_p4_bwd_data(const rotconv_plan* p, const float* gpool, const uint8_t* idx, const float* wd, float* dx_out,
                         float* part, hipStream_t st, bool raw_w) {
   const P4BwdGeom g = p4_bwd_data_geom(p);
@@ -967,11 +972,7 @@ void launch_p4_bwd_data(const rotconv_plan* p, const float* gpool, const uint8_t
       if (g.px == 4) { if (g.ncg == 4) gos(k_p4_bwd_data_shared<4, false, 4>); else gos(k_p4_bwd_data_shared<4, false, 2>); }
       else { if (g.ncg == 4) gos(k_p4_bwd_data_shared<2, false, 4>); else gos(k_p4_bwd_data_shared<2, false, 2>); }
     }
-    if (g.ksplit > 1) {
-      const size_t n_elem = (size_t)p->d.N * p->d.Cin * p->d.H * p->d.W;
-      const unsigned blocks = (unsigned)std::max<size_t>(1, std::min<size_t>((n_elem / 4 + 255) / 256, 1u << 16));
-      hipLaunchKernelGGL(k_p4_sum_dx, dim3(blocks), dim3(256), 0, st, part, dx_out, n_elem, g.ksplit);
-    }
+    if (g.ksplit > 1) launch_p4_sum_dx(part, dx_out, (size_t)p->d.N * p->d.Cin * p->d.H * p->d.W, g.ksplit, st);
     return;
   }
   const bool tight = g.lut && g.nw == 4;
@@ -987,11 +988,7 @@ void launch_p4_bwd_data(const rotconv_plan* p, const float* gpool, const uint8_t
   else if (g.lut) go(k_p4_bwd_data<2, true, 8>);
   else if (raw) go(k_p4_bwd_data<2, false, 4, true>);
   else go(k_p4_bwd_data<2, false, 4>);
-  if (g.ksplit > 1) {
-    const size_t n_elem = (size_t)p->d.N * p->d.Cin * p->d.H * p->d.W;
-    const unsigned blocks = (unsigned)std::max<size_t>(1, std::min<size_t>((n_elem / 4 + 255) / 256, 1u << 16));
-    hipLaunchKernelGGL(k_p4_sum_dx, dim3(blocks), dim3(256), 0, st, part, dx_out, n_elem, g.ksplit);
-  }
+  if (g.ksplit > 1) launch_p4_sum_dx(part, dx_out, (size_t)p->d.N * p->d.Cin * p->d.H * p->d.W, g.ksplit, st);
 }
 
 }  // namespace rotconv

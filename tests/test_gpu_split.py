@@ -110,3 +110,29 @@ def test_weight_gradient_edges(cfg):
     off = rng.random(lay.P) < 1 / 3
     ref = orc.layer_bwd(x, w, np.where(off, 0, g), idx, cfg.R, None, cfg.mode, cfg.stride, cfg.pad, cfg.G)[1]
     assert _rel(lay.pool_bwd_weight(g, np.where(off, 255, idx).astype(np.uint8)), ref) < 5e-7
+
+
+# 30-slot tiles over padded rows laid end to end, K-steps of 16 filters, blocks of 32 channels; at the sizes from which the
+# kernel is taken
+DGRAD = [
+    L("d_c33", N=2, Cin=33, H=127, W=126, Cout=72, R=4, x_dist="normal", seed=841),           # the last K-step starts early
+    L("d_f9", N=4, Cin=64, H=200, W=202, Cout=9, R=4, x_dist="normal", seed=842),             # the lane halves' filters overlap
+    L("d_f5", N=4, Cin=64, H=250, W=248, Cout=5, R=1, x_dist="normal", seed=843),             # ... and coincide
+    L("d_w4", N=4, Cin=128, H=848, W=4, Cout=128, R=4, x_dist="normal", seed=844),            # six-slot rows, shared out
+    L("d_ks", N=4, Cin=250, H=28, W=30, Cout=300, R=4, x_dist="normal", seed=845),            # shared out, ragged both ways
+    L("d_odd", N=2, Cin=48, H=181, W=181, Cout=48, R=2, x_dist="normal", seed=846),           # an odd width
+    L("d_g2", N=2, Cin=72, H=101, W=104, Cout=40, R=8, mode="steerable", pool_group=4, x_dist="normal", seed=847),
+]
+
+
+@pytest.mark.parametrize("cfg", DGRAD, ids=[c.name for c in DGRAD])
+def test_input_gradient_edges(cfg):
+    """Bar as for the forward pass: six sums per 16 filters and tap, each rounded to half an ulp."""
+    w, g = synth.make_w(cfg), synth.make_g(cfg)
+    lay = pu.GpuLayer(cfg, np.zeros((cfg.N, cfg.Cin, cfg.H, cfg.W), np.float32), w)
+    rng = np.random.default_rng(cfg.seed)
+    idx = rng.integers(0, cfg.G, lay.P).astype(np.uint8)
+    off = rng.random(lay.P) < 1 / 3
+    dy = orc.orient_maxpool_bwd(np.where(off, 0, g), idx, cfg.R, cfg.G)
+    ref = orc.rotconv_bwd_data(dy, orc.expand_bank(w, cfg.R, None, cfg.mode), cfg.H, cfg.W, cfg.stride, cfg.pad)
+    assert _rel(lay.pool_bwd_data(g, np.where(off, 255, idx).astype(np.uint8)), ref) < 1e-6
