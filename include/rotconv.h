@@ -156,7 +156,11 @@ typedef struct {
                            0 automatic (filters on the matrix instruction's M side, a lane per pixel column, for
                            layers with four banks and at most 64 input channels), 1 wherever that kernel can run,
                            -1 never (pixels on the M side, eight pixels per lane)                                   */
-  int32_t reserved[4];  /* must be 0 */
+  int32_t bf16_parts;   /* fp32 contractions of 3x3 layers as products of the operands' three bf16 parts on the bf16
+                           matrix cores (forward of layers with more than four channels, gradients of quarter-turn
+                           layers): 0 automatic (where that is the faster form), 1 wherever those kernels can run,
+                           -1 never (fp32 matrix instructions: exact products whatever the operands' magnitude)     */
+  int32_t reserved[3];  /* must be 0 */
 } rotconv_plan_options;
 
 /* Validates the descriptor, builds the orientation tables on the host and
@@ -283,6 +287,9 @@ double rotconv_plan_conv_equivalents(const rotconv_plan* plan, int pass);
  * rotconv_fwd); 3 / 4 = the unfused gradient calls rotconv_bwd_data / rotconv_bwd_weight when given
  * rotconv_workspace_bytes_unfused of scratch (with less they run "generic"). */
 const char* rotconv_plan_kernel_name(const rotconv_plan* plan, int pass);
+/* 1 if that pass (0 rotconv_pool_fwd, 1 rotconv_pool_bwd_data, 2 rotconv_pool_bwd_weight) multiplies bf16 parts of fp32
+ * operands for aligned tensors (see rotconv_plan_options.bf16_parts), else 0. */
+int rotconv_plan_bf16_parts(const rotconv_plan* plan, int pass);
 
 #ifdef __cplusplus
 }

@@ -25,7 +25,7 @@ EXPORTS = [
     "rotconv_workspace_bytes_unfused",
     "rotconv_fwd", "rotconv_bwd_data", "rotconv_bwd_weight", "orient_maxpool_fwd", "orient_maxpool_bwd",
     "rotconv_pool_fwd", "rotconv_pool_bwd_data", "rotconv_pool_bwd_weight", "rotconv_pool_fwd_static",
-    "rotconv_status_string", "rotconv_plan_kernel_name", "rotconv_steerable_reg", "rotconv_plan_conv_equivalents",
+    "rotconv_status_string", "rotconv_plan_kernel_name", "rotconv_plan_bf16_parts", "rotconv_steerable_reg", "rotconv_plan_conv_equivalents",
     "rotconv_diag_mfma_sink_bytes", "rotconv_diag_mfma", "rotconv_diag_copy",
 ]
 
@@ -57,7 +57,8 @@ class PlanOptions(ctypes.Structure):
     _fields_ = [
         ("fwd_csplit", ctypes.c_int32), ("gs", ctypes.c_int32), ("gs_chunk_mb", ctypes.c_int32),
         ("bwd_lut", ctypes.c_int32), ("fwd_base", ctypes.c_int32), ("direct", ctypes.c_int32),
-        ("direct_ty", ctypes.c_int32), ("px_fwd", ctypes.c_int32), ("reserved", ctypes.c_int32 * 4),
+        ("direct_ty", ctypes.c_int32), ("px_fwd", ctypes.c_int32), ("bf16_parts", ctypes.c_int32),
+        ("reserved", ctypes.c_int32 * 3),
     ]
 
 
@@ -104,6 +105,7 @@ def lib():
         L.rotconv_status_string.restype = ctypes.c_char_p
         L.rotconv_plan_kernel_name.argtypes = [vp, ctypes.c_int]
         L.rotconv_plan_kernel_name.restype = ctypes.c_char_p
+        L.rotconv_plan_bf16_parts.argtypes = [vp, ctypes.c_int]
         L.rotconv_diag_mfma_sink_bytes.restype = sz
         L.rotconv_diag_mfma.argtypes = [ctypes.c_int, ctypes.c_int, vp, vp, ctypes.POINTER(ctypes.c_double)]
         L.rotconv_diag_copy.argtypes = [vp, vp, sz, vp]
@@ -166,7 +168,7 @@ class Plan:
     def __init__(self, N, Cin, H, W, Cout, k=3, R=4, angles_deg: Optional[Sequence[float]] = None, mode="exact90",
                  stride=1, pad=1, pool_group=0, dtype=F32, pool_op="max", relu=False, options=None):
         """options: dict of rotconv_plan_options fields (fwd_csplit, gs, gs_chunk_mb, bwd_lut, fwd_base, direct,
-        direct_ty, px_fwd) or None."""
+        direct_ty, px_fwd, bf16_parts) or None."""
         self._h = ctypes.c_void_p()
         self._angles = None
         ang = None
@@ -244,6 +246,10 @@ class Plan:
 
     def kernel_name(self, which: int) -> str:
         return lib().rotconv_plan_kernel_name(self._h, which).decode()
+
+    def bf16_parts(self, which: int) -> bool:
+        """Does fused call `which` (0 fwd, 1 bwd_data, 2 bwd_weight) multiply bf16 parts of fp32 operands?"""
+        return bool(lib().rotconv_plan_bf16_parts(self._h, which))
 
     def workspace(self, device="cuda"):
         """A torch byte tensor of workspace_bytes on the device (allocated once per plan)."""

@@ -197,7 +197,7 @@ int rotconv_plan_create(const rotconv_desc* desc, rotconv_plan** out) {
 
 int rotconv_plan_create_opt(const rotconv_desc* desc, const rotconv_plan_options* opts, rotconv_plan** out) {
   if (!desc || !out) return ROTCONV_ERR_NULL;
-  if (opts && (opts->reserved[0] || opts->reserved[1] || opts->reserved[2] || opts->reserved[3])) return ROTCONV_ERR_UNSUPPORTED;
+  if (opts && (opts->reserved[0] || opts->reserved[1] || opts->reserved[2])) return ROTCONV_ERR_UNSUPPORTED;
   rotconv_plan* p = nullptr;
   const int rc = validate_and_build(desc, &p);
   if (rc != ROTCONV_OK) return rc;
@@ -1043,6 +1043,15 @@ const char* rotconv_plan_kernel_name(const rotconv_plan* plan, int pass) {
   if (plan->d.dtype == ROTCONV_BF16 && plan->native16[pass]) return plan->bwd_lut16[pass] ? "mfma_p4_bf16_lut" : "mfma_p4_bf16";
   if (pass == 0 && plan->fast[0] && plan->fwd_base) return "mfma_p4_base";   // the pooled forward; rotconv_fwd: mfma_p4
   return plan->fast[pass] ? "mfma_p4" : plan->gs ? "mfma_gemm_scatter" : "generic";
+}
+
+int rotconv_plan_bf16_parts(const rotconv_plan* plan, int pass) {
+  if (!plan || pass < 0 || pass > 2) return 0;
+  if (plan->avg_child) return rotconv_plan_bf16_parts(plan->avg_child, pass);
+  if (plan->pad_child && plan->pad_use[pass]) return rotconv_plan_bf16_parts(plan->pad_child, pass);
+  if (plan->direct[pass] || (pass == 0 && (plan->px16 || plan->fwd_base)) || !plan->fast[pass]) return 0;
+  if (is_bf16(plan) && plan->native16[pass]) return 0;
+  return pass == 0 ? p4_fwd_parts(plan) : pass == 1 ? s3_bwd_data_supported(plan) : s3_bwd_weight_supported(plan);
 }
 
 }  // extern "C"

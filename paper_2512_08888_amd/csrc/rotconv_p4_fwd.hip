@@ -54,12 +54,13 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 
 // KC (template parameter): K-steps (of 4 channels) per prefetch chunk: 8 (channels padded to 32), or 1 for layers
 // with at most 4 input channels (a network's first layer: channels padded to 4, an eighth of the matrix work)
+// S3: bf16 parts of the operands (rotconv_split3.h), KC = 8 only; else fp32 instructions
 int cin_pad_f32(int Cin) { return Cin <= 4 ? 4 : (Cin + 31) / 32 * 32; }
 
 // 4-byte words of one 32-channel chunk of a 16-filter block as matrix operands: [tap][part][lane][8 bf16]
 constexpr int kChunkS3 = 9 * 3 * 256;
-constexpr int kMaxCper = 5;      // chunks of a block that stay in LDS beside the edge arrays
-constexpr int chunk_words(int CinPad) { return CinPad == 4 ? 576 : kChunkS3; }
+constexpr int chunk_words(int CinPad, int s3) { return s3 ? kChunkS3 : (CinPad == 4 ? 4 : 32) * 144; }
+constexpr int max_cper(int s3) { return s3 ? 5 : 7; }      // chunks of a block that stay in LDS beside the edge arrays
 
 // UNPOOLED: write every orientation (rotconv_fwd); else max + arg-max over the bank's rotations.
 // FASTW:    W % 8 == 0 and no wave chain reaches beyond the row: no load masks, vector stores.
@@ -68,14 +69,13 @@ constexpr int chunk_words(int CinPad) { return CinPad == 4 ? 576 : kChunkS3; }
 //     banks of the plan (R = 4 NQ orientations pooled together): column n holds bank n / (16/NQ), filter n % (16/NQ);
 //     every lane places and maximises its own bank's four rotations and the maximum across the banks is a
 //     rotate-and-compare inside the 16-lane row (DPP), so no per-bank candidates go through memory.
-template <int NWX, int NWY, bool UNPOOLED, bool FASTW, bool STREAM, int KC, int NQ>
+template <int NWX, int NWY, bool UNPOOLED, bool FASTW, bool STREAM, bool S3, int KC, int NQ>
 __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restrict__ x, const float* __restrict__ wt,
                                                            const int32_t* __restrict__ rot_of,
                                                            float* __restrict__ out_val, uint8_t* __restrict__ out_idx,
                                                            P4Geom g) {
   constexpr int NW = NWX * NWY;
   constexpr int NT = 64 * NW;
-  constexpr bool S3 = KC == 8;           // bf16 parts of the operands (rotconv_split3.h); else fp32 instructions
   constexpr int CHF = S3 ? kChunkS3 : KC * 4 * 144;      // floats of one chunk of the filter block
   extern __shared__ float smem[];
   float* Wl = smem;                      // resident: [CinPad][9][16]; streamed: [2][32][9][16]
@@ -311,6 +311,10 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
             P[u][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a_cur[ks].y, bw[ks & 1][u], first && ks == 0 ? zero : P[u][1], 0, 0, 0);
           }
           a_cur[ks] = load_a(rp, cn, ks);
+          if (STREAM && ks == KC / 2) {
+            wstore((seq + 1) & 1, 0);
+            wload(last ? 0 : c + 1, 1);
+          }
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -594,7 +598,7 @@ __global__ __launch_bounds__(256) void k_p4_sum_pool(const float* __restrict__ p
   idx[e] = dead ? (uint8_t)255 : (uint8_t)bi;
 }
 
-// base bank(s) -> Q first-quadrant banks in the LDS image layout: [Q][CB][4][9][16] fp32 (at most four channels), or
+// base bank(s) -> Q first-quadrant banks in the LDS image layout: [Q][CB][CinPad][9][16] fp32, or
 // [Q][CB][chunk][tap][part][lane][8] bf16 parts; zero for padded filters / channels.
 // nq > 1: the banks are folded into the 16 columns (column n = bank n / (16/nq), filter n % (16/nq)): [CB']...
 // One thread per (bank, filter, channel or pair of channels): its taps read the same 36 or 72 bytes of w.
@@ -640,15 +644,32 @@ __global__ __launch_bounds__(256) void k_p4_pack_fwd(const float* __restrict__ w
   }
 }
 
-template <int NWX, int NWY, bool UNPOOLED, bool FASTW, bool STREAM, int KC = 8, int NQ = 1>
+template <int NWX, int NWY, bool UNPOOLED, bool FASTW, bool STREAM, bool S3, int KC = 8, int NQ = 1>
 void launch_i(const P4Geom& g, const float* x, const float* wt, const int32_t* rot_of, float* ov, uint8_t* oi,
               hipStream_t st) {
-  const size_t wfl = (size_t)(STREAM ? 2 : g.cper) * chunk_words(g.CinPad);
+  const size_t wfl = (size_t)(STREAM ? 2 : g.cper) * chunk_words(g.CinPad, g.s3);
   const size_t lds = (wfl + 4 * NWX * NWY * 128) * sizeof(float);
   const int grid = (g.units + 7) / 8 * 8;
-  auto kern = k_p4_fwd<NWX, NWY, UNPOOLED, FASTW, STREAM, KC, NQ>;
+  auto kern = k_p4_fwd<NWX, NWY, UNPOOLED, FASTW, STREAM, S3, KC, NQ>;
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * NWX * NWY), lds, st, x, wt, rot_of, ov, oi, g);
+}
+
+template <int NWX, int NWY, bool S3>
+void launch_k8(const P4Geom& g, bool fastw, bool stream, const float* x, const float* wt, const int32_t* rot_of,
+               float* ov, uint8_t* oi, hipStream_t st) {
+  if (g.out_mode == kOutUnpooled) {
+    if (stream) launch_i<NWX, NWY, true, false, true, S3>(g, x, wt, rot_of, ov, oi, st);   // deep inputs: streamed block
+    else if (fastw) launch_i<NWX, NWY, true, true, false, S3>(g, x, wt, rot_of, ov, oi, st);
+    else launch_i<NWX, NWY, true, false, false, S3>(g, x, wt, rot_of, ov, oi, st);
+  } else if (stream) {
+    if (fastw) launch_i<NWX, NWY, false, true, true, S3>(g, x, wt, rot_of, ov, oi, st);
+    else launch_i<NWX, NWY, false, false, true, S3>(g, x, wt, rot_of, ov, oi, st);   // a wave chain overhangs the row
+  } else if (fastw) {
+    launch_i<NWX, NWY, false, true, false, S3>(g, x, wt, rot_of, ov, oi, st);
+  } else {
+    launch_i<NWX, NWY, false, false, false, S3>(g, x, wt, rot_of, ov, oi, st);
+  }
 }
 
 template <int NWX, int NWY>
@@ -658,44 +679,36 @@ void launch_t(const P4Geom& g, bool fastw, bool stream, const float* x, const fl
   if (g.nq > 1) {           // banks folded into the columns: pooled output, whole K chunks; a streamed block only
                             // for rows without overhang (p4_fwd_fold sees to that)
     if (g.nq == 4) {
-      if (stream) launch_i<NWX, NWY, false, true, true, 8, 4>(g, x, wt, rot_of, ov, oi, st);
-      else if (fastw) launch_i<NWX, NWY, false, true, false, 8, 4>(g, x, wt, rot_of, ov, oi, st);
-      else launch_i<NWX, NWY, false, false, false, 8, 4>(g, x, wt, rot_of, ov, oi, st);
+      if (stream) launch_i<NWX, NWY, false, true, true, true, 8, 4>(g, x, wt, rot_of, ov, oi, st);
+      else if (fastw) launch_i<NWX, NWY, false, true, false, true, 8, 4>(g, x, wt, rot_of, ov, oi, st);
+      else launch_i<NWX, NWY, false, false, false, true, 8, 4>(g, x, wt, rot_of, ov, oi, st);
     } else {
-      if (stream) launch_i<NWX, NWY, false, true, true, 8, 2>(g, x, wt, rot_of, ov, oi, st);
-      else if (fastw) launch_i<NWX, NWY, false, true, false, 8, 2>(g, x, wt, rot_of, ov, oi, st);
-      else launch_i<NWX, NWY, false, false, false, 8, 2>(g, x, wt, rot_of, ov, oi, st);
+      if (stream) launch_i<NWX, NWY, false, true, true, true, 8, 2>(g, x, wt, rot_of, ov, oi, st);
+      else if (fastw) launch_i<NWX, NWY, false, true, false, true, 8, 2>(g, x, wt, rot_of, ov, oi, st);
+      else launch_i<NWX, NWY, false, false, false, true, 8, 2>(g, x, wt, rot_of, ov, oi, st);
     }
     return;
   }
   if (g.CinPad == 4) {      // at most 4 input channels: one K-step per row
-    if (unp && fastw) launch_i<NWX, NWY, true, true, false, 1>(g, x, wt, rot_of, ov, oi, st);
-    else if (unp) launch_i<NWX, NWY, true, false, false, 1>(g, x, wt, rot_of, ov, oi, st);
-    else if (fastw) launch_i<NWX, NWY, false, true, false, 1>(g, x, wt, rot_of, ov, oi, st);
-    else launch_i<NWX, NWY, false, false, false, 1>(g, x, wt, rot_of, ov, oi, st);
+    if (unp && fastw) launch_i<NWX, NWY, true, true, false, false, 1>(g, x, wt, rot_of, ov, oi, st);
+    else if (unp) launch_i<NWX, NWY, true, false, false, false, 1>(g, x, wt, rot_of, ov, oi, st);
+    else if (fastw) launch_i<NWX, NWY, false, true, false, false, 1>(g, x, wt, rot_of, ov, oi, st);
+    else launch_i<NWX, NWY, false, false, false, false, 1>(g, x, wt, rot_of, ov, oi, st);
     return;
   }
-  if (unp) {
-    if (stream) launch_i<NWX, NWY, true, false, true>(g, x, wt, rot_of, ov, oi, st);   // deep inputs: streamed block
-    else if (fastw) launch_i<NWX, NWY, true, true, false>(g, x, wt, rot_of, ov, oi, st);
-    else launch_i<NWX, NWY, true, false, false>(g, x, wt, rot_of, ov, oi, st);
-  } else if (stream) {
-    if (fastw) launch_i<NWX, NWY, false, true, true>(g, x, wt, rot_of, ov, oi, st);
-    else launch_i<NWX, NWY, false, false, true>(g, x, wt, rot_of, ov, oi, st);   // a wave chain overhangs the row
-  } else if (fastw) {
-    launch_i<NWX, NWY, false, true, false>(g, x, wt, rot_of, ov, oi, st);
-  } else {
-    launch_i<NWX, NWY, false, false, false>(g, x, wt, rot_of, ov, oi, st);
-  }
+  if (g.s3) launch_k8<NWX, NWY, true>(g, fastw, stream, x, wt, rot_of, ov, oi, st);
+  else launch_k8<NWX, NWY, false>(g, fastw, stream, x, wt, rot_of, ov, oi, st);
 }
 
 // Is the filter block of 16 filters too large to stay in LDS next to the edge arrays?
-bool needs_stream(int Cin) {
-  const int CinPad = cin_pad_f32(Cin);
-  return (size_t)(CinPad == 4 ? 1 : CinPad / 32) * chunk_words(CinPad) * 4 + 16384 > 160 * 1024;
+bool needs_stream(const rotconv_plan* p) {
+  const int CinPad = cin_pad_f32(p->d.Cin);
+  return (size_t)(CinPad == 4 ? 1 : CinPad / 32) * chunk_words(CinPad, p4_fwd_parts(p)) * 4 + 16384 > 160 * 1024;
 }
 
 }  // namespace
+
+bool p4_fwd_parts(const rotconv_plan* p) { return cin_pad_f32(p->d.Cin) > 4 && p->opt.bf16_parts >= 0; }
 
 bool p4_fwd_supported(const rotconv_plan* p) {
   const rotconv_desc& d = p->d;
@@ -706,8 +719,9 @@ bool p4_fwd_supported(const rotconv_plan* p) {
 }
 
 namespace {
-// Cost of a launch plan in units of 0.3 us: a wave's row step counts four per 32-channel chunk (108 matrix instructions
-// and the split of their operands) and three for placing the row; the sum of its launches' band costs.
+// Cost of a launch plan, the sum of its launches' band costs.  In units of 0.3 us with bf16 parts: a wave's row step counts
+// four per 32-channel chunk (108 matrix instructions and the split of their operands) and three for placing the row.  In
+// units of 0.5 us with fp32 instructions: four per chunk (144 matrix instructions), the placing among them.
 long plan_cost(const rotconv_plan* p, int out_mode, int csplit, int nq) {
   P4Geom gs[4];
   const int n = p4_fwd_geoms(p, out_mode, gs, 4, csplit, nq);
@@ -720,7 +734,7 @@ long plan_cost(const rotconv_plan* p, int out_mode, int csplit, int nq) {
 
 // Parts the channel contraction is split into (1: no split).  Small maps with deep inputs give the (filter block,
 // band) decomposition too few workgroups, each with a long serial contraction; splitting the 32-channel chunks over
-// workgroups (at most kMaxCper chunks each, so the filter share stays LDS-resident) costs one unpooled fp32 part per split
+// workgroups (at most max_cper chunks each, so the filter share stays LDS-resident) costs one unpooled fp32 part per split
 // and an ordered sum.  `pooled`: the caller wants the pooled output (the alternative is the fused pooled kernel,
 // with the banks folded where the plan allows it).
 int p4_fwd_csplit(const rotconv_plan* p, bool pooled) {
@@ -729,13 +743,14 @@ int p4_fwd_csplit(const rotconv_plan* p, bool pooled) {
   if (CinPad == 4 || d.W > 256) return 1;
   const int nchunk = CinPad / 32;
   if (nchunk < 2) return 1;
+  const int s3 = p4_fwd_parts(p), most = max_cper(s3);
   // Plan option fwd_csplit: 1 keeps the contraction whole, n >= 2 asks for n parts (rounded so that a part holds at
-  // most kMaxCper chunks); 0: the model.
+  // most max_cper chunks); 0: the model.
   const int forced = p->opt.fwd_csplit;
   if (forced == 1) return 1;
   if (forced >= 2) {
     const int cper = std::max((nchunk + forced - 1) / forced, (nchunk + 31) / 32);
-    if (cper <= kMaxCper) return (nchunk + cper - 1) / cper;
+    if (cper <= most) return (nchunk + cper - 1) / cper;
   }
   const int mode = pooled ? p4_fwd_pool_mode(p) : kOutUnpooled;
   const int nq = pooled && mode == kOutPartial ? p4_fwd_fold(p) : 1;
@@ -744,11 +759,11 @@ int p4_fwd_csplit(const rotconv_plan* p, bool pooled) {
   const double part_bytes = (double)d.N * d.Cout * d.R * d.H * d.W * 4.0;
   for (int s = 2; s <= 32; s *= 2) {
     const int cper = (nchunk + s - 1) / s;
-    if (cper > kMaxCper) continue;
+    if (cper > most) continue;
     const int s_eff = (nchunk + cper - 1) / cper;
     if (s_eff < 2) break;
     // parts written and read once at about 4 TB/s, and a dependent launch
-    const long over = 28 + (long)(2.0 * s_eff * part_bytes / 1.2e6);
+    const long over = s3 ? 28 + (long)(2.0 * s_eff * part_bytes / 1.2e6) : 24 + (long)(2.0 * s_eff * part_bytes / 2.0e6);
     const long c = plan_cost(p, kOutUnpooled, s_eff, 1) + over;
     if (c < best) { best = c; best_s = s_eff; }
     if (cper == 1) break;
@@ -769,6 +784,7 @@ int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, 
   base.N = d.N; base.Cin = d.Cin; base.CinPad = cin_pad_f32(d.Cin); base.H = d.H; base.W = d.W;
   base.Cout = d.Cout; base.CB = (d.Cout + 15) / 16; base.R = d.R; base.Q = p->host.Q; base.ng = p->ng;
   base.out_mode = out_mode;
+  base.s3 = p4_fwd_parts(p);
   base.relu = out_mode == kOutPooled && d.activation == ROTCONV_ACT_RELU;
   int ng = 0;
   int pos = 0;
@@ -820,7 +836,7 @@ int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, 
       const long cost = ((units + 255) / 256) * (ty + 2) * std::max(4, g.nwx * bands);
       if (best_cost < 0 || cost <= best_cost) { best_cost = cost; g.TY = ty; g.nbg = nbg; g.units = (int)units; }
     }
-    g.cost = (int)std::min<long>(best_cost * (4 * g.cper + 3) / 4, 1L << 30);
+    g.cost = (int)std::min<long>(g.s3 ? best_cost * (4 * g.cper + 3) / 4 : best_cost * g.cper, 1L << 30);
     if (nq > 1) {
       g.CB = ublk;
       g.Q = 1;
@@ -831,14 +847,15 @@ int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, 
 }
 
 // Banks folded into a wave's 16 columns for the pooled forward: the plan pools all R = 4 Q orientations of a filter
-// together, Q is 2 or 4, every bank has its four quarter turns, the channels fill whole 32-channel chunks, and the
-// filter block stays LDS-resident or is streamed under rows the wave chains cover exactly (1: no folding).
+// together, Q is 2 or 4, every bank has its four quarter turns, the channels fill whole 32-channel chunks, the products
+// are those of bf16 parts, and the filter block stays LDS-resident or is streamed under rows the wave chains cover exactly
+// (1: no folding).
 int p4_fwd_fold(const rotconv_plan* p) {
   const int Q = p->host.Q;
-  if ((Q != 2 && Q != 4) || p->ng != 1 || cin_pad_f32(p->d.Cin) == 4) return 1;
+  if ((Q != 2 && Q != 4) || p->ng != 1 || !p4_fwd_parts(p)) return 1;
   // a streamed filter block: only rows that the wave chains cover exactly (the instances without load masks)
   const int W = p->d.W;
-  if (needs_stream(p->d.Cin) && ((W & 31) || (W <= 256 && (W & (W - 1))))) return 1;
+  if (needs_stream(p) && ((W & 31) || (W <= 256 && (W & (W - 1))))) return 1;
   for (int i = 0; i < Q * 4; ++i)
     if (p->rot_of[i] < 0) return 1;
   return Q;
@@ -849,7 +866,7 @@ int fwd_blocks(const rotconv_plan* p, int nq) { return nq > 1 ? (p->d.Cout * nq 
 // words of the packed image of one filter block (of every bank, unless they are folded into its columns)
 size_t block_words(const rotconv_plan* p, int nq) {
   const int CinPad = cin_pad_f32(p->d.Cin);
-  return (size_t)(nq > 1 ? 1 : p->host.Q) * (CinPad == 4 ? 1 : CinPad / 32) * chunk_words(CinPad);
+  return (size_t)(nq > 1 ? 1 : p->host.Q) * (CinPad == 4 ? 1 : CinPad / 32) * chunk_words(CinPad, p4_fwd_parts(p));
 }
 }  // namespace
 
@@ -881,7 +898,7 @@ int p4_fwd_pool_mode(const rotconv_plan* p) {
 
 bool p4_fwd_raw_weights(const rotconv_plan* p, int nq, int csplit) {
   if (p->d.dtype != ROTCONV_F32 || p->host.Q != 1 || p->B != 1 || nq > 1) return false;
-  if (csplit < 2 && needs_stream(p->d.Cin)) return false;
+  if (csplit < 2 && needs_stream(p)) return false;
   for (int u = 0; u < 9; ++u)
     for (int z = 0; z < kMaxNnz; ++z) {
       const int src = p->host.fq_src[u * kMaxNnz + z];
@@ -894,7 +911,7 @@ void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const fl
                    float* out_val, uint8_t* out_idx, hipStream_t st, int nq, int csplit) {
   P4Geom gs[4];
   const int ng = p4_fwd_geoms(p, out_mode, gs, 4, csplit, nq);
-  const bool stream = csplit < 2 && needs_stream(p->d.Cin);
+  const bool stream = csplit < 2 && needs_stream(p);
   const int raw = p4_fwd_raw_weights(p, nq, csplit) ? 1 : 0;
   const int blocks = fwd_blocks(p, nq), CinPad = cin_pad_f32(p->d.Cin);
   const size_t fit = raw ? blocks : pack_bytes / (block_words(p, nq) * sizeof(float));
@@ -902,8 +919,9 @@ void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const fl
   for (int cb0 = 0; cb0 < blocks; cb0 += slice) {
     const int ncb = std::min(slice, blocks - cb0);
     if (!raw) {
-      const int total = (nq > 1 ? 1 : p->host.Q) * ncb * CinPad * (CinPad == 4 ? 16 : 8);
-      auto kern = CinPad == 4 ? k_p4_pack_fwd<false> : k_p4_pack_fwd<true>;
+      const bool s3 = p4_fwd_parts(p);
+      const int total = (nq > 1 ? 1 : p->host.Q) * ncb * CinPad * (s3 ? 8 : 16);
+      auto kern = s3 ? k_p4_pack_fwd<true> : k_p4_pack_fwd<false>;
       hipLaunchKernelGGL(kern, dim3((total + 255) / 256), dim3(256), 0, st, w, pack, p->dev.fq_src, p->dev.fq_coef,
                          p->dev.fq_coef64, p->host.Q, ncb, CinPad, p->d.Cin, p->d.Cout,
                          p->d.dtype == ROTCONV_BF16 ? 1 : 0, nq, cb0);

@@ -392,7 +392,8 @@ S3BwdPlan s3_bwd_plan(const rotconv_plan* p) {
 // (2x256 -> 256, 32x32), 9.7 GFLOP 209 / 99 (8x512 -> 512, 16x16).  For other turns than quarter turns D is a sum over
 // table entries and the fp32 table kernels stay the faster ones (4x128 -> 128, 128x128, 16 turns: 214 / 226).
 bool s3_bwd_data_supported(const rotconv_plan* p) {
-  if (!p4_bwd_data_supported(p) || p4_bwd_lut(p)) return false;
+  if (!p4_bwd_data_supported(p) || p4_bwd_lut(p) || p->opt.bf16_parts < 0) return false;
+  if (p->opt.bf16_parts > 0) return true;
   const rotconv_desc& d = p->d;
   const double flop = 18.0 * p->host.Q * d.N * d.Cin * d.Cout * d.H * d.W;
   return flop >= 4e9 || (flop >= 1.2e9 && s3_bwd_plan(p).g.ksplit == 1);

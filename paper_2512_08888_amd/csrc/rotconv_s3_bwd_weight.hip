@@ -357,7 +357,8 @@ __global__ __launch_bounds__(NTW, 3) void k_s3_bwd_weight(const float* __restric
 bool s3_bwd_weight_supported(const rotconv_plan* p) {
   const rotconv_desc& d = p->d;
   const size_t lim = (size_t)1 << 30;
-  return !p4_bwd_lut(p) && d.Cin > 32 && (size_t)d.Cin * d.H * d.W < lim && (size_t)d.Cout * p->ng * d.H * d.W < lim;
+  if (p4_bwd_lut(p) || p->opt.bf16_parts < 0) return false;
+  return (d.Cin > 32 || p->opt.bf16_parts > 0) && (size_t)d.Cin * d.H * d.W < lim && (size_t)d.Cout * p->ng * d.H * d.W < lim;
 }
 
 P4BwdWGeom s3_bwd_weight_geom(const rotconv_plan* p) {

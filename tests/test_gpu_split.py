@@ -136,3 +136,34 @@ def test_input_gradient_edges(cfg):
     dy = orc.orient_maxpool_bwd(np.where(off, 0, g), idx, cfg.R, cfg.G)
     ref = orc.rotconv_bwd_data(dy, orc.expand_bank(w, cfg.R, None, cfg.mode), cfg.H, cfg.W, cfg.stride, cfg.pad)
     assert _rel(lay.pool_bwd_data(g, np.where(off, 255, idx).astype(np.uint8)), ref) < 1e-6
+
+
+# the smallest layers, which the automatic choice leaves to the fp32 instructions in one pass or another, and streamed and
+# masked instances of both forms of the forward
+EITHER = [
+    L("e_1", N=1, Cin=5, H=1, W=4, Cout=1, R=4, x_dist="normal", seed=851),
+    L("e_r1", N=2, Cin=9, H=3, W=8, Cout=17, R=1, x_dist="normal", seed=852),
+    L("e_c32", N=1, Cin=32, H=5, W=32, Cout=16, R=4, x_dist="normal", seed=853),
+    L("e_c33", N=2, Cin=33, H=6, W=36, Cout=20, R=4, x_dist="normal", seed=854),
+    L("e_c225", N=1, Cin=225, H=3, W=64, Cout=16, R=2, x_dist="normal", seed=855),            # streamed in both forms
+    L("e_c260m", N=1, Cin=260, H=4, W=44, Cout=18, R=4, x_dist="normal", seed=856),           # ... rows with masks
+    L("e_g4", N=1, Cin=40, H=7, W=20, Cout=8, R=8, mode="steerable", pool_group=4, x_dist="normal", seed=857),
+    L("e_fold", N=1, Cin=64, H=7, W=32, Cout=8, R=8, mode="steerable", x_dist="normal", seed=858),
+]
+
+
+@pytest.mark.parametrize("form", [1, -1])
+@pytest.mark.parametrize("cfg", EITHER, ids=[c.name for c in EITHER])
+def test_both_forms_at_the_smallest_sizes(cfg, form):
+    """Plan option bf16_parts; bar as above."""
+    x, w, g = synth.make_x(cfg), synth.make_w(cfg), synth.make_g(cfg)
+    ref = pu.oracle_layer(cfg, x, w, g)
+    for csplit in (1, 0):
+        lay = pu.GpuLayer(cfg, x, w, options=dict(fwd_csplit=csplit, bf16_parts=form))
+        assert [lay.plan.bf16_parts(i) for i in range(3)] == [form > 0] * 3
+        yp, idx = lay.pool_fwd()
+        assert _rel(yp, ref["ypool"]) < 1e-6
+        pu.check_idx(idx, ref["y"], ref["abs_terms"], cfg.G, cfg.name)
+        assert _rel(lay.fwd().cpu().numpy(), ref["y"].reshape(lay.U)) < 1e-6
+    assert _rel(lay.pool_bwd_weight(g, ref["idx"]), ref["dw"]) < 1e-6
+    assert _rel(lay.pool_bwd_data(g, ref["idx"]), ref["dx"]) < 1e-6

@@ -1,0 +1,34 @@
+"""Which fp32 passes multiply bf16 parts of their operands (host logic only), and that the GPU cases written for those
+kernels are taken by them."""
+import pytest
+
+import test_gpu_split as gs
+from paper_2512_08888_amd import binding as rc
+
+
+def parts(*a, **k):
+    p = rc.Plan(*a, **k)
+    return [p.bf16_parts(i) for i in range(3)]
+
+
+def test_selection():
+    assert parts(8, 64, 256, 256, 64) == [True] * 3
+    assert parts(8, 64, 256, 256, 64, options=dict(bf16_parts=-1)) == [False] * 3
+    # short contractions keep the fp32 input gradient, up to 32 channels the fp32 weight gradient
+    assert parts(1, 40, 32, 32, 16) == [True, False, True]
+    assert parts(1, 16, 32, 32, 16) == [True, False, False]
+    assert parts(1, 16, 32, 32, 16, options=dict(bf16_parts=1)) == [True] * 3
+    # other turns: the forward on base products and the table gradients stay with fp32 instructions
+    assert parts(4, 128, 128, 128, 128, R=16, mode="bilinear") == [False] * 3
+    assert parts(4, 128, 128, 128, 128, R=16, mode="bilinear", options=dict(fwd_base=-1)) == [True, False, False]
+    assert parts(2, 3, 512, 512, 64)[::2] == [False, False]                             # a first layer
+    assert parts(8, 64, 256, 256, 64, dtype=rc.BF16) == [False] * 3
+    assert parts(2, 32, 96, 96, 32, k=5, pad=2) == [False] * 3
+    assert parts(3, 40, 101, 75, 24, R=8, mode="steerable", pool_group=4)[0]            # odd rows: the padded plan's
+    assert parts(8, 64, 256, 256, 64, pool_op="avg") == [True] * 3                      # the averaged bank's plan
+
+
+@pytest.mark.parametrize("cfgs,which", [(gs.FWD, 0), (gs.WGRAD, 2), (gs.DGRAD, 1)], ids=["forward", "weight", "input"])
+def test_edge_cases_reach_the_kernels_they_are_for(cfgs, which):
+    for cfg in cfgs:
+        assert rc.Plan.from_config(cfg).bf16_parts(which), cfg.name
