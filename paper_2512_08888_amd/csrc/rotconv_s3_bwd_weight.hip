@@ -22,7 +22,7 @@
 // instruction cuts the low bits of what it adds up towards minus infinity; over the pixels of a batch that offset grows
 // with their number while the sum itself grows with its root (8x64 -> 64, 256x256: 1.7e-6 of the norm).  So every
 // other split multiplies -X and turns its sums over at the end: the offsets cancel (2.3e-7, where fp32 matrix cores left
-// 3.9e-7).
+// 3.9e-7).  (What the six products leave out has no sign of its own: both operands' parts are rounded.)
 //
 // M = 32 filters, N = 32 channels, K = 16 pixels: k = 8 (l / 32) + 2 p + r is row h + r, pixel 8 ph + 4 (l / 32) + p.
 #include <hip/hip_runtime.h>
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(NTW, 3) void k_s3_bwd_weight(const float* __restric
     uint32_t* dst = dst0 + buf * DW;
 #pragma unroll
     for (int u = 0; u < 9; ++u) {
-      const S3Pair p = s3_split2(D0[u], D1[u]);
+      const S3Pair p = s3_split2<true>(D0[u], D1[u]);
 #pragma unroll
       for (int e = 0; e < 3; ++e) dst[(u * 3 + e) * 256] = p.p[e];
     }
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(NTW, 3) void k_s3_bwd_weight(const float* __restric
   auto split_x = [&](const XRaw& k, int p, u32x4 (&o)[3]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const S3Pair s = s3_split2(sign * k.v[p][0][i], sign * k.v[p][1][i]);
+      const S3Pair s = s3_split2<true>(sign * k.v[p][0][i], sign * k.v[p][1][i]);
 #pragma unroll
       for (int e = 0; e < 3; ++e) o[e][i] = s.p[e];
     }

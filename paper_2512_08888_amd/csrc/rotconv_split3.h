@@ -1,9 +1,17 @@
-// fp32 operands on the bf16 matrix cores: a float is the exact sum of three bf16 values (8 + 8 + 8 significant bits),
-// so a product of two floats is the sum of nine bf16 products, of which the six largest are taken; the three left out
-// are below 2^-23 of the product.  A bf16 16x16x32 instruction does 32 channels in 16 clk where the fp32 16x16x4
-// needs eight instructions of 32 clk, and, unlike the fp32 one, runs beside the vector ALU: six of them take 53 ns per
-// SIMD against 124 ns (measured, two waves per SIMD), and the sums round once per 32 terms instead of after each, so
-// that a dot product of 64 comes out at 0.9e-7 of its 64-bit value in norm against 1.05e-7 to 1.45e-7.
+// fp32 operands on the bf16 matrix cores: a float is the sum of three bf16 values (8 + 8 + 8 significant bits, each to
+// nearest), so a product of two floats is the sum of nine bf16 products, of which the six largest are taken.  A bf16
+// 16x16x32 instruction does 32 channels in 16 clk where the fp32 16x16x4 needs eight instructions of 32 clk, and, unlike
+// the fp32 one, runs beside the vector ALU: six of them take 53 ns per SIMD against 124 ns (measured, two waves per SIMD).
+//
+// Precision.  For v in [1, 2) the second part is at most 2^-8 and the third at most 2^-17, so the three products left out
+// come to at most 2^-24 of the product, with no sign of their own.  (Parts cut instead of rounded leave out up to 2^-21,
+// always of the product's sign.)  The matrix instruction adds its 32 terms and cuts the sum to fp32 towards minus infinity:
+// at most 2^-23, on average 2^-24, of a lone product.  Measured against 64 bits, normal operands, in norm: one product
+// 3.1e-8 (fp32 instruction 2.5e-8, parts cut 6.3e-8), two 2.8e-8 (2.9e-8, 5.4e-8), 32 of any sign 3.8e-8 (1.03e-7, 7.1e-8), 32
+// positive ones 3.4e-8 (8.6e-8, 5.6e-8).
+//
+// The parts hold a value whole while its last bit is a bf16 number: from 2^-110 up.  Below, the third part is subnormal and
+// the value is held to 2^-134.
 //
 // An infinite or NaN operand makes every sum it enters NaN (its parts do not exist).
 #pragma once
@@ -21,28 +29,37 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float s3_f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 s3_bf8 __attribute__((ext_vector_type(8)));
 
-// The upper halves of two floats side by side: `lo` in the low half.
+typedef float s3_f2 __attribute__((ext_vector_type(2)));
+typedef __bf16 s3_bf2 __attribute__((ext_vector_type(2)));
+
+// Two floats as bf16, to nearest, side by side: `lo` in the low half (one instruction).
+__device__ __forceinline__ uint32_t s3_round2(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((s3_f2{lo, hi}), s3_bf2));
+}
+// The upper halves of two floats side by side.
 __device__ __forceinline__ uint32_t s3_pack_hi(float lo, float hi) {
   return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, hi), __builtin_bit_cast(uint32_t, lo), 0x07060302u);
 }
+__device__ __forceinline__ float s3_low(uint32_t p) { return __builtin_bit_cast(float, p << 16); }
+__device__ __forceinline__ float s3_high(uint32_t p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
 
-__device__ __forceinline__ float s3_trunc(float v) {
-  return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, v) & 0xffff0000u);
-}
-
-// Two values -> their three parts, each a packed pair (truncating split: eleven vector instructions, no overflow).
+// Two values -> their three parts, each a packed pair (eleven vector instructions).  What is left after two parts has at
+// most seven bits, so cutting it (CUT) gives the same part; which of the two instructions is the faster one depends on
+// its neighbours (rounded / cut: weight gradient of 8x64 -> 64, 256x256 321 / 311 us, input gradient of 4x512 -> 512, 32x32
+// 163 / 170 us).
 struct S3Pair { uint32_t p[3]; };
+template <bool CUT = false>
 __device__ __forceinline__ S3Pair s3_split2(float a, float b) {
   S3Pair s;
-  s.p[0] = s3_pack_hi(a, b);
-  const float ra = a - s3_trunc(a), rb = b - s3_trunc(b);
-  s.p[1] = s3_pack_hi(ra, rb);
-  s.p[2] = s3_pack_hi(ra - s3_trunc(ra), rb - s3_trunc(rb));
+  s.p[0] = s3_round2(a, b);
+  const float ra = a - s3_low(s.p[0]), rb = b - s3_high(s.p[0]);
+  s.p[1] = s3_round2(ra, rb);
+  const float qa = ra - s3_low(s.p[1]), qb = rb - s3_high(s.p[1]);
+  s.p[2] = CUT ? s3_pack_hi(qa, qb) : s3_round2(qa, qb);
   return s;
 }
 
-// One stored operand value (a weight, split once per call): parts to nearest, so that what the six products leave out
-// is half as large and has no sign of its own.
+// One stored operand value (a weight, split once per call).
 __device__ __forceinline__ uint32_t s3_round_part(float v) {      // bits of a bf16 value in the upper half
   const uint32_t u = __builtin_bit_cast(uint32_t, v);
   const uint32_t r = u + 0x7fffu + ((u >> 16) & 1u);

@@ -167,3 +167,51 @@ def test_both_forms_at_the_smallest_sizes(cfg, form):
         assert _rel(lay.fwd().cpu().numpy(), ref["y"].reshape(lay.U)) < 1e-6
     assert _rel(lay.pool_bwd_weight(g, ref["idx"]), ref["dw"]) < 1e-6
     assert _rel(lay.pool_bwd_data(g, ref["idx"]), ref["dx"]) < 1e-6
+
+
+def _hard(rng, shape):
+    """Values whose low parts are as large as they get, next to random ones; any sign, seven binades."""
+    low = np.array([0xffff, 0x1ffff, 0x7fbf, 0x7fff, 0x8000, 0x8041, 0x7fffff, 0x7f7fbf], np.uint32)
+    bits = np.where(rng.random(shape) < 0.7, rng.choice(low, shape), rng.integers(0, 1 << 23, shape)).astype(np.uint32)
+    v = (bits | np.uint32(0x3f800000)).view(np.float32)
+    return np.ldexp(v, rng.integers(-3, 4, shape)) * rng.choice(np.float32([-1, 1]), shape)
+
+
+def _lone_product_error(got, ref):
+    """Largest error of a value over the value itself (zeros have to be zeros)."""
+    got = np.asarray(got, np.float64)
+    assert np.array_equal(got[ref == 0], ref[ref == 0]) and np.count_nonzero(ref) > 500
+    return float(np.max(np.abs(got - ref)[ref != 0] / np.abs(ref)[ref != 0]))
+
+
+def test_lone_products():
+    """Sums of which only one term is not zero, so that nothing averages out.  The three products of parts left out are at
+    most 2^-24 of the product, and the sum of the other six is cut to 24 bits (less than 2^-23): bar 1.02 (2^-24 + 2^-23)."""
+    bar = 1.02 * (2.0 ** -24 + 2.0 ** -23)
+    rng = np.random.default_rng(861)
+    cfg = L("s_lone", N=2, Cin=40, H=12, W=24, Cout=24, R=4, x_dist="normal", seed=861)
+    spots = np.zeros((12, 24), bool)
+    spots[1::3, 1::3] = True                                   # no window holds two of them
+    one = np.zeros((cfg.N, cfg.Cin, 12, 24), bool)             # ... each in one channel
+    ch = rng.integers(0, cfg.Cin, (cfg.N, 12, 24))
+    np.put_along_axis(one, ch[:, None], spots[None, None].repeat(cfg.N, 0), 1)
+    x, w = np.where(one, _hard(rng, one.shape), 0).astype(np.float32), _hard(rng, (1, cfg.Cout, cfg.Cin, 3, 3))
+    lay = pu.GpuLayer(cfg, x, w, options=dict(bf16_parts=1))
+    y = orc.rotconv_fwd(x, orc.expand_bank(w, cfg.R, None, cfg.mode), 1, 1)
+    assert _lone_product_error(lay.fwd().cpu().numpy(), y.reshape(lay.U)) < bar
+
+    one = np.zeros(lay.P, bool)                                # one filter per spot: lone products in the input gradient
+    co = rng.integers(0, cfg.Cout, (cfg.N, 12, 24))
+    np.put_along_axis(one, co[:, None], spots[None, None].repeat(cfg.N, 0), 1)
+    g, idx = np.where(one, _hard(rng, lay.P), 0).astype(np.float32), rng.integers(0, 4, lay.P).astype(np.uint8)
+    dy = orc.orient_maxpool_bwd(g, idx, cfg.R, cfg.G)
+    dx = orc.rotconv_bwd_data(dy, orc.expand_bank(w, cfg.R, None, cfg.mode), 12, 24, 1, 1)
+    assert _lone_product_error(lay.pool_bwd_data(g, idx), dx) < bar
+
+    g = np.zeros(lay.P, np.float32)                            # one pixel per filter: lone products in the weight gradient
+    for c in range(cfg.Cout):
+        g[rng.integers(cfg.N), c, rng.integers(12), rng.integers(24)] = _hard(rng, ())
+    x = _hard(rng, x.shape)
+    lay = pu.GpuLayer(cfg, x, w, options=dict(bf16_parts=1))
+    dw = orc.layer_bwd(x, w, g, idx, cfg.R, None, cfg.mode, 1, 1, cfg.G)[1]
+    assert _lone_product_error(lay.pool_bwd_weight(g, idx), dw) < bar
