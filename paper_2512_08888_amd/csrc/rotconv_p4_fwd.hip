@@ -62,6 +62,13 @@ constexpr int kChunkS3 = 9 * 3 * 256;
 constexpr int chunk_words(int CinPad, int s3) { return s3 ? kChunkS3 : (CinPad == 4 ? 4 : 32) * 144; }
 constexpr int max_cper(int s3) { return s3 ? 5 : 7; }      // chunks of a block that stay in LDS beside the edge arrays
 
+// The matrix instruction cuts its sums towards minus infinity, an offset of one sign in every product P_u that grows with
+// the channels while their sum grows with the root of their number (1024 -> 32 channels: 1.1e-7 of the norm, more than all
+// else together).  So the parts of every other tap's weights are stored with their signs turned, and those taps' products
+// are subtracted where they are placed: the offsets cancel (five taps against four).
+constexpr bool tap_turned(int u) { return u & 1; }
+constexpr uint32_t tap_sign(int u) { return tap_turned(u) ? 0x80008000u : 0u; }      // on a packed pair
+
 // UNPOOLED: write every orientation (rotconv_fwd); else max + arg-max over the bank's rotations.
 // FASTW:    W % 8 == 0 and no wave chain reaches beyond the row: no load masks, vector stores.
 // STREAM:   the filter block does not fit LDS: stream it in 32-channel chunks.
@@ -148,7 +155,7 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
           s3_split_weight(v0[u], a[0], a[1], a[2]);
           s3_split_weight(v1[u], b[0], b[1], b[2]);
 #pragma unroll
-          for (int k = 0; k < 3; ++k) dst[(u * 3 + k) * 256] = (uint32_t)a[k] | (uint32_t)b[k] << 16;
+          for (int k = 0; k < 3; ++k) dst[(u * 3 + k) * 256] = ((uint32_t)a[k] | (uint32_t)b[k] << 16) ^ tap_sign(u);
         }
       }
     } else {
@@ -275,9 +282,9 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
           }
           __builtin_amdgcn_sched_barrier(0);
           const u32x4* b = bw[u & 1];
-          // The smallest products first, their sum from zero: only the chunk's total meets the running sum (4x512 -> 512,
-          // 32x32: 1.05e-7 of the norm against 2.7e-7 with one chain through all chunks, fp32 matrix cores 1.3e-7; 204
-          // against 195 us; 8x64 -> 64, 256x256: 6.2e-8, 8.5e-8, 9.7e-8 and no slower).
+          // The smallest products first, their sum from zero: only the chunk's total meets the running sum, where one
+          // chain through all chunks is cut six times a chunk (4x512 -> 512, 32x32: 204 against 195 us; error 8.4e-8 of the
+          // norm, 1.3e-7 on the fp32 instructions; 8x64 -> 64, 256x256: 5.9e-8, 9.7e-8).
 #pragma unroll
           for (int t = 0; t < 2; ++t) {
             f4 s = s3_mfma(ap[t][2], b[0], f4{0.f, 0.f, 0.f, 0.f});
@@ -405,15 +412,17 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
     int grp_r = 0;                             // any rotation of the bank (its pool group)
     bool first = true;
     auto place = [&](int s, int j, float& yfin) {
-      // three taps per filter row; a sum starts from its first term (0 + v is an instruction: it is not v for v = -0)
+      // three taps per filter row; a sum starts from its first term (0 + v is an instruction: it is not v for v = -0), with
+      // parts from one that is not turned (every row of every turn has one)
       float tr[3] = {0.f, 0.f, 0.f};
       bool begun[3] = {false, false, false};
 #pragma unroll
-      for (int u = 0; u < 9; ++u) {
+      for (int k = 0; k < 9; ++k) {
+        const int u = !S3 ? k : k < 5 ? 2 * k : 2 * (k - 5) + 1;
         const int jj = j + tap_j(s, u) - 1;
         const float val = jj < 0 ? nbL[u] : jj > 7 ? nbR[u] : P[u][jj & 1][jj >> 1];
         const int ti = tap_i(s, u);
-        tr[ti] = begun[ti] ? tr[ti] + val : val;
+        tr[ti] = !begun[ti] ? val : S3 && tap_turned(u) ? tr[ti] - val : tr[ti] + val;
         begun[ti] = true;
       }
       const float t0 = tr[0], t1 = tr[1], t2 = tr[2];
@@ -632,7 +641,7 @@ __global__ __launch_bounds__(256) void k_p4_pack_fwd(const float* __restrict__ w
       s3_split_weight(s3_expand_tap(src + 9, bank_stride, q * 9 + u, in1, fq_src, fq_coef, fq_coef64, round16), b[0], b[1],
                       b[2]);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) dst[(u * 3 + k) * 256] = (uint32_t)a[k] | (uint32_t)b[k] << 16;
+      for (int k = 0; k < 3; ++k) dst[(u * 3 + k) * 256] = ((uint32_t)a[k] | (uint32_t)b[k] << 16) ^ tap_sign(u);
     }
   } else {
     const bool in = co < Cout && ci < Cin;

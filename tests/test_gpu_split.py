@@ -215,3 +215,35 @@ def test_lone_products():
     lay = pu.GpuLayer(cfg, x, w, options=dict(bf16_parts=1))
     dw = orc.layer_bwd(x, w, g, idx, cfg.R, None, cfg.mode, 1, 1, cfg.G)[1]
     assert _lone_product_error(lay.pool_bwd_weight(g, idx), dw) < bar
+
+
+def test_forward_has_no_offset():
+    """The matrix instruction cuts its sums, one sign for all: half a unit of the last place of a chunk's sum, in each of the
+    chunks x taps, would come to about 1.2e-7 of the result's norm here (2048 channels).  Four of the nine taps' products
+    are formed with the other sign, so a ninth of it may stay: 1.4e-8, bar 3e-8."""
+    cfg = L("s_deep", N=1, Cin=2048, H=8, W=32, Cout=32, R=4, x_dist="absnormal", seed=871)
+    x, w = synth.make_x(cfg), synth.make_w(cfg)
+    y = orc.rotconv_fwd(x, orc.expand_bank(w, cfg.R, None, cfg.mode), 1, 1)
+    for csplit in (1, 16):
+        lay = pu.GpuLayer(cfg, x, w, options=dict(fwd_csplit=csplit, bf16_parts=1))
+        err = lay.fwd().cpu().numpy().astype(np.float64) - y.reshape(lay.U)
+        assert abs(float(err.mean())) < 3e-8 * float(np.sqrt(np.mean(y ** 2)))
+
+
+PRECISE = [
+    L("p_plain", N=1, Cin=512, H=16, W=16, Cout=128, R=1, x_dist="absnormal", seed=872),      # sixteen parts of one chunk
+    L("p_deep", N=1, Cin=1024, H=16, W=16, Cout=64, R=1, x_dist="absnormal", seed=873),
+    L("p_few", N=1, Cin=48, H=40, W=40, Cout=24, R=4, x_dist="absnormal", seed=874),
+]
+
+
+@pytest.mark.parametrize("cfg", PRECISE, ids=[c.name for c in PRECISE])
+def test_forward_is_no_less_precise_than_fp32_instructions(cfg):
+    """Against 64 bits, on the same inputs."""
+    x, w = synth.make_x(cfg), synth.make_w(cfg)
+    y = orc.rotconv_fwd(x, orc.expand_bank(w, cfg.R, None, cfg.mode), 1, 1)
+    err = []
+    for form in (1, -1):
+        lay = pu.GpuLayer(cfg, x, w, options=dict(bf16_parts=form))
+        err.append(_rel(lay.fwd().cpu().numpy(), y.reshape(lay.U)))
+    assert err[0] <= err[1], err
