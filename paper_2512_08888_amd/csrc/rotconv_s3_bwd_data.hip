@@ -22,6 +22,11 @@
 // meet the K-step's barrier before they build, the last four after (all before: 342 against 285 us at 8x64 -> 64, 256x256).
 // Against the kernels on fp32 matrix cores: 8x64 -> 64, 256x256 379 -> 285 us, 4x512 -> 512, 32x32 213 -> 164,
 // 4x128 -> 128, 128x128 189 -> 160, 8x512 -> 512, 16x16 209 -> 99.
+//
+// Precision: the matrix instruction cuts its sums, so of a K-step's 54 per channel block only the nine main products are
+// added at the sum's full size.  Tap by tap (all 54 at full size) the error of few filters was above that of the fp32
+// instructions (48 -> 24: 1.6e-7 of the norm against 1.3e-7; now 5.6e-8; 512 -> 512: 1.9e-7, 3.9e-7, now 9.2e-8), for 1 %
+// less time.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -246,12 +251,16 @@ __global__ __launch_bounds__(NT, 2) void k_s3_bwd_data(const float* __restrict__
     if (!early) __syncthreads();
     const u32x4* nsrc = wsrc(vn, kn);
     const u32x4* wl = Wl + buf * STG + lane;
-    u32x4 wv[2][3];
+    u32x4 wv[2][3], w0[2];
 #pragma unroll
     for (int e = 0; e < 3; ++e) wv[0][e] = wl[e * 64];
 #pragma unroll
     for (int b = 0; b < TB; ++b) {
+      // A K-step's sum starts from zero and is added to the running one; the small products of all nine taps first, so
+      // that the instruction cuts the sum at its full size nine times only (the first part of the weights is read twice).
       f16v t;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) t[r] = 0.f;
 #pragma unroll
       for (int u = 0; u < 9; ++u) {
         const int st = b * 9 + u;
@@ -259,27 +268,34 @@ __global__ __launch_bounds__(NT, 2) void k_s3_bwd_data(const float* __restrict__
           if (st > 0) wstore(buf ^ 1, st / STEP - 1);
           if (st / STEP < NP) wload(nsrc, st / STEP);
         }
-        if (st + 1 < TB * 9) {
+        if (u + 1 < 9) {
 #pragma unroll
-          for (int e = 0; e < 3; ++e) wv[(st + 1) & 1][e] = wl[((st + 1) * 3 + e) * 64];
+          for (int e = 0; e < 3; ++e) wv[(u + 1) & 1][e] = wl[((st + 1) * 3 + e) * 64];
+        } else {
+          w0[0] = wl[b * 27 * 64];
         }
         if (st == TB * 9 - 5 && next) {
           if (last) set_tile(vn);
           load_raw(kn, 0, PRE);
         }
         __builtin_amdgcn_sched_barrier(0);
-        const u32x4* w = wv[st & 1];
-        // the smallest products first; a K-step's sum starts from zero and is added to the running one
-        if (u == 0) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) t[r] = 0.f;
-        }
+        const u32x4* w = wv[u & 1];
         t = mfma32(w[2], op[u][0], t);
         t = mfma32(w[0], op[u][2], t);
         t = mfma32(w[1], op[u][1], t);
         t = mfma32(w[0], op[u][1], t);
         t = mfma32(w[1], op[u][0], t);
-        t = mfma32(w[0], op[u][0], t);
+      }
+#pragma unroll
+      for (int u = 0; u < 9; ++u) {
+        if (u + 1 < 9) {
+          w0[(u + 1) & 1] = wl[(b * 9 + u + 1) * 3 * 64];
+        } else if (b + 1 < TB) {
+#pragma unroll
+          for (int e = 0; e < 3; ++e) wv[0][e] = wl[((b + 1) * 27 + e) * 64];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        t = mfma32(w0[u & 1], op[u][0], t);
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[b][r] += t[r];

@@ -247,3 +247,17 @@ def test_forward_is_no_less_precise_than_fp32_instructions(cfg):
         lay = pu.GpuLayer(cfg, x, w, options=dict(bf16_parts=form))
         err.append(_rel(lay.fwd().cpu().numpy(), y.reshape(lay.U)))
     assert err[0] <= err[1], err
+
+
+@pytest.mark.parametrize("cout", [9, 16, 24, 40, 200])
+def test_gradients_are_no_less_precise_than_fp32_instructions(cout):
+    """Against 64 bits, on the same inputs; the contraction of the input gradient runs over the filters."""
+    cfg = L(f"p_g{cout}", N=2, Cin=48, H=24, W=36, Cout=cout, R=4, x_dist="absnormal", seed=875 + cout)
+    x, w, g = synth.make_x(cfg), synth.make_w(cfg), synth.make_g(cfg)
+    idx = np.random.default_rng(cfg.seed).integers(0, 4, (cfg.N, cout, cfg.H, cfg.W)).astype(np.uint8)
+    dx, dw = orc.layer_bwd(x, w, g, idx, cfg.R, None, cfg.mode, 1, 1, cfg.G)
+    err = []
+    for form in (1, -1):
+        lay = pu.GpuLayer(cfg, x, w, options=dict(bf16_parts=form))
+        err.append((_rel(lay.pool_bwd_data(g, idx), dx), _rel(lay.pool_bwd_weight(g, idx), dw)))
+    assert err[0][0] <= err[1][0] and err[0][1] <= err[1][1], err
