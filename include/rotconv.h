@@ -50,9 +50,13 @@
  *   - `ws` is a DEVICE scratch buffer of at least rotconv_workspace_bytes(plan)
  *     bytes, 256-byte aligned; its contents are undefined between calls, and
  *     two calls sharing one ws must not overlap in time.
- *   - NaN and infinite inputs: every pooled value they reach is non-finite (an
- *     infinity may come out as NaN: fp32 products are formed from the operands'
- *     parts), and NaN passes the fused ReLU.  idx is then some orientation.
+ *   - NaN and infinite inputs: a pooled value is NaN where every response of its
+ *     group is, through the fused ReLU too, and idx is then some orientation of
+ *     the group; where only some responses are NaN it may be NaN or the maximum
+ *     of the others.  fp32 passes that multiply bf16 parts of the operands
+ *     (rotconv_plan_bf16_parts) make NaN of an infinity and of magnitudes from
+ *     3.396e38 on; all others, and these with plan option bf16_parts = -1,
+ *     follow IEEE arithmetic.
  *   - Return value: a rotconv_status.  Argument errors are found on the host
  *     before anything is launched and leave the outputs untouched.
  */

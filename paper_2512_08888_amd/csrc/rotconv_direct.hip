@@ -137,7 +137,7 @@ __global__ __launch_bounds__(256) void k_direct_fwd(const T* __restrict__ x, con
 #pragma unroll
         for (int j = NC - 2; j >= 0; --j) bi = cand[j] == best ? (PB ? j * Q + q : j) : bi;
         if (RELU) {     // fused ReLU: dead elements get idx 255 (no orientation)
-          const bool dead = !(best > 0.f);
+          const bool dead = best <= 0.f;
           best = dead ? 0.f : best;
           bi = dead ? 255 : bi;
         }

@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256) void k_fwd_generic(const float* __restrict__ x
   }
   if (FUSED && live) {
     const size_t q = ((size_t)n * g.Cout * g.ng + chan) * P + p;
-    const bool dead = g.relu && !(best > 0.f);        // fused ReLU: nothing flows back through this element
+    const bool dead = g.relu && best <= 0.f;        // fused ReLU: nothing flows back through this element
     yout[q] = dead ? 0.f : best;
     idx[q] = dead ? (uint8_t)255 : (uint8_t)best_r;
   }
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(256) void k_maxpool_fwd(const T* __restrict__ y, T*
     if (v > best) { best = v; best_raw = raw; best_r = r; }
   }
   const size_t q = ((size_t)n * g.Cout * g.ng + chan) * P + p;
-  const bool dead = g.relu && !(best > 0.f);
+  const bool dead = g.relu && best <= 0.f;
   ypool[q] = dead ? T(0) : best_raw;
   idx[q] = dead ? (uint8_t)255 : (uint8_t)best_r;
 }

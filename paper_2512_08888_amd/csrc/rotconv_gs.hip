@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256) void k_gs_place(const float* __restrict__ P, c
     }
     if (FUSED) {
       const size_t o = ((size_t)n * g.Cout * g.ng + chan) * Po + p;
-      const bool dead = g.relu && !(best > 0.f);
+      const bool dead = g.relu && best <= 0.f;
       yout[o] = dead ? 0.f : best;
       idx[o] = dead ? (uint8_t)255 : (uint8_t)best_r;
     }

@@ -402,7 +402,7 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if (g.relu) {      // fused ReLU: dead elements get idx 255
-        const bool dead = !(best[j] > 0.f);
+        const bool dead = best[j] <= 0.f;
         best[j] = dead ? 0.f : best[j];
         besti[j] = dead ? 255 : besti[j];
       }

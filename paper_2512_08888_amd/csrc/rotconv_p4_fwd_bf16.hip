@@ -402,7 +402,7 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_bf16(const uint16_t* 
     if (!UNPOOLED && g.relu) {      // fused ReLU (pooled output only): dead elements get idx 255
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const bool dead = !(best[j] > 0.f);
+        const bool dead = best[j] <= 0.f;
         best[j] = dead ? 0.f : best[j];
         pk[j >> 2] |= dead ? 0xffu << (8 * (j & 3)) : 0u;
       }
@@ -465,7 +465,7 @@ __global__ __launch_bounds__(256) void k_p4_combine_bf16(const float* __restrict
     if (bi == 255 || vq > best || (vq == best && iq < bi)) { best = vq; bi = iq; }
   }
   const size_t o = ((size_t)n * Cout * ng + chan) * HW + p;
-  const bool dead = relu && !(best > 0.f);
+  const bool dead = relu && best <= 0.f;
   ypool[o] = dead ? (uint16_t)0 : f32_to_bf16(best);
   idx[o] = dead ? (uint8_t)255 : (uint8_t)bi;
 }

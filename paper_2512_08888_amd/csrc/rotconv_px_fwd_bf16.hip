@@ -174,7 +174,7 @@ __global__ __launch_bounds__(64 * NWV, NWV == 4 ? 2 : 1) void k_px_fwd_bf16(cons
       float v = best[k];
       int bi = besti[k];
       if (RELU) {
-        const bool dead = !(v > 0.f);
+        const bool dead = v <= 0.f;
         v = dead ? 0.f : v;
         bi = dead ? 255 : bi;
       }
