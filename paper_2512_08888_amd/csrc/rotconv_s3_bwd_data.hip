@@ -409,8 +409,10 @@ S3BwdPlan s3_bwd_plan(const rotconv_plan* p) {
 // table entries and the fp32 table kernels stay the faster ones (4x128 -> 128, 128x128, 16 turns: 214 / 226).
 bool s3_bwd_data_supported(const rotconv_plan* p) {
   if (!p4_bwd_data_supported(p) || p4_bwd_lut(p) || p->opt.bf16_parts < 0) return false;
-  if (p->opt.bf16_parts > 0) return true;
   const rotconv_desc& d = p->d;
+  // a descriptor's size has to stay at or below the offset that stands for "outside"
+  if ((size_t)d.Cout * p->ng * d.H * d.W * 4 > kOutside) return false;
+  if (p->opt.bf16_parts > 0) return true;
   const double flop = 18.0 * p->host.Q * d.N * d.Cin * d.Cout * d.H * d.W;
   return flop >= 4e9 || (flop >= 1.2e9 && s3_bwd_plan(p).g.ksplit == 1);
 }
