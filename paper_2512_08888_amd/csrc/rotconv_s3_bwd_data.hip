@@ -39,13 +39,10 @@
 namespace rotconv {
 namespace {
 
-typedef float f16v __attribute__((ext_vector_type(16)));
-
 constexpr int NW = 8;                  // waves per workgroup
 constexpr int NT = 64 * NW;
 constexpr int KS = 16;                 // filters per K-step
 constexpr int BLK4 = 9 * 3 * 64;       // 16-byte operands of one K-step and 32-channel block: [tap][part][lane]
-constexpr uint32_t kOutside = 0xfffffff0u;    // byte offset beyond any descriptor's size
 
 struct S3BwdGeom {
   int N, Cin, H, W, Cout, Q, ng;
@@ -71,10 +68,6 @@ __host__ __device__ constexpr int s3_filter(int kb, int half, int i, int Cout) {
 __host__ __device__ constexpr bool s3_takes(int kb, int half, int i, int Cout) {
   const int f = s3_filter(kb, half, i, Cout);
   return f >= kb * KS && i < Cout && (half == 0 || f >= s3_first_filter(kb, Cout) + 8);
-}
-
-__device__ __forceinline__ f16v mfma32(u32x4 a, u32x4 b, f16v c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(s3_bf8, a), __builtin_bit_cast(s3_bf8, b), c, 0, 0, 0);
 }
 
 // the value of the lane to the left / right (slot - 1 / slot + 1)
@@ -226,7 +219,7 @@ __global__ __launch_bounds__(NT, 2) void k_s3_bwd_data(const float* __restrict__
     }
   };
 
-  f16v acc[TB];
+  s3_f16 acc[TB];
 #pragma unroll
   for (int j = 0; j < TB; ++j)
 #pragma unroll
@@ -258,7 +251,7 @@ __global__ __launch_bounds__(NT, 2) void k_s3_bwd_data(const float* __restrict__
     for (int b = 0; b < TB; ++b) {
       // A K-step's sum starts from zero and is added to the running one; the small products of all nine taps first, so
       // that the instruction cuts the sum at its full size nine times only (the first part of the weights is read twice).
-      f16v t;
+      s3_f16 t;
 #pragma unroll
       for (int r = 0; r < 16; ++r) t[r] = 0.f;
 #pragma unroll
@@ -280,11 +273,11 @@ __global__ __launch_bounds__(NT, 2) void k_s3_bwd_data(const float* __restrict__
         }
         __builtin_amdgcn_sched_barrier(0);
         const u32x4* w = wv[u & 1];
-        t = mfma32(w[2], op[u][0], t);
-        t = mfma32(w[0], op[u][2], t);
-        t = mfma32(w[1], op[u][1], t);
-        t = mfma32(w[0], op[u][1], t);
-        t = mfma32(w[1], op[u][0], t);
+        t = s3_mfma32(w[2], op[u][0], t);
+        t = s3_mfma32(w[0], op[u][2], t);
+        t = s3_mfma32(w[1], op[u][1], t);
+        t = s3_mfma32(w[0], op[u][1], t);
+        t = s3_mfma32(w[1], op[u][0], t);
       }
 #pragma unroll
       for (int u = 0; u < 9; ++u) {
@@ -295,7 +288,7 @@ __global__ __launch_bounds__(NT, 2) void k_s3_bwd_data(const float* __restrict__
           for (int e = 0; e < 3; ++e) wv[0][e] = wl[((b + 1) * 27 + e) * 64];
         }
         __builtin_amdgcn_sched_barrier(0);
-        t = mfma32(w0[u & 1], op[u][0], t);
+        t = s3_mfma32(w0[u & 1], op[u][0], t);
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[b][r] += t[r];

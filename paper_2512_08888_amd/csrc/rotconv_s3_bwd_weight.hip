@@ -38,14 +38,8 @@
 namespace rotconv {
 namespace {
 
-typedef float f16v __attribute__((ext_vector_type(16)));
-
 constexpr int NWV = 12, NTW = 64 * NWV;
-constexpr uint32_t kOutside = 0xfffffff0u;    // byte offset beyond any descriptor's size: reads as zero
 
-__device__ __forceinline__ f16v mfma32(u32x4 a, u32x4 b, f16v c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(s3_bf8, a), __builtin_bit_cast(s3_bf8, b), c, 0, 0, 0);
-}
 // the value of the pixel to the left / right of the lane's; the first / last lane of a 16-lane row keeps `edge`
 __device__ __forceinline__ float row_left(float edge, float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, edge), __builtin_bit_cast(int, v), 0x111, 0xf, 0xf, false));
@@ -232,7 +226,7 @@ __global__ __launch_bounds__(NTW, 3) void k_s3_bwd_weight(const float* __restric
     }
   };
 
-  f16v acc[3];
+  s3_f16 acc[3];
 #pragma unroll
   for (int j = 0; j < 3; ++j)
 #pragma unroll
@@ -259,12 +253,12 @@ __global__ __launch_bounds__(NTW, 3) void k_s3_bwd_weight(const float* __restric
         __builtin_amdgcn_sched_barrier(0);
         const u32x4* d = dv[k & 1];
         // the smallest products first; their sum starts from zero and is added to the running one
-        f16v t = mfma32(d[2], xv[0], f16v{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f});
-        t = mfma32(d[0], xv[2], t);
-        t = mfma32(d[1], xv[1], t);
-        t = mfma32(d[0], xv[1], t);
-        t = mfma32(d[1], xv[0], t);
-        t = mfma32(d[0], xv[0], t);
+        s3_f16 t = s3_mfma32(d[2], xv[0], s3_f16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f});
+        t = s3_mfma32(d[0], xv[2], t);
+        t = s3_mfma32(d[1], xv[1], t);
+        t = s3_mfma32(d[0], xv[1], t);
+        t = s3_mfma32(d[1], xv[0], t);
+        t = s3_mfma32(d[0], xv[0], t);
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[j][r] += t[r];
       }
@@ -324,7 +318,7 @@ __global__ __launch_bounds__(NTW, 3) void k_s3_bwd_weight(const float* __restric
     if (ph0) {
 #pragma unroll
       for (int i = 0; i < 12; ++i) {
-        const f16v a = acc[i / 4];
+        const s3_f16 a = acc[i / 4];
         const int r = i % 4 * 4;
         both[i * 64] = s3_f4{a[r], a[r + 1], a[r + 2], a[r + 3]};
       }

@@ -27,6 +27,7 @@ namespace rotconv {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float s3_f4 __attribute__((ext_vector_type(4)));
+typedef float s3_f16 __attribute__((ext_vector_type(16)));
 typedef __bf16 s3_bf8 __attribute__((ext_vector_type(8)));
 
 typedef float s3_f2 __attribute__((ext_vector_type(2)));
@@ -79,6 +80,14 @@ __device__ __forceinline__ void s3_split_weight(float v, uint16_t& p0, uint16_t&
 __device__ __forceinline__ s3_f4 s3_mfma(u32x4 a, u32x4 b, s3_f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(s3_bf8, a), __builtin_bit_cast(s3_bf8, b), c, 0, 0, 0);
 }
+
+__device__ __forceinline__ s3_f16 s3_mfma32(u32x4 a, u32x4 b, s3_f16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(s3_bf8, a), __builtin_bit_cast(s3_bf8, b), c, 0, 0, 0);
+}
+
+// Byte offset of positions outside an image in loads through its buffer descriptor: beyond the descriptor's size (the
+// kernels' limits on an image see to that), so that they read as zero.
+constexpr uint32_t kOutside = 0xfffffff0u;
 
 // One element (bank q, tap u) of the expansion of a base slice; src: the nine taps of (filter, channel).  round16: bf16
 // plans, the combination in fp64, rounded to fp32 and to bf16 once each.
