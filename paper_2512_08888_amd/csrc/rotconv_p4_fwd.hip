@@ -133,7 +133,7 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
     }
   };
   if (STREAM) {
-    wstage(0, 0);
+    wstage(c_lo, 0);
   } else if (g.raw_w) {
     // wt is the caller's w[Cout][Cin][9]; zeros beyond Cout / Cin
     if constexpr (S3) {
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
       const bool last = c + 1 == c_hi;
       const float* rp = last ? rp_nxt : rp_cur;
       const int cn = last ? c_lo : c + 1;
-      if (STREAM) wload(last ? 0 : c + 1, 0);      // streamed blocks are never split: c_lo = 0
+      if (STREAM) wload(cn, 0);
       const float* wc = STREAM ? wl_lane + (seq & 1) * CHF : wl_lane + (size_t)(c - c_lo) * CHF;
       if constexpr (S3) {
         // the chunk's sixteen values of this lane (eight channels x two pixels) as packed parts
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
           }
           if (STREAM && u == 4) {
             wstore((seq + 1) & 1, 0);
-            wload(last ? 0 : c + 1, 1);
+            wload(cn, 1);
           }
           __builtin_amdgcn_sched_barrier(0);
           const u32x4* b = bw[u & 1];
@@ -320,7 +320,7 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
           a_cur[ks] = load_a(rp, cn, ks);
           if (STREAM && ks == KC / 2) {
             wstore((seq + 1) & 1, 0);
-            wload(last ? 0 : c + 1, 1);
+            wload(cn, 1);
           }
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -339,8 +339,8 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
       chunk(c_lo, true);
       for (int c = c_lo + 1; c < c_hi; ++c) chunk(c, false);
     } else if (STREAM) {
-      for (int c = 0; c < nchunk; ++c) {
-        wstage(c + 1 == nchunk ? 0 : c + 1, (seq + 1) & 1);
+      for (int c = c_lo; c < c_hi; ++c) {
+        wstage(c + 1 == c_hi ? c_lo : c + 1, (seq + 1) & 1);
         __syncthreads();
         ++seq;
       }
@@ -709,10 +709,10 @@ void launch_t(const P4Geom& g, bool fastw, bool stream, const float* x, const fl
   else launch_k8<NWX, NWY, false>(g, fastw, stream, x, wt, rot_of, ov, oi, st);
 }
 
-// Is the filter block of 16 filters too large to stay in LDS next to the edge arrays?
-bool needs_stream(const rotconv_plan* p) {
-  const int CinPad = cin_pad_f32(p->d.Cin);
-  return (size_t)(CinPad == 4 ? 1 : CinPad / 32) * chunk_words(CinPad, p4_fwd_parts(p)) * 4 + 16384 > 160 * 1024;
+// Is a part's share of a block of 16 filters too large to stay in LDS next to the edge arrays?
+bool needs_stream(const rotconv_plan* p, int csplit = 1) {
+  const int nchunk = cin_pad_f32(p->d.Cin) == 4 ? 1 : cin_pad_f32(p->d.Cin) / 32;
+  return (nchunk + csplit - 1) / csplit > max_cper(p4_fwd_parts(p));
 }
 
 }  // namespace
@@ -753,13 +753,13 @@ int p4_fwd_csplit(const rotconv_plan* p, bool pooled) {
   const int nchunk = CinPad / 32;
   if (nchunk < 2) return 1;
   const int s3 = p4_fwd_parts(p), most = max_cper(s3);
-  // Plan option fwd_csplit: 1 keeps the contraction whole, n >= 2 asks for n parts (rounded so that a part holds at
-  // most max_cper chunks); 0: the model.
+  // Plan option fwd_csplit: 1 keeps the contraction whole, n >= 2 asks for n parts of equal size (as many whole chunks
+  // as that takes, at most 32 parts); 0: the model, which only looks at parts that stay in LDS.
   const int forced = p->opt.fwd_csplit;
   if (forced == 1) return 1;
   if (forced >= 2) {
     const int cper = std::max((nchunk + forced - 1) / forced, (nchunk + 31) / 32);
-    if (cper <= most) return (nchunk + cper - 1) / cper;
+    return (nchunk + cper - 1) / cper;
   }
   const int mode = pooled ? p4_fwd_pool_mode(p) : kOutUnpooled;
   const int nq = pooled && mode == kOutPartial ? p4_fwd_fold(p) : 1;
@@ -907,7 +907,7 @@ int p4_fwd_pool_mode(const rotconv_plan* p) {
 
 bool p4_fwd_raw_weights(const rotconv_plan* p, int nq, int csplit) {
   if (p->d.dtype != ROTCONV_F32 || p->host.Q != 1 || p->B != 1 || nq > 1) return false;
-  if (csplit < 2 && needs_stream(p)) return false;
+  if (needs_stream(p, csplit)) return false;
   for (int u = 0; u < 9; ++u)
     for (int z = 0; z < kMaxNnz; ++z) {
       const int src = p->host.fq_src[u * kMaxNnz + z];
@@ -920,7 +920,7 @@ void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const fl
                    float* out_val, uint8_t* out_idx, hipStream_t st, int nq, int csplit) {
   P4Geom gs[4];
   const int ng = p4_fwd_geoms(p, out_mode, gs, 4, csplit, nq);
-  const bool stream = csplit < 2 && needs_stream(p);
+  const bool stream = needs_stream(p, csplit);
   const int raw = p4_fwd_raw_weights(p, nq, csplit) ? 1 : 0;
   const int blocks = fwd_blocks(p, nq), CinPad = cin_pad_f32(p->d.Cin);
   const size_t fit = raw ? blocks : pack_bytes / (block_words(p, nq) * sizeof(float));

@@ -261,3 +261,22 @@ def test_gradients_are_no_less_precise_than_fp32_instructions(cout):
         lay = pu.GpuLayer(cfg, x, w, options=dict(bf16_parts=form))
         err.append((_rel(lay.pool_bwd_data(g, idx), dx), _rel(lay.pool_bwd_weight(g, idx), dw)))
     assert err[0][0] <= err[1][0] and err[0][1] <= err[1][1], err
+
+
+@pytest.mark.parametrize("form", [1, -1])
+@pytest.mark.parametrize("parts", [(256, 256), (192, 192, 128), (128, 128, 128, 128)], ids=lambda p: str(len(p)))
+def test_channel_split_has_the_parts_asked_for(parts, form):
+    """fwd_csplit = n on 512 channels, of which a filter block's share is streamed (8, 6 chunks of 32) or stays in LDS (4):
+    the result is, bit for bit, the ordered sum of the layer's n parts computed as layers of their own."""
+    cfg = L("s_parts", N=2, Cin=512, H=5, W=24, Cout=20, R=4, x_dist="normal", seed=881)
+    x, w = synth.make_x(cfg), synth.make_w(cfg)
+
+    def fwd(a, b, split):
+        c = L("s_part", N=2, Cin=b - a, H=5, W=24, Cout=20, R=4, x_dist="normal", seed=881)
+        lay = pu.GpuLayer(c, x[:, a:b], w[:, :, a:b], options=dict(fwd_csplit=split, bf16_parts=form))
+        return lay.fwd().cpu().numpy()
+
+    want, at = 0, 0
+    for n in parts:
+        want, at = want + fwd(at, at + n, 1), at + n
+    assert np.array_equal(fwd(0, 512, len(parts)), want)
