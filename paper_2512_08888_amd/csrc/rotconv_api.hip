@@ -117,12 +117,28 @@ size_t fwd_fast_ws_bytes(const rotconv_plan* p) {
   return fwd_pack_region(p) + std::max(fwd_extra_bytes(p), fwd_part_bytes(p, cs));
 }
 
-// What the pooled forward can make do with: banks of four bytes a weight (a larger image is packed and multiplied in
-// slices of filter blocks) and no channel split.
+// What the pooled forward can make do with: banks of four bytes a weight beside its candidates, or one filter block's
+// image beside its channel parts (a larger image is packed and multiplied in slices of filter blocks, bit for bit the
+// same result).
 size_t fwd_fast_least_bytes(const rotconv_plan* p) {
-  size_t b = p4_fwd_weights(p) * sizeof(float);
-  if (p->d.dtype == ROTCONV_BF16) b = std::max(b, p4_fwd_bf16_pack_bytes(p));
-  return align256(b) + fwd_extra_bytes(p);
+  const int cs = p->fwd_csplit[1], nq = cs == 1 && p4_fwd_pool_mode(p) == kOutPartial ? p4_fwd_fold(p) : 1;
+  const size_t block = p->fwd_base ? 0 : p4_fwd_least_pack_bytes(p, nq, cs);
+  const size_t bf = p->d.dtype == ROTCONV_BF16 ? p4_fwd_bf16_pack_bytes(p) : 0;
+  if (cs > 1) return align256(std::max(block, bf)) + std::max(fwd_extra_bytes(p), fwd_part_bytes(p, cs));
+  return align256(std::max({p4_fwd_weights(p) * sizeof(float), block, bf})) + fwd_extra_bytes(p);
+}
+
+// The fp32 forward's form and channel splits.  A layer of one filter block, whose parts cannot be packed in slices, keeps
+// the fp32 instructions where rotconv_pool_fwd_static holds its banks at four bytes a weight but not at six.
+void choose_fwd(rotconv_plan* p) {
+  auto choose = [&](int s3) {
+    p->fwd_s3 = s3;
+    p->fwd_csplit[0] = p4_fwd_csplit(p, false);
+    p->fwd_csplit[1] = p4_fwd_csplit(p, true);
+    return fwd_fast_least_bytes(p) <= ROTCONV_STATIC_SCRATCH_BYTES;
+  };
+  const int s3 = p4_fwd_parts_wanted(p);
+  if (!choose(s3) && s3 && p->d.Cout <= 16 && p->opt.bf16_parts == 0 && !choose(0)) choose(1);
 }
 
 // the fp32 path's own need (a bf16 plan adds its staging areas in front, see carve())
@@ -205,10 +221,7 @@ int rotconv_plan_create_opt(const rotconv_desc* desc, const rotconv_plan_options
   p->bwdw_splits = generic_bwdw_splits(p);
   p->ws_bytes = generic_ws_bytes(p);
   p->fast[0] = p4_fwd_supported(p) ? 1 : 0;
-  if (p->fast[0]) {
-    p->fwd_csplit[0] = p4_fwd_csplit(p, false);
-    p->fwd_csplit[1] = p4_fwd_csplit(p, true);
-  }
+  if (p->fast[0]) choose_fwd(p);
   if (p->fast[0]) p->ws_bytes = std::max(p->ws_bytes, fwd_fast_ws_bytes(p));
   // one pool group over several banks: products of the base bank only.  Maps below 32 x 32 pixels with deep inputs
   // keep the channel split of the per-bank kernel where its cost model chose one (few workgroups either way).
@@ -504,13 +517,11 @@ static int f32_rotconv_pool_fwd(const rotconv_plan* plan, const void* x, const v
     auto run = [&](int m, size_t used, float* out, uint8_t* oi, int nq, int cs) {
       launch_p4_fwd(p, m, xf, wf, reinterpret_cast<float*>(front + used), ws_bytes - used, out, oi, st, nq, cs);
     };
-    // small map, deep input: the channels are split over workgroups, summed and pooled afterwards (kept whole where
-    // a caller without a full workspace has no room for the parts and a slice of the banks)
+    // small map, deep input: the channels are split over workgroups, summed and pooled afterwards
     const int cs = p->fwd_csplit[1];
-    const size_t parts = fwd_part_bytes(p, cs);
-    if (cs > 1 && parts + p4_fwd_least_pack_bytes(p, 1, cs) <= ws_bytes) {
+    if (cs > 1) {
       float* part = reinterpret_cast<float*>(front);
-      run(kOutUnpooled, parts, part, nullptr, 1, cs);
+      run(kOutUnpooled, fwd_part_bytes(p, cs), part, nullptr, 1, cs);
       launch_p4_sum_pool(p, part, cs, yf, idx, st);
       return finish();
     }
@@ -520,9 +531,6 @@ static int f32_rotconv_pool_fwd(const rotconv_plan* plan, const void* x, const v
       return finish();
     }
     const int nq = mode == kOutPartial ? p4_fwd_fold(p) : 1;
-    // a full workspace holds all of this; the static scratch may not hold one filter block of thousands of channels
-    const size_t beside = mode == kOutPooled || nq > 1 ? 0 : fwd_extra_bytes(p);
-    if (beside + p4_fwd_least_pack_bytes(p, nq, 1) > ws_bytes) return ROTCONV_ERR_WORKSPACE;
     if (mode == kOutPooled) {
       run(mode, 0, yf, idx, 1, 1);
     } else if (nq > 1) {     // the pool group spans all banks: pooled across them inside the kernel
@@ -1051,7 +1059,7 @@ int rotconv_plan_bf16_parts(const rotconv_plan* plan, int pass) {
   if (plan->pad_child && plan->pad_use[pass]) return rotconv_plan_bf16_parts(plan->pad_child, pass);
   if (plan->direct[pass] || (pass == 0 && (plan->px16 || plan->fwd_base)) || !plan->fast[pass]) return 0;
   if (is_bf16(plan) && plan->native16[pass]) return 0;
-  return pass == 0 ? p4_fwd_parts(plan) : pass == 1 ? s3_bwd_data_supported(plan) : s3_bwd_weight_supported(plan);
+  return pass == 0 ? plan->fwd_s3 : pass == 1 ? s3_bwd_data_supported(plan) : s3_bwd_weight_supported(plan);
 }
 
 }  // extern "C"

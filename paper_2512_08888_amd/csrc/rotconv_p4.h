@@ -20,7 +20,7 @@ struct P4Geom {
   int inside;    // 1 if no segment's wave chain reaches beyond the row
   int relu;      // pooled output: clamp at 0, idx 255 where the pooled value is not positive
   int nq;        // banks folded into a wave's 16 filter columns (0 / 1: none)
-  int s3;        // products of the operands' bf16 parts (p4_fwd_parts)
+  int s3;        // products of the operands' bf16 parts (plan field fwd_s3)
   int csplit;    // parts the channel contraction is split into (1: none); a part is an unpooled fp32 map
   int cper;      // 32-channel chunks per part (all of them without a split)
   int cost;      // modelled cost of the launch (host side only)
@@ -32,7 +32,7 @@ struct P4Geom {
 
 // forward
 bool p4_fwd_supported(const rotconv_plan* p);
-bool p4_fwd_parts(const rotconv_plan* p);   // does the kernel multiply bf16 parts of the operands?
+bool p4_fwd_parts_wanted(const rotconv_plan* p);   // may the kernel multiply bf16 parts of the operands (plan field fwd_s3)?
 int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, int csplit = 1, int nq = 1);
 // parts the forward splits its channel contraction into for this plan (1: none); with a split the kernel runs in
 // the unpooled mode into `csplit` parts of N * Cout * R * H * W floats, added by one of the two kernels below

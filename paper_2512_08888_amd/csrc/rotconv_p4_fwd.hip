@@ -712,12 +712,12 @@ void launch_t(const P4Geom& g, bool fastw, bool stream, const float* x, const fl
 // Is a part's share of a block of 16 filters too large to stay in LDS next to the edge arrays?
 bool needs_stream(const rotconv_plan* p, int csplit = 1) {
   const int nchunk = cin_pad_f32(p->d.Cin) == 4 ? 1 : cin_pad_f32(p->d.Cin) / 32;
-  return (nchunk + csplit - 1) / csplit > max_cper(p4_fwd_parts(p));
+  return (nchunk + csplit - 1) / csplit > max_cper(p->fwd_s3);
 }
 
 }  // namespace
 
-bool p4_fwd_parts(const rotconv_plan* p) { return cin_pad_f32(p->d.Cin) > 4 && p->opt.bf16_parts >= 0; }
+bool p4_fwd_parts_wanted(const rotconv_plan* p) { return cin_pad_f32(p->d.Cin) > 4 && p->opt.bf16_parts >= 0; }
 
 bool p4_fwd_supported(const rotconv_plan* p) {
   const rotconv_desc& d = p->d;
@@ -752,7 +752,7 @@ int p4_fwd_csplit(const rotconv_plan* p, bool pooled) {
   if (CinPad == 4 || d.W > 256) return 1;
   const int nchunk = CinPad / 32;
   if (nchunk < 2) return 1;
-  const int s3 = p4_fwd_parts(p), most = max_cper(s3);
+  const int s3 = p->fwd_s3, most = max_cper(s3);
   // Plan option fwd_csplit: 1 keeps the contraction whole, n >= 2 asks for n parts of equal size (as many whole chunks
   // as that takes, at most 32 parts); 0: the model, which only looks at parts that stay in LDS.
   const int forced = p->opt.fwd_csplit;
@@ -777,6 +777,17 @@ int p4_fwd_csplit(const rotconv_plan* p, bool pooled) {
     if (c < best) { best = c; best_s = s_eff; }
     if (cper == 1) break;
   }
+  // rotconv_pool_fwd_static takes what its array holds.  Where that is not the modelled split, a smaller one of up to
+  // seven chunks a part (streamed) is taken if it is: 7x1504 -> 128, 9x8 pixels: 8 parts instead of 16.
+  auto fits = [&](int s) {
+    return (double)p4_fwd_least_pack_bytes(p, 1, s) + s * part_bytes <= (double)ROTCONV_STATIC_SCRATCH_BYTES;
+  };
+  if (pooled && s3 && best_s > 1 && !fits(best_s)) {
+    for (int cper = (nchunk + best_s - 1) / best_s + 1; cper <= 7; ++cper) {
+      const int s = (nchunk + cper - 1) / cper;
+      if (s > 1 && fits(s)) return s;
+    }
+  }
   return best_s;
 }
 
@@ -793,7 +804,7 @@ int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, 
   base.N = d.N; base.Cin = d.Cin; base.CinPad = cin_pad_f32(d.Cin); base.H = d.H; base.W = d.W;
   base.Cout = d.Cout; base.CB = (d.Cout + 15) / 16; base.R = d.R; base.Q = p->host.Q; base.ng = p->ng;
   base.out_mode = out_mode;
-  base.s3 = p4_fwd_parts(p);
+  base.s3 = p->fwd_s3;
   base.relu = out_mode == kOutPooled && d.activation == ROTCONV_ACT_RELU;
   int ng = 0;
   int pos = 0;
@@ -861,7 +872,7 @@ int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, 
 // (1: no folding).
 int p4_fwd_fold(const rotconv_plan* p) {
   const int Q = p->host.Q;
-  if ((Q != 2 && Q != 4) || p->ng != 1 || !p4_fwd_parts(p)) return 1;
+  if ((Q != 2 && Q != 4) || p->ng != 1 || !p->fwd_s3) return 1;
   // a streamed filter block: only rows that the wave chains cover exactly (the instances without load masks)
   const int W = p->d.W;
   if (needs_stream(p) && ((W & 31) || (W <= 256 && (W & (W - 1))))) return 1;
@@ -875,7 +886,7 @@ int fwd_blocks(const rotconv_plan* p, int nq) { return nq > 1 ? (p->d.Cout * nq 
 // words of the packed image of one filter block (of every bank, unless they are folded into its columns)
 size_t block_words(const rotconv_plan* p, int nq) {
   const int CinPad = cin_pad_f32(p->d.Cin);
-  return (size_t)(nq > 1 ? 1 : p->host.Q) * (CinPad == 4 ? 1 : CinPad / 32) * chunk_words(CinPad, p4_fwd_parts(p));
+  return (size_t)(nq > 1 ? 1 : p->host.Q) * (CinPad == 4 ? 1 : CinPad / 32) * chunk_words(CinPad, p->fwd_s3);
 }
 }  // namespace
 
@@ -928,7 +939,7 @@ void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const fl
   for (int cb0 = 0; cb0 < blocks; cb0 += slice) {
     const int ncb = std::min(slice, blocks - cb0);
     if (!raw) {
-      const bool s3 = p4_fwd_parts(p);
+      const bool s3 = p->fwd_s3;
       const int total = (nq > 1 ? 1 : p->host.Q) * ncb * CinPad * (s3 ? 8 : 16);
       auto kern = s3 ? k_p4_pack_fwd<true> : k_p4_pack_fwd<false>;
       hipLaunchKernelGGL(kern, dim3((total + 255) / 256), dim3(256), 0, st, w, pack, p->dev.fq_src, p->dev.fq_coef,

@@ -280,3 +280,35 @@ def test_channel_split_has_the_parts_asked_for(parts, form):
     for n in parts:
         want, at = want + fwd(at, at + n, 1), at + n
     assert np.array_equal(fwd(0, 512, len(parts)), want)
+
+
+STATIC = [
+    L("t_smaller", N=7, Cin=1504, H=9, W=8, Cout=128, R=4, seed=891),                   # taken with a smaller split
+    L("t_whole", N=7, Cin=128, H=36, W=8, Cout=144, R=4, seed=892),                     # not split: four chunks
+    L("t_one_block", N=1, Cin=1300, H=4, W=8, Cout=16, R=64, mode="steerable", seed=893),     # 16 banks of one filter block
+    L("t_refused", N=4, Cin=512, H=32, W=32, Cout=128, R=4, seed=894),                  # four parts of 8 MB
+]
+
+
+@pytest.mark.parametrize("cfg", STATIC, ids=[c.name for c in STATIC])
+def test_static_scratch_takes_the_same_kernels_or_refuses(cfg):
+    """The call without a workspace never changes the order of the sums to make a layer fit."""
+    plan = rc.Plan.from_config(cfg)
+    gen = torch.Generator(device="cuda").manual_seed(cfg.seed)
+    x = torch.randn((cfg.N, cfg.Cin, cfg.H, cfg.W), generator=gen, device="cuda")
+    w = torch.randn((plan.B, cfg.Cout, cfg.Cin, 3, 3), generator=gen, device="cuda")
+
+    def run(call):
+        yp = torch.full((cfg.N, plan.Cpooled, cfg.H, cfg.W), float("nan"), device="cuda")
+        idx = torch.full(yp.shape, 254, dtype=torch.uint8, device="cuda")
+        call(plan, x, w, yp, idx)
+        return yp, idx
+
+    want = run(rc.rotconv_pool_fwd)
+    if cfg.name == "t_refused":
+        with pytest.raises(rc.RotconvError) as e:
+            run(rc.rotconv_pool_fwd_static)
+        assert e.value.status == rc.ERR_WORKSPACE
+    else:
+        got = run(rc.rotconv_pool_fwd_static)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
