@@ -348,11 +348,19 @@ __global__ __launch_bounds__(NTW, 3) void k_s3_bwd_weight(const float* __restric
 // padding.  For other turns D is a sum over table entries, three times the vector work, which the matrix cores' gain
 // does not pay for: at 4x128 -> 128, 128x128, 16 turns this split took 248 us with the table in LDS, k_p4_bwd_weight's
 // table variant takes 219.
+// Nor where a workgroup has a single step and the partial sums of all take longer than it: with up to 16 filters half of
+// what is summed is padding, with one image row half of what is multiplied.  Graph replays of 600 layers of up to 64 rows,
+// fp32 instructions / these: such layers with partial sums of more than 12 MB 0.90 of the time in the mean (5x393 -> 3, 12x20:
+// 21.8 / 31.2 us; 5x415 -> 43, 1x96: 21.4 / 32.2), those of more filters and rows 1.20 (never below 0.94), with smaller partial
+// sums up to 16 filters 1.08, two steps and more 1.2 to 2.7.
 bool s3_bwd_weight_supported(const rotconv_plan* p) {
   const rotconv_desc& d = p->d;
   const size_t lim = (size_t)1 << 30;
   if (p4_bwd_lut(p) || p->opt.bf16_parts < 0) return false;
-  return (d.Cin > 32 || p->opt.bf16_parts > 0) && (size_t)d.Cin * d.H * d.W < lim && (size_t)d.Cout * p->ng * d.H * d.W < lim;
+  const P4BwdWGeom g = s3_bwd_weight_geom(p);
+  const bool one_step = g.units <= g.splits && g.rows_per <= 2;
+  const bool short_sums = one_step && (d.Cout <= 16 || d.H == 1) && 36.0 * g.splits * g.Q * g.CoutPad * g.CinPad > 12e6;
+  return ((d.Cin > 32 && !short_sums) || p->opt.bf16_parts > 0) && (size_t)d.Cin * d.H * d.W < lim && (size_t)d.Cout * p->ng * d.H * d.W < lim;
 }
 
 P4BwdWGeom s3_bwd_weight_geom(const rotconv_plan* p) {

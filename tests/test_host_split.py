@@ -26,6 +26,11 @@ def test_selection():
     assert parts(2, 32, 96, 96, 32, k=5, pad=2) == [False] * 3
     assert parts(3, 40, 101, 75, 24, R=8, mode="steerable", pool_group=4)[0]            # odd rows: the padded plan's
     assert parts(8, 64, 256, 256, 64, pool_op="avg") == [True] * 3                      # the averaged bank's plan
+    # nor do few filters or single rows take it where the partial sums are most of the work
+    assert [parts(5, 393, 12, 20, c)[2] for c in (3, 16, 17, 64)] == [False, False, True, True]
+    assert [parts(5, 415, h, 96, 43)[2] for h in (1, 2)] == [False, True]
+    assert [parts(5, c, 12, 20, 3)[2] for c in (128, 393)] == [True, False]
+    assert parts(5, 393, 12, 20, 3, options=dict(bf16_parts=1))[2]
     # an image of the pooled gradient of 2^32 - 8 bytes: positions outside it have the offset 2^32 - 16, which would lie inside
     assert parts(1, 8, 1103, 4178, 233, R=1, options=dict(bf16_parts=1))[1] is False
     assert parts(1, 8, 1103, 4176, 233, R=1, options=dict(bf16_parts=1))[1] is True
