@@ -15,10 +15,11 @@ per step.  Next to it, for every pass (and every layer of the UNet-shaped steps 
 the default line): the flops the kernel EXECUTES (the library reports the conv-equivalents
 its matrix instructions perform), the algorithmic HBM bytes, and the fraction of the roof
 max(executed flops / matrix peak of the dtype, bytes / 8 TB/s) that the measured time
-reaches (fp32: the peak of six bf16-part products, 417 TFLOP/s).  Fractions are computed from the executed count only, so none can exceed 1; rates
-at the paper's count are given as TFLOP/s.  The default line also carries the R=16 layer
+reaches (fp32: the peak of six bf16-part products, 417 TFLOP/s).  Fractions are computed from the executed count only, so
+none can exceed 1; rates at the paper's count are given as TFLOP/s.  The default line also carries the R=16 layer
 (configuration 3, fp32 and bf16), the UNet-shaped steps (configurations 4 and 5, fp32 and
-bf16) layer by layer, and the measured matrix and copy peaks of the box.
+bf16) call by call, and the measured matrix and copy peaks of the box; `--layers FILE` writes
+the same with every layer of the steps and every count to a file.
 """
 import argparse
 import json
@@ -131,6 +132,32 @@ def check_fractions(tree, where=""):
                 bad.append((f"{where}/{k_}", v))
             bad += check_fractions(v, f"{where}/{k_}")
     return bad
+
+
+def the_line(out, layers_file=None):
+    """The JSON line of a result: short enough to be read whole by a caller that keeps the last few KB of what was
+    printed.  The layer tables of the UNet-shaped steps (20 KB each) and the counts of the appended layers stay out of it;
+    `layers_file` receives everything."""
+    if layers_file:
+        with open(layers_file, "w") as f:
+            json.dump(out, f, indent=1)
+
+    def short(v):
+        if isinstance(v, dict):
+            return {k: short(x) for k, x in v.items() if k != "layers"}
+        if isinstance(v, float):
+            return int(v) if v.is_integer() else float(f"{v:.6g}")
+        return v
+
+    line = {k: short(v) if isinstance(v, dict) else v for k, v in out.items()}
+    for layer in [*line.get("c3_r16_layer", {}).values(), line.get("c2_r4_layer_bf16", {})]:
+        for name, p in layer.get("passes", {}).items():
+            layer["passes"][name] = {k: p[k] for k in ("ms", "kernel", "tflops_executed", "bound", "frac_of_roof") if k in p}
+    for step in line.get("unet_train_step", {}).values():
+        for k in ("ms_per_step_graph_replay", "loss", "rotconv_flops_algorithmic", "rotconv_flops_executed",
+                  "rotconv_flops_dense_equivalent", "rotconv_tflops_paper_count", "peak_tflops"):
+            step.pop(k, None)
+    return json.dumps(line)
 
 
 def cpu_baseline(cfg, Q):
@@ -431,7 +458,7 @@ def main_unet(args):
         "vs_baseline": None, "dtype": args.dtype, "data": "synthetic", "config": r,
         "roofline": {"bound": "mfma",
                      "kernel": "all rotation-convolution calls of the step (fwd, bwd_data, bwd_weight; 18 layers), "
-                               "at the flops they execute; per layer and pass: config.layers",
+                               "at the flops they execute",
                      "achieved": r["rotconv_tflops_executed"], "peak": r["peak_tflops"], "unit": "TFLOP/s",
                      "frac": r["rotconv_tflops_executed"] / r["peak_tflops"],
                      "frac_of_layerwise_roof": r["rotconv_frac_of_roof"], "traffic": None},
@@ -442,7 +469,7 @@ def main_unet(args):
         print(f"bench.py: fraction above 1: {bad}", file=sys.stderr)
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline_unet(args.workload)
-    print(json.dumps(out), flush=True)
+    print(the_line(out, args.layers), flush=True)
 
 
 def main():
@@ -468,6 +495,8 @@ def main():
                     help="UNet workloads: also time the step replayed from a HIP graph (ms_per_step_graph_replay)")
     ap.add_argument("--no-unet", action="store_true",
                     help="skip what the default line appends: configuration 3, the UNet-shaped steps, the measured peaks")
+    ap.add_argument("--layers", metavar="FILE", default=None,
+                    help="also write the result with the layer tables of the UNet-shaped steps and all counts to FILE")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run one plain 1 GiB device copy (2 GiB of HBM traffic) so that rocprofv3 "
@@ -540,7 +569,7 @@ def main():
         out["cpu_baseline"] = cpu_baseline(cfg, Q)
     if args.workload == "C2" and not args.no_unet and not bf and std:
         # the rest of the headline metric: the R = 16 layer (fp32 and bf16), the R = 4 layer in bf16, ms per
-        # UNet-shaped training step at R = 4 and R = 16 layer by layer, and the box's measured peaks
+        # UNet-shaped training step at R = 4 and R = 16, and the box's measured peaks
         out["c3_r16_layer"] = {"f32": layer_summary(synth.C3, 20, 3, "f32"), "bf16": layer_summary(synth.C3, 20, 3, "bf16")}
         out["c2_r4_layer_bf16"] = layer_summary(synth.C2, 20, 3, "bf16")
         out["unet_train_step"] = {n: bench_unet(n, 5, 2) for n in ("C4", "C5")}
@@ -550,7 +579,7 @@ def main():
     if bad:
         out["accounting_error"] = [f"{w}: {v}" for w, v in bad]
         print(f"bench.py: fraction above 1: {bad}", file=sys.stderr)
-    print(json.dumps(out), flush=True)
+    print(the_line(out, args.layers), flush=True)
 
 
 if __name__ == "__main__":
