@@ -55,8 +55,8 @@
  *     the group; where only some responses are NaN it may be NaN or the maximum
  *     of the others.  fp32 passes that multiply bf16 parts of the operands
  *     (rotconv_plan_bf16_parts) make NaN of an infinity and of magnitudes from
- *     3.396e38 on; all others, and these with plan option bf16_parts = -1,
- *     follow IEEE arithmetic.
+ *     3.396e38 on, and hold magnitudes below 2^-110 to 2^-134 only; all others,
+ *     and these with plan option bf16_parts = -1, follow IEEE arithmetic.
  *   - Return value: a rotconv_status.  Argument errors are found on the host
  *     before anything is launched and leave the outputs untouched.
  */

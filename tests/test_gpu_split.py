@@ -312,3 +312,31 @@ def test_static_scratch_takes_the_same_kernels_or_refuses(cfg):
     else:
         got = run(rc.rotconv_pool_fwd_static)
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+def test_small_magnitudes():
+    """From 2^-110 up the parts hold a float whole: results scale with it bit for bit.  Below, a value is held to 2^-134,
+    half a unit of the smallest bf16 number; on the fp32 instructions (bf16_parts = -1) it is not."""
+    cfg = L("s_tiny", N=1, Cin=40, H=6, W=32, Cout=24, R=4, x_dist="normal", seed=898)
+    rng = np.random.default_rng(cfg.seed)
+
+    def unit(*shape):
+        return (rng.uniform(1, 2, shape) * rng.choice([-1, 1], shape)).astype(np.float32)
+
+    x, w = unit(cfg.N, cfg.Cin, cfg.H, cfg.W), unit(1, cfg.Cout, cfg.Cin, 3, 3)
+    g, idx = unit(cfg.N, cfg.Cout, cfg.H, cfg.W), rng.integers(0, 4, (cfg.N, cfg.Cout, cfg.H, cfg.W)).astype(np.uint8)
+
+    def passes(e, form):
+        lay = pu.GpuLayer(cfg, np.ldexp(x, e), w, options=dict(bf16_parts=form))
+        gone = pu.GpuLayer(cfg, x, w, options=dict(bf16_parts=form)).pool_bwd_data(np.ldexp(g, e), idx)
+        return lay.fwd().cpu().numpy(), lay.pool_bwd_weight(g, idx), gone
+
+    whole = passes(0, 1)
+    for e in (-60, -110):
+        assert all(np.array_equal(a, np.ldexp(b, e)) for a, b in zip(passes(e, 1), whole))
+    # at most 9 * 40 (forward), 192 (weight gradient), 9 * 24 products of a value held to 2^-134 and one below 2, in units of 2^-120
+    for a, b, n in zip(passes(-120, 1), whole, (360, 192, 216)):
+        err = np.abs(np.ldexp(a.astype(np.float64), 120) - b)
+        assert 0 < err.max() < n * 2 * 2.0 ** (120 - 134) + 1e-6 * np.abs(b).max()
+    assert all(_rel(np.ldexp(a.astype(np.float64), 120), b.astype(np.float64)) < 1e-6
+               for a, b in zip(passes(-120, -1), whole))
