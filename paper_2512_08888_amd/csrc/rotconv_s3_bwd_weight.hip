@@ -210,7 +210,7 @@ __global__ __launch_bounds__(NTW, 3) void k_s3_bwd_weight(const float* __restric
   auto split_x = [&](const XRaw& k, int p, u32x4 (&o)[3]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const S3Pair s = s3_split2<true>(sign * k.v[p][0][i], sign * k.v[p][1][i]);
+      const S3Pair s = s3_split2_add(sign * k.v[p][0][i], sign * k.v[p][1][i]);
 #pragma unroll
       for (int e = 0; e < 3; ++e) o[e][i] = s.p[e];
     }
