@@ -18,17 +18,18 @@
 // Nothing R-fold ever reaches memory, and the input row is read once per bank.
 //
 // What bounds it: 108 matrix instructions (16 clk) per 32-channel chunk, row and
-// wave, and some 100 vector instructions for splitting the pixel operands beside
-// about 500 per row for the placement; eight waves of a workgroup share a row and
-// meet at its barrier, so the two add up.  8 x 64 -> 64 channels at 256 x 256, four
-// quarter turns: 0.369 ms with fp32 instructions (32 clk each, 288 per chunk pair
-// and row), 0.218 ms so; 512 -> 512 at 32 x 32, batch 4: 0.246 -> 0.187 ms.
+// wave, and some 160 vector instructions for splitting the pixel operands and adding
+// up the chunks beside about 500 per row for the placement; eight waves of a
+// workgroup share a row and meet at its barrier, so the two add up.  8 x 64 -> 64
+// channels at 256 x 256, four quarter turns: 0.369 ms with fp32 instructions (32 clk
+// each, 288 per chunk pair and row), 0.218 ms so; 512 -> 512 at 32 x 32, batch 4:
+// 0.246 -> 0.189 ms; 128 -> 128 at 128 x 128, batch 4: 0.201 -> 0.118 ms.
 //
 // The filter block (16 filters x all input channels x 9 taps x 3 parts) stays
-// resident in LDS for the life of the workgroup when it fits (Cin <= 160); deeper
-// inputs stream it through two 32-channel LDS buffers, one barrier per chunk.  Input
-// rows go straight from global memory into the A-operand registers (8-byte
-// loads, 128 B contiguous per 16 lanes), each slot refilled one chunk ahead;
+// resident in LDS for the life of the workgroup when it fits (Cin <= 160; 224 with
+// fp32 instructions); deeper inputs stream it through two 32-channel LDS buffers, one
+// barrier per chunk.  Input rows go straight from global memory into the A-operand
+// registers (8-byte loads, 128 B contiguous per 16 lanes), refilled one chunk ahead;
 // scheduling fences keep those loads and the LDS reads of the B operand where
 // they are issued (the compiler would otherwise sink them to their first use).
 //
@@ -85,7 +86,8 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
   constexpr int NT = 64 * NW;
   constexpr int CHF = S3 ? kChunkS3 : KC * 4 * 144;      // floats of one chunk of the filter block
   extern __shared__ float smem[];
-  float* Wl = smem;                      // resident: [CinPad][9][16]; streamed: [2][32][9][16]
+  float* Wl = smem;                      // [chunks of the part, or 2 if streamed][CHF]; a chunk: parts [tap][part][lane][8 bf16],
+                                         // fp32 [channel][tap][filter]
   float* EL = smem + (STREAM ? 2 * CHF : g.cper * CHF);    // [2][NW][8][16] left-edge values of every wave
   float* ER = EL + 2 * NW * 128;         // [2][NW][8][16] right-edge values
 
@@ -226,8 +228,8 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
 #pragma unroll
     for (int j = 0; j < 8; ++j) { accA[s][j] = 0.f; accB[s][j] = 0.f; }
 
-  // A operands of one 32-channel chunk; each slot is refilled for the next chunk (possibly of the
-  // next row) right after its MFMAs have been issued, so the prefetch distance is one chunk.
+  // A operands of one 32-channel chunk, refilled for the next chunk (possibly of the next row): with parts as soon as
+  // they are split, with fp32 instructions each slot right after its MFMAs.  The prefetch distance is one chunk.
   float2 a_cur[KC];
   {
     const float* rp = row_ptr(0);
@@ -245,9 +247,9 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
     const float* rp_nxt = row_ptr(t + 1);
     f4 P[9][2];   // written by the row's first K-step (accumulator input = constant zero), or zeroed below
 
-    // One 32-channel chunk: MFMAs of its eight K-steps, each slot of A refilled for the next chunk right
-    // after its MFMAs, B read from LDS one K-step ahead.  The scheduling fences keep loads and LDS reads
-    // where they are issued; left alone the compiler sinks them next to their first use and waits there.
+    // One chunk: parts tap by tap, fp32 instructions K-step by K-step, the weights read from LDS one tap or K-step ahead.
+    // The scheduling fences keep loads and LDS reads where they are issued; left alone the compiler sinks them next to
+    // their first use and waits there.
     auto chunk = [&](int c, bool first) {
       if (STREAM) asm volatile("" : "+s"(c));      // opaque: addresses are formed where they are used, not kept (and spilled) per chunk
       const bool last = c + 1 == c_hi;

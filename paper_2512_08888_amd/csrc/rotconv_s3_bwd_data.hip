@@ -20,8 +20,8 @@
 // waves of a SIMD have registers for, so the two together are 4.1 us of matrix and 2.7 us of vector work a K-step.  They
 // are kept half a K-step apart, one building its operands while the other multiplies: the first four waves of a workgroup
 // meet the K-step's barrier before they build, the last four after (all before: 342 against 285 us at 8x64 -> 64, 256x256).
-// Against the kernels on fp32 matrix cores: 8x64 -> 64, 256x256 379 -> 285 us, 4x512 -> 512, 32x32 213 -> 164,
-// 4x128 -> 128, 128x128 189 -> 160, 8x512 -> 512, 16x16 209 -> 99.
+// Against the kernels on fp32 matrix cores (the same box, us): 8x64 -> 64, 256x256 391 -> 286, 4x512 -> 512, 32x32
+// 211 -> 165, 4x128 -> 128, 128x128 187 -> 164, 8x512 -> 512, 16x16 209 -> 104.
 //
 // Precision: the matrix instruction cuts its sums, so of a K-step's 54 per channel block only the nine main products are
 // added at the sum's full size.  Tap by tap (all 54 at full size) the error of few filters was above that of the fp32
@@ -398,7 +398,7 @@ S3BwdPlan s3_bwd_plan(const rotconv_plan* p) {
 // weights' parts and, where it is shared out over workgroups, for the sum of the partial results.  Measured, fp32
 // matrix cores / bf16 parts (us): not shared out, 0.6 GFLOP 25.8 / 32.8 (8x64 -> 64, 32x32), 1.2 GFLOP 64.7 / 51.0 (4x16 -> 64, 128x128),
 // 2.4 GFLOP 45.2 / 37.8 (2x64 -> 64, 128x128); shared out, 1.2 GFLOP 26.8 / 31.8 (2x64 -> 128, 64x64), 2.4 GFLOP 40.1 / 42.5
-// (2x256 -> 256, 32x32), 9.7 GFLOP 209 / 99 (8x512 -> 512, 16x16).  For other turns than quarter turns D is a sum over
+// (2x256 -> 256, 32x32), 9.7 GFLOP 209 / 104 (8x512 -> 512, 16x16).  For other turns than quarter turns D is a sum over
 // table entries and the fp32 table kernels stay the faster ones (4x128 -> 128, 128x128, 16 turns: 214 / 226).
 bool s3_bwd_data_supported(const rotconv_plan* p) {
   if (!p4_bwd_data_supported(p) || p4_bwd_lut(p) || p->opt.bf16_parts < 0) return false;

@@ -14,10 +14,10 @@
 // instructions run beside another's matrix instructions).  LDS is double-buffered, one barrier per step; half of the
 // builders multiply first and build afterwards.
 //
-// What bounds it: with 128 channels per workgroup the matrix cores (six products: 89 us of the 125 at 4x128 -> 128,
-// 128x128; fp32 matrix cores, which need 145 us for one product each, took 185), with 64 the vector work of building
-// (about 830 instructions per SIMD and step beside 54 matrix instructions; 8x64 -> 64, 256x256: 296 us, was 352).
-// 4x512 -> 512, 32x32: 131 us, was 192; 2x256 -> 256, 32x32: 39, was 48.
+// What bounds it: with 128 channels per workgroup the matrix cores (six products: 89 us of the 118 at 4x128 -> 128,
+// 128x128; fp32 matrix cores, which need 145 us for one product each, took 182), with 64 the vector work of building
+// (about 830 instructions per SIMD and step beside 54 matrix instructions; 8x64 -> 64, 256x256: 284 us, was 370).
+// 4x512 -> 512, 32x32: 126 us, was 188; 2x256 -> 256, 32x32: 39, was 47; 8x512 -> 512, 16x16: 79, was 196.
 // Precision: the parts' sum of each 16 pixels starts from zero and only its total meets the running sum.  The matrix
 // instruction cuts the low bits of what it adds up towards minus infinity; over the pixels of a batch that offset grows
 // with their number while the sum itself grows with its root (8x64 -> 64, 256x256: 1.7e-6 of the norm).  So every
