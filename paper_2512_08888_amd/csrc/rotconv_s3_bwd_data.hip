@@ -398,7 +398,9 @@ S3BwdPlan s3_bwd_plan(const rotconv_plan* p) {
 // weights' parts and, where it is shared out over workgroups, for the sum of the partial results.  Measured, fp32
 // matrix cores / bf16 parts (us): not shared out, 0.6 GFLOP 25.8 / 32.8 (8x64 -> 64, 32x32), 1.2 GFLOP 64.7 / 51.0 (4x16 -> 64, 128x128),
 // 2.4 GFLOP 45.2 / 37.8 (2x64 -> 64, 128x128); shared out, 1.2 GFLOP 26.8 / 31.8 (2x64 -> 128, 64x64), 2.4 GFLOP 40.1 / 42.5
-// (2x256 -> 256, 32x32), 9.7 GFLOP 209 / 104 (8x512 -> 512, 16x16).  For other turns than quarter turns D is a sum over
+// (2x256 -> 256, 32x32), 9.7 GFLOP 209 / 104 (8x512 -> 512, 16x16).  Of 690 random layers on this side of the line six
+// took more than 5 % longer than on the fp32 instructions (up to 34 %; below 2.3 GFLOP, more than 64 channels, whose groups
+// share D there, rows that fit its waves); the mean took 0.58 of the time.  For other turns than quarter turns D is a sum over
 // table entries and the fp32 table kernels stay the faster ones (4x128 -> 128, 128x128, 16 turns: 214 / 226).
 bool s3_bwd_data_supported(const rotconv_plan* p) {
   if (!p4_bwd_data_supported(p) || p4_bwd_lut(p) || p->opt.bf16_parts < 0) return false;
