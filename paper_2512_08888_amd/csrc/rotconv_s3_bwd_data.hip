@@ -23,10 +23,6 @@
 // Against the kernels on fp32 matrix cores (the same box, us): 8x64 -> 64, 256x256 391 -> 286, 4x512 -> 512, 32x32
 // 211 -> 165, 4x128 -> 128, 128x128 187 -> 164, 8x512 -> 512, 16x16 209 -> 104.
 //
-// Precision: the matrix instruction cuts its sums, so of a K-step's 54 per channel block only the nine main products are
-// added at the sum's full size.  Tap by tap (all 54 at full size) the error of few filters was above that of the fp32
-// instructions (48 -> 24: 1.6e-7 of the norm against 1.3e-7; now 5.6e-8; 512 -> 512: 1.9e-7, 3.9e-7, now 9.2e-8), for 1 %
-// less time.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -79,7 +75,8 @@ __device__ __forceinline__ float from_right(float v) {
 }
 
 // TB: 32-channel blocks per workgroup (the weights of a K-step fill one of two LDS buffers).
-template <int TB>
+// LAST: the main products of all nine taps after the small ones of all, else tap by tap (see s3_mains_last).
+template <int TB, bool LAST>
 __global__ __launch_bounds__(NT, 2) void k_s3_bwd_data(const float* __restrict__ gpool, const uint8_t* __restrict__ idx,
                                                        const u32x4* __restrict__ wp, const int32_t* __restrict__ rot_of,
                                                        float* __restrict__ dx, S3BwdGeom g) {
@@ -244,14 +241,13 @@ __global__ __launch_bounds__(NT, 2) void k_s3_bwd_data(const float* __restrict__
     if (!early) __syncthreads();
     const u32x4* nsrc = wsrc(vn, kn);
     const u32x4* wl = Wl + buf * STG + lane;
-    u32x4 wv[2][3], w0[2];
+    u32x4 wv[2][3];
+    [[maybe_unused]] u32x4 w0[2];
 #pragma unroll
     for (int e = 0; e < 3; ++e) wv[0][e] = wl[e * 64];
 #pragma unroll
     for (int b = 0; b < TB; ++b) {
-      // A K-step's sum starts from zero and is added to the running one; the small products of all nine taps first, so
-      // that the instruction cuts the sum at its full size nine times only (the first part of the weights is read twice).
-      s3_f16 t;
+      s3_f16 t;      // a K-step's sum starts from zero and is added to the running one
 #pragma unroll
       for (int r = 0; r < 16; ++r) t[r] = 0.f;
 #pragma unroll
@@ -261,10 +257,10 @@ __global__ __launch_bounds__(NT, 2) void k_s3_bwd_data(const float* __restrict__
           if (st > 0) wstore(buf ^ 1, st / STEP - 1);
           if (st / STEP < NP) wload(nsrc, st / STEP);
         }
-        if (u + 1 < 9) {
+        if (LAST ? u + 1 < 9 : st + 1 < TB * 9) {
 #pragma unroll
-          for (int e = 0; e < 3; ++e) wv[(u + 1) & 1][e] = wl[((st + 1) * 3 + e) * 64];
-        } else {
+          for (int e = 0; e < 3; ++e) wv[(LAST ? u + 1 : st + 1) & 1][e] = wl[((st + 1) * 3 + e) * 64];
+        } else if (LAST) {
           w0[0] = wl[b * 27 * 64];
         }
         if (st == TB * 9 - 5 && next) {
@@ -272,23 +268,27 @@ __global__ __launch_bounds__(NT, 2) void k_s3_bwd_data(const float* __restrict__
           load_raw(kn, 0, PRE);
         }
         __builtin_amdgcn_sched_barrier(0);
-        const u32x4* w = wv[u & 1];
+        // the smallest products first
+        const u32x4* w = wv[(LAST ? u : st) & 1];
         t = s3_mfma32(w[2], op[u][0], t);
         t = s3_mfma32(w[0], op[u][2], t);
         t = s3_mfma32(w[1], op[u][1], t);
         t = s3_mfma32(w[0], op[u][1], t);
         t = s3_mfma32(w[1], op[u][0], t);
+        if constexpr (!LAST) t = s3_mfma32(w[0], op[u][0], t);
       }
+      if constexpr (LAST) {      // the first parts of the weights once more
 #pragma unroll
-      for (int u = 0; u < 9; ++u) {
-        if (u + 1 < 9) {
-          w0[(u + 1) & 1] = wl[(b * 9 + u + 1) * 3 * 64];
-        } else if (b + 1 < TB) {
+        for (int u = 0; u < 9; ++u) {
+          if (u + 1 < 9) {
+            w0[(u + 1) & 1] = wl[(b * 9 + u + 1) * 3 * 64];
+          } else if (b + 1 < TB) {
 #pragma unroll
-          for (int e = 0; e < 3; ++e) wv[0][e] = wl[((b + 1) * 27 + e) * 64];
+            for (int e = 0; e < 3; ++e) wv[0][e] = wl[((b + 1) * 27 + e) * 64];
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          t = s3_mfma32(w0[u & 1], op[u][0], t);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        t = s3_mfma32(w0[u & 1], op[u][0], t);
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[b][r] += t[r];
@@ -351,6 +351,14 @@ __global__ __launch_bounds__(256) void k_s3_pack_bwd(const float* __restrict__ w
     for (int z = 0; z < 3; ++z) dst[(u * 3 + z) * 256] = (uint32_t)pa[z] | (uint32_t)pb[z] << 16;
   }
 }
+
+// The matrix instruction cuts its sums, up to 54 times a K-step and channel block at the sum's full size when each tap's six
+// products are added in turn; with the small products of all taps first, nine times.  Error of the norm, fp32 instructions /
+// tap by tap / mains last: 9 filters 1.38e-7 / 1.55e-7 / below 6e-8, 24 filters 1.32e-7 / 1.56e-7 / 5.6e-8, 32 filters
+// 2.2e-7 / 1.7e-7 / 5.9e-8, 64 2.8e-7 / 1.7e-7 / 6.6e-8, 512 3.9e-7 / 1.9e-7 / 9.2e-8, 2048 (64 channels) 2.47e-7 / 2.48e-7 / 1.64e-7.
+// The second reading of the weights' first parts costs 3 % (8x64 -> 64, 256x256: 275.5 / 283.7 us, 4x128 -> 128, 128x128
+// 160.4 / 164.1): it is taken where the shorter form would be less precise than the fp32 instructions.
+constexpr bool s3_mains_last(int Cout) { return Cout < 32 || Cout > 1024; }
 
 struct S3BwdPlan { S3BwdGeom g; int TB; };
 
@@ -438,8 +446,11 @@ void launch_s3_bwd_data(const rotconv_plan* p, const float* gpool, const uint8_t
     hipLaunchKernelGGL(kern, dim3(std::min(256, (g.units + 7) / 8 * 8)), dim3(NT), lds, st, gpool, idx, static_cast<const u32x4*>(pack),
                        p->dev.rot_of, dx, g);
   };
-  if (b.TB == 1) go(k_s3_bwd_data<1>);
-  else go(k_s3_bwd_data<2>);
+  if (s3_mains_last(g.Cout)) {
+    if (b.TB == 1) go(k_s3_bwd_data<1, true>); else go(k_s3_bwd_data<2, true>);
+  } else {
+    if (b.TB == 1) go(k_s3_bwd_data<1, false>); else go(k_s3_bwd_data<2, false>);
+  }
   if (g.ksplit > 1) launch_p4_sum_dx(part, dx_out, (size_t)p->d.N * p->d.Cin * p->d.H * p->d.W, g.ksplit, st);
 }
 

@@ -249,7 +249,7 @@ def test_forward_is_no_less_precise_than_fp32_instructions(cfg):
     assert err[0] <= err[1], err
 
 
-@pytest.mark.parametrize("cout", [9, 16, 24, 40, 200])
+@pytest.mark.parametrize("cout", [9, 16, 24, 31, 32, 40, 200, 1024, 1025])
 def test_gradients_are_no_less_precise_than_fp32_instructions(cout):
     """Against 64 bits, on the same inputs; the contraction of the input gradient runs over the filters."""
     cfg = L(f"p_g{cout}", N=2, Cin=48, H=24, W=36, Cout=cout, R=4, x_dist="absnormal", seed=875 + cout)
