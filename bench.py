@@ -18,7 +18,7 @@ max(executed flops / matrix peak of the dtype, bytes / 8 TB/s) that the measured
 reaches (fp32: the peak of six bf16-part products, 417 TFLOP/s).  Fractions are computed from the executed count only, so
 none can exceed 1; rates at the paper's count are given as TFLOP/s.  The default line also carries the R=16 layer
 (configuration 3, fp32 and bf16), the UNet-shaped steps (configurations 4 and 5, fp32 and
-bf16) call by call, and the measured matrix and copy peaks of the box; `--layers FILE` writes
+bf16) call by call, and the measured matrix and copy peaks of the card; `--layers FILE` writes
 the same with every layer of the steps and every count to a file.
 """
 import argparse
@@ -166,7 +166,7 @@ def cpu_baseline(cfg, Q):
     from oracle import rotconv_oracle as orc
     from paper_2512_08888_amd import synth
 
-    # about 10-30 s of CPU work on the 16 host cores of the GPU machine: dense flops of the sample near 1.6e11 per pass
+    # about 10-30 s of CPU work on 16 host cores: dense flops of the sample near 1.6e11 per pass
     n_s = max(1, min(cfg.N, int(1.6e11 / (flops_dense(cfg) / cfg.N))))
     h_s = cfg.H
     if n_s == 1 and flops_dense(cfg) / cfg.N > 3.2e11:
@@ -569,7 +569,7 @@ def main():
         out["cpu_baseline"] = cpu_baseline(cfg, Q)
     if args.workload == "C2" and not args.no_unet and not bf and std:
         # the rest of the headline metric: the R = 16 layer (fp32 and bf16), the R = 4 layer in bf16, ms per
-        # UNet-shaped training step at R = 4 and R = 16, and the box's measured peaks
+        # UNet-shaped training step at R = 4 and R = 16, and the measured peaks
         out["c3_r16_layer"] = {"f32": layer_summary(synth.C3, 20, 3, "f32"), "bf16": layer_summary(synth.C3, 20, 3, "bf16")}
         out["c2_r4_layer_bf16"] = layer_summary(synth.C2, 20, 3, "bf16")
         out["unet_train_step"] = {n: bench_unet(n, 5, 2) for n in ("C4", "C5")}

@@ -20,7 +20,7 @@
 // waves of a SIMD have registers for, so the two together are 4.1 us of matrix and 2.7 us of vector work a K-step.  They
 // are kept half a K-step apart, one building its operands while the other multiplies: the first four waves of a workgroup
 // meet the K-step's barrier before they build, the last four after (all before: 342 against 285 us at 8x64 -> 64, 256x256).
-// Against the kernels on fp32 matrix cores (the same box, us): 8x64 -> 64, 256x256 391 -> 286, 4x512 -> 512, 32x32
+// Against the kernels on fp32 matrix cores (the same card, us): 8x64 -> 64, 256x256 391 -> 286, 4x512 -> 512, 32x32
 // 211 -> 165, 4x128 -> 128, 128x128 187 -> 164, 8x512 -> 512, 16x16 209 -> 104.
 //
 #include <hip/hip_runtime.h>

@@ -1,10 +1,11 @@
 """The fp32 kernels that multiply bf16 parts of their operands: edges of their tiles and of their dispatch against the
-oracle, exact scaling by powers of two (the parts of a value scale with it, whatever its magnitude), non-finite inputs,
-and banks that the static scratch holds a slice of at a time.
+oracle, both forms of the products (plan option bf16_parts), lone products and precision against the fp32 instructions,
+exact scaling by powers of two (down to where a value's parts are bf16 numbers) and what is lost below, non-finite inputs,
+channel splits, and what the static scratch takes.
 
-Error bar: a 32-term instruction rounds six sums per 32 channels, each to half an ulp of the running sum, so a sum over
-K channels and nine taps is within about sqrt(6 K / 32) * 2^-24 of its value in norm; the bar is 1e-6, four times that
-for the deepest case (K = 600).
+Error bar where none is given: a 32-term instruction cuts six sums per 32 channels, the last by up to an ulp of its own
+size, so a sum over K channels and nine taps is within about sqrt(6 K / 32) * 2^-24 of its value in norm; the bar is 1e-6,
+four times that for the deepest case (K = 600).
 """
 import numpy as np
 import pytest
