@@ -138,7 +138,8 @@ void choose_fwd(rotconv_plan* p) {
     return fwd_fast_least_bytes(p) <= ROTCONV_STATIC_SCRATCH_BYTES;
   };
   const int s3 = p4_fwd_parts_wanted(p);
-  if (!choose(s3) && s3 && p->d.Cout <= 16 && p->opt.bf16_parts == 0 && !choose(0)) choose(1);
+  if (!choose(s3) && s3 && p->d.Cout <= 16 && p->opt.bf16_parts == 0 && p4_fwd_f32_rows(p) && !choose(0)) choose(1);
+  p4_fwd_choose_launches(p);
 }
 
 // the fp32 path's own need (a bf16 plan adds its staging areas in front, see carve())
@@ -395,7 +396,8 @@ static int f32_rotconv_fwd(const rotconv_plan* plan, const void* x, const void* 
   if ((rc = ensure_device_tables(p))) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int cs = p->fwd_csplit[0];
-  if (p->fast[0] && aligned(x, 8) && aligned(ws, cs > 1 ? 256 : 16) && aligned(y, 16)) {
+  const bool odd = p->d.W & 1;       // rows whose pixel pairs the kernel does not load or store as pairs
+  if (p->fast[0] && aligned(x, odd ? 4 : 8) && aligned(ws, cs > 1 ? 256 : 16) && aligned(y, odd ? 4 : 16)) {
     const size_t parts = fwd_part_bytes(p, cs);       // small map, deep input: the channels are split over workgroups
     float* out = cs > 1 ? static_cast<float*>(ws) : static_cast<float*>(y);
     launch_p4_fwd(p, kOutUnpooled, static_cast<const float*>(x), static_cast<const float*>(w),
@@ -477,7 +479,9 @@ static int f32_orient_maxpool_bwd(const rotconv_plan* plan, const void* gpool, c
 // Does the pooled forward of an fp32 plan run the register-resident kernel for these pointers?
 static bool f32_pool_fwd_is_fast(const rotconv_plan* p, const void* x, const void* ypool, const uint8_t* idx,
                                  const void* ws) {
-  return !p->avg_child && p->fast[0] && aligned(x, 8) && aligned(ws, 256) && aligned(ypool, 16) && aligned(idx, 8);
+  const bool odd = p->d.W & 1;
+  return !p->avg_child && p->fast[0] && aligned(x, odd ? 4 : 8) && aligned(ws, 256) && aligned(ypool, odd ? 4 : 16) &&
+         aligned(idx, odd ? 1 : 8);
 }
 
 // Scratch the pooled forward of an fp32 plan needs: the packed banks (+ candidates) of the register-resident kernel;

@@ -23,20 +23,45 @@ struct P4Geom {
   int s3;        // products of the operands' bf16 parts (plan field fwd_s3)
   int csplit;    // parts the channel contraction is split into (1: none); a part is an unpooled fp32 map
   int cper;      // 32-channel chunks per part (all of them without a split)
-  int cost;      // modelled cost of the launch (host side only)
+  double cost;   // modelled time of the launch, 0.1 us (host side only)
   int cb0;       // first filter block of this launch
   int raw_w;     // the weight argument is the caller's w[Cout][Cin][9] itself (see p4_fwd_raw_weights)
   int seg_xorg[4];  // first product column of a segment's wave chain
   int seg_lo[4], seg_hi[4];  // output pixels [lo, hi) the segment stores (multiples of 8, or W)
 };
 
+// forward on bf16 parts of fp32 operands (rotconv_s3_fwd.hip)
+constexpr int kS3FwdChunk = 9 * 3 * 256;     // 4-byte words of a 32-channel chunk of a 16-filter block: [tap][part][lane][8 bf16]
+constexpr int kS3FwdResident = 5;            // chunks of a filter block that stay in LDS; more are streamed
+struct S3FwdGeom {
+  int N, Cin, CinPad, H, W, Cout, CB, R, Q, ng, out_mode, relu, nq;
+  int csplit, cper, cb0, raw_w;  // as in P4Geom
+  int stream;    // filter blocks streamed through LDS
+  int all_turns; // every bank has its four quarter turns
+  int Wv;        // columns of a row on the line of bands: the pixels and one or two empty ones
+  int line_imgs; // images on one line
+  int TY, nband; // output rows per band, bands per image
+  int nvr;       // bands on the line
+  int nstrip;    // waves that cover the line
+  int nw, nsg;   // waves per workgroup, workgroups that cover the line
+  int units;     // workgroups with work
+  double cost;   // modelled time of the launch, 0.1 us
+};
+bool s3_fwd_supported(const rotconv_plan* p);      // sizes only
+// the cheapest rows per band and waves per workgroup, or those given
+S3FwdGeom s3_fwd_geom(const rotconv_plan* p, int out_mode, int csplit, int nq, int ty = 0, int nw = 0);
+void launch_s3_fwd(const S3FwdGeom& g, const float* x, const float* wt, const int32_t* rot_of, float* out_val, uint8_t* out_idx,
+                   hipStream_t st);
+
 // forward
 bool p4_fwd_supported(const rotconv_plan* p);
+bool p4_fwd_f32_rows(const rotconv_plan* p);       // rows that the kernel on fp32 instructions takes
 bool p4_fwd_parts_wanted(const rotconv_plan* p);   // may the kernel multiply bf16 parts of the operands (plan field fwd_s3)?
-int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, int csplit = 1, int nq = 1);
+int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, int csplit = 1);
 // parts the forward splits its channel contraction into for this plan (1: none); with a split the kernel runs in
 // the unpooled mode into `csplit` parts of N * Cout * R * H * W floats, added by one of the two kernels below
 int p4_fwd_csplit(const rotconv_plan* p, bool pooled);
+void p4_fwd_choose_launches(rotconv_plan* p);   // fills fwd_launch, after the channel splits
 void launch_p4_sum_parts(const rotconv_plan* p, const float* part, int nparts, float* y, hipStream_t st);
 void launch_p4_sum_pool(const rotconv_plan* p, const float* part, int nparts, float* ypool, uint8_t* idx,
                         hipStream_t st);   // applies the plan's fused activation

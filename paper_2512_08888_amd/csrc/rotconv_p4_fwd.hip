@@ -58,33 +58,22 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 // S3: bf16 parts of the operands (rotconv_split3.h), KC = 8 only; else fp32 instructions
 int cin_pad_f32(int Cin) { return Cin <= 4 ? 4 : (Cin + 31) / 32 * 32; }
 
-// 4-byte words of one 32-channel chunk of a 16-filter block as matrix operands: [tap][part][lane][8 bf16]
-constexpr int kChunkS3 = 9 * 3 * 256;
-constexpr int chunk_words(int CinPad, int s3) { return s3 ? kChunkS3 : (CinPad == 4 ? 4 : 32) * 144; }
-constexpr int max_cper(int s3) { return s3 ? 5 : 7; }      // chunks of a block that stay in LDS beside the edge arrays
-
-// The matrix instruction cuts its sums towards minus infinity, an offset of one sign in every product P_u that grows with
-// the channels while their sum grows with the root of their number (1024 -> 32 channels: 1.1e-7 of the norm, more than all
-// else together).  So the parts of every other tap's weights are stored with their signs turned, and those taps' products
-// are subtracted where they are placed: the offsets cancel (five taps against four).
-constexpr bool tap_turned(int u) { return u & 1; }
-constexpr uint32_t tap_sign(int u) { return tap_turned(u) ? 0x80008000u : 0u; }      // on a packed pair
+// 4-byte words of one 32-channel chunk of a 16-filter block: parts as matrix operands, else [channel][tap][filter]
+constexpr int chunk_words(int CinPad, int s3) { return s3 ? kS3FwdChunk : (CinPad == 4 ? 4 : 32) * 144; }
+constexpr int max_cper(int s3) { return s3 ? kS3FwdResident : 7; }      // chunks of a block that stay in LDS
 
 // UNPOOLED: write every orientation (rotconv_fwd); else max + arg-max over the bank's rotations.
-// FASTW:    W % 8 == 0 and no wave chain reaches beyond the row: no load masks, vector stores.
+// FASTW:    W % 8 == 0 and no wave chain reaches beyond the row: no load masks, vector stores.  With bf16 parts always
+//           (other rows: rotconv_s3_fwd.hip).
 // STREAM:   the filter block does not fit LDS: stream it in 32-channel chunks.
-// NQ: banks folded into the 16 filter columns of a wave (1, 2 or 4).  NQ > 1 serves a pool group that spans all NQ
-//     banks of the plan (R = 4 NQ orientations pooled together): column n holds bank n / (16/NQ), filter n % (16/NQ);
-//     every lane places and maximises its own bank's four rotations and the maximum across the banks is a
-//     rotate-and-compare inside the 16-lane row (DPP), so no per-bank candidates go through memory.
-template <int NWX, int NWY, bool UNPOOLED, bool FASTW, bool STREAM, bool S3, int KC, int NQ>
+template <int NWX, int NWY, bool UNPOOLED, bool FASTW, bool STREAM, bool S3, int KC>
 __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restrict__ x, const float* __restrict__ wt,
                                                            const int32_t* __restrict__ rot_of,
                                                            float* __restrict__ out_val, uint8_t* __restrict__ out_idx,
                                                            P4Geom g) {
   constexpr int NW = NWX * NWY;
   constexpr int NT = 64 * NW;
-  constexpr int CHF = S3 ? kChunkS3 : KC * 4 * 144;      // floats of one chunk of the filter block
+  constexpr int CHF = S3 ? kS3FwdChunk : KC * 4 * 144;      // floats of one chunk of the filter block
   extern __shared__ float smem[];
   float* Wl = smem;                      // [chunks of the part, or 2 if streamed][CHF]; a chunk: parts [tap][part][lane][8 bf16],
                                          // fp32 [channel][tap][filter]
@@ -150,14 +139,14 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
         float v0[9], v1[9];
 #pragma unroll
         for (int u = 0; u < 9; ++u) { v0[u] = ok0 ? w0[u] : 0.f; v1[u] = ok1 ? w0[9 + u] : 0.f; }
-        uint32_t* dst = Wu + (i / 256) * kChunkS3 + i % 256;
+        uint32_t* dst = Wu + (i / 256) * kS3FwdChunk + i % 256;
 #pragma unroll
         for (int u = 0; u < 9; ++u) {
           uint16_t a[3], b[3];
           s3_split_weight(v0[u], a[0], a[1], a[2]);
           s3_split_weight(v1[u], b[0], b[1], b[2]);
 #pragma unroll
-          for (int k = 0; k < 3; ++k) dst[(u * 3 + k) * 256] = ((uint32_t)a[k] | (uint32_t)b[k] << 16) ^ tap_sign(u);
+          for (int k = 0; k < 3; ++k) dst[(u * 3 + k) * 256] = ((uint32_t)a[k] | (uint32_t)b[k] << 16) ^ (s3_tap_turned(u) ? 0x80008000u : 0u);
         }
       }
     } else {
@@ -194,11 +183,9 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
   const int nsteps = g.TY + 2;
   const int HW = g.H * g.W;
 
-  constexpr int FPB = 16 / NQ;               // filters per wave
-  const int qi = NQ > 1 ? lc / FPB : q;       // this lane's bank
   int rot[4];
 #pragma unroll
-  for (int s = 0; s < 4; ++s) rot[s] = rot_of[qi * 4 + s];
+  for (int s = 0; s < 4; ++s) rot[s] = rot_of[q * 4 + s];
 
   // A-operand loads: lane (lc, lg) reads X[ci][h][x0 + 2*lc .. +1], ci = 8*lg + i of a chunk (bf16 parts: its slice of
   // the 32-channel contraction) or 4*kstep + lg.  The address is a
@@ -407,8 +394,8 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
     // ---- place the row of products at the rotated positions (Eq. 8) --------------
     const int y = h - 1;                       // output row completed by this step
     const int px0 = x0 + 8 * lg;               // first of this lane's 8 pixels
-    const int co = NQ > 1 ? cbo * FPB + lc % FPB : cbo * 16 + lc;
-    const bool fin = t >= 2 && y < g.H && co < g.Cout && px0 >= out_lo && px0 < out_hi && (NQ == 1 || lc < FPB);
+    const int co = cbo * 16 + lc;
+    const bool fin = t >= 2 && y < g.H && co < g.Cout && px0 >= out_lo && px0 < out_hi;
     float best[8];
     uint32_t pk[2] = {0u, 0u};                 // arg-max bytes of the lane's 8 pixels
     int grp_r = 0;                             // any rotation of the bank (its pool group)
@@ -424,7 +411,7 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
         const int jj = j + tap_j(s, u) - 1;
         const float val = jj < 0 ? nbL[u] : jj > 7 ? nbR[u] : P[u][jj & 1][jj >> 1];
         const int ti = tap_i(s, u);
-        tr[ti] = !begun[ti] ? val : S3 && tap_turned(u) ? tr[ti] - val : tr[ti] + val;
+        tr[ti] = !begun[ti] ? val : S3 && s3_tap_turned(u) ? tr[ti] - val : tr[ti] + val;
         begun[ti] = true;
       }
       const float t0 = tr[0], t1 = tr[1], t2 = tr[2];
@@ -452,15 +439,11 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
       }
     } else {
       // pixel by pixel: the four rotations' values, their max and arg-max (smallest r wins ties)
-      if (NQ == 1) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-          if (rot[s] >= 0) { grp_r = rot[s]; first = false; }
-      } else {
-        first = false;      // all rotations present, one pool group (channel = co)
-      }
+      for (int s = 0; s < 4; ++s)
+        if (rot[s] >= 0) { grp_r = rot[s]; first = false; }
       // all four quarter turns in the orientation set (every closed set; wave-uniform): plain compare chain
-      const bool allrot = NQ > 1 || (rot[0] | rot[1] | rot[2] | rot[3]) >= 0;
+      const bool allrot = (rot[0] | rot[1] | rot[2] | rot[3]) >= 0;
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         float bv = 0.f;
@@ -488,20 +471,6 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
               have = true;
             }
           }
-        }
-        if (NQ > 1) {
-          // maximum across the banks: the lanes of one filter sit FPB apart inside the 16-lane row
-          auto other = [&](int ov_bits, int oi) {
-            const float ov = __builtin_bit_cast(float, ov_bits);
-            const bool take = ov > bv || (ov == bv && oi < bi);     // ties: the smallest orientation index
-            bv = take ? ov : bv;
-            bi = take ? oi : bi;
-          };
-          other(__builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, bv), 0x128, 0xf, 0xf, false),
-                __builtin_amdgcn_update_dpp(0, bi, 0x128, 0xf, 0xf, false));                       // row_ror:8
-          if (NQ == 4)
-            other(__builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, bv), 0x124, 0xf, 0xf, false),
-                  __builtin_amdgcn_update_dpp(0, bi, 0x124, 0xf, 0xf, false));                     // row_ror:4
         }
         best[j] = bv;
         pk[j >> 2] |= (uint32_t)bi << (8 * (j & 3));
@@ -611,7 +580,7 @@ __global__ __launch_bounds__(256) void k_p4_sum_pool(const float* __restrict__ p
 
 // base bank(s) -> Q first-quadrant banks in the LDS image layout: [Q][CB][CinPad][9][16] fp32, or
 // [Q][CB][chunk][tap][part][lane][8] bf16 parts; zero for padded filters / channels.
-// nq > 1: the banks are folded into the 16 columns (column n = bank n / (16/nq), filter n % (16/nq)): [CB']...
+// nq > 1: the banks are folded into the sixteen filters of a block (column n = bank n % nq of filter n / nq): [CB']...
 // One thread per (bank, filter, channel or pair of channels): its taps read the same 36 or 72 bytes of w.
 template <bool S3>
 __global__ __launch_bounds__(256) void k_p4_pack_fwd(const float* __restrict__ w, float* __restrict__ wt,
@@ -629,13 +598,13 @@ __global__ __launch_bounds__(256) void k_p4_pack_fwd(const float* __restrict__ w
   const int ci = S3 ? (i / 64) * 8 + (i % 4) * 2 : i / 16;
   const int cb = cb0 + blk % CB;
   const int fpb = 16 / nq;
-  const int q = nq > 1 ? c16 / fpb : blk / CB;
-  const int co = nq > 1 ? cb * fpb + c16 % fpb : cb * 16 + c16;
+  const int q = nq > 1 ? c16 % nq : blk / CB;
+  const int co = nq > 1 ? cb * fpb + c16 / nq : cb * 16 + c16;
   const size_t bank_stride = (size_t)Cout * Cin * 9;
   if constexpr (S3) {
     const bool in0 = co < Cout && ci < Cin, in1 = co < Cout && ci + 1 < Cin;
     const float* src = w + ((size_t)(in0 ? co : 0) * Cin + (in0 ? ci : 0)) * 9;
-    uint32_t* dst = reinterpret_cast<uint32_t*>(wt) + ((size_t)blk * (CinPad / 32) + i / 256) * kChunkS3 + i % 256;
+    uint32_t* dst = reinterpret_cast<uint32_t*>(wt) + ((size_t)blk * (CinPad / 32) + i / 256) * kS3FwdChunk + i % 256;
 #pragma unroll
     for (int u = 0; u < 9; ++u) {
       uint16_t a[3], b[3];
@@ -643,7 +612,7 @@ __global__ __launch_bounds__(256) void k_p4_pack_fwd(const float* __restrict__ w
       s3_split_weight(s3_expand_tap(src + 9, bank_stride, q * 9 + u, in1, fq_src, fq_coef, fq_coef64, round16), b[0], b[1],
                       b[2]);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) dst[(u * 3 + k) * 256] = ((uint32_t)a[k] | (uint32_t)b[k] << 16) ^ tap_sign(u);
+      for (int k = 0; k < 3; ++k) dst[(u * 3 + k) * 256] = ((uint32_t)a[k] | (uint32_t)b[k] << 16) ^ (s3_tap_turned(u) ? 0x80008000u : 0u);
     }
   } else {
     const bool in = co < Cout && ci < Cin;
@@ -655,49 +624,26 @@ __global__ __launch_bounds__(256) void k_p4_pack_fwd(const float* __restrict__ w
   }
 }
 
-template <int NWX, int NWY, bool UNPOOLED, bool FASTW, bool STREAM, bool S3, int KC = 8, int NQ = 1>
+template <int NWX, int NWY, bool UNPOOLED, bool FASTW, bool STREAM, bool S3 = false, int KC = 8>
 void launch_i(const P4Geom& g, const float* x, const float* wt, const int32_t* rot_of, float* ov, uint8_t* oi,
               hipStream_t st) {
-  const size_t wfl = (size_t)(STREAM ? 2 : g.cper) * chunk_words(g.CinPad, g.s3);
+  const size_t wfl = (size_t)(STREAM ? 2 : g.cper) * chunk_words(g.CinPad, S3);
   const size_t lds = (wfl + 4 * NWX * NWY * 128) * sizeof(float);
   const int grid = (g.units + 7) / 8 * 8;
-  auto kern = k_p4_fwd<NWX, NWY, UNPOOLED, FASTW, STREAM, S3, KC, NQ>;
+  auto kern = k_p4_fwd<NWX, NWY, UNPOOLED, FASTW, STREAM, S3, KC>;
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * NWX * NWY), lds, st, x, wt, rot_of, ov, oi, g);
-}
-
-template <int NWX, int NWY, bool S3>
-void launch_k8(const P4Geom& g, bool fastw, bool stream, const float* x, const float* wt, const int32_t* rot_of,
-               float* ov, uint8_t* oi, hipStream_t st) {
-  if (g.out_mode == kOutUnpooled) {
-    if (stream) launch_i<NWX, NWY, true, false, true, S3>(g, x, wt, rot_of, ov, oi, st);   // deep inputs: streamed block
-    else if (fastw) launch_i<NWX, NWY, true, true, false, S3>(g, x, wt, rot_of, ov, oi, st);
-    else launch_i<NWX, NWY, true, false, false, S3>(g, x, wt, rot_of, ov, oi, st);
-  } else if (stream) {
-    if (fastw) launch_i<NWX, NWY, false, true, true, S3>(g, x, wt, rot_of, ov, oi, st);
-    else launch_i<NWX, NWY, false, false, true, S3>(g, x, wt, rot_of, ov, oi, st);   // a wave chain overhangs the row
-  } else if (fastw) {
-    launch_i<NWX, NWY, false, true, false, S3>(g, x, wt, rot_of, ov, oi, st);
-  } else {
-    launch_i<NWX, NWY, false, false, false, S3>(g, x, wt, rot_of, ov, oi, st);
-  }
 }
 
 template <int NWX, int NWY>
 void launch_t(const P4Geom& g, bool fastw, bool stream, const float* x, const float* wt, const int32_t* rot_of,
               float* ov, uint8_t* oi, hipStream_t st) {
   const bool unp = g.out_mode == kOutUnpooled;
-  if (g.nq > 1) {           // banks folded into the columns: pooled output, whole K chunks; a streamed block only
-                            // for rows without overhang (p4_fwd_fold sees to that)
-    if (g.nq == 4) {
-      if (stream) launch_i<NWX, NWY, false, true, true, true, 8, 4>(g, x, wt, rot_of, ov, oi, st);
-      else if (fastw) launch_i<NWX, NWY, false, true, false, true, 8, 4>(g, x, wt, rot_of, ov, oi, st);
-      else launch_i<NWX, NWY, false, false, false, true, 8, 4>(g, x, wt, rot_of, ov, oi, st);
-    } else {
-      if (stream) launch_i<NWX, NWY, false, true, true, true, 8, 2>(g, x, wt, rot_of, ov, oi, st);
-      else if (fastw) launch_i<NWX, NWY, false, true, false, true, 8, 2>(g, x, wt, rot_of, ov, oi, st);
-      else launch_i<NWX, NWY, false, false, false, true, 8, 2>(g, x, wt, rot_of, ov, oi, st);
-    }
+  if (g.s3) {               // whole rows only (p4_fwd_geoms, s3_rows)
+    if (unp && stream) launch_i<NWX, NWY, true, true, true, true>(g, x, wt, rot_of, ov, oi, st);
+    else if (unp) launch_i<NWX, NWY, true, true, false, true>(g, x, wt, rot_of, ov, oi, st);
+    else if (stream) launch_i<NWX, NWY, false, true, true, true>(g, x, wt, rot_of, ov, oi, st);
+    else launch_i<NWX, NWY, false, true, false, true>(g, x, wt, rot_of, ov, oi, st);
     return;
   }
   if (g.CinPad == 4) {      // at most 4 input channels: one K-step per row
@@ -707,8 +653,18 @@ void launch_t(const P4Geom& g, bool fastw, bool stream, const float* x, const fl
     else launch_i<NWX, NWY, false, false, false, false, 1>(g, x, wt, rot_of, ov, oi, st);
     return;
   }
-  if (g.s3) launch_k8<NWX, NWY, true>(g, fastw, stream, x, wt, rot_of, ov, oi, st);
-  else launch_k8<NWX, NWY, false>(g, fastw, stream, x, wt, rot_of, ov, oi, st);
+  if (unp) {
+    if (stream) launch_i<NWX, NWY, true, false, true>(g, x, wt, rot_of, ov, oi, st);   // deep inputs: streamed block
+    else if (fastw) launch_i<NWX, NWY, true, true, false>(g, x, wt, rot_of, ov, oi, st);
+    else launch_i<NWX, NWY, true, false, false>(g, x, wt, rot_of, ov, oi, st);
+  } else if (stream) {
+    if (fastw) launch_i<NWX, NWY, false, true, true>(g, x, wt, rot_of, ov, oi, st);
+    else launch_i<NWX, NWY, false, false, true>(g, x, wt, rot_of, ov, oi, st);   // a wave chain overhangs the row
+  } else if (fastw) {
+    launch_i<NWX, NWY, false, true, false>(g, x, wt, rot_of, ov, oi, st);
+  } else {
+    launch_i<NWX, NWY, false, false, false>(g, x, wt, rot_of, ov, oi, st);
+  }
 }
 
 // Is a part's share of a block of 16 filters too large to stay in LDS next to the edge arrays?
@@ -719,29 +675,68 @@ bool needs_stream(const rotconv_plan* p, int csplit = 1) {
 
 }  // namespace
 
-bool p4_fwd_parts_wanted(const rotconv_plan* p) { return cin_pad_f32(p->d.Cin) > 4 && p->opt.bf16_parts >= 0; }
+bool p4_fwd_parts_wanted(const rotconv_plan* p) {
+  return cin_pad_f32(p->d.Cin) > 4 && p->opt.bf16_parts >= 0 && s3_fwd_supported(p);
+}
+
+bool p4_fwd_f32_rows(const rotconv_plan* p) {
+  // whole pixel pairs; segmented rows need whole-lane validity
+  return !(p->d.W & 1) && (p->d.W <= 256 || !(p->d.W & 31));
+}
 
 bool p4_fwd_supported(const rotconv_plan* p) {
   const rotconv_desc& d = p->d;
   if (d.k != 3 || d.stride != 1 || d.pad != 1) return false;   // bf16 plans run these kernels on widened copies
-  if (d.W & 1) return false;
-  if (d.W > 256 && (d.W & 31)) return false;          // segmented rows need whole-lane validity
-  return true;
+  if (p4_fwd_f32_rows(p)) return true;
+  // The kernel on bf16 parts takes rows of any width.  Not where the pool group spans several banks: there the padded rows'
+  // base products (k_p4_fwd_base) are one contraction instead of one per bank.  bf16 tensors: on padded rows their own kernel.
+  return d.dtype == ROTCONV_F32 && p4_fwd_parts_wanted(p) && p4_fwd_pool_mode(p) != kOutPartial;
 }
 
 namespace {
-// Cost of a launch plan, the sum of its launches' band costs.  In units of 0.3 us with bf16 parts: a wave's row step counts
-// four per 32-channel chunk (108 matrix instructions and the split of their operands) and three for placing the row.  In
-// units of 0.5 us with fp32 instructions: four per chunk (144 matrix instructions), the placing among them.
-long plan_cost(const rotconv_plan* p, int out_mode, int csplit, int nq) {
+// Time of a launch plan, the sum of its launches' band costs, in 0.1 us; a negative value where there is none.
+double plan_cost_p4(const rotconv_plan* p, int out_mode, int csplit) {
+  if (p->fwd_s3 && ((p->d.W & 7) || !p4_fwd_f32_rows(p))) return -1;
   P4Geom gs[4];
-  const int n = p4_fwd_geoms(p, out_mode, gs, 4, csplit, nq);
-  if (n < 0) return -1;
-  long c = 0;
-  for (int i = 0; i < n; ++i) c += gs[i].cost;
-  return c;
+  const int n = p4_fwd_geoms(p, out_mode, gs, 4, csplit);
+  double c = 0;
+  for (int i = 0; i < n; ++i) {
+    if (p->fwd_s3 && !gs[i].inside) return -1;      // with parts: only rows that the wave chains cover exactly
+    c += gs[i].cost;
+  }
+  return n < 0 ? -1 : c;
+}
+// With bf16 parts: does the kernel of chained waves run, or the one whose waves are on their own (rotconv_s3_fwd.hip)?  The
+// chain multiplies no column twice, the other one leaves no lane idle on other rows and divides the line of bands where it
+// likes.  Where both can run, the smaller modelled time.  130 layers of 12 to 300 rows, 12 to 600 channels and filters: on their
+// own 0.87 of the chain's time in the mean on rows of 32 to 256 pixels (3x18 -> 295, 71x128 77 -> 43 us, 8x160 -> 288, 37x64 177
+// -> 130), the chain ahead where its bands fit (8x64 -> 64, 256x256 219 / 236 us, 4x512 -> 512, 32x32 189 / 221); rows with
+// masks in the chain took twice its time (2x55 -> 213, 294x204 400 -> 181 us).
+bool chained(const rotconv_plan* p, int out_mode, int csplit, int nq) {
+  if (!p->fwd_s3) return true;
+  if (nq > 1) return false;
+  const double c = plan_cost_p4(p, out_mode, csplit);
+  return c >= 0 && c < s3_fwd_geom(p, out_mode, csplit, nq).cost;
+}
+double plan_cost(const rotconv_plan* p, int out_mode, int csplit, int nq) {
+  return chained(p, out_mode, csplit, nq) ? plan_cost_p4(p, out_mode, csplit) : s3_fwd_geom(p, out_mode, csplit, nq).cost;
 }
 }  // namespace
+
+void p4_fwd_choose_launches(rotconv_plan* p) {
+  for (int pooled = 0; pooled < 2; ++pooled) {
+    rotconv_plan::FwdLaunch& l = p->fwd_launch[pooled];
+    const int mode = pooled ? p4_fwd_pool_mode(p) : kOutUnpooled;
+    l.csplit = p->fwd_csplit[pooled];
+    l.nq = l.csplit == 1 && mode == kOutPartial ? p4_fwd_fold(p) : 1;
+    l.out_mode = l.csplit > 1 ? kOutUnpooled : l.nq > 1 ? kOutPooled : mode;
+    l.chain = chained(p, l.out_mode, l.csplit, l.nq);
+    if (l.chain) continue;
+    const S3FwdGeom g = s3_fwd_geom(p, l.out_mode, l.csplit, l.nq);
+    l.ty = g.TY;
+    l.nw = g.nw;
+  }
+}
 
 // Parts the channel contraction is split into (1: no split).  Small maps with deep inputs give the (filter block,
 // band) decomposition too few workgroups, each with a long serial contraction; splitting the 32-channel chunks over
@@ -765,7 +760,7 @@ int p4_fwd_csplit(const rotconv_plan* p, bool pooled) {
   }
   const int mode = pooled ? p4_fwd_pool_mode(p) : kOutUnpooled;
   const int nq = pooled && mode == kOutPartial ? p4_fwd_fold(p) : 1;
-  long best = plan_cost(p, nq > 1 ? kOutPooled : mode, 1, nq);
+  double best = plan_cost(p, nq > 1 ? kOutPooled : mode, 1, nq);
   int best_s = 1;
   const double part_bytes = (double)d.N * d.Cout * d.R * d.H * d.W * 4.0;
   for (int s = 2; s <= 32; s *= 2) {
@@ -774,8 +769,8 @@ int p4_fwd_csplit(const rotconv_plan* p, bool pooled) {
     const int s_eff = (nchunk + cper - 1) / cper;
     if (s_eff < 2) break;
     // parts written and read once at about 4 TB/s, and a dependent launch
-    const long over = s3 ? 28 + (long)(2.0 * s_eff * part_bytes / 1.2e6) : 24 + (long)(2.0 * s_eff * part_bytes / 2.0e6);
-    const long c = plan_cost(p, kOutUnpooled, s_eff, 1) + over;
+    const double over = (s3 ? 80. : 120.) + s_eff * part_bytes / 0.2e6;
+    const double c = plan_cost(p, kOutUnpooled, s_eff, 1) + over;
     if (c < best) { best = c; best_s = s_eff; }
     if (cper == 1) break;
   }
@@ -795,7 +790,7 @@ int p4_fwd_csplit(const rotconv_plan* p, bool pooled) {
 
 // Cut the row into segments of at most 256 product columns; all segments of one launch share nwx.
 // Returns the number of launches (geoms) written.
-int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, int csplit, int nq) {
+int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, int csplit) {
   const rotconv_desc& d = p->d;
   P4Geom base{};
   {
@@ -849,35 +844,24 @@ int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, 
     // Rows per band: short bands cost halo rows (a band of ty rows computes ty + 2 rows of products) but give
     // more workgroups when the problem is small.  Cost of a choice = rounds of workgroups over the 256 CUs x row
     // steps per wave x how many waves share a SIMD (a workgroup whose bands reach beyond the image leaves waves idle).
-    // nq > 1 (banks folded into the columns): one unit covers all banks of 16 / nq filters
-    const int ublk = nq > 1 ? (d.Cout * nq + 15) / 16 : g.Q * g.CB;
     for (int ty : {1, 2, 4, 8, 16, 32, 64}) {
       const int nbg = (d.H + nwy * ty - 1) / (nwy * ty);
-      const long units = (long)d.N * ublk * nbg * g.nseg * g.csplit;
+      const long units = (long)d.N * g.Q * g.CB * nbg * g.nseg * g.csplit;
       const int bands = nbg > 1 ? nwy : std::min(nwy, (d.H + ty - 1) / ty);
       const long cost = ((units + 255) / 256) * (ty + 2) * std::max(4, g.nwx * bands);
       if (best_cost < 0 || cost <= best_cost) { best_cost = cost; g.TY = ty; g.nbg = nbg; g.units = (int)units; }
     }
-    g.cost = (int)std::min<long>(g.s3 ? best_cost * (4 * g.cper + 3) / 4 : best_cost * g.cper, 1L << 30);
-    if (nq > 1) {
-      g.CB = ublk;
-      g.Q = 1;
-    }
-    g.nq = nq;
+    // in 0.1 us; best_cost counts the rows of a wave alone on its SIMD as four, of two that share one as eight
+    g.cost = g.s3 ? best_cost * (28.7 * g.cper + 13.) / 8. + 30. + 8. * g.cper : 5. * best_cost * g.cper;
   }
   return ng;
 }
 
-// Banks folded into a wave's 16 columns for the pooled forward: the plan pools all R = 4 Q orientations of a filter
-// together, Q is 2 or 4, every bank has its four quarter turns, the channels fill whole 32-channel chunks, the products
-// are those of bf16 parts, and the filter block stays LDS-resident or is streamed under rows the wave chains cover exactly
-// (1: no folding).
+// Banks folded into a wave's sixteen filters for the pooled forward: the plan pools all R = 4 Q orientations of a filter
+// together, Q is 2 or 4, every bank has its four quarter turns, and the products are those of bf16 parts (1: no folding).
 int p4_fwd_fold(const rotconv_plan* p) {
   const int Q = p->host.Q;
   if ((Q != 2 && Q != 4) || p->ng != 1 || !p->fwd_s3) return 1;
-  // a streamed filter block: only rows that the wave chains cover exactly (the instances without load masks)
-  const int W = p->d.W;
-  if (needs_stream(p) && ((W & 31) || (W <= 256 && (W & (W - 1))))) return 1;
   for (int i = 0; i < Q * 4; ++i)
     if (p->rot_of[i] < 0) return 1;
   return Q;
@@ -931,8 +915,12 @@ bool p4_fwd_raw_weights(const rotconv_plan* p, int nq, int csplit) {
 
 void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const float* w, float* pack, size_t pack_bytes,
                    float* out_val, uint8_t* out_idx, hipStream_t st, int nq, int csplit) {
+  const rotconv_plan::FwdLaunch* l = nullptr;
+  for (const auto& c : p->fwd_launch)
+    if (c.out_mode == out_mode && c.csplit == csplit && c.nq == nq) l = &c;
+  const bool s3 = p->fwd_s3, chain = l ? l->chain : chained(p, out_mode, csplit, nq);
   P4Geom gs[4];
-  const int ng = p4_fwd_geoms(p, out_mode, gs, 4, csplit, nq);
+  const int ng = chain ? p4_fwd_geoms(p, out_mode, gs, 4, csplit) : 0;
   const bool stream = needs_stream(p, csplit);
   const int raw = p4_fwd_raw_weights(p, nq, csplit) ? 1 : 0;
   const int blocks = fwd_blocks(p, nq), CinPad = cin_pad_f32(p->d.Cin);
@@ -941,12 +929,20 @@ void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const fl
   for (int cb0 = 0; cb0 < blocks; cb0 += slice) {
     const int ncb = std::min(slice, blocks - cb0);
     if (!raw) {
-      const bool s3 = p->fwd_s3;
       const int total = (nq > 1 ? 1 : p->host.Q) * ncb * CinPad * (s3 ? 8 : 16);
       auto kern = s3 ? k_p4_pack_fwd<true> : k_p4_pack_fwd<false>;
       hipLaunchKernelGGL(kern, dim3((total + 255) / 256), dim3(256), 0, st, w, pack, p->dev.fq_src, p->dev.fq_coef,
                          p->dev.fq_coef64, p->host.Q, ncb, CinPad, p->d.Cin, p->d.Cout,
                          p->d.dtype == ROTCONV_BF16 ? 1 : 0, nq, cb0);
+    }
+    const float* wt = raw ? w : pack;
+    if (!chain) {
+      S3FwdGeom g = s3_fwd_geom(p, out_mode, csplit, nq, l ? l->ty : 0, l ? l->nw : 0);
+      g.raw_w = raw;
+      g.units = g.units / g.CB * ncb;
+      g.CB = ncb;
+      g.cb0 = cb0;
+      launch_s3_fwd(g, x, wt, p->dev.rot_of, out_val, out_idx, st);
     }
     for (int i = 0; i < ng; ++i) {
       P4Geom g = gs[i];
@@ -955,7 +951,6 @@ void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const fl
       g.CB = ncb;
       g.cb0 = cb0;
       const bool fastw = (p->d.W & 7) == 0 && g.inside;   // no lane reaches beyond the row: no masks, vector stores
-      const float* wt = raw ? w : pack;
       switch (g.nwx) {
         case 1: launch_t<1, 8>(g, fastw, stream, x, wt, p->dev.rot_of, out_val, out_idx, st); break;
         case 2: launch_t<2, 4>(g, fastw, stream, x, wt, p->dev.rot_of, out_val, out_idx, st); break;
