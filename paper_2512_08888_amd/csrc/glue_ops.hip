@@ -300,15 +300,21 @@ __device__ __forceinline__ void head_load_w(const T* __restrict__ w, float* wl, 
   __syncthreads();
 }
 
-// y[n][co][p] = sum_ci w[co][ci] x[n][ci][p]
+// y[n][co][p] = sum_ci w[co][ci] x[n][ci][p].  A workgroup takes 64 pixel vectors, each of its four waves a quarter of the
+// channels; the quarters meet in LDS (0 + 2 and 1 + 3, then the two).  (All channels in one thread: 28 us for 64 channels of 2x128x128
+// pixels, 128 waves with a chain of 64 loads each.)
 template <typename T>
 __global__ __launch_bounds__(256) void k_head_fwd(const T* __restrict__ x, const T* __restrict__ w, T* __restrict__ y,
                                                   int Cin, int Cout, size_t P, size_t nvec) {
   constexpr int V = Elt<T>::V;
   extern __shared__ float wl[];
+  __shared__ float part[2][HEAD_CO * V][64];      // with w at most 64 KB
   head_load_w(w, wl, Cin, Cout);
   const size_t pv = P / V;
-  for (size_t v = (size_t)blockIdx.x * 256 + threadIdx.x; v < nvec; v += (size_t)gridDim.x * 256) {
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+  const int quarter = (Cin + 3) / 4, c0 = wave * quarter, c1 = min(Cin, c0 + quarter);
+  for (size_t vb = (size_t)blockIdx.x * 64; vb < nvec; vb += (size_t)gridDim.x * 64) {
+    const size_t v = min(vb + lane, nvec - 1);
     const size_t n = v / pv, p = (v - n * pv) * V;
     const T* xp = x + n * Cin * P + p;
     float acc[HEAD_CO][V];
@@ -316,7 +322,8 @@ __global__ __launch_bounds__(256) void k_head_fwd(const T* __restrict__ x, const
     for (int co = 0; co < HEAD_CO; ++co)
 #pragma unroll
       for (int k = 0; k < V; ++k) acc[co][k] = 0.f;
-    for (int ci = 0; ci < Cin; ++ci) {
+#pragma unroll 4
+    for (int ci = c0; ci < c1; ++ci) {
       float xv[V];
       Elt<T>::ldv(xp + (size_t)ci * P, xv);
 #pragma unroll
@@ -326,13 +333,31 @@ __global__ __launch_bounds__(256) void k_head_fwd(const T* __restrict__ x, const
         for (int k = 0; k < V; ++k) acc[co][k] = fmaf(wv, xv[k], acc[co][k]);
       }
     }
+    auto put = [&](int slot) {
 #pragma unroll
-    for (int co = 0; co < HEAD_CO; ++co)
-      if (co < Cout) Elt<T>::stv(y + (n * Cout + co) * P + p, acc[co]);
+      for (int i = 0; i < HEAD_CO * V; ++i) part[slot][i][lane] = acc[i / V][i % V];
+    };
+    auto add = [&](int slot) {
+#pragma unroll
+      for (int i = 0; i < HEAD_CO * V; ++i) acc[i / V][i % V] += part[slot][i][lane];
+    };
+    if (wave >= 2) put(wave - 2);
+    __syncthreads();
+    if (wave < 2) add(wave);
+    __syncthreads();
+    if (wave == 1) put(0);
+    __syncthreads();
+    if (wave == 0) {
+      add(0);
+#pragma unroll
+      for (int co = 0; co < HEAD_CO; ++co)
+        if (co < Cout && vb + lane < nvec) Elt<T>::stv(y + (n * Cout + co) * P + p, acc[co]);
+    }
+    __syncthreads();
   }
 }
 
-// dx[n][ci][p] = sum_co w[co][ci] dy[n][co][p]
+// dx[n][ci][p] = sum_co w[co][ci] dy[n][co][p]; blockIdx.y: a share of the channels
 template <typename T>
 __global__ __launch_bounds__(256) void k_head_bwd_data(const T* __restrict__ dy, const T* __restrict__ w,
                                                        T* __restrict__ dx, int Cin, int Cout, size_t P, size_t nvec) {
@@ -353,7 +378,9 @@ __global__ __launch_bounds__(256) void k_head_bwd_data(const T* __restrict__ dy,
       }
     }
     T* dp = dx + n * Cin * P + p;
-    for (int ci = 0; ci < Cin; ++ci) {
+    const int share = (Cin + gridDim.y - 1) / gridDim.y, c0 = blockIdx.y * share, c1 = min(Cin, c0 + share);
+#pragma unroll 2
+    for (int ci = c0; ci < c1; ++ci) {
       float o[V];
 #pragma unroll
       for (int k = 0; k < V; ++k) o[k] = 0.f;
@@ -370,7 +397,7 @@ __global__ __launch_bounds__(256) void k_head_bwd_data(const T* __restrict__ dy,
 
 // part[blockIdx.x][co][ci] = sum over the workgroup's pixel vectors of dy[n][co][p] x[n][ci][p].  blockIdx.y picks
 // a group of 64 input channels, wave j of the workgroup's four takes sixteen of them; every wave walks all of the
-// workgroup's pixel vectors (64 per step), then adds its lanes' sums in a butterfly and lane 0 stores them.
+// workgroup's pixel vectors (64 per step), then adds up its lanes' sums.
 template <typename T>
 __global__ __launch_bounds__(256) void k_head_bwd_weight(const T* __restrict__ x, const T* __restrict__ dy,
                                                          float* __restrict__ part, int Cin, int Cout, size_t P,
@@ -413,26 +440,38 @@ __global__ __launch_bounds__(256) void k_head_bwd_weight(const T* __restrict__ x
         for (int k = 0; k < V; ++k) acc[c][co] = fmaf(g[co][k], xv[k], acc[c][co]);
     }
   }
+  // Over the lanes: every step halves the sums a lane keeps (126 exchanges; a butterfly of each sum takes 768).  Lane l ends
+  // with sums 2 l and 2 l + 1 of the sixteen channels x HEAD_CO.
+  static_assert(16 * HEAD_CO == 128, "two sums a lane");
+  float a[128];
+#pragma unroll
+  for (int i = 0; i < 128; ++i) a[i] = acc[i / HEAD_CO][i % HEAD_CO];
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    const bool hi = lane & m;
+#pragma unroll
+    for (int i = 0; i < 2 * m; ++i) {
+      const float send = hi ? a[i] : a[i + 2 * m], keep = hi ? a[i + 2 * m] : a[i];
+      a[i] = keep + __shfl_xor(send, m);
+    }
+  }
   float* out = part + (size_t)blockIdx.x * Cout * Cin;
 #pragma unroll
-  for (int c = 0; c < 16; ++c)
-#pragma unroll
-    for (int co = 0; co < HEAD_CO; ++co) {
-      float s = acc[c][co];
-#pragma unroll
-      for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m);
-      if (lane == 0 && co < Cout && ci0 + c < Cin) out[(size_t)co * Cin + ci0 + c] = s;
-    }
+  for (int i = 0; i < 2; ++i) {
+    const int c = (2 * lane + i) / HEAD_CO, co = (2 * lane + i) % HEAD_CO;
+    if (co < Cout && ci0 + c < Cin) out[(size_t)co * Cin + ci0 + c] = a[i];
+  }
 }
 
 // The streaming head kernels apply when the vectors line up: P a multiple of the 16-byte vector, aligned tensors.
 bool head_fast(int Cin, int Cout, size_t P, int bf, const void* a, const void* b) {
   return Cout <= HEAD_CO && Cin <= HEAD_CIN && P % (bf ? 8 : 4) == 0 && aligned16(a) && aligned16(b);
 }
-// Workgroups of the head's weight gradient: at least eight pixel vectors per lane, at most HEAD_PARTS.
+// Workgroups of the head's weight gradient: at least one pixel vector per lane (eight: 42 us for 64 channels of 2x128x128
+// pixels, sixteen workgroups), at most HEAD_PARTS.
 int head_parts(int N, size_t P) {
   const size_t nvec = (size_t)N * P / 4;
-  return (int)std::max<size_t>(1, std::min<size_t>(HEAD_PARTS, nvec / 512));
+  return (int)std::max<size_t>(1, std::min<size_t>(HEAD_PARTS, nvec / 64));
 }
 
 // Splits of the contraction for the weight gradients (K = pixels of one image): about 1024 workgroups,
@@ -578,9 +617,9 @@ int conv1x1_fwd_g(const void* x, const void* w, void* y, int N, int Cin, int Cou
   if (head_fast(Cin, Cout, P, bf, x, y)) {
     const size_t nvec = (size_t)N * P / (bf ? 8 : 4);
     const size_t lds = (size_t)Cin * HEAD_CO * sizeof(float);
-    if (bf) hipLaunchKernelGGL(k_head_fwd<uint16_t>, dim3(blocks_for(nvec)), dim3(256), lds, S(stream), (const uint16_t*)x,
+    if (bf) hipLaunchKernelGGL(k_head_fwd<uint16_t>, dim3(blocks_for(nvec * 4)), dim3(256), lds, S(stream), (const uint16_t*)x,
                                (const uint16_t*)w, (uint16_t*)y, Cin, Cout, P, nvec);
-    else hipLaunchKernelGGL(k_head_fwd<float>, dim3(blocks_for(nvec)), dim3(256), lds, S(stream), (const float*)x,
+    else hipLaunchKernelGGL(k_head_fwd<float>, dim3(blocks_for(nvec * 4)), dim3(256), lds, S(stream), (const float*)x,
                             (const float*)w, (float*)y, Cin, Cout, P, nvec);
     return finish();
   }
@@ -598,9 +637,12 @@ int conv1x1_bwd_data_g(const void* dy, const void* w, void* dx, int N, int Cin, 
   if (head_fast(Cin, Cout, P, bf, dy, dx)) {
     const size_t nvec = (size_t)N * P / (bf ? 8 : 4);
     const size_t lds = (size_t)Cin * HEAD_CO * sizeof(float);
-    if (bf) hipLaunchKernelGGL(k_head_bwd_data<uint16_t>, dim3(blocks_for(nvec)), dim3(256), lds, S(stream),
+    // 1024 workgroups where the pixels alone do not give as many
+    const unsigned pb = blocks_for(nvec);
+    const dim3 grid(pb, std::max(1u, std::min({1024u / pb, (unsigned)Cin / 4u, 16u})));
+    if (bf) hipLaunchKernelGGL(k_head_bwd_data<uint16_t>, grid, dim3(256), lds, S(stream),
                                (const uint16_t*)dy, (const uint16_t*)w, (uint16_t*)dx, Cin, Cout, P, nvec);
-    else hipLaunchKernelGGL(k_head_bwd_data<float>, dim3(blocks_for(nvec)), dim3(256), lds, S(stream), (const float*)dy,
+    else hipLaunchKernelGGL(k_head_bwd_data<float>, grid, dim3(256), lds, S(stream), (const float*)dy,
                             (const float*)w, (float*)dx, Cin, Cout, P, nvec);
     return finish();
   }

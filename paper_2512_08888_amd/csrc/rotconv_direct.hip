@@ -23,7 +23,9 @@
 // bf16 plans: x is widened on load, the banks were rounded to bf16 when they were packed (products of bf16 values are
 // exact in fp32, the sums are fp32), the pooled value is rounded once.
 #include <algorithm>
+#include <type_traits>
 
+#include "rotconv_expand.h"
 #include "rotconv_bf16.h"
 #include "rotconv_direct.h"
 #include "rotconv_lanepx.h"
@@ -159,38 +161,29 @@ __global__ __launch_bounds__(256) void k_direct_fwd(const T* __restrict__ x, con
   }
 }
 
-// One thread per (filter, bank, channel): its nine taps of the first-quadrant bank from the base bank(s) (Eq. 5,
+// One thread per (filter, bank, channel) and three taps (blockIdx.y) of the first-quadrant bank from the base bank(s) (Eq. 5,
 // Eq. 17 / the plan's expansion table).  bf16 plans: the combination in fp64, rounded to fp32 and to bf16 once each,
 // as every kernel of a bf16 plan forms its banks.
-__global__ __launch_bounds__(256) void k_direct_pack(const void* __restrict__ w, float* __restrict__ wb,
-                                                     const int32_t* __restrict__ fq_src,
-                                                     const float* __restrict__ fq_coef,
-                                                     const double* __restrict__ fq_coef64, int Q, int Cin, int Cout,
-                                                     int CoutPad, int pitch, int is16) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
+template <typename T>
+__global__ __launch_bounds__(256) void k_direct_pack(const T* __restrict__ w, float* __restrict__ wb, ExpandTables tab, int Q,
+                                                     int Cin, int Cout, int CoutPad, int pitch) {
+  const int e = blockIdx.x * 256 + threadIdx.x, u0 = blockIdx.y * 3;
   const int npc = Cin + 1;                        // threads per (filter, bank): the last one clears the row's pad
   if (e >= CoutPad * Q * npc) return;
   const int ci = e % npc, q = (e / npc) % Q, co = e / (npc * Q);
   float* dst = wb + (size_t)(co * Q + q) * pitch;
   if (ci >= Cin) {
-    for (int i = Cin * 9; i < pitch; ++i) dst[i] = 0.f;
+    if (u0 == 0)
+      for (int i = Cin * 9; i < pitch; ++i) dst[i] = 0.f;
     return;
   }
   const bool in = co < Cout;
-  const int slices = Cout * Cin;
-  const size_t base = (size_t)(in ? co * Cin + ci : 0) * 9;
-  for (int u = 0; u < 9; ++u) {
-    float acc = 0.f;
-    double a64 = 0.0;
-    for (int z = 0; z < kMaxNnz; ++z) {
-      const int s = fq_src[(q * 9 + u) * kMaxNnz + z];
-      if (!in || s < 0) continue;
-      const size_t o = base + (size_t)(s / 9) * slices * 9 + s % 9;
-      if (is16) a64 += fq_coef64[(q * 9 + u) * kMaxNnz + z] * (double)bf16_to_f32(static_cast<const uint16_t*>(w)[o]);
-      else acc += fq_coef[(q * 9 + u) * kMaxNnz + z] * static_cast<const float*>(w)[o];
-    }
-    dst[ci * 9 + u] = is16 ? bf16_to_f32(f32_to_bf16((float)a64)) : acc;
-  }
+  const T* src = w + (size_t)(in ? co * Cin + ci : 0) * 9;
+  float v[3];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) v[j] = expand_tap(src, (size_t)Cout * Cin * 9, 9, q, u0 + j, in, tab, sizeof(T) == 2);
+#pragma unroll
+  for (int j = 0; j < 3; ++j) dst[ci * 9 + u0 + j] = v[j];
 }
 
 // ---- weight gradient of such layers with a single bank (R = 4 exact quarter turns) -------------------------------
@@ -523,8 +516,12 @@ void launch_direct_fwd(const rotconv_plan* p, const void* x, const void* w, void
   const int CoutPad = (d.Cout + fb - 1) / fb * fb;
   const bool is16 = d.dtype == ROTCONV_BF16;
   const int total = CoutPad * Q * (d.Cin + 1);
-  hipLaunchKernelGGL(k_direct_pack, dim3((total + 255) / 256), dim3(256), 0, st, w, wb, p->dev.fq_src, p->dev.fq_coef,
-                     p->dev.fq_coef64, Q, d.Cin, d.Cout, CoutPad, pitch, is16 ? 1 : 0);
+  auto pack = [&](auto* wp) {
+    using T = std::remove_const_t<std::remove_pointer_t<decltype(wp)>>;
+    hipLaunchKernelGGL(k_direct_pack<T>, dim3((total + 255) / 256, 3), dim3(256), 0, st, wp, wb, expand_tables(p), Q, d.Cin,
+                       d.Cout, CoutPad, pitch);
+  };
+  if (is16) pack(static_cast<const uint16_t*>(w)); else pack(static_cast<const float*>(w));
   const DirGeom g = direct_geom(p);
   const bool relu = d.activation == ROTCONV_ACT_RELU;
   const bool pb = p->ng > 1;       // pool groups of four quarter turns: every bank pooled on its own

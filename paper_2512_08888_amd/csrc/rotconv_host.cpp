@@ -185,6 +185,11 @@ int validate_and_build(const rotconv_desc* desc, rotconv_plan** out) {
         t.fq_coef64[(q * kk + u) * kMaxNnz + e] = nz[e].coef;
       }
     }
+  p->base_bank = t.Q == 1 && B == 1;
+  for (int i = 0; i < t.Q * kk * kMaxNnz; ++i) {
+    const bool first = i % kMaxNnz == 0;
+    if (first ? t.fq_src[i] != i / kMaxNnz || t.fq_coef[i] != 1.0f : t.fq_src[i] >= 0) p->base_bank = 0;
+  }
   // W^(r)[R_s(u)] = F_phi[u]: the row of first-quadrant tap u becomes the row of its turned tap.
   t.exp_src.assign(d.R * kk * kMaxNnz, -1);
   t.exp_coef.assign(d.R * kk * kMaxNnz, 0.f);

@@ -78,6 +78,7 @@ struct rotconv_plan {
   rotconv_plan_options opt{};   // tuning switches (all zero: automatic); the plans a plan owns inherit them
   std::vector<double> angles;
   int B = 1, G = 1, ng = 1, Ho = 0, Wo = 0, kk = 0;
+  int base_bank = 0;            // one first-quadrant bank, which is the base bank itself
   rotconv::HostTables host;
   std::vector<int32_t> rot_of;  // [Q*4]
   rotconv::DeviceTables dev;    // uploaded on first launch

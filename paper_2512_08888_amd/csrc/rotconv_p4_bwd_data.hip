@@ -26,6 +26,7 @@
 #include <algorithm>
 #include <cstdlib>
 
+#include "rotconv_expand.h"
 #include "rotconv_bf16.h"
 #include "rotconv_kernels.h"
 #include "rotconv_p4.h"
@@ -770,6 +771,7 @@ __global__ __launch_bounds__(256) void k_p4_sum_dx(const float* __restrict__ par
   const size_t n4 = n_elem / 4;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 256) {
     f4 a = reinterpret_cast<const f4*>(part)[i];
+#pragma unroll 4
     for (int k = 1; k < nparts; ++k) a += reinterpret_cast<const f4*>(part + (size_t)k * n_elem)[i];
     reinterpret_cast<f4*>(dx)[i] = a;
   }
@@ -781,15 +783,13 @@ __global__ __launch_bounds__(256) void k_p4_sum_dx(const float* __restrict__ par
 }
 
 // base bank(s) -> Q first-quadrant banks laid out [Q][CoutPad][9][CinPad] (zero padded).
-__global__ __launch_bounds__(256) void k_p4_pack_bwd(const float* __restrict__ w, float* __restrict__ wd,
-                                                     const int32_t* __restrict__ fq_src,
-                                                     const float* __restrict__ fq_coef,
-                                                     const double* __restrict__ fq_coef64, int Q, int CoutPad,
-                                                     int CinPad, int Cin, int Cout, int round16, int base) {
-  // base: the base bank itself (Q = 1, no expansion)
-  // One thread per (bank, filter, channel position): its nine taps read the same 36 bytes of w.
+__global__ __launch_bounds__(256) void k_p4_pack_bwd(const float* __restrict__ w, float* __restrict__ wd, ExpandTables tab,
+                                                     int Q, int CoutPad, int CinPad, int Cin, int Cout, int round16,
+                                                     int base) {
+  // base: the base banks themselves (Q counts them, no expansion)
+  // One thread per (bank, filter, channel position) and three taps (blockIdx.y).
   const int total = Q * CoutPad * CinPad;
-  const int e = blockIdx.x * 256 + threadIdx.x;
+  const int e = blockIdx.x * 256 + threadIdx.x, u0 = blockIdx.y * 3;
   if (e >= total) return;
   // Inside each group of 64 channels position p holds channel (p % 4) * 16 + p / 4, so that the four
   // 16-channel blocks of a lane's channel sit side by side (one 16-byte LDS read per tap in the kernel).
@@ -798,30 +798,21 @@ __global__ __launch_bounds__(256) void k_p4_pack_bwd(const float* __restrict__ w
   const int co = (e / CinPad) % CoutPad;
   const int q = e / (CinPad * CoutPad);
   const bool in = co < Cout && ci < Cin;
-  const int slices = Cout * Cin;
+  const size_t bank_stride = (size_t)Cout * Cin * 9;
   const float* src = w + (size_t)(in ? co * Cin + ci : 0) * 9;
   float* dst = wd + ((size_t)(q * CoutPad + co) * 9) * CinPad + pos;
+  float v[3];
 #pragma unroll
-  for (int u = 0; u < 9; ++u) {
-    float acc = 0.f;
-    if (base) {       // q counts the base banks
-      acc = in ? src[(size_t)q * slices * 9 + u] : 0.f;
-    } else if (round16) {     // bf16 plans: the combination in fp64, rounded to fp32 and to bf16 once each
-      double a64 = 0.0;
-      for (int z = 0; z < kMaxNnz; ++z) {
-        const int s = fq_src[(q * 9 + u) * kMaxNnz + z];
-        if (in && s >= 0) a64 += fq_coef64[(q * 9 + u) * kMaxNnz + z] * (double)src[(size_t)(s / 9) * slices * 9 + s % 9];
-      }
-      acc = bf16_to_f32(f32_to_bf16((float)a64));
+  for (int j = 0; j < 3; ++j) {
+    if (base) {
+      const float b = src[q * bank_stride + u0 + j];
+      v[j] = in ? b : 0.f;
     } else {
-#pragma unroll
-      for (int z = 0; z < kMaxNnz; ++z) {
-        const int s = fq_src[(q * 9 + u) * kMaxNnz + z];
-        if (in && s >= 0) acc += fq_coef[(q * 9 + u) * kMaxNnz + z] * src[(size_t)(s / 9) * slices * 9 + s % 9];
-      }
+      v[j] = expand_tap(src, bank_stride, 9, q, u0 + j, in, tab, round16);
     }
-    dst[(size_t)u * CinPad] = acc;
   }
+#pragma unroll
+  for (int j = 0; j < 3; ++j) dst[(size_t)(u0 + j) * CinPad] = v[j];
 }
 
 }  // namespace
@@ -943,9 +934,8 @@ void launch_p4_pack_bwd(const rotconv_plan* p, const float* w, float* wd, hipStr
     return;
   }
   const int total = g.Q * g.CoutPad * g.CinPad;
-  hipLaunchKernelGGL(k_p4_pack_bwd, dim3((total + 255) / 256), dim3(256), 0, st, w, wd, p->dev.fq_src, p->dev.fq_coef,
-                     p->dev.fq_coef64,
-                     g.Q, g.CoutPad, g.CinPad, g.Cin, g.Cout, p->d.dtype == ROTCONV_BF16 ? 1 : 0, g.lut);
+  hipLaunchKernelGGL(k_p4_pack_bwd, dim3((total + 255) / 256, 3), dim3(256), 0, st, w, wd, expand_tables(p), g.Q,
+                     g.CoutPad, g.CinPad, g.Cin, g.Cout, p->d.dtype == ROTCONV_BF16 ? 1 : 0, g.lut);
 }
 
 void launch_p4_sum_dx(const float* part, float* dx, size_t n, int splits, hipStream_t st) {

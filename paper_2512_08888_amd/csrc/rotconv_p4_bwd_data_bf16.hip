@@ -45,6 +45,7 @@
 #include <algorithm>
 
 #include "rotconv_bf16.h"
+#include "rotconv_expand.h"
 #include "rotconv_kernels.h"
 #include "rotconv_p4.h"
 #include "rotconv_p4_taps.h"
@@ -436,12 +437,10 @@ __global__ __launch_bounds__(256) void k_p4_sum_dx_parts(const float* __restrict
 // bf16 base bank(s) -> Q first-quadrant banks (fp32 combination rounded to bf16 once) in the LDS image layout
 // of the input-gradient kernel: [16-channel block][Q][K-step of 32 filters][9 taps][4 k-groups][16 channels][8 filters].
 __global__ __launch_bounds__(256) void k_p4_pack_bwd_bf16(const uint16_t* __restrict__ w, uint16_t* __restrict__ wt,
-                                                          const int32_t* __restrict__ fq_src,
-                                                          const double* __restrict__ fq_coef, int Q, int CIB,
-                                                          int CoutPad, int Cin, int Cout) {
-  // One thread per (bank, filter, channel): its nine taps read the same 18 bytes of w.
+                                                          ExpandTables tab, int Q, int CIB, int CoutPad, int Cin, int Cout) {
+  // One thread per (bank, filter, channel) and three taps (blockIdx.y).
   const int total = CIB * Q * CoutPad * 16;
-  const int e = blockIdx.x * 256 + threadIdx.x;
+  const int e = blockIdx.x * 256 + threadIdx.x, u0 = blockIdx.y * 3;
   if (e >= total) return;
   const int c8 = e % 8;
   const int n16 = (e / 8) % 16;
@@ -451,29 +450,20 @@ __global__ __launch_bounds__(256) void k_p4_pack_bwd_bf16(const uint16_t* __rest
   const int cib = e / (16 * CoutPad * Q);
   const int co = chunk * 32 + kg * 8 + c8, ci = cib * 16 + n16;
   const bool in = co < Cout && ci < Cin;
-  const int slices = Cout * Cin;
   const uint16_t* src = w + (size_t)(in ? co * Cin + ci : 0) * 9;
   uint16_t* dst = wt + (size_t)(e / 512) * 4608 + e % 512;      // + u * 512
+  float v[3];
 #pragma unroll
-  for (int u = 0; u < 9; ++u) {
-    double acc = 0.0;     // the combination in fp64, rounded to fp32 and to bf16 once each
+  for (int j = 0; j < 3; ++j) v[j] = expand_tap(src, (size_t)Cout * Cin * 9, 9, q, u0 + j, in, tab, true);
 #pragma unroll
-    for (int z = 0; z < kMaxNnz; ++z) {
-      const int s = fq_src[(q * 9 + u) * kMaxNnz + z];
-      if (in && s >= 0)
-        acc += fq_coef[(q * 9 + u) * kMaxNnz + z] * (double)bf16_to_f32(src[(size_t)(s / 9) * slices * 9 + s % 9]);
-    }
-    dst[u * 512] = f32_to_bf16((float)acc);
-  }
+  for (int j = 0; j < 3; ++j) dst[(u0 + j) * 512] = f32_to_bf16(v[j]);
 }
 
 // The same banks in the sparse layout: [16-channel block][Q][K-step][half h][orbit o][lgB][16 channels][jg][t];
 // element (jg, t) of lane (lgB, channel) is tap t of orbit o (corners R_t(0), edges R_t(1), centre for every t) of
 // the filter that the A lane (lgA = 2 (jg / 2) + lgB / 2) holds as pair p = 2 (lgB % 2) + jg % 2 of half h.
 __global__ __launch_bounds__(256) void k_p4_pack_bwd_bf16s(const uint16_t* __restrict__ w, uint16_t* __restrict__ wt,
-                                                           const int32_t* __restrict__ fq_src,
-                                                           const double* __restrict__ fq_coef, int Q, int CIB,
-                                                           int CoutPad, int Cin, int Cout) {
+                                                           ExpandTables tab, int Q, int CIB, int CoutPad, int Cin, int Cout) {
   // One thread per (bank, filter, channel): the nine taps go to three orbits x four positions (the centre four times).
   const int per_step = CHBS / 2;                      // elements of one K-step
   const int total = CIB * Q * (CoutPad / 32) * 2 * 256;
@@ -487,20 +477,10 @@ __global__ __launch_bounds__(256) void k_p4_pack_bwd_bf16s(const uint16_t* __res
   const int lgA = 2 * (jg / 2) + lgB / 2, pr = 2 * (lgB % 2) + jg % 2;
   const int co = chunk * 32 + 8 * lgA + 4 * h + pr, ci = cib * 16 + n16;
   const bool in = co < Cout && ci < Cin;
-  const int slices = Cout * Cin;
   const uint16_t* src = w + (size_t)(in ? co * Cin + ci : 0) * 9;
   float val[9];
 #pragma unroll
-  for (int u = 0; u < 9; ++u) {
-    double acc = 0.0;     // the combination in fp64, rounded to fp32 and to bf16 once each
-#pragma unroll
-    for (int z = 0; z < kMaxNnz; ++z) {
-      const int s = fq_src[(q * 9 + u) * kMaxNnz + z];
-      if (in && s >= 0)
-        acc += fq_coef[(q * 9 + u) * kMaxNnz + z] * (double)bf16_to_f32(src[(size_t)(s / 9) * slices * 9 + s % 9]);
-    }
-    val[u] = (float)acc;
-  }
+  for (int u = 0; u < 9; ++u) val[u] = expand_tap(src, (size_t)Cout * Cin * 9, 9, q, u, in, tab, true);
   uint16_t* dst = wt + (size_t)step * per_step + h * 3072 + lgB * 256 + n16 * 16 + jg * 4;    // + o * 1024 + t
 #pragma unroll
   for (int o = 0; o < 3; ++o) {
@@ -652,13 +632,13 @@ void launch_p4_pack_bwd_bf16(const rotconv_plan* p, const uint16_t* w, uint16_t*
   const int CIB = (p->d.Cin + 15) / 16, CoutPad = cout_pad(p->d.Cout);
   if (use_sparse(p)) {
     const int total = CIB * p->host.Q * (CoutPad / 32) * 512;
-    hipLaunchKernelGGL(k_p4_pack_bwd_bf16s, dim3((total + 255) / 256), dim3(256), 0, st, w, wt, p->dev.fq_src,
-                       p->dev.fq_coef64, p->host.Q, CIB, CoutPad, p->d.Cin, p->d.Cout);
+    hipLaunchKernelGGL(k_p4_pack_bwd_bf16s, dim3((total + 255) / 256), dim3(256), 0, st, w, wt, expand_tables(p),
+                       p->host.Q, CIB, CoutPad, p->d.Cin, p->d.Cout);
     return;
   }
   const int total = CIB * p->host.Q * CoutPad * 16;
-  hipLaunchKernelGGL(k_p4_pack_bwd_bf16, dim3((total + 255) / 256), dim3(256), 0, st, w, wt, p->dev.fq_src,
-                     p->dev.fq_coef64, p->host.Q, CIB, CoutPad, p->d.Cin, p->d.Cout);
+  hipLaunchKernelGGL(k_p4_pack_bwd_bf16, dim3((total + 255) / 256, 3), dim3(256), 0, st, w, wt, expand_tables(p),
+                     p->host.Q, CIB, CoutPad, p->d.Cin, p->d.Cout);
 }
 
 // part: scratch of p4_bwd_data_bf16_part_bytes() bytes (unused when that is 0)

@@ -479,6 +479,7 @@ __global__ __launch_bounds__(256) void k_sum_dx_bf16(const float* __restrict__ p
                                                      int nparts) {
   for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n_elem; e += (size_t)gridDim.x * 256) {
     float v = part[e];
+#pragma unroll 4
     for (int k = 1; k < nparts; ++k) v += part[(size_t)k * n_elem + e];
     dx[e] = f32_to_bf16(v);
   }

@@ -1336,8 +1336,18 @@ __global__ __launch_bounds__(256) void k_p4_sum_splits(const float* __restrict__
   const int e = blockIdx.x * 32 + (threadIdx.x % 32);
   const int grp = threadIdx.x / 32;
   float s = 0.f;
-  if (e < n_elem)
-    for (int sp = grp; sp < splits; sp += 8) s += partial[(size_t)sp * n_elem + e];
+  if (e < n_elem) {
+    const float* src = partial + e;
+    int sp = grp;
+    for (; sp + 56 < splits; sp += 64) {      // eight loads on their way, added in ascending order
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = src[(size_t)(sp + 8 * i) * n_elem];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) s += v[i];
+    }
+    for (; sp < splits; sp += 8) s += src[(size_t)sp * n_elem];
+  }
   red[grp][threadIdx.x % 32] = s;
   __syncthreads();
   if (grp == 0 && e < n_elem) {
@@ -1348,20 +1358,38 @@ __global__ __launch_bounds__(256) void k_p4_sum_splits(const float* __restrict__
 
 // The same sum for large images (many elements, few splits): one thread per four elements adds the splits in
 // ascending order, every access a full 16-byte lane access.
-template <bool RELAYOUT>
 __global__ __launch_bounds__(256) void k_p4_sum_splits_wide(const float* __restrict__ partial, float* __restrict__ out,
-                                                            int n4, int splits, DwLayout L) {
+                                                            int n4, int splits) {
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= n4) return;
   const f4* src = reinterpret_cast<const f4*>(partial);
   f4 s = src[e];
+#pragma unroll 4
   for (int sp = 1; sp < splits; ++sp) s += src[(size_t)sp * n4 + e];
-  if (!RELAYOUT) {
-    reinterpret_cast<f4*>(out)[e] = s;
-  } else {
+  reinterpret_cast<f4*>(out)[e] = s;
+}
+
+// ... and where the sum goes straight to dw[b][co][ci][u]: a workgroup takes the nine taps of 64 channels of a filter, so that
+// what it writes is one piece of 576 floats, turned round in LDS.  (Each sum written where it belongs, 36 bytes from the next
+// channel's: 19 us for 512 -> 512 channels and four splits; 13 so.)
+__global__ __launch_bounds__(192) void k_p4_sum_splits_dw(const float* __restrict__ partial, float* __restrict__ dw, int n_elem,
+                                                          int splits, DwLayout L) {
+  __shared__ float t[64 * 9];
+  const int co = blockIdx.x, ci0 = blockIdx.y * 64, b = blockIdx.z;
+  const int u = threadIdx.x / 16, c4 = threadIdx.x % 16 * 4;
+  if (u < 9 && ci0 + c4 < L.CinPad) {      // CinPad is a multiple of 16
+    const size_t n4 = n_elem / 4;
+    const f4* src = reinterpret_cast<const f4*>(partial) + (((size_t)(b * 9 + u) * L.CoutPad + co) * L.CinPad + ci0 + c4) / 4;
+    f4 s = src[0];
+#pragma unroll 4
+    for (int sp = 1; sp < splits; ++sp) s += src[sp * n4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) put_sum<true>(out, 4 * e + i, s[i], L);
+    for (int i = 0; i < 4; ++i) t[(c4 + i) * 9 + u] = s[i];
   }
+  __syncthreads();
+  const int n = min(64, L.Cin - ci0) * 9;
+  float* out = dw + (((size_t)b * L.Cout + co) * L.Cin + ci0) * 9;
+  for (int i = threadIdx.x; i < n; i += 192) out[i] = t[i];
 }
 
 // Stage 2: the transposed first-quadrant expansion (Eq. 16 / adjoint of Eq. 17):
@@ -1369,25 +1397,25 @@ __global__ __launch_bounds__(256) void k_p4_sum_splits_wide(const float* __restr
 __global__ __launch_bounds__(256) void k_p4_reduce_w(const float* __restrict__ dF, float* __restrict__ dw,
                                                      const int32_t* __restrict__ fqt_ptr,
                                                      const int32_t* __restrict__ fqt_col,
-                                                     const float* __restrict__ fqt_coef, int B, int Cout, int Cin,
+                                                     const float* __restrict__ fqt_coef, int Cout, int Cin,
                                                      int CoutPad, int CinPad, int base) {
-  // one thread per (bank, filter, channel): its nine taps are nine consecutive floats of dw
-  const int total = B * Cout * Cin;
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= total) return;
+  // one thread per (filter, channel), three taps (blockIdx.y) of base bank blockIdx.z
+  const int e = blockIdx.x * 256 + threadIdx.x, u0 = blockIdx.y * 3, b = blockIdx.z;
+  if (e >= Cout * Cin) return;
   const int ci = e % Cin;
-  const int co = (e / Cin) % Cout;
-  const int b = e / (Cin * Cout);
+  const int co = e / Cin;
   const size_t plane = (size_t)CoutPad * CinPad;
   const float* src = dF + (size_t)co * CinPad + ci;
-  float* dst = dw + (size_t)e * 9;
+  float* dst = dw + ((size_t)b * Cout * Cin + e) * 9;
 #pragma unroll
-  for (int ub = 0; ub < 9; ++ub) {
+  for (int ub = u0; ub < u0 + 3; ++ub) {
     float acc = 0.f;
     if (base) {       // dF already is the base banks' gradient: only the layout changes
       acc = src[(size_t)(b * 9 + ub) * plane];
     } else {
-      for (int z = fqt_ptr[b * 9 + ub]; z < fqt_ptr[b * 9 + ub + 1]; ++z) acc += fqt_coef[z] * src[(size_t)fqt_col[z] * plane];
+      const int z1 = fqt_ptr[b * 9 + ub + 1];
+#pragma unroll 4
+      for (int z = fqt_ptr[b * 9 + ub]; z < z1; ++z) acc += fqt_coef[z] * src[(size_t)fqt_col[z] * plane];
     }
     dst[ub] = acc;
   }
@@ -1456,14 +1484,7 @@ size_t p4_bwd_weight_ws_floats(const rotconv_plan* p) {
 // partial sums of the splits -> dF (fixed order) -> dw through the transposed expansion; one launch where that
 // expansion is the identity
 static bool dw_is_relayout(const rotconv_plan* p, const P4BwdWGeom& g) {
-  if (g.lut) return true;
-  if (g.Q != 1 || p->B != 1) return false;
-  for (int u = 0; u < 9; ++u)
-    for (int z = 0; z < kMaxNnz; ++z) {
-      const int src = p->host.fq_src[u * kMaxNnz + z];
-      if (z == 0 ? (src != u || p->host.fq_coef[u * kMaxNnz] != 1.0f) : src >= 0) return false;
-    }
-  return true;
+  return g.lut || p->base_bank;
 }
 static void finish_dw(const rotconv_plan* p, const P4BwdWGeom& g, float* partial, float* dw, hipStream_t st) {
   const int n_elem = g.Q * 9 * g.CoutPad * g.CinPad;      // a multiple of 16
@@ -1473,17 +1494,16 @@ static void finish_dw(const rotconv_plan* p, const P4BwdWGeom& g, float* partial
   if (g.splits > 1) {
     dF = relayout ? dw : partial + (size_t)g.splits * n_elem;
     if (n_elem >= (1 << 18)) {
-      if (relayout) hipLaunchKernelGGL(k_p4_sum_splits_wide<true>, dim3((n_elem / 4 + 255) / 256), dim3(256), 0, st, partial, dF, n_elem / 4, g.splits, L);
-      else hipLaunchKernelGGL(k_p4_sum_splits_wide<false>, dim3((n_elem / 4 + 255) / 256), dim3(256), 0, st, partial, dF, n_elem / 4, g.splits, L);
+      if (relayout) hipLaunchKernelGGL(k_p4_sum_splits_dw, dim3(g.Cout, (g.Cin + 63) / 64, g.Q), dim3(192), 0, st, partial, dw, n_elem, g.splits, L);
+      else hipLaunchKernelGGL(k_p4_sum_splits_wide, dim3((n_elem / 4 + 255) / 256), dim3(256), 0, st, partial, dF, n_elem / 4, g.splits);
     } else {
       if (relayout) hipLaunchKernelGGL(k_p4_sum_splits<true>, dim3((n_elem + 31) / 32), dim3(256), 0, st, partial, dF, n_elem, g.splits, L);
       else hipLaunchKernelGGL(k_p4_sum_splits<false>, dim3((n_elem + 31) / 32), dim3(256), 0, st, partial, dF, n_elem, g.splits, L);
     }
     if (relayout) return;
   }
-  const int total = p->B * g.Cout * g.Cin;
-  hipLaunchKernelGGL(k_p4_reduce_w, dim3((total + 255) / 256), dim3(256), 0, st, dF, dw, p->dev.fqt_ptr,
-                     p->dev.fqt_col, p->dev.fqt_coef, p->B, g.Cout, g.Cin, g.CoutPad, g.CinPad, g.lut);
+  hipLaunchKernelGGL(k_p4_reduce_w, dim3((g.Cout * g.Cin + 255) / 256, 3, p->B), dim3(256), 0, st, dF, dw, p->dev.fqt_ptr,
+                     p->dev.fqt_col, p->dev.fqt_coef, g.Cout, g.Cin, g.CoutPad, g.CinPad, g.lut);
 }
 
 void launch_p4_bwd_weight(const rotconv_plan* p, const float* x, const float* gpool, const uint8_t* idx,

@@ -43,6 +43,7 @@
 #include <cstdlib>
 
 #include "rotconv_bf16.h"
+#include "rotconv_expand.h"
 #include "rotconv_kernels.h"
 #include "rotconv_p4.h"
 #include "rotconv_p4_taps.h"
@@ -544,6 +545,7 @@ __global__ __launch_bounds__(256) void k_p4_sum_parts(const float* __restrict__ 
   const size_t n4 = n_elem / 4;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 256) {
     f4 a = reinterpret_cast<const f4*>(part)[i];
+#pragma unroll 8
     for (int k = 1; k < nparts; ++k) a += reinterpret_cast<const f4*>(part + (size_t)k * n_elem)[i];
     reinterpret_cast<f4*>(y)[i] = a;
   }
@@ -570,6 +572,7 @@ __global__ __launch_bounds__(256) void k_p4_sum_pool(const float* __restrict__ p
   int bi = -1;
   for (int r = grp; r < R; r += ng) {
     float v = yb[(size_t)r * HW];
+#pragma unroll 8
     for (int k = 1; k < nparts; ++k) v += yb[(size_t)k * n_elem + (size_t)r * HW];
     if (bi < 0 || v > best) { best = v; bi = r; }
   }
@@ -581,17 +584,15 @@ __global__ __launch_bounds__(256) void k_p4_sum_pool(const float* __restrict__ p
 // base bank(s) -> Q first-quadrant banks in the LDS image layout: [Q][CB][CinPad][9][16] fp32, or
 // [Q][CB][chunk][tap][part][lane][8] bf16 parts; zero for padded filters / channels.
 // nq > 1: the banks are folded into the sixteen filters of a block (column n = bank n % nq of filter n / nq): [CB']...
-// One thread per (bank, filter, channel or pair of channels): its taps read the same 36 or 72 bytes of w.
+// One thread per (bank, filter, channel or pair of channels) and three taps (blockIdx.y).
 template <bool S3>
-__global__ __launch_bounds__(256) void k_p4_pack_fwd(const float* __restrict__ w, float* __restrict__ wt,
-                                                     const int32_t* __restrict__ fq_src,
-                                                     const float* __restrict__ fq_coef,
-                                                     const double* __restrict__ fq_coef64, int Q, int CB, int CinPad,
-                                                     int Cin, int Cout, int round16, int nq, int cb0) {
+__global__ __launch_bounds__(256) void k_p4_pack_fwd(const float* __restrict__ w, float* __restrict__ wt, ExpandTables tab,
+                                                     int Q, int CB, int CinPad, int Cin, int Cout, int round16, int nq,
+                                                     int cb0) {
   constexpr int CPT = S3 ? 2 : 1;                   // channels per thread
   const int per = CinPad * 16 / CPT;                // threads per block of sixteen filters
   const int total = (nq > 1 ? 1 : Q) * CB * per;
-  const int e = blockIdx.x * 256 + threadIdx.x;
+  const int e = blockIdx.x * 256 + threadIdx.x, u0 = blockIdx.y * 3;
   if (e >= total) return;
   const int blk = e / per, i = e % per;
   const int c16 = S3 ? (i / 4) % 16 : i % 16;
@@ -603,24 +604,33 @@ __global__ __launch_bounds__(256) void k_p4_pack_fwd(const float* __restrict__ w
   const size_t bank_stride = (size_t)Cout * Cin * 9;
   if constexpr (S3) {
     const bool in0 = co < Cout && ci < Cin, in1 = co < Cout && ci + 1 < Cin;
-    const float* src = w + ((size_t)(in0 ? co : 0) * Cin + (in0 ? ci : 0)) * 9;
+    const float* s0 = w + ((size_t)(in0 ? co : 0) * Cin + (in0 ? ci : 0)) * 9;
+    const float* s1 = w + ((size_t)(in1 ? co : 0) * Cin + (in1 ? ci + 1 : 0)) * 9;
     uint32_t* dst = reinterpret_cast<uint32_t*>(wt) + ((size_t)blk * (CinPad / 32) + i / 256) * kS3FwdChunk + i % 256;
+    float va[3], vb[3];
 #pragma unroll
-    for (int u = 0; u < 9; ++u) {
+    for (int j = 0; j < 3; ++j) {
+      va[j] = expand_tap(s0, bank_stride, 9, q, u0 + j, in0, tab, round16);
+      vb[j] = expand_tap(s1, bank_stride, 9, q, u0 + j, in1, tab, round16);
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
       uint16_t a[3], b[3];
-      s3_split_weight(s3_expand_tap(src, bank_stride, q * 9 + u, in0, fq_src, fq_coef, fq_coef64, round16), a[0], a[1], a[2]);
-      s3_split_weight(s3_expand_tap(src + 9, bank_stride, q * 9 + u, in1, fq_src, fq_coef, fq_coef64, round16), b[0], b[1],
-                      b[2]);
+      s3_split_weight(va[j], a[0], a[1], a[2]);
+      s3_split_weight(vb[j], b[0], b[1], b[2]);
+      const uint32_t turn = s3_tap_turned(u0 + j) ? 0x80008000u : 0u;
 #pragma unroll
-      for (int k = 0; k < 3; ++k) dst[(u * 3 + k) * 256] = ((uint32_t)a[k] | (uint32_t)b[k] << 16) ^ (s3_tap_turned(u) ? 0x80008000u : 0u);
+      for (int k = 0; k < 3; ++k) dst[((u0 + j) * 3 + k) * 256] = ((uint32_t)a[k] | (uint32_t)b[k] << 16) ^ turn;
     }
   } else {
     const bool in = co < Cout && ci < Cin;
     const float* src = w + (size_t)(in ? co * Cin + ci : 0) * 9;
     float* dst = wt + (size_t)(e / 16) * 144 + c16;
+    float v[3];
 #pragma unroll
-    for (int u = 0; u < 9; ++u)
-      dst[u * 16] = s3_expand_tap(src, bank_stride, q * 9 + u, in, fq_src, fq_coef, fq_coef64, round16);
+    for (int j = 0; j < 3; ++j) v[j] = expand_tap(src, bank_stride, 9, q, u0 + j, in, tab, round16);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) dst[(u0 + j) * 16] = v[j];
   }
 }
 
@@ -903,14 +913,7 @@ int p4_fwd_pool_mode(const rotconv_plan* p) {
 }
 
 bool p4_fwd_raw_weights(const rotconv_plan* p, int nq, int csplit) {
-  if (p->d.dtype != ROTCONV_F32 || p->host.Q != 1 || p->B != 1 || nq > 1) return false;
-  if (needs_stream(p, csplit)) return false;
-  for (int u = 0; u < 9; ++u)
-    for (int z = 0; z < kMaxNnz; ++z) {
-      const int src = p->host.fq_src[u * kMaxNnz + z];
-      if (z == 0 ? (src != u || p->host.fq_coef[u * kMaxNnz] != 1.0f) : src >= 0) return false;
-    }
-  return true;
+  return p->d.dtype == ROTCONV_F32 && p->base_bank && nq == 1 && !needs_stream(p, csplit);
 }
 
 void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const float* w, float* pack, size_t pack_bytes,
@@ -931,9 +934,8 @@ void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const fl
     if (!raw) {
       const int total = (nq > 1 ? 1 : p->host.Q) * ncb * CinPad * (s3 ? 8 : 16);
       auto kern = s3 ? k_p4_pack_fwd<true> : k_p4_pack_fwd<false>;
-      hipLaunchKernelGGL(kern, dim3((total + 255) / 256), dim3(256), 0, st, w, pack, p->dev.fq_src, p->dev.fq_coef,
-                         p->dev.fq_coef64, p->host.Q, ncb, CinPad, p->d.Cin, p->d.Cout,
-                         p->d.dtype == ROTCONV_BF16 ? 1 : 0, nq, cb0);
+      hipLaunchKernelGGL(kern, dim3((total + 255) / 256, 3), dim3(256), 0, st, w, pack, expand_tables(p), p->host.Q, ncb,
+                         CinPad, p->d.Cin, p->d.Cout, p->d.dtype == ROTCONV_BF16 ? 1 : 0, nq, cb0);
     }
     const float* wt = raw ? w : pack;
     if (!chain) {

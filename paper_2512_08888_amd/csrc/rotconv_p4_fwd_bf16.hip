@@ -474,12 +474,14 @@ __global__ __launch_bounds__(256) void k_p4_combine_bf16(const float* __restrict
 // to bf16 once each) in the LDS image layout [Q][CB][chunk][9 taps][4 k-groups][16 filters][8 channels]; zero for
 // padded filters / channels.
 // nq > 1: the banks are folded into the 16 columns (column n = bank n / (16/nq), filter n % (16/nq)): [CB'][chunk]...
-// One thread per (filter, channel): it reads the 9 NB taps of its base filter(s) once and forms all Q banks with
-// wave-uniform fp64 coefficients (dense [Q][9][NS] matrices, NS = 9 source taps per base bank).
+// One thread per (filter, channel) and bank (blockIdx.y): it reads the 9 NB taps of its base filter(s) and forms the bank's
+// with wave-uniform fp64 coefficients (dense [Q][9][NS] matrices, NS = 9 source taps per base bank), or copies them where
+// the bank is the base bank.  (All banks in one thread: 17 us for 256 -> 256 channels and four banks, the chain of its
+// coefficient loads; 6 so.)
 template <int NS>
 __global__ __launch_bounds__(256) void k_p4_pack_fwd_bf16(const uint16_t* __restrict__ w, uint16_t* __restrict__ wt,
                                                           const double* __restrict__ dense, int Q, int CB, int CinPad,
-                                                          int Cin, int Cout, int nq) {
+                                                          int Cin, int Cout, int nq, int identity) {
   const int fpb = nq > 1 ? 16 / nq : 16;                 // filters of a block that are distinct filters
   const int total = CB * CinPad * fpb;
   const int e = blockIdx.x * 256 + threadIdx.x;
@@ -496,18 +498,22 @@ __global__ __launch_bounds__(256) void k_p4_pack_fwd_bf16(const uint16_t* __rest
   double wv[NS];
 #pragma unroll
   for (int s = 0; s < NS; ++s) wv[s] = in ? (double)bf16_to_f32(src[(size_t)(s / 9) * slices * 9 + s % 9]) : 0.0;
-  for (int q = 0; q < Q; ++q) {
-    const int f16 = nq > 1 ? q * fpb + fs : fs;
-    const int blk = nq > 1 ? cb : q * CB + cb;
-    uint16_t* dst = wt + ((size_t)blk * (CinPad / 32) + chunk) * 4608 + (kg * 16 + f16) * 8 + c8;      // + u * 512
-    const double* dq = dense + (size_t)q * 9 * NS;
+  const int q = blockIdx.y;
+  const int f16 = nq > 1 ? q * fpb + fs : fs;
+  const int blk = nq > 1 ? cb : q * CB + cb;
+  uint16_t* dst = wt + ((size_t)blk * (CinPad / 32) + chunk) * 4608 + (kg * 16 + f16) * 8 + c8;      // + u * 512
+  if (identity) {
 #pragma unroll
-    for (int u = 0; u < 9; ++u) {
-      double acc = 0.0;     // the combination in fp64, rounded to fp32 and to bf16 once each
+    for (int u = 0; u < 9; ++u) dst[u * 512] = f32_to_bf16((float)wv[u]);
+    return;
+  }
+  const double* dq = dense + (size_t)q * 9 * NS;
 #pragma unroll
-      for (int s = 0; s < NS; ++s) acc += dq[u * NS + s] * wv[s];
-      dst[u * 512] = f32_to_bf16((float)acc);
-    }
+  for (int u = 0; u < 9; ++u) {
+    double acc = 0.0;     // the combination in fp64, rounded to fp32 and to bf16 once each
+#pragma unroll
+    for (int s = 0; s < NS; ++s) acc += dq[u * NS + s] * wv[s];
+    dst[u * 512] = f32_to_bf16((float)acc);
   }
 }
 
@@ -592,11 +598,11 @@ void launch_p4_pack_fwd_bf16(const rotconv_plan* p, int nq, const uint16_t* w, u
   const int CinPad = cin_pad(p->d.Cin), CB = nq > 1 ? (p->d.Cout * nq + 15) / 16 : (p->d.Cout + 15) / 16;
   const int total = CB * CinPad * (nq > 1 ? 16 / nq : 16);
   if (p->B == 1)
-    hipLaunchKernelGGL(k_p4_pack_fwd_bf16<9>, dim3((total + 255) / 256), dim3(256), 0, st, w, wt, p->dev.fq_dense64,
-                       p->host.Q, CB, CinPad, p->d.Cin, p->d.Cout, nq);
+    hipLaunchKernelGGL(k_p4_pack_fwd_bf16<9>, dim3((total + 255) / 256, p->host.Q), dim3(256), 0, st, w, wt, p->dev.fq_dense64,
+                       p->host.Q, CB, CinPad, p->d.Cin, p->d.Cout, nq, p->base_bank);
   else
-    hipLaunchKernelGGL(k_p4_pack_fwd_bf16<18>, dim3((total + 255) / 256), dim3(256), 0, st, w, wt, p->dev.fq_dense64,
-                       p->host.Q, CB, CinPad, p->d.Cin, p->d.Cout, nq);
+    hipLaunchKernelGGL(k_p4_pack_fwd_bf16<18>, dim3((total + 255) / 256, p->host.Q), dim3(256), 0, st, w, wt, p->dev.fq_dense64,
+                       p->host.Q, CB, CinPad, p->d.Cin, p->d.Cout, nq, p->base_bank);
 }
 
 // out_val: bf16 [N][C'][H][W] (kOutPooled), bf16 [N][Cout*R][H][W] (kOutUnpooled) or fp32 per-bank

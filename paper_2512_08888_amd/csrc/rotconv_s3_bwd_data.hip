@@ -27,6 +27,7 @@
 
 #include <algorithm>
 
+#include "rotconv_expand.h"
 #include "rotconv_kernels.h"
 #include "rotconv_p4.h"
 #include "rotconv_p4_taps.h"
@@ -323,15 +324,13 @@ __global__ __launch_bounds__(NT, 2) void k_s3_bwd_data(const float* __restrict__
 }
 
 // banks -> [channel group][K-step (bank, 16 filters)][32-channel block of the group][tap][part][lane][8 filters].
-// One thread per (block, K-step, channel, pair of filters).
-__global__ __launch_bounds__(256) void k_s3_pack_bwd(const float* __restrict__ w, uint32_t* __restrict__ wp,
-                                                     const int32_t* __restrict__ fq_src, const float* __restrict__ fq_coef,
-                                                     const double* __restrict__ fq_coef64, int nblk, int bpg, int nk, int nkb,
-                                                     int Cin, int Cout, int round16) {
+// One thread per (block, K-step, channel, pair of filters) and three taps (blockIdx.y).
+__global__ __launch_bounds__(256) void k_s3_pack_bwd(const float* __restrict__ w, uint32_t* __restrict__ wp, ExpandTables tab,
+                                                     int nblk, int bpg, int nk, int nkb, int Cin, int Cout, int round16) {
   const size_t total = (size_t)nblk * nk * 256;
   const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (e >= total) return;
-  const int i = (int)(e % 256), cp = i % 4, l = i / 4;
+  const int i = (int)(e % 256), cp = i % 4, l = i / 4, u0 = blockIdx.y * 3;
   const int k = (int)(e / 256 % nk), blk = (int)(e / 256 / nk);
   const int ci = blk * 32 + l % 32, half = l / 32, kb = k % nkb, q = k / nkb;
   const int co0 = s3_filter(kb, half, cp * 2, Cout), co1 = s3_filter(kb, half, cp * 2 + 1, Cout);
@@ -340,15 +339,19 @@ __global__ __launch_bounds__(256) void k_s3_pack_bwd(const float* __restrict__ w
   const float* s0 = w + ((size_t)(in0 ? co0 : 0) * Cin + (in0 ? ci : 0)) * 9;
   const float* s1 = w + ((size_t)(in1 ? co1 : 0) * Cin + (in1 ? ci : 0)) * 9;
   uint32_t* dst = wp + (((size_t)(blk / bpg) * nk + k) * bpg + blk % bpg) * (BLK4 * 4) + i;
+  float a[3], b[3];
 #pragma unroll
-  for (int u = 0; u < 9; ++u) {
-    const float a = s3_expand_tap(s0, bank_stride, q * 9 + u, in0, fq_src, fq_coef, fq_coef64, round16);
-    const float b = s3_expand_tap(s1, bank_stride, q * 9 + u, in1, fq_src, fq_coef, fq_coef64, round16);
+  for (int j = 0; j < 3; ++j) {
+    a[j] = expand_tap(s0, bank_stride, 9, q, u0 + j, in0, tab, round16);
+    b[j] = expand_tap(s1, bank_stride, 9, q, u0 + j, in1, tab, round16);
+  }
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
     uint16_t pa[3], pb[3];
-    s3_split_weight(a, pa[0], pa[1], pa[2]);
-    s3_split_weight(b, pb[0], pb[1], pb[2]);
+    s3_split_weight(a[j], pa[0], pa[1], pa[2]);
+    s3_split_weight(b[j], pb[0], pb[1], pb[2]);
 #pragma unroll
-    for (int z = 0; z < 3; ++z) dst[(u * 3 + z) * 256] = (uint32_t)pa[z] | (uint32_t)pb[z] << 16;
+    for (int z = 0; z < 3; ++z) dst[((u0 + j) * 3 + z) * 256] = (uint32_t)pa[z] | (uint32_t)pb[z] << 16;
   }
 }
 
@@ -436,8 +439,8 @@ void launch_s3_bwd_data(const rotconv_plan* p, const float* gpool, const uint8_t
   const S3BwdGeom& g = b.g;
   const int bpg = b.TB, nblk = g.ncg * bpg;
   const size_t total = (size_t)nblk * g.nk * 256;
-  hipLaunchKernelGGL(k_s3_pack_bwd, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, w, static_cast<uint32_t*>(pack),
-                     p->dev.fq_src, p->dev.fq_coef, p->dev.fq_coef64, nblk, bpg, g.nk, g.nkb, g.Cin, g.Cout,
+  hipLaunchKernelGGL(k_s3_pack_bwd, dim3((unsigned)((total + 255) / 256), 3), dim3(256), 0, st, w,
+                     static_cast<uint32_t*>(pack), expand_tables(p), nblk, bpg, g.nk, g.nkb, g.Cin, g.Cout,
                      p->d.dtype == ROTCONV_BF16 ? 1 : 0);
   float* dx = g.ksplit > 1 ? part : dx_out;
   const size_t lds = (size_t)2 * b.TB * BLK4 * 16;

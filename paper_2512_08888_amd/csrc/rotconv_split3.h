@@ -112,26 +112,4 @@ __device__ __host__ constexpr bool s3_tap_turned(int u) { return u & 1; }
 // kernels' limits on an image see to that), so that they read as zero.
 constexpr uint32_t kOutside = 0xfffffff0u;
 
-// One element (bank q, tap u) of the expansion of a base slice; src: the nine taps of (filter, channel).  round16: bf16
-// plans, the combination in fp64, rounded to fp32 and to bf16 once each.
-__device__ __forceinline__ float s3_expand_tap(const float* __restrict__ src, size_t bank_stride, int row, bool in,
-                                               const int32_t* __restrict__ fq_src, const float* __restrict__ fq_coef,
-                                               const double* __restrict__ fq_coef64, int round16) {
-  if (round16) {
-    double a64 = 0.0;
-    for (int z = 0; z < kMaxNnz; ++z) {
-      const int s = fq_src[row * kMaxNnz + z];
-      if (in && s >= 0) a64 += fq_coef64[row * kMaxNnz + z] * (double)src[(size_t)(s / 9) * bank_stride + s % 9];
-    }
-    return bf16_to_f32(f32_to_bf16((float)a64));
-  }
-  float acc = 0.f;
-#pragma unroll
-  for (int z = 0; z < kMaxNnz; ++z) {
-    const int s = fq_src[row * kMaxNnz + z];
-    if (in && s >= 0) acc += fq_coef[row * kMaxNnz + z] * src[(size_t)(s / 9) * bank_stride + s % 9];
-  }
-  return acc;
-}
-
 }  // namespace rotconv
