@@ -1,15 +1,20 @@
 // GEMMs on the matrix cores for the network glue around the rotation convolution (2x2
 // transposed-convolution up-sampling, 1x1 head): C = op(A) * op(B), optionally batched and/or
-// split along K with an ordered reduction afterwards.  Two kernels of the same shape, 128 x 128
-// tiles, four waves of 64 x 64 (sixteen accumulators each), operands staged through LDS, the next
-// tile prefetched into registers while the current one is multiplied:
-//   k_gemm    fp32 operands, 16x16x4 fp32 instruction, 16-deep tiles, LDS k-major;
-//   k_gemm16  bfloat16 operands, 16x16x32 bf16 instruction (fp32 accumulation), 32-deep tiles,
-//             LDS row-major with the contraction index contiguous.
+// split along K with an ordered reduction afterwards.  Three kernels, operands staged through LDS,
+// the next tile prefetched into registers while the current one is multiplied:
+//   k_gemm_s3 fp32 operands in three bf16 parts (rotconv_split3.h), 16x16x32 bf16 instruction, 32-deep
+//             tiles of 64 x 64 or 128 x 128;
+//   k_gemm    fp32 operands, 16x16x4 fp32 instruction, 16-deep tiles of 128 x 128, LDS k-major (layers
+//             whose plan keeps the fp32 instructions);
+//   k_gemm16  bfloat16 operands, 16x16x32 bf16 instruction (fp32 accumulation), 32-deep tiles of
+//             128 x 128, LDS row-major with the contraction index contiguous.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "glue_internal.h"
 #include "rotconv_bf16.h"
+#include "rotconv_split3.h"
 
 namespace rotconv {
 namespace {
@@ -285,6 +290,183 @@ __global__ __launch_bounds__(NT) void k_gemm16(const uint16_t* __restrict__ A, c
   }
 }
 
+// fp32 operands in three bf16 parts: tiles of 32 T x 32 T x 32 (T = 2 or 4), four waves of T x T 16 x 16 tiles.  A thread
+// fetches eight consecutive k of a row (two rows with T = 4), splits them and writes three 16-byte pieces; LDS holds the
+// parts row-major (pitch 40 halfwords, as k_gemm16), so a fragment is one ds_read_b128.  The six products of a K-step are
+// summed from zero, smallest first, and only their total meets the running sum; every other K-step multiplies -A and is
+// subtracted, so that the instruction's cut towards minus infinity cancels.
+//
+// What bounds it: the vector work of the split (44 instructions per eight elements) and one matrix instruction per 16 clk; a
+// launch of few tiles is a chain of K-steps of one workgroup per CU, one of few K-steps the way of its loads and stores: small
+// tiles there (T = 2 below 512 tiles of 128 x 128 or four K-steps).  Against k_gemm: 512 x 1024 x 256 (two) 28 -> 11 us, 256 x 1024 x 512 (two) 47 -> 16.
+typedef f4 f4u __attribute__((aligned(4)));
+template <bool TA, bool TB, int T>
+__global__ __launch_bounds__(NT) void k_gemm_s3(const float* __restrict__ A, const float* __restrict__ B,
+                                               float* __restrict__ C, GemmArgs p) {
+  constexpr int TM = 32 * T, NJ = T / 2;            // rows of a tile; pieces of eight k per thread and operand
+  constexpr int OPW = 3 * TM * PITCH16;             // halfwords of an operand's tile
+  extern __shared__ uint16_t sm16[];                // [2][A, B][part][row][PITCH16]
+  const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, lg = lane / 16, lc = lane % 16;
+  const int m0 = blockIdx.x * TM, n0 = blockIdx.y * TM;
+  const int z = blockIdx.z, batch = z / p.splitk, ks = z % p.splitk;
+  const int kchunk = ((p.K + p.splitk - 1) / p.splitk + 31) / 32 * 32;
+  const int kbeg = ks * kchunk, kend = min(p.K, kbeg + kchunk);
+  const float* Ap = A + (size_t)batch * p.strideA;
+  const float* Bp = B + (size_t)batch * p.strideB;
+  const size_t Cbase = (size_t)z * p.strideC;
+  constexpr bool AKM = TA, BKM = !TB;               // operand stored k-major
+  // the thread's piece j: row and first k inside the tile
+  auto prow = [&](bool km, int j) { return km ? tid % TM : tid / 4 + 64 * j; };
+  auto pk = [&](bool km, int j) { return 8 * (km ? tid / TM + (NT / TM) * j : tid % 4); };
+  static_assert((NT / TM) * NJ == 4, "four pieces of eight k per row");
+
+  // A K-step's compute is short beside a load's way, so SETS - 1 K-steps are on their way in registers.
+  constexpr int SETS = T == 2 ? 4 : 2;
+  float ra[SETS][NJ][8], rb[SETS][NJ][8];
+  // eight values of a row from k on; outside the matrix zero (every address is one of the operand's)
+  auto fetch = [&](auto full_c, float (&r)[8], const float* base, bool km, int ld, int row, int rows, int k, bool shuf) {
+    constexpr bool full = decltype(full_c)::value;  // the K-step lies inside the chunk
+    const bool rok = row < rows;
+    const int rr = rok ? row : 0;
+    auto at = [&](int i) { return full ? k + i : min(k + i, p.K - 1); };
+    auto keep = [&](int i, float v) { r[i] = rok && (full || k + i < kend) ? v : 0.f; };
+    if (shuf) {
+      if (km) {                                     // k = (co, a, b), row = pixel
+        const float* s = base + shuf_pix(rr, p.shufW);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) keep(i, s[shuf_row(at(i), p.shufH, p.shufW)]);
+      } else {                                      // k = pixel, row = (co, a, b)
+        const float* s = base + shuf_row(rr, p.shufH, p.shufW);
+        const int kf = at(0);
+        int h = kf / p.shufW, w = kf - h * p.shufW;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          keep(i, s[(size_t)(4 * h) * p.shufW + 2 * w]);
+          if (full || k + i + 1 < p.K) {
+            const bool wrap = w + 1 == p.shufW;
+            w = wrap ? 0 : w + 1;
+            h += wrap;
+          }
+        }
+      }
+    } else if (km) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) keep(i, base[(size_t)at(i) * ld + rr]);
+    } else if (full) {
+      const f4u* s = reinterpret_cast<const f4u*>(base + (size_t)rr * ld + k);
+      const f4 a = s[0], b = s[1];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) keep(i, i < 4 ? a[i & 3] : b[i & 3]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) keep(i, base[(size_t)rr * ld + at(i)]);
+    }
+  };
+  auto gload = [&](int set, int k0) {
+    auto all = [&](auto full_c) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        fetch(full_c, ra[set][j], Ap, AKM, p.lda, m0 + prow(AKM, j), p.M, k0 + pk(AKM, j), false);
+        fetch(full_c, rb[set][j], Bp, BKM, p.ldb, n0 + prow(BKM, j), p.N, k0 + pk(BKM, j), p.shufB);
+      }
+    };
+    if (k0 + 32 <= kend) all(std::true_type{}); else all(std::false_type{});
+  };
+  auto put = [&](uint16_t* op, const float (&r)[8], int row, int k, bool neg) {
+    u32x4 o[3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const S3Pair s = s3_split2(neg ? -r[2 * i] : r[2 * i], neg ? -r[2 * i + 1] : r[2 * i + 1]);
+#pragma unroll
+      for (int e = 0; e < 3; ++e) o[e][i] = s.p[e];
+    }
+#pragma unroll
+    for (int e = 0; e < 3; ++e) *reinterpret_cast<u32x4*>(op + (size_t)e * TM * PITCH16 + row * PITCH16 + k) = o[e];
+  };
+  auto sstore = [&](int buf, int set, bool neg) {
+    uint16_t* a = sm16 + buf * 2 * OPW;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      put(a, ra[set][j], prow(AKM, j), pk(AKM, j), neg);
+      put(a + OPW, rb[set][j], prow(BKM, j), pk(BKM, j), false);
+    }
+  };
+
+  f4 acc[T][T];
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int j = 0; j < T; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+  const int wm = (wave / 2) * 16 * T, wn = (wave % 2) * 16 * T;
+  auto multiply = [&](int buf, bool neg) {
+    const uint16_t* a = sm16 + buf * 2 * OPW + (wm + lc) * PITCH16 + 8 * lg;
+    const uint16_t* b = sm16 + buf * 2 * OPW + OPW + (wn + lc) * PITCH16 + 8 * lg;
+    u32x4 av[T][3];
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+      for (int e = 0; e < 3; ++e) av[i][e] = *reinterpret_cast<const u32x4*>(a + (e * TM + 16 * i) * PITCH16);
+#pragma unroll
+    for (int j = 0; j < T; ++j) {
+      u32x4 bv[3];
+#pragma unroll
+      for (int e = 0; e < 3; ++e) bv[e] = *reinterpret_cast<const u32x4*>(b + (e * TM + 16 * j) * PITCH16);
+      f4 s[T];
+      auto product = [&](int ae, int be) {
+#pragma unroll
+        for (int i = 0; i < T; ++i) s[i] = s3_mfma(av[i][ae], bv[be], s[i]);
+      };
+#pragma unroll
+      for (int i = 0; i < T; ++i) s[i] = f4{0.f, 0.f, 0.f, 0.f};
+      product(2, 0);
+      product(0, 2);
+      product(1, 1);
+      product(1, 0);
+      product(0, 1);
+      product(0, 0);
+#pragma unroll
+      for (int i = 0; i < T; ++i) acc[i][j] = neg ? acc[i][j] - s[i] : acc[i][j] + s[i];
+    }
+  };
+
+  if (kbeg < kend) {
+#pragma unroll
+    for (int i = 0; i + 1 < SETS; ++i)
+      if (kbeg + 32 * i < kend) gload(i, kbeg + 32 * i);
+    sstore(0, 0, false);
+    __syncthreads();
+    bool more = true;
+    for (int k0 = kbeg; more; k0 += 32 * SETS) {
+#pragma unroll
+      for (int st = 0; st < SETS; ++st) {            // K-steps of either sign in turn
+        const int k = k0 + 32 * st;
+        if (!more) continue;
+        more = k + 32 < kend;
+        if (k + 32 * (SETS - 1) < kend) gload((st + SETS - 1) % SETS, k + 32 * (SETS - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(st & 1, st & 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) sstore((st + 1) & 1, (st + 1) % SETS, (st + 1) & 1);
+        __syncthreads();
+      }
+    }
+  }
+  // accumulator tile (i, j): rows m = wm + 16 i + 4 lg + r, column n = wn + 16 j + lc
+#pragma unroll
+  for (int j = 0; j < T; ++j) {
+    const int gn = n0 + wn + 16 * j + lc;
+    if (gn >= p.N) continue;
+    const size_t coff = Cbase + (p.shufC ? shuf_pix(gn, p.shufW) : (size_t)gn);
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int gm = m0 + wm + 16 * i + 4 * lg + r;
+        if (gm < p.M) C[coff + (p.shufC ? shuf_row(gm, p.shufH, p.shufW) : (size_t)gm * p.ldc)] = acc[i][j][r];
+      }
+  }
+}
+
 // out[e] = sum_z part[z][e].  A block covers 32 elements x 8 interleaved groups of parts, each added in ascending order, then
 // the groups in a fixed tree.  (One thread per element: 15 us for the 128 parts of 128 x 8 elements, the chain of its loads.)
 __global__ __launch_bounds__(256) void k_sum_parts(const float* __restrict__ part, float* __restrict__ out, size_t n,
@@ -305,6 +487,20 @@ __global__ __launch_bounds__(256) void k_sum_parts(const float* __restrict__ par
 
 }  // namespace
 
+template <int T>
+void launch_gemm_s3(const GemmArgs& a, const float* A, const float* B, float* C, hipStream_t st) {
+  const int tm = 32 * T;
+  const size_t lds = (size_t)2 * 2 * 3 * tm * PITCH16 * sizeof(uint16_t);
+  dim3 grid((a.M + tm - 1) / tm, (a.N + tm - 1) / tm, a.batch * a.splitk);
+  auto go = [&](auto kern) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(kern, grid, dim3(NT), lds, st, A, B, C, a);
+  };
+  if (a.transA && a.transB) go(k_gemm_s3<true, true, T>);
+  else if (a.transA) go(k_gemm_s3<true, false, T>);
+  else if (a.transB) go(k_gemm_s3<false, true, T>);
+  else go(k_gemm_s3<false, false, T>);
+}
 void launch_gemm_f32(const GemmArgs& a, const void* A, const void* B, void* C, hipStream_t st) {
   dim3 grid((a.M + BM - 1) / BM, (a.N + BN - 1) / BN, a.batch * a.splitk);
   const float* Af = static_cast<const float*>(A);
@@ -329,6 +525,12 @@ void launch_gemm(const GemmArgs& a, const void* A, const void* B, void* C, hipSt
   // the glue uses three storage combinations: all fp32, bf16 operands with an fp32 or a bf16 result
   if (a.bf16A && a.bf16B && a.bf16C) launch_gemm_bf16<true>(a, A, B, C, st);
   else if (a.bf16A && a.bf16B) launch_gemm_bf16<false>(a, A, B, C, st);
+  else if (!a.fp32_instr) {
+    const long tiles = (long)((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch * a.splitk;
+    const float *Af = static_cast<const float*>(A), *Bf = static_cast<const float*>(B);
+    if (tiles >= 512 && a.K >= 128 * a.splitk) launch_gemm_s3<4>(a, Af, Bf, static_cast<float*>(C), st);
+    else launch_gemm_s3<2>(a, Af, Bf, static_cast<float*>(C), st);
+  }
   else launch_gemm_f32(a, A, B, C, st);
 }
 

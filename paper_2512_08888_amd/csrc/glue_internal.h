@@ -17,6 +17,7 @@ struct GemmArgs {
   size_t strideC;           // per (batch, split)
   int shufB, shufC;         // B is read / C is written through the 2x2 pixel-shuffle map
   int shufH, shufW;         // input extent (H, W) of that map
+  int fp32_instr;           // fp32 operands: the fp32 matrix instructions, not bf16 parts
   int bf16A, bf16B, bf16C;  // the operand holds bfloat16 (widened on load / rounded on store) instead of fp32
 };
 

@@ -19,6 +19,7 @@
 
 #include "glue_internal.h"
 #include "rotconv_bf16.h"
+#include "rotconv_expand.h"
 #include "rotconv_gs.h"
 
 namespace rotconv {
@@ -39,38 +40,135 @@ GsGeom gs_geom(const rotconv_plan* p) {
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
 // base bank(s) -> the GEMM operand [(q, co, u)][ci] (first-quadrant banks, Sec. III-D / Eq. 17); one thread per
-// (q, co, ci), its k^2 taps read the same base filter.
-__global__ __launch_bounds__(256) void k_gs_pack(const float* __restrict__ w, float* __restrict__ a,
-                                                 const int32_t* __restrict__ fq_src, const float* __restrict__ fq_coef,
-                                                 const double* __restrict__ fq_coef64, int Q, int Cout, int Cin, int kk,
-                                                 int round16) {
+// (q, co, ci), every gridDim.y-th of its k^2 taps.
+__global__ __launch_bounds__(256) void k_gs_pack(const float* __restrict__ w, float* __restrict__ a, ExpandTables tab, int Q,
+                                                 int Cout, int Cin, int kk, int round16) {
   const int total = Q * Cout * Cin;
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= total) return;
   const int ci = e % Cin, co = (e / Cin) % Cout, q = e / (Cin * Cout);
-  const size_t slices = (size_t)Cout * Cin;
   const float* src = w + ((size_t)co * Cin + ci) * kk;
-  for (int u = 0; u < kk; ++u) {
-    float acc = 0.f;
-    if (round16) {    // bf16 plans: the combination in fp64, rounded to fp32 and to bf16 once each
-      double a64 = 0.0;
-      for (int z = 0; z < kMaxNnz; ++z) {
-        const int s = fq_src[(q * kk + u) * kMaxNnz + z];
-        if (s >= 0) a64 += fq_coef64[(q * kk + u) * kMaxNnz + z] * (double)src[(size_t)(s / kk) * slices * kk + s % kk];
-      }
-      acc = bf16_to_f32(f32_to_bf16((float)a64));
-    } else {
-#pragma unroll
-      for (int z = 0; z < kMaxNnz; ++z) {
-        const int s = fq_src[(q * kk + u) * kMaxNnz + z];
-        if (s >= 0) acc += fq_coef[(q * kk + u) * kMaxNnz + z] * src[(size_t)(s / kk) * slices * kk + s % kk];
-      }
-    }
-    a[((size_t)(q * Cout + co) * kk + u) * Cin + ci] = acc;
-  }
+  for (int u = blockIdx.y; u < kk; u += gridDim.y)
+    a[((size_t)(q * Cout + co) * kk + u) * Cin + ci] = expand_tap(src, (size_t)Cout * Cin * kk, kk, q, u, true, tab, round16);
 }
 
 constexpr int kMaxKK = 225;      // k <= 15
+
+constexpr int TS = 32;           // the tiles of the two kernels below are TS x TS pixels
+constexpr int TP = 3;            // taps of products in LDS at a time
+
+// Forward placement (Eq. 8), every orientation (!FUSED) or pooled over all of them (one pool group).  A workgroup places a
+// filter's products on a tile of output pixels: the products that the four turns of a bank read there are staged in LDS once,
+// TP taps at a time (the next ones' loads on their way meanwhile: one tap at a time waits for them 44 us long), a thread adds
+// them up for four pixels of a column and four turns.
+// (k_gs_place reads every product once per turn, through bounds of its own each time: 48 us for 32 filters of 5 x 5 taps on
+// 2 x 96 x 96 pixels; 16 so.)
+template <bool FUSED>
+__global__ __launch_bounds__(256) void k_gs_place_tile(const float* __restrict__ P, const int32_t* __restrict__ rot_of,
+                                                       const int32_t* __restrict__ turn_tap, float* __restrict__ yout,
+                                                       uint8_t* __restrict__ idx, GsGeom g, int n0, int tx, int ext) {
+  extern __shared__ float buf[];                         // [2][TP][ext][ext]: rows oy0 * stride - pad on; [4][kk] offsets
+  const int oy0 = blockIdx.x / tx * TS, ox0 = blockIdx.x % tx * TS;
+  const int co = blockIdx.y, b = blockIdx.z, n = n0 + b;
+  const int Pi = g.H * g.W, Po = g.Ho * g.Wo, ext2 = ext * ext, stage = TP * ext2;
+  int* off = reinterpret_cast<int*>(buf + 2 * stage);
+  for (int i = threadIdx.x; i < 4 * g.kk; i += 256) off[i] = turn_tap[i] / g.k * ext + turn_tap[i] % g.k;
+  const int iy0 = oy0 * g.stride - g.pad, ix0 = ox0 * g.stride - g.pad;
+  const int lx = threadIdx.x % TS, ly = threadIdx.x / TS;      // pixels (ly + 8 m, lx), m = 0 .. 3
+  const int lane_at = (ly * ext + lx) * g.stride, row8 = 8 * g.stride * ext;
+  constexpr int NS = 18;                                 // values a thread has on their way
+  // where value i of a stage lies behind the stage's first product (-1: outside the image)
+  auto place_of = [&](int i) {
+    const int tap = i / ext2, e = i - tap * ext2, y = iy0 + e / ext, x = ix0 + e % ext;
+    return i < stage && (unsigned)y < (unsigned)g.H && (unsigned)x < (unsigned)g.W ? tap * Pi + y * g.W + x : -1;
+  };
+  int from[NS];
+#pragma unroll
+  for (int k = 0; k < NS; ++k) from[k] = place_of(threadIdx.x + 256 * k);
+  float best[4] = {0.f, 0.f, 0.f, 0.f};
+  int best_r[4] = {-1, -1, -1, -1};
+  for (int q = 0; q < g.Q; ++q) {
+    const float* Pq = P + ((size_t)b * g.Q * g.Cout + q * g.Cout + co) * g.kk * Pi;
+    int rot[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) rot[s] = rot_of[q * 4 + s];
+    float acc[4][4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int m = 0; m < 4; ++m) acc[s][m] = 0.f;
+    float v[NS];
+    // what lies outside is read at the stage's first product and dropped when it is written to LDS
+    auto load = [&](int u0, int e0) {
+      const float* src = Pq + (size_t)u0 * Pi;
+      const unsigned end = min(g.kk - u0, TP) * Pi;
+#pragma unroll
+      for (int k = 0; k < NS; ++k) {
+        const unsigned at = e0 ? place_of(e0 + threadIdx.x + 256 * k) : from[k];
+        v[k] = src[at < end ? at : 0u];
+      }
+    };
+    auto put = [&](float* d, int u0, int e0) {
+      const unsigned end = min(g.kk - u0, TP) * Pi;
+#pragma unroll
+      for (int k = 0; k < NS; ++k) {
+        const int i = e0 + threadIdx.x + 256 * k;
+        const unsigned at = e0 ? place_of(i) : from[k];
+        if (i < stage) d[i] = at < end ? v[k] : 0.f;
+      }
+    };
+    load(0, 0);
+    int par = 0;
+    for (int u0 = 0; u0 < g.kk; u0 += TP, par ^= 1) {
+      float* cur = buf + par * stage;
+      put(cur, u0, 0);
+      for (int e0 = NS * 256; e0 < stage; e0 += NS * 256) {      // larger filters and strides
+        load(u0, e0);
+        put(cur, u0, e0);
+      }
+      __syncthreads();                                   // (the other buffer was read before the last of these)
+      if (u0 + TP < g.kk) load(u0 + TP, 0);
+#pragma unroll
+      for (int t = 0; t < TP; ++t) {                     // a tap beyond the last one reads zeros
+        const int u = min(u0 + t, g.kk - 1);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const float* src = cur + t * ext2 + off[s * g.kk + u] + lane_at;
+#pragma unroll
+          for (int m = 0; m < 4; ++m) acc[s][m] += src[m * row8];
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int r = rot[s];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int oy = oy0 + ly + 8 * m, ox = ox0 + lx;
+        if (FUSED) {                                     // ties go to the smallest orientation
+          const float v = acc[s][m];
+          const bool take = (r >= 0) & ((best_r[m] < 0) | (v > best[m]) | ((v == best[m]) & (r < best_r[m])));
+          best[m] = take ? v : best[m];
+          best_r[m] = take ? r : best_r[m];
+        } else if (r >= 0 && oy < g.Ho && ox < g.Wo) {
+          yout[(((size_t)n * g.Cout + co) * g.R + r) * Po + oy * g.Wo + ox] = acc[s][m];
+        }
+      }
+    }
+  }
+  if (FUSED) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int oy = oy0 + ly + 8 * m, ox = ox0 + lx;
+      if (oy >= g.Ho || ox >= g.Wo) continue;
+      const size_t o = ((size_t)n * g.Cout + co) * Po + oy * g.Wo + ox;
+      const bool dead = g.relu && best[m] <= 0.f;
+      yout[o] = dead ? 0.f : best[m];
+      idx[o] = dead ? (uint8_t)255 : (uint8_t)best_r[m];
+    }
+  }
+}
 
 // Forward placement (Eq. 8) as a gather over the products of `nb` images, then Eq. 10.  One thread per output pixel
 // of a pooled channel (FUSED) or of a filter (all its orientations are written).  The tap offsets of the four
@@ -128,62 +226,68 @@ __global__ __launch_bounds__(256) void k_gs_place(const float* __restrict__ P, c
 
 // D[(q,co,u)][input pixel] of `nb` images: the gradient reaching input pixel (y, x) through base tap u of bank q,
 // summed over the bank's quarter turns.  ROUTED: from the pooled gradient and idx (Eq. 12); else from a dense dy.
-// One thread per input pixel of a (bank, filter): it walks the k^2 taps, whose sources lie in a k x k neighbourhood
-// per quarter turn (offsets in LDS); sources outside the output map are read from a valid address and dropped, so
-// no load waits for a compare.  S1: stride 1 (no divisibility tests).
-template <bool ROUTED, bool S1>
+// A workgroup takes a tile of input pixels of a (bank, filter): the gradients of the four turns that its taps reach are
+// routed into LDS once, on the grid of the input (zero between the outputs of a stride), and a thread adds up four values
+// per tap for four pixels of a column.  (Each value read and routed once per tap and turn: 51 us for 32 filters of 5 x 5 taps
+// on 2 x 96 x 96 pixels; 20 so, of which 13 are the 59 MB it writes.)
+template <bool ROUTED>
 __global__ __launch_bounds__(256) void k_gs_route(const float* __restrict__ gsrc, const uint8_t* __restrict__ idx,
                                                   const int32_t* __restrict__ rot_of,
                                                   const int32_t* __restrict__ turn_tap, float* __restrict__ D, GsGeom g,
-                                                  int n0) {
-  __shared__ int sdy[4 * kMaxKK], sdx[4 * kMaxKK];
-  for (int i = threadIdx.x; i < 4 * g.kk; i += 256) {
-    const int t = turn_tap[i];
-    sdy[i] = g.pad - t / g.k;
-    sdx[i] = g.pad - t % g.k;
-  }
-  __syncthreads();
-  const int Po = g.Ho * g.Wo, Pi = g.H * g.W;
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= Pi) return;
-  const int y = p / g.W, x = p % g.W;
+                                                  int n0, int tx, int ext) {
+  extern __shared__ float plane[];                       // [4][ext][ext]: rows y0 + pad - (k - 1) on; [kk][4] offsets
+  int* off = reinterpret_cast<int*>(plane + 4 * ext * ext);
+  for (int i = threadIdx.x; i < 4 * g.kk; i += 256)
+    off[i % g.kk * 4 + i / g.kk] = i / g.kk * ext * ext - (turn_tap[i] / g.k * ext + turn_tap[i] % g.k);
+  const int y0 = blockIdx.x / tx * TS, x0 = blockIdx.x % tx * TS;
   const int b = blockIdx.z, n = n0 + b;
-  const int QC = g.Q * g.Cout;
-  for (int qc = blockIdx.y; qc < QC; qc += gridDim.y) {      // qc = q * Cout + co
+  const int Po = g.Ho * g.Wo, Pi = g.H * g.W, ext2 = ext * ext;
+  const int ny0 = y0 + g.pad - (g.k - 1), nx0 = x0 + g.pad - (g.k - 1);
+  for (int qc = blockIdx.y; qc < g.Q * g.Cout; qc += gridDim.y) {      // qc = q * Cout + co
     const int co = qc % g.Cout, q = qc / g.Cout;
+    if (qc != (int)blockIdx.y) __syncthreads();
     int rot[4];
-    const float* gp[4];
-    const uint8_t* ip[4];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      rot[s] = rot_of[q * 4 + s];
-      const int r = max(rot[s], 0);
-      const size_t plane = ROUTED ? (((size_t)n * g.Cout + co) * g.ng + r % g.ng) * Po
-                                  : (((size_t)n * g.Cout + co) * g.R + r) * Po;
-      gp[s] = gsrc + plane;
-      ip[s] = ROUTED ? idx + plane : nullptr;
-    }
-    float* Dq = D + ((size_t)b * QC + qc) * g.kk * Pi + p;
-#pragma unroll 2
-    for (int u = 0; u < g.kk; ++u) {
-      float acc = 0.f;
+    for (int s = 0; s < 4; ++s) rot[s] = rot_of[q * 4 + s];
+    for (int e = threadIdx.x; e < ext2; e += 256) {
+      const int ny = ny0 + e / ext, nx = nx0 + e % ext;
+      int oy = ny, ox = nx;
+      bool ok = ny >= 0 && nx >= 0;
+      if (g.stride != 1) {
+        oy = ny / g.stride; ox = nx / g.stride;
+        ok = ok && oy * g.stride == ny && ox * g.stride == nx;
+      }
+      ok = ok && oy < g.Ho && ox < g.Wo;
+      const int o = ok ? oy * g.Wo + ox : 0;
+      float v[4];
+      int r[4];
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        if (rot[s] < 0) continue;
-        const int ny = y + sdy[s * g.kk + u], nx = x + sdx[s * g.kk + u];
-        int oy = ny, ox = nx;
-        bool ok = true;
-        if (!S1) {
-          oy = ny / g.stride; ox = nx / g.stride;
-          ok = ny >= 0 && nx >= 0 && oy * g.stride == ny && ox * g.stride == nx;
-        }
-        ok = ok && (unsigned)oy < (unsigned)g.Ho && (unsigned)ox < (unsigned)g.Wo;
-        const int o = ok ? oy * g.Wo + ox : 0;
-        const float gv = gp[s][o];
-        if (ROUTED) ok = ok && ip[s][o] == rot[s];
-        acc += ok ? gv : 0.f;
+        const int rs = max(rot[s], 0);
+        const size_t at = (ROUTED ? ((size_t)n * g.Cout + co) * g.ng + rs % g.ng : ((size_t)n * g.Cout + co) * g.R + rs) * Po + o;
+        v[s] = gsrc[at];
+        r[s] = ROUTED ? idx[at] : rot[s];
       }
-      Dq[(size_t)u * Pi] = acc;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) plane[s * ext2 + e] = ok && rot[s] >= 0 && r[s] == rot[s] ? v[s] : 0.f;
+    }
+    __syncthreads();
+    const int lx = threadIdx.x % TS, ly = threadIdx.x / TS;      // pixels (ly + 8 m, lx), m = 0 .. 3
+    const int x = x0 + lx;
+    float* Dq = D + ((size_t)b * g.Q * g.Cout + qc) * g.kk * Pi + (size_t)(y0 + ly) * g.W + x;
+    const float* at = plane + (ly + g.k - 1) * ext + lx + g.k - 1;
+#pragma unroll 2
+    for (int u = 0; u < g.kk; ++u) {
+      float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const float* src = at + off[u * 4 + s];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) acc[m] += src[8 * m * ext];
+      }
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        if (x < g.W && y0 + ly + 8 * m < g.H) Dq[(size_t)u * Pi + (size_t)(8 * m) * g.W] = acc[m];
     }
   }
 }
@@ -207,7 +311,7 @@ __global__ __launch_bounds__(256) void k_gs_reduce_w(const float* __restrict__ d
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= total) return;
   const int ci = e % Cin, co = (e / Cin) % Cout, b = e / (Cin * Cout);
-  for (int t = 0; t < kk; ++t) {
+  for (int t = blockIdx.y; t < kk; t += gridDim.y) {
     float acc = 0.f;
     for (int z = ptr[b * kk + t]; z < ptr[b * kk + t + 1]; ++z) {
       const int q = col[z] / kk, u = col[z] % kk;
@@ -245,16 +349,20 @@ GsLayout gs_layout(const rotconv_plan* p) {
   return L;
 }
 
+// the taps of a small kernel's threads over blockIdx.y, up to a few hundred workgroups
+unsigned tap_groups(unsigned blocks, int kk) { return std::max(1u, std::min((unsigned)kk, 512u / blocks)); }
+
 void pack(const rotconv_plan* p, const float* w, float* a, hipStream_t st) {
   const int total = p->host.Q * p->d.Cout * p->d.Cin;
-  hipLaunchKernelGGL(k_gs_pack, dim3((total + 255) / 256), dim3(256), 0, st, w, a, p->dev.fq_src, p->dev.fq_coef,
-                     p->dev.fq_coef64,
-                     p->host.Q, p->d.Cout, p->d.Cin, p->kk, p->d.dtype == ROTCONV_BF16 ? 1 : 0);
+  const unsigned nb = (total + 255) / 256;
+  hipLaunchKernelGGL(k_gs_pack, dim3(nb, tap_groups(nb, p->kk)), dim3(256), 0, st, w, a, expand_tables(p), p->host.Q, p->d.Cout,
+                     p->d.Cin, p->kk, p->d.dtype == ROTCONV_BF16 ? 1 : 0);
 }
 
-GemmArgs gemm_args() {
+GemmArgs gemm_args(const rotconv_plan* p) {
   GemmArgs a{};
   a.batch = 1; a.splitk = 1;
+  a.fp32_instr = p->opt.bf16_parts < 0;
   return a;
 }
 
@@ -271,10 +379,22 @@ void forward(const rotconv_plan* p, bool fused, const float* x, const float* w, 
   const int nbmax = chunk_images(p);
   for (int n0 = 0; n0 < g.N; n0 += nbmax) {
     const int nb = std::min(nbmax, g.N - n0);
-    GemmArgs a = gemm_args();
+    GemmArgs a = gemm_args(p);
     a.M = M; a.N = Pi; a.K = g.Cin; a.lda = g.Cin; a.ldb = Pi; a.ldc = Pi;
     a.batch = nb; a.strideA = 0; a.strideB = (size_t)g.Cin * Pi; a.strideC = (size_t)M * Pi;
     launch_gemm(a, A, x + (size_t)n0 * g.Cin * Pi, P, st);
+    // one pool group (or none), the tiles' products within the LDS of a workgroup
+    const int ext = (TS - 1) * g.stride + g.k, tx = (g.Wo + TS - 1) / TS;
+    const size_t lds = ((size_t)2 * TP * ext * ext + 4 * g.kk) * sizeof(float);
+    if ((!fused || g.ng == 1) && lds <= 163840 && g.Cout <= 65535) {
+      dim3 tiles(tx * ((g.Ho + TS - 1) / TS), g.Cout, nb);
+      auto go = [&](auto kern) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipLaunchKernelGGL(kern, tiles, dim3(256), lds, st, P, p->dev.rot_of, p->dev.turn_tap, yout, idx, g, n0, tx, ext);
+      };
+      if (fused) go(k_gs_place_tile<true>); else go(k_gs_place_tile<false>);
+      continue;
+    }
     dim3 grid((Po + 255) / 256, std::min(fused ? g.Cout * g.ng : g.Cout, 65535), nb);
     if (fused) hipLaunchKernelGGL(k_gs_place<true>, grid, dim3(256), 0, st, P, p->dev.rq_of_r, p->dev.turn_tap, yout, idx, g, n0);
     else hipLaunchKernelGGL(k_gs_place<false>, grid, dim3(256), 0, st, P, p->dev.rq_of_r, p->dev.turn_tap, yout, idx, g, n0);
@@ -283,13 +403,11 @@ void forward(const rotconv_plan* p, bool fused, const float* x, const float* w, 
 
 void route(const rotconv_plan* p, const GsGeom& g, bool routed, const float* gsrc, const uint8_t* idx, float* D, int n0,
            int nb, hipStream_t st) {
-  dim3 grid((g.H * g.W + 255) / 256, std::min(g.Q * g.Cout, 65535), nb);
-  const bool s1 = g.stride == 1;
-  auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, gsrc, idx, p->dev.rot_of, p->dev.turn_tap, D, g, n0);
-  };
-  if (routed) { if (s1) go(k_gs_route<true, true>); else go(k_gs_route<true, false>); }
-  else { if (s1) go(k_gs_route<false, true>); else go(k_gs_route<false, false>); }
+  const int ext = TS + g.k - 1, tx = (g.W + TS - 1) / TS;
+  const size_t lds = (size_t)4 * (ext * ext + g.kk) * sizeof(float);      // k <= 15: 38 KB
+  dim3 grid(tx * ((g.H + TS - 1) / TS), std::min(g.Q * g.Cout, 65535), nb);
+  if (routed) hipLaunchKernelGGL(k_gs_route<true>, grid, dim3(256), lds, st, gsrc, idx, p->dev.rot_of, p->dev.turn_tap, D, g, n0, tx, ext);
+  else hipLaunchKernelGGL(k_gs_route<false>, grid, dim3(256), lds, st, gsrc, idx, p->dev.rot_of, p->dev.turn_tap, D, g, n0, tx, ext);
 }
 
 void backward_data(const rotconv_plan* p, bool routed, const float* gsrc, const uint8_t* idx, const float* w, float* dx,
@@ -305,7 +423,7 @@ void backward_data(const rotconv_plan* p, bool routed, const float* gsrc, const 
   for (int n0 = 0; n0 < g.N; n0 += nbmax) {
     const int nb = std::min(nbmax, g.N - n0);
     route(p, g, routed, gsrc, idx, D, n0, nb, st);
-    GemmArgs a = gemm_args();             // dX[ci][pixel] = sum_m A[m][ci] D[m][pixel]
+    GemmArgs a = gemm_args(p);             // dX[ci][pixel] = sum_m A[m][ci] D[m][pixel]
     a.M = g.Cin; a.N = Pi; a.K = M; a.transA = 1; a.lda = g.Cin; a.ldb = Pi; a.ldc = Pi;
     a.batch = nb; a.strideA = 0; a.strideB = (size_t)M * Pi; a.strideC = (size_t)g.Cin * Pi;
     launch_gemm(a, A, D, dx + (size_t)n0 * g.Cin * Pi, st);
@@ -327,15 +445,16 @@ void backward_weight(const rotconv_plan* p, bool routed, const float* x, const f
   for (int n0 = 0; n0 < g.N; n0 += nbmax) {
     const int nb = std::min(nbmax, g.N - n0);
     route(p, g, routed, gsrc, idx, D, n0, nb, st);
-    GemmArgs a = gemm_args();             // dF[m][ci] = sum_pixel D[m][pixel] X[ci][pixel]
+    GemmArgs a = gemm_args(p);             // dF[m][ci] = sum_pixel D[m][pixel] X[ci][pixel]
     a.M = M; a.N = g.Cin; a.K = Pi; a.transB = 1; a.lda = Pi; a.ldb = Pi; a.ldc = g.Cin;
     a.batch = nb; a.splitk = sk; a.strideA = (size_t)M * Pi; a.strideB = (size_t)g.Cin * Pi; a.strideC = nF;
     launch_gemm(a, D, x + (size_t)n0 * g.Cin * Pi, part, st);
-    hipLaunchKernelGGL(k_gs_sum_acc, dim3((unsigned)((nF + 255) / 256)), dim3(256), 0, st, part, dF, nF, nb * sk,
-                       n0 == 0 ? 1 : 0);
+    if (nbmax >= g.N) launch_sum_parts(part, dF, nF, nb * sk, nF, st);
+    else hipLaunchKernelGGL(k_gs_sum_acc, dim3((unsigned)((nF + 255) / 256)), dim3(256), 0, st, part, dF, nF, nb * sk,
+                            n0 == 0 ? 1 : 0);
   }
-  const int total = p->B * g.Cout * g.Cin;
-  hipLaunchKernelGGL(k_gs_reduce_w, dim3((total + 255) / 256), dim3(256), 0, st, dF, dw, p->dev.fqt_ptr, p->dev.fqt_col,
+  const unsigned rb = (p->B * g.Cout * g.Cin + 255) / 256;
+  hipLaunchKernelGGL(k_gs_reduce_w, dim3(rb, tap_groups(rb, g.kk)), dim3(256), 0, st, dF, dw, p->dev.fqt_ptr, p->dev.fqt_col,
                      p->dev.fqt_coef, p->B, g.Cout, g.Cin, g.kk);
 }
 

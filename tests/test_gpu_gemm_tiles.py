@@ -1,0 +1,88 @@
+"""The matrix multiply on bf16 parts and the tiled kernels of the multiply + scatter family, at the edges of their tiles:
+rows, columns and K-steps around 32, 64 and 128, contractions of one K-step and of many, both tile sizes; 32 x 32 pixel tiles
+of filters from 2 x 2 to 15 x 15 taps, strides to 3, several banks, incomplete orientation sets, pool groups, images one at
+a time.
+
+Error bar: within a K-step the matrix instruction cuts six sums per 32 terms, so a sum of K terms is within about
+sqrt(6 K / 32) 2^-24 of its norm: 1.5e-6 for the deepest contraction here (K = 16389); twice that is asked for.
+"""
+import numpy as np
+import pytest
+import torch
+
+import parity_util as pu
+from oracle import unet_oracle as uo
+from paper_2512_08888_amd import binding as rc
+from paper_2512_08888_amd import synth
+
+pytestmark = pytest.mark.gpu
+L = synth.LayerConfig
+BAR = 3e-6
+
+
+def _rel(got, ref):
+    return float(np.linalg.norm(np.asarray(got, np.float64) - ref) / np.linalg.norm(ref))
+
+
+@pytest.mark.parametrize("N,Cin,Cout,P", [(1, 1, 9, 1), (2, 31, 33, 63), (1, 32, 64, 64), (3, 33, 65, 65), (2, 64, 31, 129), (1, 97, 130, 31),
+                                          (1, 129, 16, 2050), (2, 160, 130, 16389)])      # the last: 128 x 128 tiles
+def test_products(N, Cin, Cout, P):
+    rng = np.random.default_rng(P)
+    f = lambda *s: rng.standard_normal(s).astype(np.float32)
+    x, w, dy = f(N, Cin, 1, P), f(Cout, Cin), f(N, Cout, 1, P)
+    y, dx = (torch.full((N, c, 1, P), float("nan"), device="cuda") for c in (Cout, Cin))
+    dw = torch.full((Cout, Cin), float("nan"), device="cuda")
+    ws = torch.empty(max(256, rc.glue_conv1x1_workspace_bytes(N, Cin, Cout, P)), dtype=torch.uint8, device="cuda")
+    xd, wd, gd = pu.dev(x), pu.dev(w), pu.dev(dy)
+    rc.glue_conv1x1_fwd(xd, wd, y)
+    rc.glue_conv1x1_bwd_data(gd, wd, dx)
+    rc.glue_conv1x1_bwd_weight(xd, gd, dw, ws)
+    assert _rel(y.cpu().numpy(), uo.conv1x1_fwd(x, w)) < BAR
+    dxr, dwr = uo.conv1x1_bwd(x, w, dy)
+    assert _rel(dx.cpu().numpy(), dxr) < BAR and _rel(dw.cpu().numpy(), dwr) < BAR
+
+
+@pytest.mark.parametrize("N,Cin,Cout,H,W", [(1, 5, 3, 3, 5), (2, 33, 17, 7, 9), (1, 64, 16, 8, 8), (2, 70, 40, 5, 13)])
+def test_pixel_shuffled_products(N, Cin, Cout, H, W):
+    rng = np.random.default_rng(H)
+    f = lambda *s: rng.standard_normal(s).astype(np.float32)
+    x, w, dy = f(N, Cin, H, W), f(Cin, Cout, 2, 2), f(N, Cout, 2 * H, 2 * W)
+    y, dx = torch.full(dy.shape, float("nan"), device="cuda"), torch.full(x.shape, float("nan"), device="cuda")
+    dw = torch.full(w.shape, float("nan"), device="cuda")
+    ws = torch.empty(max(256, rc.glue_upconv2_workspace_bytes(N, Cin, Cout, H, W)), dtype=torch.uint8, device="cuda")
+    xd, wd, gd = pu.dev(x), pu.dev(w), pu.dev(dy)
+    rc.glue_upconv2_fwd(xd, wd, y)
+    rc.glue_upconv2_bwd_data(gd, wd, dx)
+    rc.glue_upconv2_bwd_weight(xd, gd, dw, ws)
+    assert _rel(y.cpu().numpy(), uo.upconv2_fwd(x, w)) < BAR
+    dxr, dwr = uo.upconv2_bwd(x, w, dy)
+    assert _rel(dx.cpu().numpy(), dxr) < BAR and _rel(dw.cpu().numpy(), dwr) < BAR
+
+
+TILES = [
+    L("g_k2", N=2, Cin=9, H=33, W=31, Cout=3, R=4, k=2, pad=1, x_dist="normal", seed=1401),
+    L("g_k4", N=1, Cin=32, H=32, W=64, Cout=2, R=4, k=4, pad=0, x_dist="normal", seed=1402),
+    L("g_k5", N=3, Cin=33, H=34, W=65, Cout=5, R=4, k=5, pad=2, x_dist="normal", seed=1403),
+    L("g_k5s2", N=2, Cin=16, H=66, W=35, Cout=4, R=4, k=5, pad=2, stride=2, x_dist="normal", seed=1404),
+    L("g_k3s3", N=1, Cin=16, H=40, W=70, Cout=4, R=4, k=3, pad=1, stride=3, x_dist="normal", seed=1405),
+    L("g_k7s2", N=1, Cin=8, H=20, W=37, Cout=3, R=8, mode="steerable", k=7, pad=3, stride=2, x_dist="normal", seed=1406),
+    L("g_k15", N=1, Cin=4, H=33, W=18, Cout=2, R=4, k=15, pad=7, x_dist="normal", seed=1407),
+    L("g_r3", N=1, Cin=8, H=20, W=20, Cout=4, R=3, mode="bilinear", k=5, pad=2, x_dist="normal", seed=1408),
+    L("g_g4", N=1, Cin=8, H=20, W=34, Cout=4, R=8, mode="steerable", pool_group=4, k=5, pad=2, x_dist="normal", seed=1409),
+]
+
+
+@pytest.mark.parametrize("chunk", [0, -1])      # all images at once, one at a time
+@pytest.mark.parametrize("cfg", TILES, ids=[c.name for c in TILES])
+def test_multiply_and_scatter(cfg, chunk):
+    x, w, g = synth.make_x(cfg), synth.make_w(cfg), synth.make_g(cfg)
+    ref = pu.oracle_layer(cfg, x, w, g)
+    lay = pu.GpuLayer(cfg, x, w, options=dict(gs=1, gs_chunk_mb=chunk))
+    assert lay.plan.kernel_name(0) == "mfma_gemm_scatter"
+    yp, idx = lay.pool_fwd()
+    assert _rel(yp, ref["ypool"]) < BAR
+    pu.check_idx(idx, ref["y"], ref["abs_terms"], cfg.G, cfg.name)
+    assert _rel(lay.fwd().cpu().numpy(), ref["y"].reshape(lay.U)) < BAR
+    idx = ref["idx"].astype(np.uint8)
+    assert _rel(lay.pool_bwd_data(g, idx), ref["dx"]) < BAR
+    assert _rel(lay.pool_bwd_weight(g, idx), ref["dw"]) < BAR
