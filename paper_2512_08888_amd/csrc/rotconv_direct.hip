@@ -392,9 +392,10 @@ DirWGeom direct_wgeom(const rotconv_plan* p) {
   int ty = std::min(std::max(p->opt.direct_ty, 1), d.H);
   if (p->opt.direct_ty <= 0) {
     long best = -1;
-    for (int t = std::min(8, d.H); t <= std::min(128, d.H); ++t) {
+    for (int t = std::min(2, d.H); t <= std::min(128, d.H); ++t) {
       const long nb = (long)d.N * ((d.H + t - 1) / t);
       const long waves = ((nb * (d.W + 2) - 1 + kSeg - 1) / kSeg) * g.nfb;
+      if (t < 8 && t < d.H && waves > 1024) continue;
       const long cost = ((waves + 1023) / 1024) * (t + 2);
       if (best < 0 || cost < best) { best = cost; ty = t; }
     }
@@ -431,13 +432,16 @@ DirGeom direct_geom(const rotconv_plan* p) {
   g.nfb = (d.Cout + direct_fb(p->host.Q) - 1) / direct_fb(p->host.Q);
   // Rows per band: a band of TY rows forms TY + 2 rows of products, so long bands waste the least; but the chip's
   // 1024 SIMDs hold all waves of these launches at once, and the launch ends when the SIMD with the most waves does:
-  // the band height with the smallest (waves per SIMD, rounded up) x (TY + 2).
+  // the band height with the smallest (waves per SIMD, rounded up) x (TY + 2).  Bands of fewer than eight rows only where
+  // every wave has a SIMD of its own: a small map is a few waves with a long chain of instructions each (3 -> 8 channels,
+  // 64 x 64: 21 us with bands of eight rows, 8 with one).
   int ty = std::min(std::max(p->opt.direct_ty, 1), d.H);
   if (p->opt.direct_ty <= 0) {
     long best = -1;
-    for (int t = std::min(8, d.H); t <= std::min(64, d.H); ++t) {
+    for (int t = 1; t <= std::min(64, d.H); ++t) {
       const long nb = (long)d.N * ((d.H + t - 1) / t);
       const long waves = ((nb * (d.W + 2) - 1 + kSeg - 1) / kSeg) * g.nfb;
+      if (t < 8 && t < d.H && waves > 1024) continue;
       const long cost = ((waves + 1023) / 1024) * (t + 2);
       if (best < 0 || cost < best) { best = cost; ty = t; }
     }
