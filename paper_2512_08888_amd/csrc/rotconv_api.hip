@@ -581,7 +581,8 @@ static int f32_rotconv_pool_bwd_data(const rotconv_plan* plan, const void* gpool
     launch_fill_u8(idx0, p->n_yp, 0, st);
     return rotconv_pool_bwd_data(p->avg_child, gpool, idx0, wavg, dx, c + L.child, p->avg_child->ws_bytes, stream);
   }
-  if (p->fast[1] && aligned(gpool, 8) && aligned(idx, 2) && aligned(dx, 16) && aligned(ws, 16)) {
+  const bool odd = p->d.W & 1;       // (such rows are loaded and stored pixel by pixel)
+  if (p->fast[1] && aligned(gpool, odd ? 4 : 8) && aligned(idx, odd ? 1 : 2) && aligned(dx, odd ? 4 : 16) && aligned(ws, 16)) {
     if (s3_bwd_data_supported(p)) {
       float* part = reinterpret_cast<float*>(static_cast<char*>(ws) + align256(s3_bwd_data_pack_bytes(p)));
       launch_s3_bwd_data(p, static_cast<const float*>(gpool), idx, static_cast<const float*>(w), ws, static_cast<float*>(dx), part, st);
@@ -628,7 +629,8 @@ static int f32_rotconv_pool_bwd_weight(const rotconv_plan* plan, const void* x, 
     launch_avg_bank_bwd(p, dwavg, rep, dw, st);
     return finish();
   }
-  if (p->fast[2] && aligned(x, 16) && aligned(gpool, 16) && aligned(idx, 4) && aligned(ws, 16)) {
+  const bool pixels = p->d.W & 3;       // (such rows are loaded pixel by pixel)
+  if (p->fast[2] && aligned(x, pixels ? 4 : 16) && aligned(gpool, pixels ? 4 : 16) && aligned(idx, pixels ? 1 : 4) && aligned(ws, 16)) {
     launch_p4_bwd_weight(p, static_cast<const float*>(x), static_cast<const float*>(gpool), idx,
                          static_cast<float*>(ws), dw, st);
     return finish();

@@ -119,6 +119,7 @@ struct P4BwdGeom {
 bool p4_bwd_lut_choice(const rotconv_plan* p);   // whether the fp32 gradients should use the routed-gradient table
 bool p4_bwd_lut(const rotconv_plan* p);          // the plan's setting (contraction over the base bank)
 bool p4_bwd_lut16_choice(const rotconv_plan* p); // the same question for the kernels that take bf16 tensors
+bool p4_bwd_data_layer(const rotconv_plan* p);      // the layers of the register-resident kernels, but for the width of their rows
 bool p4_bwd_data_supported(const rotconv_plan* p);
 // launch_p4_bwd_data takes the caller's w in place of the packed banks and launch_p4_pack_bwd is not called
 bool p4_bwd_data_raw_weights(const rotconv_plan* p);

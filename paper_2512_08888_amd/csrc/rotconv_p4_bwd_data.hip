@@ -831,13 +831,17 @@ bool p4_bwd_lut16_choice(const rotconv_plan* p) {
   return p->opt.bwd_lut >= 0;
 }
 
-bool p4_bwd_data_supported(const rotconv_plan* p) {
+bool p4_bwd_data_layer(const rotconv_plan* p) {
   const rotconv_desc& d = p->d;
   if (d.k != 3 || d.stride != 1 || d.pad != 1) return false;   // bf16 plans run these kernels on widened copies
-  if (d.W & 1) return false;
   // the kernels address one image of the pooled gradient with 32-bit byte offsets
   if ((size_t)d.Cout * p->ng * d.H * d.W >= ((size_t)1 << 30)) return false;
   return p4_fwd_pool_mode(p) != kOutUnpooled;  // every bank inside one pool group
+}
+
+// odd rows on bf16 parts (fp32 tensors) only
+bool p4_bwd_data_supported(const rotconv_plan* p) {
+  return p4_bwd_data_layer(p) && (!(p->d.W & 1) || (p->d.dtype == ROTCONV_F32 && s3_bwd_data_supported(p)));
 }
 
 P4BwdGeom p4_bwd_data_geom(const rotconv_plan* p) {

@@ -1426,8 +1426,9 @@ __global__ __launch_bounds__(256) void k_p4_reduce_w(const float* __restrict__ d
 bool p4_bwd_weight_supported(const rotconv_plan* p) {
   const rotconv_desc& d = p->d;
   if (d.k != 3 || d.stride != 1 || d.pad != 1) return false;   // bf16 plans run these kernels on widened copies
-  if (d.W & 3) return false;
-  return p4_fwd_pool_mode(p) != kOutUnpooled;
+  if (p4_fwd_pool_mode(p) == kOutUnpooled) return false;
+  // rows of any width on bf16 parts (fp32 tensors); the others' loads are of four pixels
+  return !(d.W & 3) || (d.dtype == ROTCONV_F32 && s3_bwd_weight_supported(p));
 }
 
 P4BwdWGeom p4_bwd_weight_geom(const rotconv_plan* p, bool lut, bool share) {

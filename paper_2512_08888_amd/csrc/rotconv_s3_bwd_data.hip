@@ -405,22 +405,19 @@ S3BwdPlan s3_bwd_plan(const rotconv_plan* p) {
 
 }  // namespace
 
-// Where the matrix cores bound the fp32 kernel: the contraction has to be long enough to pay for the packing of the
-// weights' parts and, where it is shared out over workgroups, for the sum of the partial results.  Measured, fp32
-// matrix cores / bf16 parts (us): not shared out, 0.6 GFLOP 25.8 / 32.8 (8x64 -> 64, 32x32), 1.2 GFLOP 64.7 / 51.0 (4x16 -> 64, 128x128),
-// 2.4 GFLOP 45.2 / 37.8 (2x64 -> 64, 128x128); shared out, 1.2 GFLOP 26.8 / 31.8 (2x64 -> 128, 64x64), 2.4 GFLOP 40.1 / 42.5
-// (2x256 -> 256, 32x32), 9.7 GFLOP 209 / 104 (8x512 -> 512, 16x16).  Of 690 random layers on this side of the line six
-// took more than 5 % longer than on the fp32 instructions (up to 34 %; below 2.3 GFLOP, more than 64 channels, whose groups
-// share D there, rows that fit its waves); the mean took 0.58 of the time.  For other turns than quarter turns D is a sum over
-// table entries and the fp32 table kernels stay the faster ones (4x128 -> 128, 128x128, 16 turns: 214 / 226).
+// The fp32 instructions only where the launch is too short for the packing of the weights' parts to pay and their blocks of 64
+// channels are filled.  Fp32 instructions / bf16 parts on 170 random layers of 12 to 300 rows and columns, from 0.02 GFLOP: up to 32
+// channels never longer on parts (nor, with up to four, below: 1x3 -> 8, 64x64 16 / 13 us), with more, below 0.3 GFLOP, 0.8 to 1.2 times the time, above it one layer of 145 took longer (1x96 -> 51, 122x64 26.0 / 27.4 us), the mean 0.62 of the time (5x32 -> 384, 262x12
+// 220 / 55, 8x64 -> 64, 32x32 26 / 24, 2x256 -> 256, 32x32 40 / 39).  Odd rows always: the fp32 instructions take them through
+// copies to padded rows.  For other turns than quarter turns D is a sum over table entries and the fp32 table kernels stay
+// the faster ones (4x128 -> 128, 128x128, 16 turns: 214 / 226).
 bool s3_bwd_data_supported(const rotconv_plan* p) {
-  if (!p4_bwd_data_supported(p) || p4_bwd_lut(p) || p->opt.bf16_parts < 0) return false;
+  if (!p4_bwd_data_layer(p) || p4_bwd_lut(p) || p->opt.bf16_parts < 0) return false;
   const rotconv_desc& d = p->d;
   // a descriptor's size has to stay at or below the offset that stands for "outside"
   if ((size_t)d.Cout * p->ng * d.H * d.W * 4 > kOutside) return false;
-  if (p->opt.bf16_parts > 0) return true;
   const double flop = 18.0 * p->host.Q * d.N * d.Cin * d.Cout * d.H * d.W;
-  return flop >= 4e9 || (flop >= 1.2e9 && s3_bwd_plan(p).g.ksplit == 1);
+  return p->opt.bf16_parts > 0 || (d.W & 1) || d.Cin <= 4 || flop >= (d.Cin <= 32 ? 0.02e9 : 0.3e9);
 }
 
 size_t s3_bwd_data_pack_bytes(const rotconv_plan* p) {

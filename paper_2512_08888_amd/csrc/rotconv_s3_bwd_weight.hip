@@ -48,7 +48,8 @@ __device__ __forceinline__ float row_right(float edge, float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, edge), __builtin_bit_cast(int, v), 0x101, 0xf, 0xf, false));
 }
 
-template <int CB>
+// RAGGED: W % 4 != 0, X is loaded pixel by pixel (a branch instead made the other rows 15 us slower: 8x64 -> 64, 256x256).
+template <int CB, bool RAGGED>
 __global__ __launch_bounds__(NTW, 3) void k_s3_bwd_weight(const float* __restrict__ x, const float* __restrict__ gpool,
                                                           const uint8_t* __restrict__ idx, const int32_t* __restrict__ rot_of,
                                                           float* __restrict__ partial, P4BwdWGeom g) {
@@ -202,8 +203,14 @@ __global__ __launch_bounds__(NTW, 3) void k_s3_bwd_weight(const float* __restric
       for (int r = 0; r < 2; ++r) {
         const int h = s.h0 + 2 * s.j - 2 + r;
         const bool ok = (ci < g.Cin) & (px < g.W) & (h < s.h1) & (s.j > 0) & live(s);
-        const uint32_t o = ok ? (xplane + (uint32_t)(h * g.W + px)) * 4u : kOutside;
-        k.v[p][r] = __builtin_bit_cast(s3_f4, __builtin_amdgcn_raw_buffer_load_b128(rx, o, 0, 0));
+        const uint32_t o = (xplane + (uint32_t)(h * g.W + px)) * 4u;
+        if constexpr (RAGGED) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            k.v[p][r][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rx, ok & (px + i < g.W) ? o + 4u * i : kOutside, 0, 0));
+        } else {
+          k.v[p][r] = __builtin_bit_cast(s3_f4, __builtin_amdgcn_raw_buffer_load_b128(rx, ok ? o : kOutside, 0, 0));
+        }
       }
     }
   };
@@ -343,9 +350,9 @@ __global__ __launch_bounds__(NTW, 3) void k_s3_bwd_weight(const float* __restric
 
 }  // namespace
 
-// Quarter turns only, more than 32 channels, and an image of either operand within a 32-bit byte offset.  With 32
-// channels or fewer the vector work of D is shared by one column of tiles and half of the workgroup's tiles would be
-// padding.  For other turns D is a sum over table entries, three times the vector work, which the matrix cores' gain
+// Quarter turns only, more than sixteen channels, and an image of either operand within a 32-bit byte offset.  With sixteen
+// channels or fewer three quarters of the workgroup's tiles would be padding, where k_p4_bwd_weight has blocks of sixteen:
+// 1.4 times its time in the mean of 45 layers; with 17 to 32, which it pads to 64, 0.77 (2x26 -> 380, 212x100 390 -> 207 us).  For other turns D is a sum over table entries, three times the vector work, which the matrix cores' gain
 // does not pay for: at 4x128 -> 128, 128x128, 16 turns this split took 248 us with the table in LDS, k_p4_bwd_weight's
 // table variant takes 219.
 // Nor where a workgroup has a single step and the partial sums of all take longer than it: with up to 16 filters half of
@@ -360,7 +367,7 @@ bool s3_bwd_weight_supported(const rotconv_plan* p) {
   const P4BwdWGeom g = s3_bwd_weight_geom(p);
   const bool one_step = g.units <= g.splits && g.rows_per <= 2;
   const bool short_sums = one_step && (d.Cout <= 16 || d.H == 1) && 36.0 * g.splits * g.Q * g.CoutPad * g.CinPad > 12e6;
-  return ((d.Cin > 32 && !short_sums) || p->opt.bf16_parts > 0) && (size_t)d.Cin * d.H * d.W < lim && (size_t)d.Cout * p->ng * d.H * d.W < lim;
+  return ((d.Cin > 16 && !short_sums) || p->opt.bf16_parts > 0) && (size_t)d.Cin * d.H * d.W < lim && (size_t)d.Cout * p->ng * d.H * d.W < lim;
 }
 
 P4BwdWGeom s3_bwd_weight_geom(const rotconv_plan* p) {
@@ -401,7 +408,11 @@ void launch_s3_bwd_weight(const rotconv_plan* p, const P4BwdWGeom& g, const floa
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(NTW), lds, st, x, gpool, idx, p->dev.rot_of, partial, g);
   };
-  if (g.ncb == 4) go(k_s3_bwd_weight<4>); else go(k_s3_bwd_weight<2>);
+  if (g.W & 3) {
+    if (g.ncb == 4) go(k_s3_bwd_weight<4, true>); else go(k_s3_bwd_weight<2, true>);
+  } else {
+    if (g.ncb == 4) go(k_s3_bwd_weight<4, false>); else go(k_s3_bwd_weight<2, false>);
+  }
 }
 
 }  // namespace rotconv
