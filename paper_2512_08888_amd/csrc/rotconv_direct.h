@@ -13,6 +13,10 @@ size_t direct_fwd_pack_floats(const rotconv_plan* p);
 void launch_direct_fwd(const rotconv_plan* p, const void* x, const void* w, void* ypool, uint8_t* idx, float* wb,
                        hipStream_t st);
 
+// the same on bf16 parts: fp32 plans of at most three channels, a single bank of four quarter turns
+bool first_fwd_supported(const rotconv_plan* p, const void* x, const void* ypool, const void* idx);
+void launch_first_fwd(const rotconv_plan* p, const float* x, const float* w, float* ypool, uint8_t* idx, hipStream_t st);
+
 // weight gradient (single-bank layers): `part` holds direct_bwd_weight_ws_floats(p) floats of partial sums
 bool direct_bwd_weight_supported(const rotconv_plan* p);
 size_t direct_bwd_weight_ws_floats(const rotconv_plan* p);

@@ -20,6 +20,8 @@
 //   * max / arg-max over all R orientations of a filter in ascending orientation order (smallest index wins ties),
 //     the fused ReLU, one 4-byte (2-byte for bf16 tensors) store and one idx byte per lane and filter.
 //
+// fp32 layers of at most three channels, R = 4 and rows of whole quads run k_first_fwd (rotconv_first.hip) instead.
+//
 // bf16 plans: x is widened on load, the banks were rounded to bf16 when they were packed (products of bf16 values are
 // exact in fp32, the sums are fp32), the pooled value is rounded once.
 #include <algorithm>
@@ -515,6 +517,10 @@ size_t direct_fwd_pack_floats(const rotconv_plan* p) {
 
 void launch_direct_fwd(const rotconv_plan* p, const void* x, const void* w, void* ypool, uint8_t* idx, float* wb,
                        hipStream_t st) {
+  if (first_fwd_supported(p, x, ypool, idx)) {
+    launch_first_fwd(p, static_cast<const float*>(x), static_cast<const float*>(w), static_cast<float*>(ypool), idx, st);
+    return;
+  }
   const rotconv_desc& d = p->d;
   const int Q = p->host.Q, fb = direct_fb(Q), pitch = direct_pitch(d.Cin);
   const int CoutPad = (d.Cout + fb - 1) / fb * fb;
