@@ -360,8 +360,16 @@ __global__ __launch_bounds__(256) void k_s3_pack_bwd(const float* __restrict__ w
 // tap by tap / mains last: 9 filters 1.38e-7 / 1.55e-7 / below 6e-8, 24 filters 1.32e-7 / 1.56e-7 / 5.6e-8, 32 filters
 // 2.2e-7 / 1.7e-7 / 5.9e-8, 64 2.8e-7 / 1.7e-7 / 6.6e-8, 512 3.9e-7 / 1.9e-7 / 9.2e-8, 2048 (64 channels) 2.47e-7 / 2.48e-7 / 1.64e-7.
 // The second reading of the weights' first parts costs 3 % (8x64 -> 64, 256x256: 275.5 / 283.7 us, 4x128 -> 128, 128x128
-// 160.4 / 164.1): it is taken where the shorter form would be less precise than the fp32 instructions.
-constexpr bool s3_mains_last(int Cout) { return Cout < 32 || Cout > 1024; }
+// 160.4 / 164.1): it is taken where the shorter form would be less precise than the fp32 instructions.  That is also so on
+// small layers, for which the kernel on fp32 instructions shares the contraction out in short sums (1x112 -> 240, 17x61: fp32
+// instructions 1.59e-7, tap by tap 1.9e-7, mains last 9.2e-8; no time lost that could be measured, 42.6 / 43.0 us both gradients).
+double s3_bwd_data_flop(const rotconv_plan* p) {
+  return 18.0 * p->host.Q * p->d.N * p->d.Cin * p->d.Cout * p->d.H * p->d.W;
+}
+bool s3_mains_last(const rotconv_plan* p, int ksplit) {
+  const double flop = s3_bwd_data_flop(p);
+  return p->d.Cout < 32 || p->d.Cout > 1024 || flop < 1.2e9 || (flop < 4e9 && ksplit > 1);
+}
 
 struct S3BwdPlan { S3BwdGeom g; int TB; };
 
@@ -406,9 +414,10 @@ S3BwdPlan s3_bwd_plan(const rotconv_plan* p) {
 }  // namespace
 
 // The fp32 instructions only where the launch is too short for the packing of the weights' parts to pay and their blocks of 64
-// channels are filled.  Fp32 instructions / bf16 parts on 170 random layers of 12 to 300 rows and columns, from 0.02 GFLOP: up to 32
-// channels never longer on parts (nor, with up to four, below: 1x3 -> 8, 64x64 16 / 13 us), with more, below 0.3 GFLOP, 0.8 to 1.2 times the time, above it one layer of 145 took longer (1x96 -> 51, 122x64 26.0 / 27.4 us), the mean 0.62 of the time (5x32 -> 384, 262x12
-// 220 / 55, 8x64 -> 64, 32x32 26 / 24, 2x256 -> 256, 32x32 40 / 39).  Odd rows always: the fp32 instructions take them through
+// channels are filled.  Fp32 instructions / bf16 parts on 170 random layers of 12 to 300 rows and columns, from 0.02 GFLOP: up
+// to 32 channels never longer on parts (nor, with up to four, below: 1x3 -> 8, 64x64 16 / 13 us); with more, below 0.3 GFLOP,
+// 0.8 to 1.2 times the time; above it one layer of 145 took longer (1x96 -> 51, 122x64 26.0 / 27.4 us), the mean 0.62 of the
+// time (5x32 -> 384, 262x12 220 / 55, 8x64 -> 64, 32x32 26 / 24, 2x256 -> 256, 32x32 40 / 39).  Odd rows always: the fp32 instructions take them through
 // copies to padded rows.  For other turns than quarter turns D is a sum over table entries and the fp32 table kernels stay
 // the faster ones (4x128 -> 128, 128x128, 16 turns: 214 / 226).
 bool s3_bwd_data_supported(const rotconv_plan* p) {
@@ -416,7 +425,7 @@ bool s3_bwd_data_supported(const rotconv_plan* p) {
   const rotconv_desc& d = p->d;
   // a descriptor's size has to stay at or below the offset that stands for "outside"
   if ((size_t)d.Cout * p->ng * d.H * d.W * 4 > kOutside) return false;
-  const double flop = 18.0 * p->host.Q * d.N * d.Cin * d.Cout * d.H * d.W;
+  const double flop = s3_bwd_data_flop(p);
   return p->opt.bf16_parts > 0 || (d.W & 1) || d.Cin <= 4 || flop >= (d.Cin <= 32 ? 0.02e9 : 0.3e9);
 }
 
@@ -446,7 +455,7 @@ void launch_s3_bwd_data(const rotconv_plan* p, const float* gpool, const uint8_t
     hipLaunchKernelGGL(kern, dim3(std::min(256, (g.units + 7) / 8 * 8)), dim3(NT), lds, st, gpool, idx, static_cast<const u32x4*>(pack),
                        p->dev.rot_of, dx, g);
   };
-  if (s3_mains_last(g.Cout)) {
+  if (s3_mains_last(p, g.ksplit)) {
     if (b.TB == 1) go(k_s3_bwd_data<1, true>); else go(k_s3_bwd_data<2, true>);
   } else {
     if (b.TB == 1) go(k_s3_bwd_data<1, false>); else go(k_s3_bwd_data<2, false>);
