@@ -54,9 +54,11 @@
  *     group is, through the fused ReLU too, and idx is then some orientation of
  *     the group; where only some responses are NaN it may be NaN or the maximum
  *     of the others.  fp32 passes that multiply bf16 parts of the operands
- *     (rotconv_plan_bf16_parts) make NaN of an infinity and of magnitudes from
- *     3.396e38 on, and hold magnitudes below 2^-110 to 2^-134 only; all others,
- *     and these with plan option bf16_parts = -1, follow IEEE arithmetic.
+ *     (rotconv_plan_bf16_parts, and the matrix multiply + scatter family) may make NaN
+ *     of an infinity and of magnitudes from 3.396e38 on, and hold magnitudes below
+ *     2^-110 to 2^-134 only (so does the pooled forward of first layers, which
+ *     keeps infinities); all others, and these with plan option bf16_parts = -1,
+ *     follow IEEE arithmetic.
  *   - Return value: a rotconv_status.  Argument errors are found on the host
  *     before anything is launched and leave the outputs untouched.
  */
@@ -154,15 +156,16 @@ typedef struct {
   int32_t fwd_base;     /* fp32 forward of such layers: 0 automatic (products of the base bank only, combined
                            into the banks' products on the vector ALU), -1 never (one contraction per bank)    */
   int32_t direct;       /* layers with at most four input channels (a network's first layer): 0 automatic (the
-                           pooled forward on the vector-ALU kernel, no matrix instructions), -1 never             */
-  int32_t direct_ty;    /* rows per band of that kernel: 0 automatic, n > 0 = n                                   */
+                           pooled forward by kernels of their own: on the vector ALU, or, fp32 with at most three
+                           channels, R = 4 and W a multiple of four, on bf16 parts), -1 never                      */
+  int32_t direct_ty;    /* rows per band of the vector-ALU kernel: 0 automatic, n > 0 = n and always that kernel    */
   int32_t px_fwd;       /* bf16 pooled forward of layers with 8 to 128 input channels pooled over all orientations:
                            0 automatic (filters on the matrix instruction's M side, a lane per pixel column, for
                            layers with four banks and at most 64 input channels), 1 wherever that kernel can run,
                            -1 never (pixels on the M side, eight pixels per lane)                                   */
   int32_t bf16_parts;   /* fp32 contractions of 3x3 layers as products of the operands' three bf16 parts on the bf16
-                           matrix cores (forward of layers with more than four channels, gradients of quarter-turn
-                           layers): 0 automatic (where that is the faster form), 1 wherever those kernels can run,
+                           matrix cores (forward of layers with more than four channels and of first layers of R = 4,
+                           gradients of quarter-turn layers, the matrix multiply + scatter family): 0 automatic (where that is the faster form), 1 wherever those kernels can run,
                            -1 never (fp32 matrix instructions: exact products whatever the operands' magnitude)     */
   int32_t reserved[3];  /* must be 0 */
 } rotconv_plan_options;
@@ -286,7 +289,7 @@ double rotconv_plan_conv_equivalents(const rotconv_plan* plan, int pass);
 /* Name of the kernel family a call of the given kind on this plan uses ("generic", "mfma_p4", "mfma_p4_base" (the
  * pooled forward on products of the base bank), "mfma_p4_bf16", "mfma_p4_bf16_lut" (a bf16 gradient whose routed
  * gradients are folded into the base taps in fp32 and rounded to bf16 once, the matrix operand), "mfma_gemm_scatter",
- * "valu_direct" (layers with at most four input channels: vector ALU only), "mfma_px_bf16" (the bf16 pooled forward with
+ * "valu_direct" (layers with at most four input channels: kernels of their own, see the plan option), "mfma_px_bf16" (the bf16 pooled forward with
  * a lane per pixel column)).  pass: 0 / 1 / 2 = the fused calls rotconv_pool_fwd / _bwd_data / _bwd_weight (and
  * rotconv_fwd); 3 / 4 = the unfused gradient calls rotconv_bwd_data / rotconv_bwd_weight when given
  * rotconv_workspace_bytes_unfused of scratch (with less they run "generic"). */

@@ -436,7 +436,7 @@ DirGeom direct_geom(const rotconv_plan* p) {
   // 1024 SIMDs hold all waves of these launches at once, and the launch ends when the SIMD with the most waves does:
   // the band height with the smallest (waves per SIMD, rounded up) x (TY + 2).  Bands of fewer than eight rows only where
   // every wave has a SIMD of its own: a small map is a few waves with a long chain of instructions each (3 -> 8 channels,
-  // 64 x 64: 21 us with bands of eight rows, 8 with one).
+  // 64 x 64: 21 us with bands of eight rows, 8.4 with one; short bands beyond that: 2x3 -> 64, 512x512 4 % slower).
   int ty = std::min(std::max(p->opt.direct_ty, 1), d.H);
   if (p->opt.direct_ty <= 0) {
     long best = -1;

@@ -1,7 +1,7 @@
 // Expansion of the base bank(s) into first-quadrant banks (Sec. III-D / Eq. 17) inside the kernels that pack a layer's
 // weights.  These kernels are small and run ahead of a large one that waits for them, so their time is the length of their
 // chain of dependent loads: every load of a tap is issued whether its coefficient is used or not (under a branch each would be
-// waited for before the next: 12-17 us a launch, 6-8 so), the plans whose bank is the base bank itself look nothing up, and
+// waited for before the next: 12-17 us a launch, 5-9 so), the plans whose bank is the base bank itself look nothing up, and
 // a thread forms three taps of nine.
 #pragma once
 

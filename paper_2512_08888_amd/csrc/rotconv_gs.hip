@@ -62,7 +62,7 @@ constexpr int TP = 3;            // taps of products in LDS at a time
 // TP taps at a time (the next ones' loads on their way meanwhile: one tap at a time waits for them 44 us long), a thread adds
 // them up for four pixels of a column and four turns.
 // (k_gs_place reads every product once per turn, through bounds of its own each time: 48 us for 32 filters of 5 x 5 taps on
-// 2 x 96 x 96 pixels; 16 so.)
+// 2 x 96 x 96 pixels; 33 so.)
 template <bool FUSED>
 __global__ __launch_bounds__(256) void k_gs_place_tile(const float* __restrict__ P, const int32_t* __restrict__ rot_of,
                                                        const int32_t* __restrict__ turn_tap, float* __restrict__ yout,

@@ -1371,7 +1371,7 @@ __global__ __launch_bounds__(256) void k_p4_sum_splits_wide(const float* __restr
 
 // ... and where the sum goes straight to dw[b][co][ci][u]: a workgroup takes the nine taps of 64 channels of a filter, so that
 // what it writes is one piece of 576 floats, turned round in LDS.  (Each sum written where it belongs, 36 bytes from the next
-// channel's: 19 us for 512 -> 512 channels and four splits; 13 so.)
+// channel's: 19 us for 512 -> 512 channels and four splits; 8.5 so.)
 __global__ __launch_bounds__(192) void k_p4_sum_splits_dw(const float* __restrict__ partial, float* __restrict__ dw, int n_elem,
                                                           int splits, DwLayout L) {
   __shared__ float t[64 * 9];

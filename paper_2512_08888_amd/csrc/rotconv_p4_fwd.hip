@@ -37,6 +37,9 @@
 // into segments that overlap by 8 pixels (the products of the overlap are
 // recomputed, about 6 % at W = 512); a segment writes only the pixels whose
 // both neighbours it holds.
+//
+// With bf16 parts this kernel takes rows that the chained waves cover exactly (W % 8 == 0 and a whole number of waves); other
+// rows run k_s3_fwd (rotconv_s3_fwd.hip), whose waves need nothing of each other.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -477,7 +477,7 @@ __global__ __launch_bounds__(256) void k_p4_combine_bf16(const float* __restrict
 // One thread per (filter, channel) and bank (blockIdx.y): it reads the 9 NB taps of its base filter(s) and forms the bank's
 // with wave-uniform fp64 coefficients (dense [Q][9][NS] matrices, NS = 9 source taps per base bank), or copies them where
 // the bank is the base bank.  (All banks in one thread: 17 us for 256 -> 256 channels and four banks, the chain of its
-// coefficient loads; 6 so.)
+// coefficient loads; 8.4 so.)
 template <int NS>
 __global__ __launch_bounds__(256) void k_p4_pack_fwd_bf16(const uint16_t* __restrict__ w, uint16_t* __restrict__ wt,
                                                           const double* __restrict__ dense, int Q, int CB, int CinPad,

@@ -1,6 +1,6 @@
 // Fast weight-gradient kernel for 3x3, stride 1, pad 1 (fp32 tensors), fused with the orientation max-pool backward
 // (paper Eq. 12, 14, 16 in shared-product form), on the bf16 matrix cores with operands split into three bf16 parts
-// (rotconv_split3.h); layers with more than 32 input channels.
+// (rotconv_split3.h); layers with more than 16 input channels.
 //
 //   dF_q[co,ci,u] = sum_{n,h,x} D^q_u[co,h,x] * X[ci,h,x]
 //   D^q_u[co,h,x] = sum_s Delta_(q,s)[co, h+1-i_s(u), x+1-j_s(u)],   Delta_r = G * 1[idx == r]
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(NTW, 3) void k_s3_bwd_weight(const float* __restric
         if constexpr (RAGGED) {
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            k.v[p][r][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rx, ok & (px + i < g.W) ? o + 4u * i : kOutside, 0, 0));
+            k.v[p][r][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rx, (ok & (px + i < g.W)) ? o + 4u * i : kOutside, 0, 0));
         } else {
           k.v[p][r] = __builtin_bit_cast(s3_f4, __builtin_amdgcn_raw_buffer_load_b128(rx, ok ? o : kOutside, 0, 0));
         }
@@ -352,8 +352,8 @@ __global__ __launch_bounds__(NTW, 3) void k_s3_bwd_weight(const float* __restric
 
 // Quarter turns only, more than sixteen channels, and an image of either operand within a 32-bit byte offset.  With sixteen
 // channels or fewer three quarters of the workgroup's tiles would be padding, where k_p4_bwd_weight has blocks of sixteen:
-// 1.4 times its time in the mean of 45 layers; with 17 to 32, which it pads to 64, 0.77 (2x26 -> 380, 212x100 390 -> 207 us).  For other turns D is a sum over table entries, three times the vector work, which the matrix cores' gain
-// does not pay for: at 4x128 -> 128, 128x128, 16 turns this split took 248 us with the table in LDS, k_p4_bwd_weight's
+// 1.4 times its time in the mean of 45 layers; with 17 to 32, which it pads to 64, 0.77 (2x26 -> 380, 212x100 390 -> 207 us).
+// For other turns D is a sum over table entries, three times the vector work, which the matrix cores' gain does not pay for: at 4x128 -> 128, 128x128, 16 turns this split took 248 us with the table in LDS, k_p4_bwd_weight's
 // table variant takes 219.
 // Nor where a workgroup has a single step and the partial sums of all take longer than it: with up to 16 filters half of
 // what is summed is padding, with one image row half of what is multiplied.  Graph replays of 600 layers of up to 64 rows,
