@@ -7,7 +7,9 @@
  * Same conventions as rotconv.h: plain C; every tensor pointer is DEVICE memory owned by the
  * caller, dense row-major fp32 NCHW (labels int32, max-pool indices uint8); `stream` is a
  * hipStream_t passed as void*; calls only enqueue; outputs are overwritten unless said
- * otherwise; results are bitwise reproducible.  Return value: a rotconv_status
+ * otherwise; results are bitwise reproducible.  The fp32 matrix products (transposed
+ * convolution, 1x1 heads of more than 8 classes) of small tensors multiply bf16 parts of the
+ * operands: an infinity or a magnitude from 3.396e38 on makes NaN there.  Return value: a rotconv_status
  * (ROTCONV_ERR_NULL, ROTCONV_ERR_SHAPE, ROTCONV_ERR_WORKSPACE, ROTCONV_ERR_LAUNCH).
  */
 #ifndef UNETGLUE_H

@@ -290,17 +290,23 @@ __global__ __launch_bounds__(NT) void k_gemm16(const uint16_t* __restrict__ A, c
   }
 }
 
-// fp32 operands in three bf16 parts: tiles of 32 T x 32 T x 32 (T = 2 or 4), four waves of T x T 16 x 16 tiles.  A thread
-// fetches eight consecutive k of a row (two rows with T = 4), splits them and writes three 16-byte pieces; LDS holds the
-// parts row-major (pitch 40 halfwords, as k_gemm16), so a fragment is one ds_read_b128.  The six products of a K-step are
-// summed from zero, smallest first, and only their total meets the running sum; every other K-step multiplies -A and is
-// subtracted, so that the instruction's cut towards minus infinity cancels.
+// fp32 operands in three bf16 parts: tiles of 64 x 64 x 32, four waves of 2 x 2 tiles of 16 x 16.  A thread fetches eight
+// consecutive k of a row, splits them and writes three 16-byte pieces; LDS holds the parts row-major (pitch 40 halfwords, as
+// k_gemm16), so a fragment is one ds_read_b128.  The six products of a K-step are summed from zero, smallest first, and only
+// their total meets the running sum; every other K-step multiplies -A and is subtracted, so that the instruction's cut towards
+// minus infinity cancels.
 //
-// What bounds it: the vector work of the split (44 instructions per eight elements) and one matrix instruction per 16 clk; a
-// launch of few tiles is a chain of K-steps of one workgroup per CU, one of few K-steps the way of its loads and stores: small
-// tiles there (T = 2 below 512 tiles of 128 x 128 or four K-steps).  Against k_gemm: 512 x 1024 x 256 (two) 28 -> 11 us, 256 x 1024 x 512 (two) 47 -> 16.
+// For launches that do not fill the chip with k_gemm's tiles: there the time is a workgroup's chain of K-steps, and this kernel
+// has shorter ones, four times as many workgroups and three steps' loads on their way (one step ahead only: 78 instead of
+// 44 us where the contraction is 800 long and 288 tiles are all there are).  k_gemm / this, two images of the up-convolutions of
+// 256 -> 128 channels at 32 x 32 and 128 -> 64 at 64 x 64, us for both: forward 56 / 29, input gradient 94 / 40, weight gradient
+// (few tiles of a long K, split) 33 / 33.  On a full chip the vector work of the split (44 instructions per eight elements, by
+// every workgroup that reads them) bounds it: see launch_gemm.
+//
+// An infinite or NaN operand, or one from 3.396e38 on, makes NaN of the sums it enters.
 typedef f4 f4u __attribute__((aligned(4)));
-template <bool TA, bool TB, int T>
+constexpr int T = 2;                                // 16 x 16 tiles of a wave, either way
+template <bool TA, bool TB>
 __global__ __launch_bounds__(NT) void k_gemm_s3(const float* __restrict__ A, const float* __restrict__ B,
                                                float* __restrict__ C, GemmArgs p) {
   constexpr int TM = 32 * T, NJ = T / 2;            // rows of a tile; pieces of eight k per thread and operand
@@ -467,8 +473,20 @@ __global__ __launch_bounds__(NT) void k_gemm_s3(const float* __restrict__ A, con
   }
 }
 
-// out[e] = sum_z part[z][e].  A block covers 32 elements x 8 interleaved groups of parts, each added in ascending order, then
-// the groups in a fixed tree.  (One thread per element: 15 us for the 128 parts of 128 x 8 elements, the chain of its loads.)
+// out[e] = sum_z part[z][e], ascending.  A thread per element fills the chip from 65536 of them.
+__global__ __launch_bounds__(256) void k_sum_parts_wide(const float* __restrict__ part, float* __restrict__ out, size_t n,
+                                                        int nparts, size_t stride) {
+  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (e >= n) return;
+  float s = 0.f;
+#pragma unroll 4
+  for (int z = 0; z < nparts; ++z) s += part[(size_t)z * stride + e];
+  out[e] = s;
+}
+
+// The same for fewer elements.  A block covers 32 elements x 8 interleaved groups of parts, each added in ascending order, then
+// the groups in a fixed tree.  (One thread per element: 15 us for the 128 parts of 128 x 8 elements, the chain of its loads.  On 1024 x 2048
+// elements of four parts these groups are half idle: 8 us longer than a thread per element.)
 __global__ __launch_bounds__(256) void k_sum_parts(const float* __restrict__ part, float* __restrict__ out, size_t n,
                                                    int nparts, size_t stride) {
   __shared__ float red[8][32];
@@ -487,7 +505,6 @@ __global__ __launch_bounds__(256) void k_sum_parts(const float* __restrict__ par
 
 }  // namespace
 
-template <int T>
 void launch_gemm_s3(const GemmArgs& a, const float* A, const float* B, float* C, hipStream_t st) {
   const int tm = 32 * T;
   const size_t lds = (size_t)2 * 2 * 3 * tm * PITCH16 * sizeof(uint16_t);
@@ -496,10 +513,10 @@ void launch_gemm_s3(const GemmArgs& a, const float* A, const float* B, float* C,
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(kern, grid, dim3(NT), lds, st, A, B, C, a);
   };
-  if (a.transA && a.transB) go(k_gemm_s3<true, true, T>);
-  else if (a.transA) go(k_gemm_s3<true, false, T>);
-  else if (a.transB) go(k_gemm_s3<false, true, T>);
-  else go(k_gemm_s3<false, false, T>);
+  if (a.transA && a.transB) go(k_gemm_s3<true, true>);
+  else if (a.transA) go(k_gemm_s3<true, false>);
+  else if (a.transB) go(k_gemm_s3<false, true>);
+  else go(k_gemm_s3<false, false>);
 }
 void launch_gemm_f32(const GemmArgs& a, const void* A, const void* B, void* C, hipStream_t st) {
   dim3 grid((a.M + BM - 1) / BM, (a.N + BN - 1) / BN, a.batch * a.splitk);
@@ -525,17 +542,19 @@ void launch_gemm(const GemmArgs& a, const void* A, const void* B, void* C, hipSt
   // the glue uses three storage combinations: all fp32, bf16 operands with an fp32 or a bf16 result
   if (a.bf16A && a.bf16B && a.bf16C) launch_gemm_bf16<true>(a, A, B, C, st);
   else if (a.bf16A && a.bf16B) launch_gemm_bf16<false>(a, A, B, C, st);
-  else if (!a.fp32_instr) {
-    const long tiles = (long)((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch * a.splitk;
-    const float *Af = static_cast<const float*>(A), *Bf = static_cast<const float*>(B);
-    if (tiles >= 512 && a.K >= 128 * a.splitk) launch_gemm_s3<4>(a, Af, Bf, static_cast<float*>(C), st);
-    else launch_gemm_s3<2>(a, Af, Bf, static_cast<float*>(C), st);
-  }
+  // Fp32 operands: bf16 parts where the launch is below 512 tiles of 128 x 128 and, contracting over pixels (B transposed; many
+  // images and splits of few tiles), a matrix below 32.  Parts / fp32 instructions, up-convolutions of 55 random sizes, mean (most):
+  // forward below 256 tiles 0.40 to 0.68 (0.85), 256 to 511 0.87 (0.96), from 512 1.09, from 1024 1.17 (1.31); input gradient 0.34 to
+  // 0.80 (0.92), from 512 0.99, from 1024 1.04; weight gradient below 32 tiles 0.22 to 0.98, 32 to 128 1.04 (1.15).
+  else if (const long mn = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
+           !a.fp32_instr && mn * a.batch * a.splitk < 512 && !(a.transB && mn >= 32))
+    launch_gemm_s3(a, static_cast<const float*>(A), static_cast<const float*>(B), static_cast<float*>(C), st);
   else launch_gemm_f32(a, A, B, C, st);
 }
 
 void launch_sum_parts(const float* part, float* out, size_t n, int nparts, size_t stride, hipStream_t st) {
-  hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, part, out, n, nparts, stride);
+  if (n >= 65536) hipLaunchKernelGGL(k_sum_parts_wide, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part, out, n, nparts, stride);
+  else hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, part, out, n, nparts, stride);
 }
 
 }  // namespace rotconv

@@ -1,7 +1,7 @@
 """The matrix multiply on bf16 parts and the tiled kernels of the multiply + scatter family, at the edges of their tiles:
-rows, columns and K-steps around 32, 64 and 128, contractions of one K-step and of many, both tile sizes; 32 x 32 pixel tiles
-of filters from 2 x 2 to 15 x 15 taps, strides to 3, several banks, incomplete orientation sets, pool groups, images one at
-a time.
+rows, columns and K-steps around 32, 64 and 128, contractions of one K-step and of many, both sides of the rule that keeps
+large products on the fp32 instruction; 32 x 32 pixel tiles of filters from 2 x 2 to 15 x 15 taps, strides to 3, several
+banks, incomplete orientation sets, pool groups, images one at a time.
 
 Error bar: within a K-step the matrix instruction cuts six sums per 32 terms, so a sum of K terms is within about
 sqrt(6 K / 32) 2^-24 of its norm: 1.5e-6 for the deepest contraction here (K = 16389); twice that is asked for.
@@ -25,7 +25,7 @@ def _rel(got, ref):
 
 
 @pytest.mark.parametrize("N,Cin,Cout,P", [(1, 1, 9, 1), (2, 31, 33, 63), (1, 32, 64, 64), (3, 33, 65, 65), (2, 64, 31, 129), (1, 97, 130, 31),
-                                          (1, 129, 16, 2050), (2, 160, 130, 16389)])      # the last: 128 x 128 tiles
+                                          (1, 129, 16, 2050), (2, 160, 130, 16389)])      # the last: fp32 instructions
 def test_products(N, Cin, Cout, P):
     rng = np.random.default_rng(P)
     f = lambda *s: rng.standard_normal(s).astype(np.float32)
