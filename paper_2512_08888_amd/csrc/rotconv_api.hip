@@ -387,17 +387,42 @@ int rotconv_plan_routed_table(const rotconv_plan* plan, float* T) {
 
 }  // extern "C" (the fp32 implementations below have internal linkage)
 
+// Does the unpooled forward of an fp32 plan run the register-resident kernel for these pointers?
+static bool f32_fwd_is_fast(const rotconv_plan* p, const void* x, const void* y, const void* ws) {
+  const bool odd = p->d.W & 1;       // rows whose pixel pairs the kernel does not load or store as pairs
+  return p->fast[0] && aligned(x, odd ? 4 : 8) && aligned(ws, p->fwd_csplit[0] > 1 ? 256 : 16) && aligned(y, odd ? 4 : 16);
+}
+
+// Scratch of either forward off the register-resident kernels: the products of a few images, or the rotated banks.
+static size_t f32_other_fwd_need(const rotconv_plan* p) {
+  return p->gs ? gs_ws_bytes(p) : align256((size_t)p->d.R * p->d.Cout * p->d.Cin * p->kk * sizeof(float));
+}
+
+// Scratch the unpooled forward of an fp32 plan needs for these pointers, whatever the plan's other calls need.
+static size_t f32_fwd_need(const rotconv_plan* p, const void* x, const void* y, const char* ws) {
+  if (p->pad_child && p->pad_use[0]) {
+    const PadLayout L = pad_layout(p);
+    return L.child + f32_fwd_need(p->pad_child, ws + L.in, ws + L.out, ws + L.child);
+  }
+  const int cs = p->fwd_csplit[0];
+  return f32_fwd_is_fast(p, x, y, ws) ? fwd_part_bytes(p, cs) + p4_fwd_least_pack_bytes(p, 1, cs) : f32_other_fwd_need(p);
+}
+
+static int fwd_impl(const rotconv_plan* plan, const void* x, const void* w, void* y, void* ws, size_t ws_bytes,
+                    void* stream, bool own_need);
+
+// own_need: `ws` has to hold what this call touches (f32_fwd_need), not the plan's largest call
 static int f32_rotconv_fwd(const rotconv_plan* plan, const void* x, const void* w, void* y, void* ws, size_t ws_bytes,
-                void* stream) {
+                void* stream, bool own_need = false) {
   if (!plan || !x || !w || !y) return ROTCONV_ERR_NULL;
-  int rc = check_ws_inner(plan, ws, ws_bytes);
-  if (rc) return rc;
+  const size_t need = own_need ? f32_fwd_need(plan, x, y, static_cast<const char*>(ws)) : plan->ws_inner;
+  if (need && (!ws || ws_bytes < need)) return ROTCONV_ERR_WORKSPACE;
+  int rc;
   rotconv_plan* p = const_cast<rotconv_plan*>(plan);
   if ((rc = ensure_device_tables(p))) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int cs = p->fwd_csplit[0];
-  const bool odd = p->d.W & 1;       // rows whose pixel pairs the kernel does not load or store as pairs
-  if (p->fast[0] && aligned(x, odd ? 4 : 8) && aligned(ws, cs > 1 ? 256 : 16) && aligned(y, odd ? 4 : 16)) {
+  if (f32_fwd_is_fast(p, x, y, ws)) {
     const size_t parts = fwd_part_bytes(p, cs);       // small map, deep input: the channels are split over workgroups
     float* out = cs > 1 ? static_cast<float*>(ws) : static_cast<float*>(y);
     launch_p4_fwd(p, kOutUnpooled, static_cast<const float*>(x), static_cast<const float*>(w),
@@ -484,11 +509,14 @@ static bool f32_pool_fwd_is_fast(const rotconv_plan* p, const void* x, const voi
          aligned(idx, odd ? 1 : 8);
 }
 
-// Scratch the pooled forward of an fp32 plan needs: the packed banks (+ candidates) of the register-resident kernel;
-// every other route is sized by the plan's largest call.
+// Scratch the pooled forward of an fp32 plan needs for these pointers, whatever the plan's other calls need: the packed
+// banks (+ candidates) of the register-resident kernel, the averaged bank and its convolution, or the other families'.
 static size_t f32_pool_fwd_need(const rotconv_plan* p, const void* x, const void* ypool, const uint8_t* idx,
                                 const void* ws) {
-  return f32_pool_fwd_is_fast(p, x, ypool, idx, ws) ? std::min(p->ws_inner, fwd_fast_least_bytes(p)) : p->ws_inner;
+  if (f32_pool_fwd_is_fast(p, x, ypool, idx, ws)) return std::min(p->ws_inner, fwd_fast_least_bytes(p));
+  if (!p->avg_child) return f32_other_fwd_need(p);
+  const AvgLayout L = avg_layout(p);
+  return L.child + f32_fwd_need(p->avg_child, x, ypool, static_cast<const char*>(ws) + L.child);
 }
 
 // no_upload: the caller may not allocate, so a plan whose tables are not on this device yet is refused
@@ -510,7 +538,7 @@ static int f32_rotconv_pool_fwd(const rotconv_plan* plan, const void* x, const v
     float* wavg = reinterpret_cast<float*>(c + L.wavg);
     launch_expand_bank(p, static_cast<const float*>(w), wexp, st);
     launch_avg_bank(p, wexp, wavg, st);
-    return rotconv_fwd(p->avg_child, x, wavg, ypool, c + L.child, p->avg_child->ws_bytes, stream);
+    return fwd_impl(p->avg_child, x, wavg, ypool, c + L.child, ws_bytes - L.child, stream, own_need);
   }
   if (f32_pool_fwd_is_fast(p, x, ypool, idx, ws)) {
     const int mode = p4_fwd_pool_mode(p);
@@ -676,14 +704,17 @@ const uint16_t* h16(const void* p) { return static_cast<const uint16_t*>(p); }
 struct PadCtx {
   const rotconv_plan* ch;
   char *in, *out, *idx, *cws;
+  size_t cws_bytes;
   int es, W, Wp;
   size_t rows_x, rows_p, rows_u;    // rows of the input, the pooled and the unpooled maps
   hipStream_t st;
 };
-int pad_ctx(const rotconv_plan* p, void* ws, size_t ws_bytes, void* stream, PadCtx* c) {
-  if (!ws || ws_bytes < p->ws_bytes) return ROTCONV_ERR_WORKSPACE;
+// need: the least the scratch has to hold (the child's share is what lies behind the staging areas)
+int pad_ctx(const rotconv_plan* p, void* ws, size_t ws_bytes, void* stream, PadCtx* c, size_t need) {
+  if (!ws || ws_bytes < need) return ROTCONV_ERR_WORKSPACE;
   const PadLayout L = pad_layout(p);
   char* b = static_cast<char*>(ws);
+  c->cws_bytes = ws_bytes - L.child;
   c->ch = p->pad_child;
   c->in = b + L.in; c->out = b + L.out; c->idx = b + L.idx; c->cws = b + L.child;
   c->es = is_bf16(p) ? 2 : 4;
@@ -697,19 +728,20 @@ int pad_ctx(const rotconv_plan* p, void* ws, size_t ws_bytes, void* stream, PadC
 
 }  // namespace
 
-int rotconv_fwd(const rotconv_plan* plan, const void* x, const void* w, void* y, void* ws, size_t ws_bytes,
-                void* stream) {
+static int fwd_impl(const rotconv_plan* plan, const void* x, const void* w, void* y, void* ws, size_t ws_bytes,
+                    void* stream, bool own_need) {
   if (!plan || !x || !w || !y) return ROTCONV_ERR_NULL;
   if (plan->pad_child && plan->pad_use[0]) {
     PadCtx c;
-    int rc = pad_ctx(plan, ws, ws_bytes, stream, &c);
+    int rc = pad_ctx(plan, ws, ws_bytes, stream, &c,
+                     own_need ? f32_fwd_need(plan, x, y, static_cast<const char*>(ws)) : plan->ws_bytes);
     if (rc) return rc;
     launch_repitch(x, c.in, c.rows_x, c.W, c.Wp, c.es, 0, c.st);
-    if ((rc = rotconv_fwd(c.ch, c.in, w, c.out, c.cws, c.ch->ws_bytes, stream))) return rc;
+    if ((rc = fwd_impl(c.ch, c.in, w, c.out, c.cws, c.cws_bytes, stream, own_need))) return rc;
     launch_repitch(c.out, y, c.rows_u, c.Wp, c.W, c.es, 0, c.st);
     return finish();
   }
-  if (!is_bf16(plan)) return f32_rotconv_fwd(plan, x, w, y, ws, ws_bytes, stream);
+  if (!is_bf16(plan)) return f32_rotconv_fwd(plan, x, w, y, ws, ws_bytes, stream, own_need);
   if (!ws || ws_bytes < plan->ws_bytes) return ROTCONV_ERR_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (plan->native16[0] && aligned(x, 4) && aligned(w, 2) && aligned(ws, 256) && aligned(y, 16)) {
@@ -728,6 +760,11 @@ int rotconv_fwd(const rotconv_plan* plan, const void* x, const void* w, void* y,
   if (rc) return rc;
   launch_narrow(s.y, static_cast<uint16_t*>(y), plan->n_yu, st);
   return finish();
+}
+
+int rotconv_fwd(const rotconv_plan* plan, const void* x, const void* w, void* y, void* ws, size_t ws_bytes,
+                void* stream) {
+  return fwd_impl(plan, x, w, y, ws, ws_bytes, stream, false);
 }
 
 int rotconv_bwd_data(const rotconv_plan* plan, const void* dy, const void* w, void* dx, void* ws, size_t ws_bytes,
@@ -789,8 +826,6 @@ bool bf16_pool_fwd_is_native(const rotconv_plan* plan, const void* x, const void
          aligned(idx, 8);
 }
 
-// Bytes of `ws` one call of the pooled forward touches, by the route it takes for these pointers (never more than
-// rotconv_workspace_bytes, which is the largest need of any call on the plan).
 // Does the pooled forward run the vector-ALU kernel of layers with at most four input channels for these pointers?
 bool pool_fwd_is_direct(const rotconv_plan* p, const void* x, const void* ypool, const void* ws) {
   const size_t es = is_bf16(p) ? 2 : 4;
@@ -801,14 +836,21 @@ bool pool_fwd_is_px16(const rotconv_plan* p, const void* x, const void* ypool, c
   return p->px16 && aligned(x, 2) && aligned(ypool, 2) && aligned(ws, 16);
 }
 
+// Bytes of `ws` one call of the pooled forward touches, by the route it takes for these pointers (never more than
+// rotconv_workspace_bytes, which is the largest need of any call on the plan).
 size_t pool_fwd_need(const rotconv_plan* plan, const void* x, const void* w, const void* ypool, const uint8_t* idx,
                      const void* ws) {
-  if (plan->pad_child && plan->pad_use[0]) return plan->ws_bytes;             // staging copies + the padded plan
+  const char* c = static_cast<const char*>(ws);
+  if (plan->pad_child && plan->pad_use[0]) {                                  // staging copies + the padded plan's call
+    const PadLayout L = pad_layout(plan);
+    return L.child + pool_fwd_need(plan->pad_child, c + L.in, w, c + L.out, reinterpret_cast<const uint8_t*>(c + L.idx), c + L.child);
+  }
   if (pool_fwd_is_px16(plan, x, ypool, ws)) return align256(px_fwd_bf16_pack_bytes(plan));
   if (pool_fwd_is_direct(plan, x, ypool, ws)) return align256(direct_fwd_pack_floats(plan) * sizeof(float));
   if (!is_bf16(plan)) return f32_pool_fwd_need(plan, x, ypool, idx, ws);
-  if (bf16_pool_fwd_is_native(plan, x, w, ypool, idx, ws)) return std::min(plan->ws_bytes, fwd_fast_least_bytes(plan));
-  return plan->ws_bytes;                                                      // fp32 staging areas in front
+  if (bf16_pool_fwd_is_native(plan, x, w, ypool, idx, ws)) return align256(p4_fwd_bf16_pack_bytes(plan)) + fwd_extra_bytes(plan);
+  const Stage s = carve(plan, const_cast<void*>(ws), 0);                      // fp32 staging areas in front
+  return (size_t)(static_cast<const char*>(s.inner) - c) + f32_pool_fwd_need(plan, s.x, s.y, idx, s.inner);
 }
 
 // own_need: `ws` has to hold what this call touches (pool_fwd_need), not the plan's largest call.
@@ -819,10 +861,10 @@ int pool_fwd_impl(const rotconv_plan* plan, const void* x, const void* w, void* 
   if (plan->pad_child && plan->pad_use[0]) {
     if (no_upload && !tables_on_current_device(plan->pad_child)) return ROTCONV_ERR_UNSUPPORTED;
     PadCtx c;
-    int rc = pad_ctx(plan, ws, ws_bytes, stream, &c);
+    int rc = pad_ctx(plan, ws, ws_bytes, stream, &c, own_need ? pool_fwd_need(plan, x, w, ypool, idx, ws) : plan->ws_bytes);
     if (rc) return rc;
     launch_repitch(x, c.in, c.rows_x, c.W, c.Wp, c.es, 0, c.st);
-    if ((rc = pool_fwd_impl(c.ch, c.in, w, c.out, reinterpret_cast<uint8_t*>(c.idx), c.cws, c.ch->ws_bytes, stream, false,
+    if ((rc = pool_fwd_impl(c.ch, c.in, w, c.out, reinterpret_cast<uint8_t*>(c.idx), c.cws, c.cws_bytes, stream, own_need,
                             no_upload)))
       return rc;
     launch_repitch(c.out, ypool, c.rows_p, c.Wp, c.W, c.es, 0, c.st);
@@ -881,7 +923,7 @@ int pool_fwd_impl(const rotconv_plan* plan, const void* x, const void* w, void* 
   const Stage s = carve(plan, ws, ws_bytes);
   launch_widen(h16(x), s.x, plan->n_x, st);
   launch_widen(h16(w), s.w, plan->n_w, st);
-  const int rc = f32_rotconv_pool_fwd(plan, s.x, s.w, s.y, idx, s.inner, s.inner_bytes, stream, false, no_upload);
+  const int rc = f32_rotconv_pool_fwd(plan, s.x, s.w, s.y, idx, s.inner, s.inner_bytes, stream, own_need, no_upload);
   if (rc) return rc;
   launch_narrow(s.y, static_cast<uint16_t*>(ypool), plan->n_yp, st);
   return finish();
@@ -937,7 +979,7 @@ int rotconv_pool_bwd_data(const rotconv_plan* plan, const void* gpool, const uin
   if (!plan || !gpool || (!idx && !plan->avg_child) || !w || !dx) return ROTCONV_ERR_NULL;
   if (plan->pad_child && plan->pad_use[1]) {     // padded columns: zero gradient, idx 255 (matches no orientation)
     PadCtx c;
-    int rc = pad_ctx(plan, ws, ws_bytes, stream, &c);
+    int rc = pad_ctx(plan, ws, ws_bytes, stream, &c, plan->ws_bytes);
     if (rc) return rc;
     launch_repitch(gpool, c.out, c.rows_p, c.W, c.Wp, c.es, 0, c.st);
     launch_repitch(idx, c.idx, c.rows_p, c.W, c.Wp, 1, 0xff, c.st);
@@ -980,7 +1022,7 @@ int rotconv_pool_bwd_weight(const rotconv_plan* plan, const void* x, const void*
   if (!plan || !x || !gpool || (!idx && !plan->avg_child) || !dw) return ROTCONV_ERR_NULL;
   if (plan->pad_child && plan->pad_use[2]) {
     PadCtx c;
-    const int rc = pad_ctx(plan, ws, ws_bytes, stream, &c);
+    const int rc = pad_ctx(plan, ws, ws_bytes, stream, &c, plan->ws_bytes);
     if (rc) return rc;
     launch_repitch(x, c.in, c.rows_x, c.W, c.Wp, c.es, 0, c.st);
     launch_repitch(gpool, c.out, c.rows_p, c.W, c.Wp, c.es, 0, c.st);

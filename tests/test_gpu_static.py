@@ -1,0 +1,52 @@
+"""rotconv_pool_fwd_static takes every layer whose pooled forward fits its scratch by itself, whatever the plan's other calls
+need, and gives bit for bit what rotconv_pool_fwd gives."""
+import pytest
+import torch
+
+from paper_2512_08888_amd import binding as rc
+from paper_2512_08888_amd import synth
+
+pytestmark = pytest.mark.gpu
+L = synth.LayerConfig
+
+# pooled forwards of 9 to 16 MB beside weight gradients of more than 16 MB, and calls on tensors off their alignment
+OWN = [
+    (L("pad16", N=1, Cin=23, H=64, W=348, Cout=8, R=1, seed=2201), dict(dtype=rc.BF16), 0),
+    (L("pad16_odd", N=13, Cin=30, H=72, W=1, Cout=4, R=1, seed=2202), dict(dtype=rc.BF16), 0),
+    (L("native16", N=8, Cin=313, H=100, W=2, Cout=91, R=16, mode="bilinear", seed=2203), dict(dtype=rc.BF16), 0),
+    (L("avg", N=1, Cin=26, H=212, W=223, Cout=2, R=4, seed=2204), dict(pool_op="avg"), 0),
+    (L("avg_even", N=6, Cin=19, H=43, W=130, Cout=5, R=1, seed=2205), dict(pool_op="avg"), 0),
+    (L("avg16", N=8, Cin=30, H=157, W=36, Cout=2, R=2, seed=2206), dict(pool_op="avg", dtype=rc.BF16), 0),
+    (L("off", N=4, Cin=19, H=50, W=16, Cout=60, R=1, seed=2207), {}, 1),
+    (L("off_k5", N=2, Cin=16, H=20, W=22, Cout=8, R=4, k=5, pad=2, seed=2208), {}, 1),
+]
+
+
+def _both(cfg, over, off):
+    plan = rc.Plan.from_config(cfg, **over)
+    dt = torch.bfloat16 if over.get("dtype") == rc.BF16 else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(cfg.seed)
+
+    def t(shape, dtype, fill=None):      # `off` elements off its alignment
+        n = 1
+        for s in shape:
+            n *= s
+        v = torch.empty(n + off, dtype=dtype, device="cuda")[off:].view(shape)
+        return v.copy_(torch.randn(shape, generator=gen, device="cuda")) if fill is None else v.fill_(fill)
+
+    x = t((cfg.N, cfg.Cin, cfg.H, cfg.W), dt)
+    w = t((plan.B, cfg.Cout, cfg.Cin, cfg.k, cfg.k), dt)
+    out = []
+    for call in (rc.rotconv_pool_fwd, rc.rotconv_pool_fwd_static):
+        yp = t((cfg.N, plan.Cpooled, plan.Ho, plan.Wo), dt, float("nan"))
+        idx = t(yp.shape, torch.uint8, 254)
+        call(plan, x, w, yp, None if over.get("pool_op") == "avg" else idx)
+        out.append((yp, idx))
+    torch.cuda.synchronize()
+    assert torch.isfinite(out[0][0].float()).all()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("cfg,over,off", OWN, ids=[c.name for c, _, _ in OWN])
+def test_own_need(cfg, over, off):
+    _both(cfg, over, off)
