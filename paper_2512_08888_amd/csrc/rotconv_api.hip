@@ -128,15 +128,30 @@ size_t fwd_fast_least_bytes(const rotconv_plan* p) {
   return align256(std::max({p4_fwd_weights(p) * sizeof(float), block, bf})) + fwd_extra_bytes(p);
 }
 
-// The fp32 forward's form and channel splits.  A layer of one filter block, whose parts cannot be packed in slices, keeps
+// The fp32 forward's form and channel splits.  Of the splits whose parts rotconv_pool_fwd_static does not hold, only those
+// are taken that the chained waves would make too, where the whole contraction is one it holds: the waves on their own split
+// more (4x994 -> 69, 19x70, eight turns: eight parts of 12 MB, modelled 206 us instead of 291), and layers that the call
+// takes stay taken.  A layer of one filter block, whose parts cannot be packed in slices, keeps
 // the fp32 instructions where rotconv_pool_fwd_static holds its banks at four bytes a weight but not at six.
 void choose_fwd(rotconv_plan* p) {
+  // fp32 copies in front of a call's scratch: widened ones of bf16 tensors; padded ones of odd rows, on chained waves
+  const rotconv_desc& d = p->d;
+  const double hw4 = 4.0 * d.N * d.H * d.W, nx = hw4 * d.Cin, ny = hw4 * d.Cout * d.R;
+  const double widened = d.dtype == ROTCONV_BF16 ? nx + ny + 36.0 * p->B * d.Cout * d.Cin : 0.;
+  const double padded = d.dtype == ROTCONV_F32 && (d.W & 1) ? nx + ny : 0.;
   auto choose = [&](int s3) {
     p->fwd_s3 = s3;
     p->fwd_csplit[0] = p4_fwd_csplit(p, false);
     p->fwd_csplit[1] = p4_fwd_csplit(p, true);
-    return fwd_fast_least_bytes(p) <= ROTCONV_STATIC_SCRATCH_BYTES;
+    const auto fits = [&](double front) { return front + fwd_fast_least_bytes(p) <= (double)ROTCONV_STATIC_SCRATCH_BYTES; };
+    const int split = p->fwd_csplit[1];
+    if (split > 1 && s3 && p->opt.fwd_csplit == 0 && !fits(widened) && p4_fwd_chain_whole(p)) {
+      p->fwd_csplit[1] = 1;
+      if (!fits(widened + padded)) p->fwd_csplit[1] = split;
+    }
+    return fits(0.);
   };
+
   const int s3 = p4_fwd_parts_wanted(p);
   if (!choose(s3) && s3 && p->d.Cout <= 16 && p->opt.bf16_parts == 0 && p4_fwd_f32_rows(p) && !choose(0)) choose(1);
   p4_fwd_choose_launches(p);

@@ -24,6 +24,7 @@ struct P4Geom {
   int csplit;    // parts the channel contraction is split into (1: none); a part is an unpooled fp32 map
   int cper;      // 32-channel chunks per part (all of them without a split)
   double cost;   // modelled time of the launch, 0.1 us (host side only)
+  long rows;     // the row steps behind it: four for a wave alone on its SIMD, eight for two that share one
   int cb0;       // first filter block of this launch
   int raw_w;     // the weight argument is the caller's w[Cout][Cin][9] itself (see p4_fwd_raw_weights)
   int seg_xorg[4];  // first product column of a segment's wave chain
@@ -57,10 +58,11 @@ void launch_s3_fwd(const S3FwdGeom& g, const float* x, const float* wt, const in
 bool p4_fwd_supported(const rotconv_plan* p);
 bool p4_fwd_f32_rows(const rotconv_plan* p);       // rows that the kernel on fp32 instructions takes
 bool p4_fwd_parts_wanted(const rotconv_plan* p);   // may the kernel multiply bf16 parts of the operands (plan field fwd_s3)?
-int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, int csplit = 1);
+int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, int csplit = 1, int nq = 1);
 // parts the forward splits its channel contraction into for this plan (1: none); with a split the kernel runs in
 // the unpooled mode into `csplit` parts of N * Cout * R * H * W floats, added by one of the two kernels below
 int p4_fwd_csplit(const rotconv_plan* p, bool pooled);
+bool p4_fwd_chain_whole(const rotconv_plan* p);
 void p4_fwd_choose_launches(rotconv_plan* p);   // fills fwd_launch, after the channel splits
 void launch_p4_sum_parts(const rotconv_plan* p, const float* part, int nparts, float* y, hipStream_t st);
 void launch_p4_sum_pool(const rotconv_plan* p, const float* part, int nparts, float* ypool, uint8_t* idx,

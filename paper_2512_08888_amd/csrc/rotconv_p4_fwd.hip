@@ -801,9 +801,36 @@ int p4_fwd_csplit(const rotconv_plan* p, bool pooled) {
   return best_s;
 }
 
-// Cut the row into segments of at most 256 product columns; all segments of one launch share nwx.
-// Returns the number of launches (geoms) written.
-int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, int csplit) {
+// Are the chained waves alone (rows that they overhang masked) no faster with a split, pooled?  In units of 0.3 us: four per
+// 32-channel chunk and row step of a wave and three for the placing; a split's parts at 4 TB/s and 8 us of launches.
+bool p4_fwd_chain_whole(const rotconv_plan* p) {
+  const rotconv_desc& d = p->d;
+  const int nchunk = cin_pad_f32(d.Cin) / 32, mode = p4_fwd_pool_mode(p);
+  auto cost = [&](int out_mode, int csplit, int nq) {
+    P4Geom gs[4];
+    const int n = p4_fwd_geoms(p, out_mode, gs, 4, csplit, nq);
+    long c = 0;
+    for (int i = 0; i < n; ++i) c += gs[i].rows * (4 * gs[i].cper + 3) / 4;
+    return n < 0 ? -1L : c;
+  };
+  // banks fold into a chain's columns where the block stays in LDS or the chain fits the row
+  int nq = mode == kOutPartial ? p4_fwd_fold(p) : 1;
+  if (needs_stream(p) && ((d.W & 31) || (d.W <= 256 && (d.W & (d.W - 1))))) nq = 1;
+  const long whole = cost(nq > 1 ? kOutPooled : mode, 1, nq);
+  const double part_bytes = (double)d.N * d.Cout * d.R * d.H * d.W * 4.0;
+  for (int s = 2; s <= 32; s *= 2) {
+    const int cper = (nchunk + s - 1) / s, s_eff = (nchunk + cper - 1) / cper;
+    if (cper > max_cper(1)) continue;
+    if (s_eff < 2) break;
+    if (cost(kOutUnpooled, s_eff, 1) + 28 + (long)(s_eff * part_bytes / 0.6e6) < whole) return false;
+    if (cper == 1) break;
+  }
+  return true;
+}
+
+// Cut the row into segments of at most 256 product columns; all segments of one launch share nwx.  nq: banks folded into
+// the filters of a block.  Returns the number of launches (geoms) written.
+int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, int csplit, int nq) {
   const rotconv_desc& d = p->d;
   P4Geom base{};
   {
@@ -859,11 +886,12 @@ int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, 
     // steps per wave x how many waves share a SIMD (a workgroup whose bands reach beyond the image leaves waves idle).
     for (int ty : {1, 2, 4, 8, 16, 32, 64}) {
       const int nbg = (d.H + nwy * ty - 1) / (nwy * ty);
-      const long units = (long)d.N * g.Q * g.CB * nbg * g.nseg * g.csplit;
+      const long units = (long)d.N * (nq > 1 ? (d.Cout * nq + 15) / 16 : g.Q * g.CB) * nbg * g.nseg * g.csplit;
       const int bands = nbg > 1 ? nwy : std::min(nwy, (d.H + ty - 1) / ty);
       const long cost = ((units + 255) / 256) * (ty + 2) * std::max(4, g.nwx * bands);
       if (best_cost < 0 || cost <= best_cost) { best_cost = cost; g.TY = ty; g.nbg = nbg; g.units = (int)units; }
     }
+    g.rows = best_cost;
     // in 0.1 us; best_cost counts the rows of a wave alone on its SIMD as four, of two that share one as eight
     g.cost = g.s3 ? best_cost * (28.7 * g.cper + 13.) / 8. + 30. + 8. * g.cper : 5. * best_cost * g.cper;
   }

@@ -50,3 +50,16 @@ def _both(cfg, over, off):
 @pytest.mark.parametrize("cfg,over,off", OWN, ids=[c.name for c, _, _ in OWN])
 def test_own_need(cfg, over, off):
     _both(cfg, over, off)
+
+
+# layers of which the waves on their own would make more parts than the scratch holds: the contraction stays whole
+WHOLE = [
+    L("w_r2", N=4, Cin=238, H=10, W=80, Cout=331, R=2, seed=2211),
+    L("w_steer", N=6, Cin=378, H=12, W=206, Cout=27, R=8, mode="steerable", pool_group=4, seed=2212),
+    L("w_r8", N=3, Cin=1207, H=134, W=4, Cout=113, R=8, mode="bilinear", seed=2213),
+]
+
+
+@pytest.mark.parametrize("cfg", WHOLE, ids=[c.name for c in WHOLE])
+def test_not_split_beyond_the_scratch(cfg):
+    _both(cfg, {}, 0)
