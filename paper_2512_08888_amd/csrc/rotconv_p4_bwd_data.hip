@@ -35,6 +35,7 @@ namespace rotconv {
 namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef f4 f4u __attribute__((aligned(4)));      // four floats at any float's address
 
 constexpr int NCB = 4;                 // 16-channel blocks per wave
 constexpr int CIG = 16 * NCB;          // input channels per workgroup
@@ -765,15 +766,16 @@ __global__ __launch_bounds__(256) void k_p4_pack_bwd_shared(const float* __restr
   for (int u = 0; u < 9; ++u) dst[(size_t)u * 64 * 4] = in ? src[u] : 0.f;
 }
 
-// dx[e] = sum over the bank splits, ascending, of part[s][e] (four elements per thread, scalar tail).
+// dx[e] = sum over the bank splits, ascending, of part[s][e] (four elements per thread, scalar tail).  The parts lie on
+// 16 bytes only where n_elem is a multiple of four, and dx of odd rows anywhere.
 __global__ __launch_bounds__(256) void k_p4_sum_dx(const float* __restrict__ part, float* __restrict__ dx, size_t n_elem,
                                                    int nparts) {
   const size_t n4 = n_elem / 4;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 256) {
-    f4 a = reinterpret_cast<const f4*>(part)[i];
+    f4 a = reinterpret_cast<const f4u*>(part)[i];
 #pragma unroll 4
-    for (int k = 1; k < nparts; ++k) a += reinterpret_cast<const f4*>(part + (size_t)k * n_elem)[i];
-    reinterpret_cast<f4*>(dx)[i] = a;
+    for (int k = 1; k < nparts; ++k) a += reinterpret_cast<const f4u*>(part + (size_t)k * n_elem)[i];
+    reinterpret_cast<f4u*>(dx)[i] = a;
   }
   for (size_t e = n4 * 4 + (size_t)blockIdx.x * 256 + threadIdx.x; e < n_elem; e += (size_t)gridDim.x * 256) {
     float v = part[e];

@@ -54,6 +54,7 @@ namespace rotconv {
 namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef f4 f4u __attribute__((aligned(4)));      // four floats at any float's address
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef float f2 __attribute__((ext_vector_type(2)));
@@ -413,14 +414,15 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_bwd_data_bf16(const uint1
   }
 }
 
-// dx = bf16(sum over splits, ascending, of the fp32 partials); n8 = elements / 8 (8 elements per thread).
+// dx = bf16(sum over splits, ascending, of the fp32 partials); n8 = elements / 8 (8 elements per thread).  The partials lie
+// on 16 bytes only where n_elem is a multiple of four.
 __global__ __launch_bounds__(256) void k_p4_sum_dx_parts(const float* __restrict__ part, uint16_t* __restrict__ dx,
                                                          size_t n_elem, int ksplit) {
   const size_t n8 = n_elem / 8;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += (size_t)gridDim.x * 256) {
-    f4 a = reinterpret_cast<const f4*>(part)[2 * i], b = reinterpret_cast<const f4*>(part)[2 * i + 1];
+    f4 a = reinterpret_cast<const f4u*>(part)[2 * i], b = reinterpret_cast<const f4u*>(part)[2 * i + 1];
     for (int k = 1; k < ksplit; ++k) {
-      const f4* p = reinterpret_cast<const f4*>(part + (size_t)k * n_elem);
+      const f4u* p = reinterpret_cast<const f4u*>(part + (size_t)k * n_elem);
       a += p[2 * i];
       b += p[2 * i + 1];
     }

@@ -56,6 +56,7 @@ namespace rotconv {
 namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef f4 f4u __attribute__((aligned(4)));      // four floats at any float's address
 
 // KC (template parameter): K-steps (of 4 channels) per prefetch chunk: 8 (channels padded to 32), or 1 for layers
 // with at most 4 input channels (a network's first layer: channels padded to 4, an eighth of the matrix work)
@@ -542,15 +543,16 @@ __global__ __launch_bounds__(256) void k_p4_combine(const float* __restrict__ pv
   idx[o] = dead ? (uint8_t)255 : (uint8_t)bi;
 }
 
-// Channel split: y = sum of the parts, ascending (four elements per thread, scalar tail).
+// Channel split: y = sum of the parts, ascending (four elements per thread, scalar tail).  The parts lie on 16 bytes only where
+// n_elem is a multiple of four, and y of odd rows anywhere.
 __global__ __launch_bounds__(256) void k_p4_sum_parts(const float* __restrict__ part, float* __restrict__ y,
                                                       size_t n_elem, int nparts) {
   const size_t n4 = n_elem / 4;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 256) {
-    f4 a = reinterpret_cast<const f4*>(part)[i];
+    f4 a = reinterpret_cast<const f4u*>(part)[i];
 #pragma unroll 8
-    for (int k = 1; k < nparts; ++k) a += reinterpret_cast<const f4*>(part + (size_t)k * n_elem)[i];
-    reinterpret_cast<f4*>(y)[i] = a;
+    for (int k = 1; k < nparts; ++k) a += reinterpret_cast<const f4u*>(part + (size_t)k * n_elem)[i];
+    reinterpret_cast<f4u*>(y)[i] = a;
   }
   for (size_t e = n4 * 4 + (size_t)blockIdx.x * 256 + threadIdx.x; e < n_elem; e += (size_t)gridDim.x * 256) {
     float v = part[e];
