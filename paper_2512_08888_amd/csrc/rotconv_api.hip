@@ -402,10 +402,22 @@ int rotconv_plan_routed_table(const rotconv_plan* plan, float* T) {
 
 }  // extern "C" (the fp32 implementations below have internal linkage)
 
+// Alignment that the register-resident forward needs: that of a float (and a byte) where the waves are on their own, eight
+// bytes of x for the pixel pairs of the others, vectors of the results where those kernels write them themselves (not the
+// sums, maxima and combinations of what they leave in the scratch, which go element by element).
+struct FwdAlign { size_t x, y, idx; };
+static FwdAlign fwd_align(const rotconv_plan* p, bool pooled) {
+  if (pooled && p->fwd_base) return {8, 16, 8};
+  const rotconv_plan::FwdLaunch& l = p->fwd_launch[pooled];
+  if (!l.chain) return {4, 4, 1};
+  const bool direct = l.csplit == 1 && l.out_mode == (pooled ? kOutPooled : kOutUnpooled);
+  return {8, (size_t)(direct ? 16 : 4), (size_t)(direct ? 8 : 1)};
+}
+
 // Does the unpooled forward of an fp32 plan run the register-resident kernel for these pointers?
 static bool f32_fwd_is_fast(const rotconv_plan* p, const void* x, const void* y, const void* ws) {
-  const bool odd = p->d.W & 1;       // rows whose pixel pairs the kernel does not load or store as pairs
-  return p->fast[0] && aligned(x, odd ? 4 : 8) && aligned(ws, p->fwd_csplit[0] > 1 ? 256 : 16) && aligned(y, odd ? 4 : 16);
+  const FwdAlign a = fwd_align(p, false);
+  return p->fast[0] && aligned(x, a.x) && aligned(ws, p->fwd_csplit[0] > 1 ? 256 : 16) && aligned(y, a.y);
 }
 
 // Scratch of either forward off the register-resident kernels: the products of a few images, or the rotated banks.
@@ -519,9 +531,8 @@ static int f32_orient_maxpool_bwd(const rotconv_plan* plan, const void* gpool, c
 // Does the pooled forward of an fp32 plan run the register-resident kernel for these pointers?
 static bool f32_pool_fwd_is_fast(const rotconv_plan* p, const void* x, const void* ypool, const uint8_t* idx,
                                  const void* ws) {
-  const bool odd = p->d.W & 1;
-  return !p->avg_child && p->fast[0] && aligned(x, odd ? 4 : 8) && aligned(ws, 256) && aligned(ypool, odd ? 4 : 16) &&
-         aligned(idx, odd ? 1 : 8);
+  const FwdAlign a = fwd_align(p, true);
+  return !p->avg_child && p->fast[0] && aligned(x, a.x) && aligned(ws, 256) && aligned(ypool, a.y) && aligned(idx, a.idx);
 }
 
 // Scratch the pooled forward of an fp32 plan needs for these pointers, whatever the plan's other calls need: the packed

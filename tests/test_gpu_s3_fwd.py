@@ -7,6 +7,7 @@ sqrt(6 K / 32) * 2^-24 of its value in norm; 1e-6 is four times that for the dee
 """
 import numpy as np
 import pytest
+import torch
 
 import parity_util as pu
 from paper_2512_08888_amd import binding as rc
@@ -76,3 +77,40 @@ def test_weights_that_are_not_finite_do_not_reach_through_the_padding(W, tap):
     dy, dx = tap // 3 - 1, tap % 3 - 1
     want[:, 1, max(0, -dy):9 - max(0, dy), max(0, -dx):W - max(0, dx)] = True
     assert np.array_equal(bad, want)
+
+
+UNALIGNED = [
+    (_case("wide", 2, 9, 5, 300, 7, 1301), {}),                    # a row of more than 256 pixels, no whole waves
+    (_case("narrow", 1, 40, 7, 18, 5, 1302), {}),
+    (_case("odd", 1, 40, 7, 21, 5, 1303), {}),
+    (_case("split", 1, 96, 6, 18, 5, 1304), dict(fwd_csplit=3)),
+    (_case("fold", 1, 36, 6, 22, 11, 1305, R=8, mode="steerable"), dict(fwd_base=-1)),
+    (_case("partial", 1, 24, 6, 300, 7, 1306, R=6, mode="bilinear"), dict(fwd_base=-1)),
+    (_case("cut", 1, 16, 6, 26, 6, 1307, pool_group=2), {}),
+    (_case("chain_split", 2, 96, 6, 64, 5, 1308), dict(fwd_csplit=3)),     # waves chained over the row: x at eight bytes
+]
+
+
+@pytest.mark.parametrize("cfg,opt", UNALIGNED, ids=[c.name for c, _ in UNALIGNED])
+def test_tensors_off_their_alignment_take_the_same_kernel(cfg, opt):
+    """An image out of a batch: bit for bit the result on aligned tensors (the generic kernels add up in another order)."""
+    x, w, g = synth.make_x(cfg), synth.make_w(cfg), synth.make_g(cfg)
+    lay = pu.GpuLayer(cfg, x, w, options=opt)
+    step = 2 if cfg.name == "chain_split" else 1
+
+    def run(off):
+        def at(shape, dt, v):
+            n = int(np.prod(shape))
+            return torch.full((n + off,), v, dtype=dt, device="cuda")[off:].view(shape)
+        xd, yp, idx, yu = at(x.shape, torch.float32, 0.), at(lay.P, torch.float32, np.nan), at(lay.P, torch.uint8, 254), at(lay.U, torch.float32, np.nan)
+        xd.copy_(lay.x)
+        rc.rotconv_pool_fwd(lay.plan, xd, lay.w, yp, idx)
+        rc.rotconv_fwd(lay.plan, xd, lay.w, yu)
+        return yp, idx, yu
+
+    want = run(0)
+    ref = pu.oracle_layer(cfg, x, w, g)
+    assert _rel(want[0].cpu().numpy(), ref["ypool"]) < 1e-6
+    for off in (step, 3 * step):
+        got = run(off)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and torch.equal(got[2], want[2]), off
