@@ -295,7 +295,8 @@ double rotconv_plan_conv_equivalents(const rotconv_plan* plan, int pass);
  * rotconv_workspace_bytes_unfused of scratch (with less they run "generic"). */
 const char* rotconv_plan_kernel_name(const rotconv_plan* plan, int pass);
 /* 1 if that pass (0 rotconv_pool_fwd, 1 rotconv_pool_bwd_data, 2 rotconv_pool_bwd_weight) multiplies bf16 parts of fp32
- * operands for aligned tensors (see rotconv_plan_options.bf16_parts), else 0. */
+ * operands for aligned tensors (see rotconv_plan_options.bf16_parts), else 0.  First layers ("valu_direct") and the matrix
+ * multiply + scatter family are among them. */
 int rotconv_plan_bf16_parts(const rotconv_plan* plan, int pass);
 
 #ifdef __cplusplus

@@ -538,17 +538,20 @@ void launch_gemm_bf16(const GemmArgs& a, const void* A, const void* B, void* C, 
   else if (a.transB) hipLaunchKernelGGL((k_gemm16<false, true, OUT16>), grid, dim3(NT), 0, st, A16, B16, C, a);
   else hipLaunchKernelGGL((k_gemm16<false, false, OUT16>), grid, dim3(NT), 0, st, A16, B16, C, a);
 }
+// Fp32 operands: bf16 parts where the launch is below 512 tiles of 128 x 128 and, contracting over pixels (B transposed; many
+// images and splits of few tiles), a matrix below 32.  Parts / fp32 instructions, up-convolutions of 55 random sizes, mean (most):
+// forward below 256 tiles 0.40 to 0.68 (0.85), 256 to 511 0.87 (0.96), from 512 1.09, from 1024 1.17 (1.31); input gradient 0.34 to
+// 0.80 (0.92), from 512 0.99, from 1024 1.04; weight gradient below 32 tiles 0.22 to 0.98, 32 to 128 1.04 (1.15).
+bool gemm_on_parts(const GemmArgs& a) {
+  if (a.bf16A || a.parts < 0 || (a.N + 63) / 64 > 65535) return false;
+  const long mn = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
+  return a.parts > 0 || (mn * a.batch * a.splitk < 512 && !(a.transB && mn >= 32));
+}
 void launch_gemm(const GemmArgs& a, const void* A, const void* B, void* C, hipStream_t st) {
   // the glue uses three storage combinations: all fp32, bf16 operands with an fp32 or a bf16 result
   if (a.bf16A && a.bf16B && a.bf16C) launch_gemm_bf16<true>(a, A, B, C, st);
   else if (a.bf16A && a.bf16B) launch_gemm_bf16<false>(a, A, B, C, st);
-  // Fp32 operands: bf16 parts where the launch is below 512 tiles of 128 x 128 and, contracting over pixels (B transposed; many
-  // images and splits of few tiles), a matrix below 32.  Parts / fp32 instructions, up-convolutions of 55 random sizes, mean (most):
-  // forward below 256 tiles 0.40 to 0.68 (0.85), 256 to 511 0.87 (0.96), from 512 1.09, from 1024 1.17 (1.31); input gradient 0.34 to
-  // 0.80 (0.92), from 512 0.99, from 1024 1.04; weight gradient below 32 tiles 0.22 to 0.98, 32 to 128 1.04 (1.15).
-  else if (const long mn = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
-           !a.fp32_instr && mn * a.batch * a.splitk < 512 && !(a.transB && mn >= 32))
-    launch_gemm_s3(a, static_cast<const float*>(A), static_cast<const float*>(B), static_cast<float*>(C), st);
+  else if (gemm_on_parts(a)) launch_gemm_s3(a, static_cast<const float*>(A), static_cast<const float*>(B), static_cast<float*>(C), st);
   else launch_gemm_f32(a, A, B, C, st);
 }
 

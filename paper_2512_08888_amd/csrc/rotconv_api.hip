@@ -1098,6 +1098,7 @@ double rotconv_plan_conv_equivalents(const rotconv_plan* plan, int pass) {
   if (plan->pad_child && plan->pad_use[pass]) return rotconv_plan_conv_equivalents(plan->pad_child, pass);
   const int Q = plan->host.Q, B = plan->B;
   if (plan->avg_child) return (double)plan->ng * rotconv_plan_conv_equivalents(plan->avg_child, pass);
+  if (pass == 0 && plan->direct[0] && first_fwd_layer(plan)) return plan->d.R;     // the turns are rows of one contraction
   if (plan->direct[pass]) return Q;     // one product set per first-quadrant bank, on the vector ALU
   if (plan->d.dtype == ROTCONV_BF16 && plan->native16[pass]) {
     int present = 0;      // orientations in the set: the bf16 gradient kernels multiply every quarter turn on its own
@@ -1131,7 +1132,9 @@ int rotconv_plan_bf16_parts(const rotconv_plan* plan, int pass) {
   if (!plan || pass < 0 || pass > 2) return 0;
   if (plan->avg_child) return rotconv_plan_bf16_parts(plan->avg_child, pass);
   if (plan->pad_child && plan->pad_use[pass]) return rotconv_plan_bf16_parts(plan->pad_child, pass);
-  if (plan->direct[pass] || (pass == 0 && (plan->px16 || plan->fwd_base)) || !plan->fast[pass]) return 0;
+  if (plan->direct[pass]) return pass == 0 && first_fwd_layer(plan);
+  if (!plan->fast[pass] && plan->gs) return gs_on_parts(plan, pass);
+  if ((pass == 0 && (plan->px16 || plan->fwd_base)) || !plan->fast[pass]) return 0;
   if (is_bf16(plan) && plan->native16[pass]) return 0;
   return pass == 0 ? plan->fwd_s3 : pass == 1 ? s3_bwd_data_supported(plan) : s3_bwd_weight_supported(plan);
 }

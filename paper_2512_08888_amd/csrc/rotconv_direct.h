@@ -14,6 +14,7 @@ void launch_direct_fwd(const rotconv_plan* p, const void* x, const void* w, void
                        hipStream_t st);
 
 // the same on bf16 parts: fp32 plans of at most three channels, a single bank of four quarter turns
+bool first_fwd_layer(const rotconv_plan* p);      // ... for tensors on their alignment
 bool first_fwd_supported(const rotconv_plan* p, const void* x, const void* ypool, const void* idx);
 void launch_first_fwd(const rotconv_plan* p, const float* x, const float* w, float* ypool, uint8_t* idx, hipStream_t st);
 

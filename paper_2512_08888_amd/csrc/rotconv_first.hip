@@ -239,15 +239,18 @@ __global__ __launch_bounds__(256, 2) void k_first_fwd(const float* __restrict__ 
 
 // The four quarter turns of unchanged filters in their order, rows of whole quads, tensors within a 32-bit offset, aligned
 // outputs; four channels are 36 terms, more than an instruction has.
-bool first_fwd_supported(const rotconv_plan* p, const void* x, const void* ypool, const void* idx) {
+bool first_fwd_layer(const rotconv_plan* p) {
   const rotconv_desc& d = p->d;
   if (d.dtype != ROTCONV_F32 || d.Cin > 3 || d.W % 4 || p->ng != 1 || d.R != 4 || p->host.Q != 1 || !p->base_bank) return false;
   if (p->opt.bf16_parts < 0 || p->opt.direct_ty > 0) return false;          // the vector-ALU kernel asked for
   for (int s = 0; s < 4; ++s)
     if (p->rot_of[s] != s) return false;
   const double hw4 = 4.0 * d.N * d.H * d.W;
-  return hw4 * d.Cin < 4e9 && hw4 * d.Cout < 4e9 && reinterpret_cast<uintptr_t>(x) % 4 == 0 &&
-         reinterpret_cast<uintptr_t>(ypool) % 16 == 0 && reinterpret_cast<uintptr_t>(idx) % 4 == 0;
+  return hw4 * d.Cin < 4e9 && hw4 * d.Cout < 4e9;
+}
+bool first_fwd_supported(const rotconv_plan* p, const void* x, const void* ypool, const void* idx) {
+  return first_fwd_layer(p) && reinterpret_cast<uintptr_t>(x) % 4 == 0 && reinterpret_cast<uintptr_t>(ypool) % 16 == 0 &&
+         reinterpret_cast<uintptr_t>(idx) % 4 == 0;
 }
 
 void launch_first_fwd(const rotconv_plan* p, const float* x, const float* w, float* ypool, uint8_t* idx, hipStream_t st) {

@@ -359,10 +359,23 @@ void pack(const rotconv_plan* p, const float* w, float* a, hipStream_t st) {
                      p->d.Cin, p->kk, p->d.dtype == ROTCONV_BF16 ? 1 : 0);
 }
 
-GemmArgs gemm_args(const rotconv_plan* p) {
+// The product of a pass (0 forward, 1 input gradient, 2 weight gradient) for nb images.
+GemmArgs gemm_args(const rotconv_plan* p, int pass, int nb) {
+  const int M = p->host.Q * p->d.Cout * p->kk, Pi = p->d.H * p->d.W, Cin = p->d.Cin;
+  const size_t products = (size_t)M * Pi, image = (size_t)Cin * Pi;
   GemmArgs a{};
-  a.batch = 1; a.splitk = 1;
-  a.fp32_instr = p->opt.bf16_parts < 0;
+  a.batch = nb; a.splitk = 1;
+  a.parts = p->opt.bf16_parts;
+  if (pass == 0) {               // P[m][pixel] = sum_ci A[m][ci] X[ci][pixel]
+    a.M = M; a.N = Pi; a.K = Cin; a.lda = Cin; a.ldb = Pi; a.ldc = Pi;
+    a.strideB = image; a.strideC = products;
+  } else if (pass == 1) {        // dX[ci][pixel] = sum_m A[m][ci] D[m][pixel]
+    a.M = Cin; a.N = Pi; a.K = M; a.transA = 1; a.lda = Cin; a.ldb = Pi; a.ldc = Pi;
+    a.strideB = products; a.strideC = image;
+  } else {                       // dF[m][ci] = sum_pixel D[m][pixel] X[ci][pixel]
+    a.M = M; a.N = Cin; a.K = Pi; a.transB = 1; a.lda = Pi; a.ldb = Pi; a.ldc = Cin;
+    a.splitk = bwdw_splitk(p, chunk_images(p)); a.strideA = products; a.strideB = image; a.strideC = (size_t)M * Cin;
+  }
   return a;
 }
 
@@ -375,14 +388,11 @@ void forward(const rotconv_plan* p, bool fused, const float* x, const float* w, 
   float* A = reinterpret_cast<float*>(c + L.a);
   float* P = reinterpret_cast<float*>(c + L.pd);
   pack(p, w, A, st);
-  const int M = g.Q * g.Cout * g.kk, Pi = g.H * g.W, Po = g.Ho * g.Wo;
+  const int Pi = g.H * g.W, Po = g.Ho * g.Wo;
   const int nbmax = chunk_images(p);
   for (int n0 = 0; n0 < g.N; n0 += nbmax) {
     const int nb = std::min(nbmax, g.N - n0);
-    GemmArgs a = gemm_args(p);
-    a.M = M; a.N = Pi; a.K = g.Cin; a.lda = g.Cin; a.ldb = Pi; a.ldc = Pi;
-    a.batch = nb; a.strideA = 0; a.strideB = (size_t)g.Cin * Pi; a.strideC = (size_t)M * Pi;
-    launch_gemm(a, A, x + (size_t)n0 * g.Cin * Pi, P, st);
+    launch_gemm(gemm_args(p, 0, nb), A, x + (size_t)n0 * g.Cin * Pi, P, st);
     // one pool group (or none), the tiles' products within the LDS of a workgroup
     const int ext = (TS - 1) * g.stride + g.k, tx = (g.Wo + TS - 1) / TS;
     const size_t lds = ((size_t)2 * TP * ext * ext + 4 * g.kk) * sizeof(float);
@@ -418,15 +428,12 @@ void backward_data(const rotconv_plan* p, bool routed, const float* gsrc, const 
   float* A = reinterpret_cast<float*>(c + L.a);
   float* D = reinterpret_cast<float*>(c + L.pd);
   pack(p, w, A, st);
-  const int M = g.Q * g.Cout * g.kk, Pi = g.H * g.W;
+  const int Pi = g.H * g.W;
   const int nbmax = chunk_images(p);
   for (int n0 = 0; n0 < g.N; n0 += nbmax) {
     const int nb = std::min(nbmax, g.N - n0);
     route(p, g, routed, gsrc, idx, D, n0, nb, st);
-    GemmArgs a = gemm_args(p);             // dX[ci][pixel] = sum_m A[m][ci] D[m][pixel]
-    a.M = g.Cin; a.N = Pi; a.K = M; a.transA = 1; a.lda = g.Cin; a.ldb = Pi; a.ldc = Pi;
-    a.batch = nb; a.strideA = 0; a.strideB = (size_t)M * Pi; a.strideC = (size_t)g.Cin * Pi;
-    launch_gemm(a, A, D, dx + (size_t)n0 * g.Cin * Pi, st);
+    launch_gemm(gemm_args(p, 1, nb), A, D, dx + (size_t)n0 * g.Cin * Pi, st);
   }
 }
 
@@ -440,17 +447,14 @@ void backward_weight(const rotconv_plan* p, bool routed, const float* x, const f
   float* dF = reinterpret_cast<float*>(c + L.dF);
   const int M = g.Q * g.Cout * g.kk, Pi = g.H * g.W;
   const int nbmax = chunk_images(p);
-  const int sk = bwdw_splitk(p, nbmax);
   const size_t nF = (size_t)M * g.Cin;
   for (int n0 = 0; n0 < g.N; n0 += nbmax) {
     const int nb = std::min(nbmax, g.N - n0);
     route(p, g, routed, gsrc, idx, D, n0, nb, st);
-    GemmArgs a = gemm_args(p);             // dF[m][ci] = sum_pixel D[m][pixel] X[ci][pixel]
-    a.M = M; a.N = g.Cin; a.K = Pi; a.transB = 1; a.lda = Pi; a.ldb = Pi; a.ldc = g.Cin;
-    a.batch = nb; a.splitk = sk; a.strideA = (size_t)M * Pi; a.strideB = (size_t)g.Cin * Pi; a.strideC = nF;
+    const GemmArgs a = gemm_args(p, 2, nb);
     launch_gemm(a, D, x + (size_t)n0 * g.Cin * Pi, part, st);
-    if (nbmax >= g.N) launch_sum_parts(part, dF, nF, nb * sk, nF, st);
-    else hipLaunchKernelGGL(k_gs_sum_acc, dim3((unsigned)((nF + 255) / 256)), dim3(256), 0, st, part, dF, nF, nb * sk,
+    if (nbmax >= g.N) launch_sum_parts(part, dF, nF, nb * a.splitk, nF, st);
+    else hipLaunchKernelGGL(k_gs_sum_acc, dim3((unsigned)((nF + 255) / 256)), dim3(256), 0, st, part, dF, nF, nb * a.splitk,
                             n0 == 0 ? 1 : 0);
   }
   const unsigned rb = (p->B * g.Cout * g.Cin + 255) / 256;
@@ -479,6 +483,12 @@ size_t gs_chunk_budget(const rotconv_plan* p) {
 }
 
 size_t gs_ws_bytes(const rotconv_plan* p) { return gs_layout(p).total; }
+
+// (the last images may be fewer than the others at a time)
+bool gs_on_parts(const rotconv_plan* p, int pass) {
+  const int nb = std::min(chunk_images(p), p->d.N), rest = p->d.N % nb;
+  return gemm_on_parts(gemm_args(p, pass, nb)) || (rest && gemm_on_parts(gemm_args(p, pass, rest)));
+}
 
 void launch_gs_fwd(const rotconv_plan* p, const float* x, const float* w, float* y, void* ws, hipStream_t st) {
   forward(p, false, x, w, y, nullptr, ws, st);

@@ -32,7 +32,7 @@ def test_forward(cfg, relu):
     x, w, g = synth.make_x(cfg), synth.make_w(cfg), synth.make_g(cfg)
     ref = pu.oracle_layer(cfg, x, w, g)
     lay = pu.GpuLayer(cfg, x, w, relu=bool(relu))
-    assert lay.plan.kernel_name(0) == "valu_direct"
+    assert lay.plan.kernel_name(0) == "valu_direct" and lay.plan.bf16_parts(0)
     yp, idx = lay.pool_fwd()
     dead = ref["ypool"] <= 0
     if relu:
@@ -68,3 +68,22 @@ def test_values_beyond_the_parts(where):
         window[:, :, 1:4, 69:72] = True
         assert np.isfinite(yp[~window]).all() and not np.isfinite(yp[window]).any()
         assert np.isposinf(yp[window]).any()
+
+
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("at", [(0, 0), (2, 5), (5, 71)])
+def test_nan(at, relu):
+    """A NaN pixel makes NaN what it reaches in the instruction's sums, a NaN weight its filter (which is summed in fp32)."""
+    cfg = L("nan", N=1, Cin=3, H=6, W=72, Cout=6, seed=2110, x_dist="normal")
+    x, w = synth.make_x(cfg), synth.make_w(cfg)
+    x[0, 1, at[0], at[1]] = np.nan
+    lay = pu.GpuLayer(cfg, x, w, relu=relu)
+    assert lay.plan.bf16_parts(0)
+    yp, _ = lay.pool_fwd()
+    window = np.zeros(yp.shape, bool)
+    window[:, :, max(0, at[0] - 1):at[0] + 2, max(0, at[1] - 1):at[1] + 2] = True
+    assert np.isnan(yp[window]).all() and np.isfinite(yp[~window]).all()
+    x[0, 1, at[0], at[1]] = 0
+    w[0, 4, 1, 1, 1] = np.nan
+    yp, _ = pu.GpuLayer(cfg, x, w, relu=relu).pool_fwd()
+    assert np.isnan(yp[:, 4]).all() and np.isfinite(np.delete(yp, 4, 1)).all()

@@ -78,7 +78,7 @@ def test_multiply_and_scatter(cfg, chunk):
     x, w, g = synth.make_x(cfg), synth.make_w(cfg), synth.make_g(cfg)
     ref = pu.oracle_layer(cfg, x, w, g)
     lay = pu.GpuLayer(cfg, x, w, options=dict(gs=1, gs_chunk_mb=chunk))
-    assert lay.plan.kernel_name(0) == "mfma_gemm_scatter"
+    assert lay.plan.kernel_name(0) == "mfma_gemm_scatter" and lay.plan.bf16_parts(1)
     yp, idx = lay.pool_fwd()
     assert _rel(yp, ref["ypool"]) < BAR
     pu.check_idx(idx, ref["y"], ref["abs_terms"], cfg.G, cfg.name)

@@ -21,9 +21,18 @@ def test_selection():
     # other turns: the forward on base products and the table gradients stay with fp32 instructions
     assert parts(4, 128, 128, 128, 128, R=16, mode="bilinear") == [False] * 3
     assert parts(4, 128, 128, 128, 128, R=16, mode="bilinear", options=dict(fwd_base=-1)) == [True, False, False]
-    assert parts(2, 3, 512, 512, 64)[::2] == [False, False]                             # a first layer
+    # a first layer: its forward alone, unless the vector ALU is asked for, by form, by band or by what it alone takes
+    assert parts(2, 3, 512, 512, 64)[::2] == [True, False]
+    for other in (dict(options=dict(bf16_parts=-1)), dict(options=dict(direct_ty=1)), dict(dtype=rc.BF16), dict(R=16, mode="bilinear")):
+        assert parts(2, 3, 512, 512, 64, **other)[::2] == [False, False], other
+    assert not parts(2, 3, 512, 510, 64)[0] and not parts(2, 4, 512, 512, 64)[0]
     assert parts(8, 64, 256, 256, 64, dtype=rc.BF16) == [False] * 3
-    assert parts(2, 32, 96, 96, 32, k=5, pad=2) == [False] * 3
+    # matrix multiply + scatter: products of fewer than 512 tiles of 128 x 128 (forward 7 x 72 an image, input gradient 72,
+    # weight gradient 7 in 36 parts)
+    assert parts(2, 32, 96, 96, 32, k=5, pad=2) == [False, True, True]
+    assert parts(1, 32, 96, 96, 32, k=5, pad=2) == [True] * 3
+    assert parts(1, 32, 96, 96, 32, k=5, pad=2, options=dict(bf16_parts=-1)) == [False] * 3
+    assert parts(2, 32, 96, 96, 32, k=5, pad=2, options=dict(bf16_parts=1)) == [True] * 3
     assert parts(3, 40, 101, 75, 24, R=8, mode="steerable", pool_group=4)[0]            # odd rows: the padded plan's
     assert parts(8, 64, 256, 256, 64, pool_op="avg") == [True] * 3                      # the averaged bank's plan
     # nor do few filters or single rows take it where the partial sums are most of the work
