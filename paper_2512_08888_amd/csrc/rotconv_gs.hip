@@ -5,6 +5,7 @@
 //   forward   P[(q,co,u)][pixel] = sum_ci F_q[co,ci,u] X[ci,pixel]        one GEMM per image, M = Q Cout k^2
 //             Y_r[co,yo,xo] = sum_u P[(q,co,u)][yo s + i - pad, xo s + j - pad],  (i,j) = where quarter turn s_r puts
 //             base tap u (Eq. 8), then max / arg-max over the pool group (Eq. 10)      -- the scatter, as a gather
+//             (P of odd u is stored with its sign turned, see tap_sign)
 //   gradients D[(q,co,u)][pixel] = sum_s Delta_(q,s)[co, (y + pad - i)/s, (x + pad - j)/s]   (Eq. 12 routed, or a dense dy)
 //             dX = F^T D (one GEMM per image, Eq. 13/15);  dF = D X^T (one GEMM per image, split along the pixels,
 //             parts added in order, Eq. 14/16), then the transposed first-quadrant expansion.
@@ -39,17 +40,25 @@ GsGeom gs_geom(const rotconv_plan* p) {
 
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
+// In the forward the products of every other tap are formed with their sign turned and subtracted where they are placed.  The
+// matrix instruction on bf16 parts cuts its sums towards minus infinity, an offset of one sign in each product that would
+// grow with the k^2 taps while their sum grows with k: up to 32 channels a product is one such sum (15 x 15 taps, 8
+// channels: offset 1.5e-7 of the norm and error 2.96e-7 without the signs, no offset and 2.54e-7 with them, 2.57e-7 on the
+// fp32 instruction).
+__device__ __forceinline__ constexpr float tap_sign(int u) { return u % 2 ? -1.f : 1.f; }
+
 // base bank(s) -> the GEMM operand [(q, co, u)][ci] (first-quadrant banks, Sec. III-D / Eq. 17); one thread per
-// (q, co, ci), every gridDim.y-th of its k^2 taps.
+// (q, co, ci), every gridDim.y-th of its k^2 taps.  turned: with the signs of the forward
 __global__ __launch_bounds__(256) void k_gs_pack(const float* __restrict__ w, float* __restrict__ a, ExpandTables tab, int Q,
-                                                 int Cout, int Cin, int kk, int round16) {
+                                                 int Cout, int Cin, int kk, int round16, int turned) {
   const int total = Q * Cout * Cin;
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= total) return;
   const int ci = e % Cin, co = (e / Cin) % Cout, q = e / (Cin * Cout);
   const float* src = w + ((size_t)co * Cin + ci) * kk;
   for (int u = blockIdx.y; u < kk; u += gridDim.y)
-    a[((size_t)(q * Cout + co) * kk + u) * Cin + ci] = expand_tap(src, (size_t)Cout * Cin * kk, kk, q, u, true, tab, round16);
+    a[((size_t)(q * Cout + co) * kk + u) * Cin + ci] =
+        (turned ? tap_sign(u) : 1.f) * expand_tap(src, (size_t)Cout * Cin * kk, kk, q, u, true, tab, round16);
 }
 
 constexpr int kMaxKK = 225;      // k <= 15
@@ -131,11 +140,12 @@ __global__ __launch_bounds__(256) void k_gs_place_tile(const float* __restrict__
 #pragma unroll
       for (int t = 0; t < TP; ++t) {                     // a tap beyond the last one reads zeros
         const int u = min(u0 + t, g.kk - 1);
+        const float sign = tap_sign(u0 + t);
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
           const float* src = cur + t * ext2 + off[s * g.kk + u] + lane_at;
 #pragma unroll
-          for (int m = 0; m < 4; ++m) acc[s][m] += src[m * row8];
+          for (int m = 0; m < 4; ++m) acc[s][m] = fmaf(sign, src[m * row8], acc[s][m]);
         }
       }
     }
@@ -207,7 +217,7 @@ __global__ __launch_bounds__(256) void k_gs_place(const float* __restrict__ P, c
         const int yi = oy + ty[u], xi = ox + tx[u];
         const bool ok = (unsigned)yi < (unsigned)g.H && (unsigned)xi < (unsigned)g.W;
         const float v = Pq[(size_t)u * Pi + (ok ? yi * g.W + xi : 0)];
-        acc += ok ? v : 0.f;
+        acc = fmaf(tap_sign(u), ok ? v : 0.f, acc);
       }
       if (FUSED) {
         if (best_r < 0 || acc > best) { best = acc; best_r = r; }
@@ -352,11 +362,11 @@ GsLayout gs_layout(const rotconv_plan* p) {
 // the taps of a small kernel's threads over blockIdx.y, up to a few hundred workgroups
 unsigned tap_groups(unsigned blocks, int kk) { return std::max(1u, std::min((unsigned)kk, 512u / blocks)); }
 
-void pack(const rotconv_plan* p, const float* w, float* a, hipStream_t st) {
+void pack(const rotconv_plan* p, const float* w, float* a, bool turned, hipStream_t st) {
   const int total = p->host.Q * p->d.Cout * p->d.Cin;
   const unsigned nb = (total + 255) / 256;
   hipLaunchKernelGGL(k_gs_pack, dim3(nb, tap_groups(nb, p->kk)), dim3(256), 0, st, w, a, expand_tables(p), p->host.Q, p->d.Cout,
-                     p->d.Cin, p->kk, p->d.dtype == ROTCONV_BF16 ? 1 : 0);
+                     p->d.Cin, p->kk, p->d.dtype == ROTCONV_BF16 ? 1 : 0, turned ? 1 : 0);
 }
 
 // The product of a pass (0 forward, 1 input gradient, 2 weight gradient) for nb images.
@@ -387,7 +397,7 @@ void forward(const rotconv_plan* p, bool fused, const float* x, const float* w, 
   char* c = static_cast<char*>(ws);
   float* A = reinterpret_cast<float*>(c + L.a);
   float* P = reinterpret_cast<float*>(c + L.pd);
-  pack(p, w, A, st);
+  pack(p, w, A, true, st);
   const int Pi = g.H * g.W, Po = g.Ho * g.Wo;
   const int nbmax = chunk_images(p);
   for (int n0 = 0; n0 < g.N; n0 += nbmax) {
@@ -427,7 +437,7 @@ void backward_data(const rotconv_plan* p, bool routed, const float* gsrc, const 
   char* c = static_cast<char*>(ws);
   float* A = reinterpret_cast<float*>(c + L.a);
   float* D = reinterpret_cast<float*>(c + L.pd);
-  pack(p, w, A, st);
+  pack(p, w, A, false, st);
   const int Pi = g.H * g.W;
   const int nbmax = chunk_images(p);
   for (int n0 = 0; n0 < g.N; n0 += nbmax) {

@@ -11,6 +11,7 @@ import pytest
 import torch
 
 import parity_util as pu
+from oracle import rotconv_oracle as orc
 from oracle import unet_oracle as uo
 from paper_2512_08888_amd import binding as rc
 from paper_2512_08888_amd import synth
@@ -86,3 +87,22 @@ def test_multiply_and_scatter(cfg, chunk):
     idx = ref["idx"].astype(np.uint8)
     assert _rel(lay.pool_bwd_data(g, idx), ref["dx"]) < BAR
     assert _rel(lay.pool_bwd_weight(g, idx), ref["dw"]) < BAR
+
+
+@pytest.mark.parametrize("k,Cin", [(2, 8), (5, 4), (5, 32), (9, 16), (15, 8)])
+def test_forward_has_no_offset(k, Cin):
+    """A product of up to 32 channels is one sum, which the matrix instruction cuts: half a unit of its last place, one sign for
+    all, would come to k * 1e-8 of the result's norm over the k^2 taps.  Every other tap has the other sign, so one product's
+    offset may stay: 3e-8 / k; bar 1.5e-8.  Then the sums over the taps, the same in both forms, are the larger part of the
+    error, which is at most that of the fp32 instruction (2 % for the spread of the two)."""
+    cfg = L("g_off", N=1, Cin=Cin, H=40, W=40, Cout=8, R=4, k=k, pad=k // 2, x_dist="absnormal", seed=1420 + k)
+    x, w = synth.make_x(cfg), synth.make_w(cfg)
+    y = orc.rotconv_fwd(x, orc.expand_bank(w, cfg.R, None, cfg.mode), 1, cfg.pad)
+    err = []
+    for form in (0, -1):
+        lay = pu.GpuLayer(cfg, x, w, options=dict(gs=1, bf16_parts=form))
+        assert lay.plan.bf16_parts(0) == (form == 0)
+        d = lay.fwd().cpu().numpy().astype(np.float64) - y.reshape(lay.U)
+        err.append(np.linalg.norm(d))
+        assert abs(d.mean()) < 1.5e-8 * np.sqrt(np.mean(y ** 2))
+    assert err[0] <= 1.02 * err[1], err
