@@ -107,9 +107,9 @@ size_t fwd_extra_bytes(const rotconv_plan* p) {
   return 0;
 }
 
-// One unpooled part per channel split.
-size_t fwd_part_bytes(const rotconv_plan* p, int cs) {
-  return cs > 1 ? align256((size_t)cs * p->d.N * p->d.Cout * p->d.R * p->d.H * p->d.W * 4) : 0;
+// One unpooled part per channel split (of all filters, or of some).
+size_t fwd_part_bytes(const rotconv_plan* p, int cs, int filters = 0) {
+  return cs > 1 ? align256((size_t)cs * p->d.N * (filters ? filters : p->d.Cout) * p->d.R * p->d.H * p->d.W * 4) : 0;
 }
 
 size_t fwd_fast_ws_bytes(const rotconv_plan* p) {
@@ -124,14 +124,15 @@ size_t fwd_fast_least_bytes(const rotconv_plan* p) {
   const int cs = p->fwd_csplit[1], nq = cs == 1 && p4_fwd_pool_mode(p) == kOutPartial ? p4_fwd_fold(p) : 1;
   const size_t block = p->fwd_base ? 0 : p4_fwd_least_pack_bytes(p, nq, cs);
   const size_t bf = p->d.dtype == ROTCONV_BF16 ? p4_fwd_bf16_pack_bytes(p) : 0;
-  if (cs > 1) return align256(std::max(block, bf)) + std::max(fwd_extra_bytes(p), fwd_part_bytes(p, cs));
+  if (cs > 1) return align256(std::max(block, bf)) + fwd_part_bytes(p, cs, p->fwd_sliced ? std::min(16, p->d.Cout) : 0);
   return align256(std::max({p4_fwd_weights(p) * sizeof(float), block, bf})) + fwd_extra_bytes(p);
 }
 
-// The fp32 forward's form and channel splits.  Of the splits whose parts rotconv_pool_fwd_static does not hold, only those
-// are taken that the chained waves would make too, where the whole contraction is one it holds: the waves on their own split
-// more (4x994 -> 69, 19x70, eight turns: eight parts of 12 MB, modelled 206 us instead of 291), and layers that the call
-// takes stay taken.  A layer of one filter block, whose parts cannot be packed in slices, keeps
+// The fp32 forward's form and channel splits.  The waves on their own split more layers than the chained ones (4x994 -> 69, 19x70,
+// eight turns: eight parts of 12 MB, modelled 206 us instead of 291), which must not cost the call without a workspace a
+// layer that it took: where chained waves would not split and the whole contraction is one that rotconv_pool_fwd_static
+// holds, it takes the parts in slices of filter blocks, bit for bit the same, or, where one block's do not fit, the contraction
+// stays whole for every call.  A layer of one filter block, whose parts cannot be packed in slices, keeps
 // the fp32 instructions where rotconv_pool_fwd_static holds its banks at four bytes a weight but not at six.
 void choose_fwd(rotconv_plan* p) {
   // fp32 copies in front of a call's scratch: widened ones of bf16 tensors; padded ones of odd rows, on chained waves
@@ -145,9 +146,16 @@ void choose_fwd(rotconv_plan* p) {
     p->fwd_csplit[1] = p4_fwd_csplit(p, true);
     const auto fits = [&](double front) { return front + fwd_fast_least_bytes(p) <= (double)ROTCONV_STATIC_SCRATCH_BYTES; };
     const int split = p->fwd_csplit[1];
+    p->fwd_sliced = 0;
     if (split > 1 && s3 && p->opt.fwd_csplit == 0 && !fits(widened) && p4_fwd_chain_whole(p)) {
       p->fwd_csplit[1] = 1;
-      if (!fits(widened + padded)) p->fwd_csplit[1] = split;
+      const bool whole = fits(widened + padded);
+      p->fwd_csplit[1] = split;
+      p->fwd_sliced = whole;
+      if (whole && !fits(widened)) {
+        p->fwd_csplit[1] = 1;
+        p->fwd_sliced = 0;
+      }
     }
     return fits(0.);
   };
@@ -579,8 +587,17 @@ static int f32_rotconv_pool_fwd(const rotconv_plan* plan, const void* x, const v
     const int cs = p->fwd_csplit[1];
     if (cs > 1) {
       float* part = reinterpret_cast<float*>(front);
-      run(kOutUnpooled, fwd_part_bytes(p, cs), part, nullptr, 1, cs);
-      launch_p4_sum_pool(p, part, cs, yf, idx, st);
+      const size_t block = p4_fwd_least_pack_bytes(p, 1, cs);
+      const int blocks = (p->d.Cout + 15) / 16;
+      int per = blocks;                        // filter blocks at a time
+      if (p->fwd_sliced)
+        while (per > 1 && fwd_part_bytes(p, cs, std::min(p->d.Cout, 16 * per)) + block > ws_bytes) --per;
+      for (int b = 0; b < blocks; b += per) {
+        const int end = std::min(blocks, b + per), nc = std::min(p->d.Cout, 16 * end) - 16 * b;
+        const size_t used = fwd_part_bytes(p, cs, nc);
+        launch_p4_fwd_parts(p, b, end, xf, wf, reinterpret_cast<float*>(front + used), ws_bytes - used, part, st, cs);
+        launch_p4_sum_pool(p, part, cs, yf, idx, 16 * b, nc, st);
+      }
       return finish();
     }
     if (p->fwd_base) {     // the pool group spans all banks: products of the base bank, banks combined in the kernel

@@ -101,6 +101,7 @@ struct rotconv_plan {
   int px16 = 0;                 // bf16 pooled forward: the kernel with a lane per pixel column (filters on M)
   int fwd_s3 = 0;               // fast fp32 forward: products of the operands' bf16 parts (else fp32 instructions)
   int fwd_csplit[2] = {1, 1};   // fast forward: channel splits for the unpooled / the pooled output (1: none)
+  int fwd_sliced = 0;           // the pooled split goes through small scratch in slices of filter blocks
   // ... and the launches of the two, modelled once: which kernel, its rows per band and waves per workgroup
   struct FwdLaunch { int out_mode = -1, csplit = 0, nq = 0, chain = 0, ty = 0, nw = 0; } fwd_launch[2];
   // Average pooling (Eq. 9 / Eq. 11): the fused calls run one ordinary convolution (this R = 1 plan with

@@ -26,6 +26,7 @@ struct P4Geom {
   double cost;   // modelled time of the launch, 0.1 us (host side only)
   long rows;     // the row steps behind it: four for a wave alone on its SIMD, eight for two that share one
   int cb0;       // first filter block of this launch
+  int out_c0, out_c;   // unpooled: the first filter of the output tensor, and how many it has
   int raw_w;     // the weight argument is the caller's w[Cout][Cin][9] itself (see p4_fwd_raw_weights)
   int seg_xorg[4];  // first product column of a segment's wave chain
   int seg_lo[4], seg_hi[4];  // output pixels [lo, hi) the segment stores (multiples of 8, or W)
@@ -36,7 +37,7 @@ constexpr int kS3FwdChunk = 9 * 3 * 256;     // 4-byte words of a 32-channel chu
 constexpr int kS3FwdResident = 5;            // chunks of a filter block that stay in LDS; more are streamed
 struct S3FwdGeom {
   int N, Cin, CinPad, H, W, Cout, CB, R, Q, ng, out_mode, relu, nq;
-  int csplit, cper, cb0, raw_w;  // as in P4Geom
+  int csplit, cper, cb0, out_c0, out_c, raw_w;  // as in P4Geom
   int stream;    // filter blocks streamed through LDS
   int all_turns; // every bank has its four quarter turns
   int Wv;        // columns of a row on the line of bands: the pixels and one or two empty ones
@@ -65,8 +66,9 @@ int p4_fwd_csplit(const rotconv_plan* p, bool pooled);
 bool p4_fwd_chain_whole(const rotconv_plan* p);
 void p4_fwd_choose_launches(rotconv_plan* p);   // fills fwd_launch, after the channel splits
 void launch_p4_sum_parts(const rotconv_plan* p, const float* part, int nparts, float* y, hipStream_t st);
-void launch_p4_sum_pool(const rotconv_plan* p, const float* part, int nparts, float* ypool, uint8_t* idx,
-                        hipStream_t st);   // applies the plan's fused activation
+// of filters [c0, c0 + nc), which the parts hold; applies the plan's fused activation
+void launch_p4_sum_pool(const rotconv_plan* p, const float* part, int nparts, float* ypool, uint8_t* idx, int c0, int nc,
+                        hipStream_t st);
 size_t p4_fwd_pack_floats(const rotconv_plan* p);
 int p4_fwd_pool_mode(const rotconv_plan* p);
 int p4_fwd_fold(const rotconv_plan* p);   // banks a wave can fold into its columns for the pooled forward (1: none)
@@ -81,6 +83,9 @@ bool p4_fwd_raw_weights(const rotconv_plan* p, int nq = 1, int csplit = 1);
 size_t p4_fwd_least_pack_bytes(const rotconv_plan* p, int nq, int csplit);
 void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const float* w, float* pack, size_t pack_bytes,
                    float* out_val, uint8_t* out_idx, hipStream_t st, int nq = 1, int csplit = 1);
+// Unpooled channel parts of the filters of blocks [b0, b1) alone, bit for bit as in the layer's: out_val holds no others.
+void launch_p4_fwd_parts(const rotconv_plan* p, int b0, int b1, const float* x, const float* w, float* pack, size_t pack_bytes,
+                         float* out_val, hipStream_t st, int csplit);
 void launch_p4_combine(const rotconv_plan* p, const float* pv, const uint8_t* pi, float* ypool, uint8_t* idx,
                        hipStream_t st);   // applies the plan's fused activation
 

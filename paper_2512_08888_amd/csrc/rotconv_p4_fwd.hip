@@ -431,7 +431,7 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd(const float* __restri
 #pragma unroll
         for (int j = 0; j < 8; ++j) place(s, j, yfin[j]);
         if (fin && rot[s] >= 0) {
-          float* o = out_val + ((((size_t)sp * g.N + n) * g.Cout + co) * g.R + rot[s]) * HW + (size_t)y * g.W + px0;
+          float* o = out_val + ((((size_t)sp * g.N + n) * g.out_c + co - g.out_c0) * g.R + rot[s]) * HW + (size_t)y * g.W + px0;
           if (FASTW) {
             reinterpret_cast<f4*>(o)[0] = f4{yfin[0], yfin[1], yfin[2], yfin[3]};
             reinterpret_cast<f4*>(o)[1] = f4{yfin[4], yfin[5], yfin[6], yfin[7]};
@@ -562,11 +562,11 @@ __global__ __launch_bounds__(256) void k_p4_sum_parts(const float* __restrict__ 
 }
 
 // Channel split, pooled: every orientation's sum over the parts (ascending), then max / arg-max over the pool
-// group (first maximum wins) and the fused activation.  One thread per pooled element.
+// group (first maximum wins) and the fused activation.  One thread per pooled element of the C filters from c0 on.
 __global__ __launch_bounds__(256) void k_p4_sum_pool(const float* __restrict__ part, float* __restrict__ ypool,
-                                                     uint8_t* __restrict__ idx, size_t n_elem, int nparts, int NC,
-                                                     int R, int ng, int HW, int relu) {
-  const size_t total = (size_t)NC * ng * HW;       // NC = N * Cout
+                                                     uint8_t* __restrict__ idx, size_t n_elem, int nparts, int N, int C,
+                                                     int c0, int Cout, int R, int ng, int HW, int relu) {
+  const size_t total = (size_t)N * C * ng * HW;
   const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (e >= total) return;
   const int px = (int)(e % HW);
@@ -581,9 +581,10 @@ __global__ __launch_bounds__(256) void k_p4_sum_pool(const float* __restrict__ p
     for (int k = 1; k < nparts; ++k) v += yb[(size_t)k * n_elem + (size_t)r * HW];
     if (bi < 0 || v > best) { best = v; bi = r; }
   }
+  const size_t o = e + ((size_t)((uint32_t)nc / (uint32_t)C) * (Cout - C) + c0) * ng * HW;
   const bool dead = relu && best <= 0.f;
-  ypool[e] = dead ? 0.f : best;
-  idx[e] = dead ? (uint8_t)255 : (uint8_t)bi;
+  ypool[o] = dead ? 0.f : best;
+  idx[o] = dead ? (uint8_t)255 : (uint8_t)bi;
 }
 
 // base bank(s) -> Q first-quadrant banks in the LDS image layout: [Q][CB][CinPad][9][16] fp32, or
@@ -841,7 +842,7 @@ int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, 
     base.csplit = (nchunk + base.cper - 1) / base.cper;
   }
   base.N = d.N; base.Cin = d.Cin; base.CinPad = cin_pad_f32(d.Cin); base.H = d.H; base.W = d.W;
-  base.Cout = d.Cout; base.CB = (d.Cout + 15) / 16; base.R = d.R; base.Q = p->host.Q; base.ng = p->ng;
+  base.Cout = d.Cout; base.out_c0 = 0; base.out_c = d.Cout; base.CB = (d.Cout + 15) / 16; base.R = d.R; base.Q = p->host.Q; base.ng = p->ng;
   base.out_mode = out_mode;
   base.s3 = p->fwd_s3;
   base.relu = out_mode == kOutPooled && d.activation == ROTCONV_ACT_RELU;
@@ -949,8 +950,10 @@ bool p4_fwd_raw_weights(const rotconv_plan* p, int nq, int csplit) {
   return p->d.dtype == ROTCONV_F32 && p->base_bank && nq == 1 && !needs_stream(p, csplit);
 }
 
-void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const float* w, float* pack, size_t pack_bytes,
-                   float* out_val, uint8_t* out_idx, hipStream_t st, int nq, int csplit) {
+namespace {
+// The blocks [b0, b1) of sixteen filters; out_val holds the filters of these only.
+void launch_blocks(const rotconv_plan* p, int b0, int b1, int out_mode, const float* x, const float* w, float* pack,
+                   size_t pack_bytes, float* out_val, uint8_t* out_idx, hipStream_t st, int nq, int csplit) {
   const rotconv_plan::FwdLaunch* l = nullptr;
   for (const auto& c : p->fwd_launch)
     if (c.out_mode == out_mode && c.csplit == csplit && c.nq == nq) l = &c;
@@ -959,11 +962,12 @@ void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const fl
   const int ng = chain ? p4_fwd_geoms(p, out_mode, gs, 4, csplit) : 0;
   const bool stream = needs_stream(p, csplit);
   const int raw = p4_fwd_raw_weights(p, nq, csplit) ? 1 : 0;
-  const int blocks = fwd_blocks(p, nq), CinPad = cin_pad_f32(p->d.Cin);
-  const size_t fit = raw ? blocks : pack_bytes / (block_words(p, nq) * sizeof(float));
-  const int slice = (int)std::max<size_t>(1, std::min<size_t>(blocks, fit));
-  for (int cb0 = 0; cb0 < blocks; cb0 += slice) {
-    const int ncb = std::min(slice, blocks - cb0);
+  const int CinPad = cin_pad_f32(p->d.Cin);
+  const int out_c0 = b0 * 16, out_c = std::min(p->d.Cout, b1 * 16) - out_c0;      // (unpooled, banks not folded)
+  const size_t fit = raw ? b1 - b0 : pack_bytes / (block_words(p, nq) * sizeof(float));
+  const int slice = (int)std::max<size_t>(1, std::min<size_t>(b1 - b0, fit));
+  for (int cb0 = b0; cb0 < b1; cb0 += slice) {
+    const int ncb = std::min(slice, b1 - cb0);
     if (!raw) {
       const int total = (nq > 1 ? 1 : p->host.Q) * ncb * CinPad * (s3 ? 8 : 16);
       auto kern = s3 ? k_p4_pack_fwd<true> : k_p4_pack_fwd<false>;
@@ -977,6 +981,8 @@ void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const fl
       g.units = g.units / g.CB * ncb;
       g.CB = ncb;
       g.cb0 = cb0;
+      g.out_c0 = out_c0;
+      g.out_c = out_c;
       launch_s3_fwd(g, x, wt, p->dev.rot_of, out_val, out_idx, st);
     }
     for (int i = 0; i < ng; ++i) {
@@ -985,6 +991,8 @@ void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const fl
       g.units = g.units / g.CB * ncb;
       g.CB = ncb;
       g.cb0 = cb0;
+      g.out_c0 = out_c0;
+      g.out_c = out_c;
       const bool fastw = (p->d.W & 7) == 0 && g.inside;   // no lane reaches beyond the row: no masks, vector stores
       switch (g.nwx) {
         case 1: launch_t<1, 8>(g, fastw, stream, x, wt, p->dev.rot_of, out_val, out_idx, st); break;
@@ -996,19 +1004,31 @@ void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const fl
   }
 }
 
+}  // namespace
+
+void launch_p4_fwd(const rotconv_plan* p, int out_mode, const float* x, const float* w, float* pack, size_t pack_bytes,
+                   float* out_val, uint8_t* out_idx, hipStream_t st, int nq, int csplit) {
+  launch_blocks(p, 0, fwd_blocks(p, nq), out_mode, x, w, pack, pack_bytes, out_val, out_idx, st, nq, csplit);
+}
+
+void launch_p4_fwd_parts(const rotconv_plan* p, int b0, int b1, const float* x, const float* w, float* pack, size_t pack_bytes,
+                         float* out_val, hipStream_t st, int csplit) {
+  launch_blocks(p, b0, b1, kOutUnpooled, x, w, pack, pack_bytes, out_val, nullptr, st, 1, csplit);
+}
+
 void launch_p4_sum_parts(const rotconv_plan* p, const float* part, int nparts, float* y, hipStream_t st) {
   const size_t n_elem = (size_t)p->d.N * p->d.Cout * p->d.R * p->d.H * p->d.W;
   const unsigned blocks = (unsigned)std::max<size_t>(1, std::min<size_t>((n_elem / 4 + 255) / 256, 4096));
   hipLaunchKernelGGL(k_p4_sum_parts, dim3(blocks), dim3(256), 0, st, part, y, n_elem, nparts);
 }
 
-void launch_p4_sum_pool(const rotconv_plan* p, const float* part, int nparts, float* ypool, uint8_t* idx,
+void launch_p4_sum_pool(const rotconv_plan* p, const float* part, int nparts, float* ypool, uint8_t* idx, int c0, int nc,
                         hipStream_t st) {
   const int HW = p->d.H * p->d.W;
-  const size_t n_elem = (size_t)p->d.N * p->d.Cout * p->d.R * HW;
-  const size_t total = (size_t)p->d.N * p->d.Cout * p->ng * HW;
+  const size_t n_elem = (size_t)p->d.N * nc * p->d.R * HW;
+  const size_t total = (size_t)p->d.N * nc * p->ng * HW;
   hipLaunchKernelGGL(k_p4_sum_pool, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, part, ypool, idx, n_elem,
-                     nparts, p->d.N * p->d.Cout, p->d.R, p->ng, HW, p->d.activation == ROTCONV_ACT_RELU ? 1 : 0);
+                     nparts, p->d.N, nc, c0, p->d.Cout, p->d.R, p->ng, HW, p->d.activation == ROTCONV_ACT_RELU ? 1 : 0);
 }
 
 void launch_p4_combine(const rotconv_plan* p, const float* pv, const uint8_t* pi, float* ypool, uint8_t* idx,

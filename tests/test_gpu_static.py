@@ -52,14 +52,18 @@ def test_own_need(cfg, over, off):
     _both(cfg, over, off)
 
 
-# layers of which the waves on their own would make more parts than the scratch holds: the contraction stays whole
+# layers of which the waves on their own make more parts than the scratch holds: they go through it in slices of filters
+# (several blocks, a ragged one, several images), or, where those of sixteen filters do not fit, the contraction stays whole
 WHOLE = [
     L("w_r2", N=4, Cin=238, H=10, W=80, Cout=331, R=2, seed=2211),
     L("w_steer", N=6, Cin=378, H=12, W=206, Cout=27, R=8, mode="steerable", pool_group=4, seed=2212),
+    L("w_odd", N=13, Cin=230, H=3, W=133, Cout=118, R=4, seed=2214),
+    L("w_relu", N=2, Cin=256, H=64, W=64, Cout=128, R=4, seed=2215),
+    L("w_one", N=1, Cin=655, H=294, W=80, Cout=46, R=4, seed=2216),
     L("w_r8", N=3, Cin=1207, H=134, W=4, Cout=113, R=8, mode="bilinear", seed=2213),
 ]
 
 
 @pytest.mark.parametrize("cfg", WHOLE, ids=[c.name for c in WHOLE])
-def test_not_split_beyond_the_scratch(cfg):
-    _both(cfg, {}, 0)
+def test_split_beyond_the_scratch(cfg):
+    _both(cfg, dict(relu=cfg.name == "w_relu"), 0)
