@@ -54,11 +54,12 @@
  *     group is, through the fused ReLU too, and idx is then some orientation of
  *     the group; where only some responses are NaN it may be NaN or the maximum
  *     of the others.  fp32 passes that multiply bf16 parts of the operands
- *     (rotconv_plan_bf16_parts, and the matrix multiply + scatter family) may make NaN
- *     of an infinity and of magnitudes from 3.396e38 on, and hold magnitudes below
- *     2^-110 to 2^-134 only (so does the pooled forward of first layers, which
- *     keeps infinities); all others, and these with plan option bf16_parts = -1,
- *     follow IEEE arithmetic.
+ *     (rotconv_plan_bf16_parts) may make NaN of an infinity and of magnitudes from
+ *     3.396e38 on, and hold magnitudes below 2^-110 to 2^-134 only.  Of these, the
+ *     pooled forward of first layers keeps infinities and large magnitudes, and the
+ *     matrix multiply + scatter family keeps both and, beside operands up to 2^10,
+ *     small ones: it forms sums that are not finite or below 2^-100 again in fp32.
+ *     All others, and these with plan option bf16_parts = -1, follow IEEE arithmetic.
  *   - Return value: a rotconv_status.  Argument errors are found on the host
  *     before anything is launched and leave the outputs untouched.
  */

@@ -9,7 +9,9 @@
  * hipStream_t passed as void*; calls only enqueue; outputs are overwritten unless said
  * otherwise; results are bitwise reproducible.  The fp32 matrix products (transposed
  * convolution, 1x1 heads of more than 8 classes) of small tensors multiply bf16 parts of the
- * operands: an infinity or a magnitude from 3.396e38 on makes NaN there.  Return value: a rotconv_status
+ * operands and form sums that are not finite, or below 2^-100, again in fp32: infinities, NaN and
+ * magnitudes are those of fp32 arithmetic whatever the size, but for an operand below 2^-110 beside
+ * one above 2^10, which is held to 2^-134 there.  Return value: a rotconv_status
  * (ROTCONV_ERR_NULL, ROTCONV_ERR_SHAPE, ROTCONV_ERR_WORKSPACE, ROTCONV_ERR_LAUNCH).
  */
 #ifndef UNETGLUE_H

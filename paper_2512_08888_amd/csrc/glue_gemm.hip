@@ -303,7 +303,10 @@ __global__ __launch_bounds__(NT) void k_gemm16(const uint16_t* __restrict__ A, c
 // (few tiles of a long K, split) 33 / 33.  On a full chip the vector work of the split (44 instructions per eight elements, by
 // every workgroup that reads them) bounds it: see launch_gemm.
 //
-// An infinite or NaN operand, or one from 3.396e38 on, makes NaN of the sums it enters.
+// The parts of an infinity, of a NaN and of a magnitude from 3.396e38 on make NaN of the sums they enter, and a magnitude below
+// 2^-110 is held to 2^-134 only, which a sum of 2^-100 and more does not show beside factors of up to 2^10.  So a tile with a sum
+// that is not finite, or below 2^-100 and not zero, is multiplied again on the fp32 instruction, as k_gemm does it (looking for
+// such sums after they are stored: 0.2 to 0.5 us a launch of 30 to 44).
 typedef f4 f4u __attribute__((aligned(4)));
 constexpr int T = 2;                                // 16 x 16 tiles of a wave, either way
 template <bool TA, bool TB>
@@ -458,18 +461,70 @@ __global__ __launch_bounds__(NT) void k_gemm_s3(const float* __restrict__ A, con
     }
   }
   // accumulator tile (i, j): rows m = wm + 16 i + 4 lg + r, column n = wn + 16 j + lc
+  auto store = [&]() {
 #pragma unroll
-  for (int j = 0; j < T; ++j) {
-    const int gn = n0 + wn + 16 * j + lc;
-    if (gn >= p.N) continue;
-    const size_t coff = Cbase + (p.shufC ? shuf_pix(gn, p.shufW) : (size_t)gn);
+    for (int j = 0; j < T; ++j) {
+      const int gn = n0 + wn + 16 * j + lc;
+      if (gn >= p.N) continue;
+      const size_t coff = Cbase + (p.shufC ? shuf_pix(gn, p.shufW) : (size_t)gn);
+#pragma unroll
+      for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int gm = m0 + wm + 16 * i + 4 * lg + r;
+          if (gm < p.M) C[coff + (p.shufC ? shuf_row(gm, p.shufH, p.shufW) : (size_t)gm * p.ldc)] = acc[i][j][r];
+        }
+    }
+  };
+  store();
+  // Sums that the parts may not hold.  As bits, the largest of the positive and of the negative ones, and the smallest
+  // magnitude (2 |bits| - 1 puts zero last).
+  uint32_t low = 0xffffffffu, neg = 0u;
+  int pos = 0;
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int j = 0; j < T; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float v = acc[i][j][r];
+        const uint32_t u = __builtin_bit_cast(uint32_t, v);
+        low = min(low, (u << 1) - 1u);
+        neg = max(neg, u);
+        pos = max(pos, (int)u);
+      }
+  constexpr uint32_t kLeast = (127u - 100u) << 24;
+  if (__builtin_expect(__any((low < kLeast - 1u) | (neg >= 0xff800000u) | (pos >= 0x7f800000)), 0)) {      // (the wave by itself, straight from memory)
+    const int m = m0 + wm + lc, n = n0 + wn + lc;
 #pragma unroll
     for (int i = 0; i < T; ++i)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int gm = m0 + wm + 16 * i + 4 * lg + r;
-        if (gm < p.M) C[coff + (p.shufC ? shuf_row(gm, p.shufH, p.shufW) : (size_t)gm * p.ldc)] = acc[i][j][r];
+      for (int j = 0; j < T; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+    for (int k = kbeg + lg; k - lg < kend; k += 4) {
+      const int kc = min(k, kend - 1);
+      float a[T], b[T];
+#pragma unroll
+      for (int i = 0; i < T; ++i) {
+        const int r = min(m + 16 * i, p.M - 1);
+        a[i] = Ap[TA ? (size_t)kc * p.lda + r : (size_t)r * p.lda + kc];
       }
+#pragma unroll
+      for (int j = 0; j < T; ++j) {
+        const int r = min(n + 16 * j, p.N - 1);
+        b[j] = Bp[p.shufB ? (TB ? shuf_row(r, p.shufH, p.shufW) + shuf_pix(kc, p.shufW) : shuf_pix(r, p.shufW) + shuf_row(kc, p.shufH, p.shufW))
+                          : TB ? (size_t)r * p.ldb + kc : (size_t)kc * p.ldb + r];
+      }
+#pragma unroll
+      for (int i = 0; i < T; ++i) a[i] = k < kend ? a[i] : 0.f;
+#pragma unroll
+      for (int j = 0; j < T; ++j) b[j] = k < kend ? b[j] : 0.f;
+#pragma unroll
+      for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = 0; j < T; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+    store();
   }
 }
 

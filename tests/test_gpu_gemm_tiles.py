@@ -106,3 +106,53 @@ def test_forward_has_no_offset(k, Cin):
         err.append(np.linalg.norm(d))
         assert abs(d.mean()) < 1.5e-8 * np.sqrt(np.mean(y ** 2))
     assert err[0] <= 1.02 * err[1], err
+
+
+def _same(got, ref):
+    """Infinities where the reference has them, of its sign, and its values elsewhere."""
+    got = np.asarray(got, np.float64)
+    fin = np.isfinite(ref)
+    assert np.array_equal(got[~fin], ref[~fin]) and np.isfinite(got[fin]).all() and fin.any()
+    assert _rel(got[fin], ref[fin]) < BAR
+
+
+@pytest.mark.parametrize("what", ["inf", "large", "tiny"])
+def test_values_beyond_the_parts(what):
+    """An infinity, 3.4e38 (which no bf16 part holds) and magnitudes of which the parts hold 14 bits: as on the fp32 instruction,
+    in tiles with them and in the others, for products of every kind."""
+    rng = np.random.default_rng(5)
+    N, Cin, Cout, H, W = 2, 70, 20, 9, 13
+    f = lambda *s: rng.standard_normal(s).astype(np.float32)
+
+    def hit(a):
+        if what == "tiny":
+            return np.ldexp(a, -120)
+        a.reshape(-1)[a.size // 3] = np.inf if what == "inf" else 3.4e38
+        return a
+
+    w = np.clip(f(Cin, Cout, 2, 2), -0.9, 0.9)
+    x, dy = f(N, Cin, H, W), f(N, Cout, 2 * H, 2 * W)
+    xb, gb = hit(x.copy()), hit(dy.copy())
+    y, dx = torch.full(dy.shape, float("nan"), device="cuda"), torch.full(x.shape, float("nan"), device="cuda")
+    dw = torch.full(w.shape, float("nan"), device="cuda")
+    ws = torch.empty(rc.glue_upconv2_workspace_bytes(N, Cin, Cout, H, W), dtype=torch.uint8, device="cuda")
+    small = lambda a: np.clip(a, -0.9, 0.9)
+    rc.glue_upconv2_fwd(pu.dev(xb), pu.dev(w), y)
+    rc.glue_upconv2_bwd_data(pu.dev(gb), pu.dev(w), dx)
+    rc.glue_upconv2_bwd_weight(pu.dev(xb), pu.dev(small(dy)), dw, ws)
+    with np.errstate(over="ignore", invalid="ignore"):
+        f32 = lambda r: r.astype(np.float32).astype(np.float64) if what != "tiny" else r
+        _same(y.cpu().numpy(), f32(uo.upconv2_fwd(xb, w)))
+        _same(dx.cpu().numpy(), f32(uo.upconv2_bwd(x, w, gb)[0]))
+        _same(dw.cpu().numpy(), f32(uo.upconv2_bwd(xb, w, small(dy))[1]))
+    cfg = L("g_big", N=1, Cin=33, H=20, W=22, Cout=4, R=4, k=5, pad=2, x_dist="normal", seed=1430)
+    x, w, g = hit(synth.make_x(cfg)), synth.make_w(cfg), np.asarray(synth.make_g(cfg), np.float32)
+    idx = rng.integers(0, 4, (1, 4, 20, 22)).astype(np.uint8)
+    out = []
+    for form in (1, -1):
+        lay = pu.GpuLayer(cfg, x, w, options=dict(gs=1, bf16_parts=form))
+        out.append((lay.fwd().cpu().numpy(), lay.pool_bwd_data(hit(g.copy()), idx), lay.pool_bwd_weight(small(g), idx)))
+    for a, b in zip(*out):
+        assert np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(np.isinf(a), np.isinf(b))
+        fin = np.isfinite(b)
+        assert _rel(a[fin], b[fin].astype(np.float64)) < BAR
