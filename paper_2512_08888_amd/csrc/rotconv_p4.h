@@ -26,7 +26,6 @@ struct P4Geom {
   double cost;   // modelled time of the launch, 0.1 us (host side only)
   long rows;     // the row steps behind it: four for a wave alone on its SIMD, eight for two that share one
   int cb0;       // first filter block of this launch
-  int out_c0, out_c;   // unpooled: the first filter of the output tensor, and how many it has
   int raw_w;     // the weight argument is the caller's w[Cout][Cin][9] itself (see p4_fwd_raw_weights)
   int seg_xorg[4];  // first product column of a segment's wave chain
   int seg_lo[4], seg_hi[4];  // output pixels [lo, hi) the segment stores (multiples of 8, or W)
@@ -37,7 +36,7 @@ constexpr int kS3FwdChunk = 9 * 3 * 256;     // 4-byte words of a 32-channel chu
 constexpr int kS3FwdResident = 5;            // chunks of a filter block that stay in LDS; more are streamed
 struct S3FwdGeom {
   int N, Cin, CinPad, H, W, Cout, CB, R, Q, ng, out_mode, relu, nq;
-  int csplit, cper, cb0, out_c0, out_c, raw_w;  // as in P4Geom
+  int csplit, cper, cb0, raw_w;  // as in P4Geom
   int stream;    // filter blocks streamed through LDS
   int all_turns; // every bank has its four quarter turns
   int Wv;        // columns of a row on the line of bands: the pixels and one or two empty ones

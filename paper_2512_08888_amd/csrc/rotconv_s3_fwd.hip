@@ -243,14 +243,13 @@ __global__ __launch_bounds__(64 * NWMAX, 2) void k_s3_fwd(const float* __restric
   const int co0 = cbo * FPB + lg * FPL;                // the lane's first filter
   // planes between filters, and what lies in front of the line's first image
   const uint32_t fplanes = UNPOOLED ? g.R : g.out_mode == kOutPooled ? g.ng : 1;
-  const size_t oimg = (size_t)(UNPOOLED ? g.out_c : g.Cout) * fplanes * HW;
+  const size_t oimg = (size_t)g.Cout * fplanes * HW;
   const size_t obase = ((UNPOOLED ? (size_t)sp : g.out_mode == kOutPartial ? (size_t)q : 0) * g.N + img) * oimg;
   const uint32_t osize = (uint32_t)(oimg * g.line_imgs);
   const auto ro = __builtin_amdgcn_make_buffer_rsrc(out_val + obase, 0, (int)(osize * 4u), 0x27000);
   const auto ri = __builtin_amdgcn_make_buffer_rsrc(out_idx + (UNPOOLED ? 0 : obase), 0, (int)(UNPOOLED ? 0 : osize), 0x27000);
   const uint32_t fstep = fplanes * (uint32_t)HW;       // elements from a filter to the next
-  const uint32_t oc = UNPOOLED ? (uint32_t)nl * (uint32_t)g.out_c + (uint32_t)(co0 - g.out_c0) : (uint32_t)nl * (uint32_t)g.Cout + (uint32_t)co0;
-  const uint32_t oo = oc * fstep + (uint32_t)(grp * HW) + (uint32_t)((y0 - 2) * g.W + px);
+  const uint32_t oo = ((uint32_t)nl * (uint32_t)g.Cout + (uint32_t)co0) * fstep + (uint32_t)(grp * HW) + (uint32_t)((y0 - 2) * g.W + px);
   const int nf = max(0, min(FPL, g.Cout - co0));       // filters of the lane that exist
   const bool st0 = ok0 && lc > 0, st1 = ok1 && lc < 15;
 
@@ -476,7 +475,6 @@ S3FwdGeom s3_fwd_geom(const rotconv_plan* p, int out_mode, int csplit, int nq, i
   S3FwdGeom g{};
   g.N = d.N; g.Cin = d.Cin; g.CinPad = (d.Cin + 31) / 32 * 32; g.H = d.H; g.W = d.W; g.Cout = d.Cout; g.R = d.R;
   g.ng = p->ng; g.out_mode = out_mode; g.nq = nq;
-  g.out_c0 = 0; g.out_c = d.Cout;
   const int nchunk = g.CinPad / 32;
   g.cper = (nchunk + csplit - 1) / csplit;
   g.csplit = (nchunk + g.cper - 1) / g.cper;
