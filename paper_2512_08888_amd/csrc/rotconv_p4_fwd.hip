@@ -906,7 +906,7 @@ int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, 
 // together, Q is 2 or 4, every bank has its four quarter turns, and the products are those of bf16 parts (1: no folding).
 int p4_fwd_fold(const rotconv_plan* p) {
   const int Q = p->host.Q;
-  if ((Q != 2 && Q != 4) || p->ng != 1 || !p->fwd_s3) return 1;
+  if ((Q != 2 && Q != 4) || p->ng != 1 || !p->fwd_s3 || (p->d.W & 1)) return 1;      // (odd rows: p4_fwd_supported pads them)
   for (int i = 0; i < Q * 4; ++i)
     if (p->rot_of[i] < 0) return 1;
   return Q;

@@ -451,11 +451,13 @@ void launch_u(const S3FwdGeom& g, const float* x, const float* wt, const int32_t
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(kern, dim3((g.units + 7) / 8 * 8), dim3(64 * g.nw), lds, st, x, wt, rot_of, ov, oi, g);
   };
-  if (g.W & 1) {
-    if (g.stream) go(k_s3_fwd<OUT, true, NQ, true>); else go(k_s3_fwd<OUT, false, NQ, true>);
-  } else {
-    if (g.stream) go(k_s3_fwd<OUT, true, NQ, false>); else go(k_s3_fwd<OUT, false, NQ, false>);
+  if constexpr (NQ == 1) {      // banks are folded on even rows only (p4_fwd_fold)
+    if (g.W & 1) {
+      if (g.stream) go(k_s3_fwd<OUT, true, 1, true>); else go(k_s3_fwd<OUT, false, 1, true>);
+      return;
+    }
   }
+  if (g.stream) go(k_s3_fwd<OUT, true, NQ, false>); else go(k_s3_fwd<OUT, false, NQ, false>);
 }
 
 // A tensor that a buffer descriptor reaches, with kOutside beyond it.

@@ -49,3 +49,12 @@ def test_selection():
 def test_edge_cases_reach_the_kernels_they_are_for(cfgs, which):
     for cfg in cfgs:
         assert rc.Plan.from_config(cfg).bf16_parts(which), cfg.name
+
+
+def test_odd_rows_of_pool_groups_over_several_banks_are_padded():
+    """The folded forward has no instances for odd rows: its plans copy them to padded rows, whose workspace shows."""
+    for kw in (dict(R=8, mode="steerable"), dict(R=16, mode="bilinear")):
+        for opt in (None, dict(fwd_base=-1)):
+            odd, even = (rc.Plan(2, 24, 40, W, 12, options=opt, **kw) for W in (39, 40))
+            assert odd.kernel_name(0) == even.kernel_name(0)
+            assert odd.workspace_bytes > even.workspace_bytes
