@@ -1,11 +1,11 @@
 // GEMMs on the matrix cores for the network glue around the rotation convolution (2x2
 // transposed-convolution up-sampling, 1x1 head): C = op(A) * op(B), optionally batched and/or
 // split along K with an ordered reduction afterwards.  Three kernels, operands staged through LDS,
-// the next tile prefetched into registers while the current one is multiplied:
+// the next tiles prefetched into registers while the current one is multiplied:
 //   k_gemm_s3 fp32 operands in three bf16 parts (rotconv_split3.h), 16x16x32 bf16 instruction, 32-deep
-//             tiles of 64 x 64 or 128 x 128;
-//   k_gemm    fp32 operands, 16x16x4 fp32 instruction, 16-deep tiles of 128 x 128, LDS k-major (layers
-//             whose plan keeps the fp32 instructions);
+//             tiles of 64 x 64, for launches that do not fill the chip (gemm_on_parts);
+//   k_gemm    fp32 operands, 16x16x4 fp32 instruction, 16-deep tiles of 128 x 128, LDS k-major: large
+//             products, and layers whose plan keeps the fp32 instructions;
 //   k_gemm16  bfloat16 operands, 16x16x32 bf16 instruction (fp32 accumulation), 32-deep tiles of
 //             128 x 128, LDS row-major with the contraction index contiguous.
 #include <hip/hip_runtime.h>
@@ -309,10 +309,11 @@ __global__ __launch_bounds__(NT) void k_gemm16(const uint16_t* __restrict__ A, c
 // such sums after they are stored: 0.2 to 0.5 us a launch of 30 to 44).
 typedef f4 f4u __attribute__((aligned(4)));
 constexpr int T = 2;                                // 16 x 16 tiles of a wave, either way
+constexpr int TM = 32 * T;                          // rows and columns of a workgroup's tile
+constexpr int SETS = 4;                             // K-steps of operands in registers and on their way
 template <bool TA, bool TB>
 __global__ __launch_bounds__(NT) void k_gemm_s3(const float* __restrict__ A, const float* __restrict__ B,
                                                float* __restrict__ C, GemmArgs p) {
-  constexpr int TM = 32 * T, NJ = T / 2;            // rows of a tile; pieces of eight k per thread and operand
   constexpr int OPW = 3 * TM * PITCH16;             // halfwords of an operand's tile
   extern __shared__ uint16_t sm16[];                // [2][A, B][part][row][PITCH16]
   const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, lg = lane / 16, lc = lane % 16;
@@ -324,14 +325,13 @@ __global__ __launch_bounds__(NT) void k_gemm_s3(const float* __restrict__ A, con
   const float* Bp = B + (size_t)batch * p.strideB;
   const size_t Cbase = (size_t)z * p.strideC;
   constexpr bool AKM = TA, BKM = !TB;               // operand stored k-major
-  // the thread's piece j: row and first k inside the tile
-  auto prow = [&](bool km, int j) { return km ? tid % TM : tid / 4 + 64 * j; };
-  auto pk = [&](bool km, int j) { return 8 * (km ? tid / TM + (NT / TM) * j : tid % 4); };
-  static_assert((NT / TM) * NJ == 4, "four pieces of eight k per row");
+  // the thread's piece of eight k of an operand: its row and first k inside the tile
+  static_assert(NT == 4 * TM, "four pieces of eight k per row");
+  auto prow = [&](bool km) { return km ? tid % TM : tid / 4; };
+  auto pk = [&](bool km) { return 8 * (km ? tid / TM : tid % 4); };
 
   // A K-step's compute is short beside a load's way, so SETS - 1 K-steps are on their way in registers.
-  constexpr int SETS = T == 2 ? 4 : 2;
-  float ra[SETS][NJ][8], rb[SETS][NJ][8];
+  float ra[SETS][8], rb[SETS][8];
   // eight values of a row from k on; outside the matrix zero (every address is one of the operand's)
   auto fetch = [&](auto full_c, float (&r)[8], const float* base, bool km, int ld, int row, int rows, int k, bool shuf) {
     constexpr bool full = decltype(full_c)::value;  // the K-step lies inside the chunk
@@ -373,11 +373,8 @@ __global__ __launch_bounds__(NT) void k_gemm_s3(const float* __restrict__ A, con
   };
   auto gload = [&](int set, int k0) {
     auto all = [&](auto full_c) {
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        fetch(full_c, ra[set][j], Ap, AKM, p.lda, m0 + prow(AKM, j), p.M, k0 + pk(AKM, j), false);
-        fetch(full_c, rb[set][j], Bp, BKM, p.ldb, n0 + prow(BKM, j), p.N, k0 + pk(BKM, j), p.shufB);
-      }
+      fetch(full_c, ra[set], Ap, AKM, p.lda, m0 + prow(AKM), p.M, k0 + pk(AKM), false);
+      fetch(full_c, rb[set], Bp, BKM, p.ldb, n0 + prow(BKM), p.N, k0 + pk(BKM), p.shufB);
     };
     if (k0 + 32 <= kend) all(std::true_type{}); else all(std::false_type{});
   };
@@ -394,11 +391,8 @@ __global__ __launch_bounds__(NT) void k_gemm_s3(const float* __restrict__ A, con
   };
   auto sstore = [&](int buf, int set, bool neg) {
     uint16_t* a = sm16 + buf * 2 * OPW;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      put(a, ra[set][j], prow(AKM, j), pk(AKM, j), neg);
-      put(a + OPW, rb[set][j], prow(BKM, j), pk(BKM, j), false);
-    }
+    put(a, ra[set], prow(AKM), pk(AKM), neg);
+    put(a + OPW, rb[set], prow(BKM), pk(BKM), false);
   };
 
   f4 acc[T][T];
@@ -561,9 +555,8 @@ __global__ __launch_bounds__(256) void k_sum_parts(const float* __restrict__ par
 }  // namespace
 
 void launch_gemm_s3(const GemmArgs& a, const float* A, const float* B, float* C, hipStream_t st) {
-  const int tm = 32 * T;
-  const size_t lds = (size_t)2 * 2 * 3 * tm * PITCH16 * sizeof(uint16_t);
-  dim3 grid((a.M + tm - 1) / tm, (a.N + tm - 1) / tm, a.batch * a.splitk);
+  const size_t lds = (size_t)2 * 2 * 3 * TM * PITCH16 * sizeof(uint16_t);
+  dim3 grid((a.M + TM - 1) / TM, (a.N + TM - 1) / TM, a.batch * a.splitk);
   auto go = [&](auto kern) {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(kern, grid, dim3(NT), lds, st, A, B, C, a);
@@ -593,12 +586,16 @@ void launch_gemm_bf16(const GemmArgs& a, const void* A, const void* B, void* C, 
   else if (a.transB) hipLaunchKernelGGL((k_gemm16<false, true, OUT16>), grid, dim3(NT), 0, st, A16, B16, C, a);
   else hipLaunchKernelGGL((k_gemm16<false, false, OUT16>), grid, dim3(NT), 0, st, A16, B16, C, a);
 }
-// Fp32 operands: bf16 parts where the launch is below 512 tiles of 128 x 128 and, contracting over pixels (B transposed; many
-// images and splits of few tiles), a matrix below 32.  Parts / fp32 instructions, up-convolutions of 55 random sizes, mean (most):
+// Fp32 operands: bf16 parts where the launch, with its images and splits, is below 512 tiles of 128 x 128 and, contracting over
+// pixels (B transposed), a matrix below 32.  Parts / fp32 instructions, up-convolutions of 55 random sizes, mean (most):
 // forward below 256 tiles 0.40 to 0.68 (0.85), 256 to 511 0.87 (0.96), from 512 1.09, from 1024 1.17 (1.31); input gradient 0.34 to
 // 0.80 (0.92), from 512 0.99, from 1024 1.04; weight gradient below 32 tiles 0.22 to 0.98, 32 to 128 1.04 (1.15).
+// Weight gradients of small matrices reach 512 tiles by their splits alone, which are chosen for the other kernel's tiles: a
+// layer of 5 x 5 taps on 2 x 96 x 96 pixels is on parts (504 tiles), on 2 x 98 x 98 it is not (518).  On that side parts would
+// still be the faster form for the multiply + scatter family (5 x 5 and 7 x 7 taps, 98 to 160 pixels: 0.60 to 0.77 of the call's
+// time), but not for the up-convolutions and heads (0.42 to 1.33 of it, eleven sizes), so the line stays where it is for both.
 bool gemm_on_parts(const GemmArgs& a) {
-  if (a.bf16A || a.parts < 0 || (a.N + 63) / 64 > 65535) return false;
+  if (a.bf16A || a.parts < 0 || (a.N + TM - 1) / TM > 65535) return false;
   const long mn = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
   return a.parts > 0 || (mn * a.batch * a.splitk < 512 && !(a.transB && mn >= 32));
 }
