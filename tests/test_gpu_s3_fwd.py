@@ -45,11 +45,8 @@ CASES = [_case(f"w{w}", 2, 9, 7, w, 18, 1000 + w) for w in (1, 2, 3, 14, 15, 27,
 ]
 
 
-@pytest.mark.parametrize("csplit", [0, 1, 3])
-@pytest.mark.parametrize("cfg", CASES, ids=[c.name for c in CASES])
+@pytest.mark.parametrize("cfg,csplit", [pytest.param(c, s, id=f"{c.name}-{s}") for c in CASES for s in (0, 1, 3) if s < 3 or c.Cin > 64])
 def test_forward(cfg, csplit):
-    if csplit == 3 and cfg.Cin <= 64:
-        pytest.skip("fewer than three chunks")
     x, w, g = synth.make_x(cfg), synth.make_w(cfg), synth.make_g(cfg)
     ref = pu.oracle_layer(cfg, x, w, g)
     lay = pu.GpuLayer(cfg, x, w, options=dict(fwd_csplit=csplit, fwd_base=-1))
