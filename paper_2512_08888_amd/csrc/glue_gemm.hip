@@ -304,9 +304,9 @@ __global__ __launch_bounds__(NT) void k_gemm16(const uint16_t* __restrict__ A, c
 // every workgroup that reads them) bounds it: see launch_gemm.
 //
 // The parts of an infinity, of a NaN and of a magnitude from 3.396e38 on make NaN of the sums they enter, and a magnitude below
-// 2^-110 is held to 2^-134 only, which a sum of 2^-100 and more does not show beside factors of up to 2^10.  So a tile with a sum
-// that is not finite, or below 2^-100 and not zero, is multiplied again on the fp32 instruction, as k_gemm does it (looking for
-// such sums after they are stored: 0.2 to 0.5 us a launch of 30 to 44).
+// 2^-110 is held to 2^-134 only, which a sum of 2^-100 and more does not show beside factors of up to 2^10.  So a wave with a sum
+// that is not finite, or below 2^-100 and not zero, multiplies its tile again on the fp32 instruction, as k_gemm does it, and
+// such sums, but no others, are replaced (looking for them after they are stored: 0.2 to 0.5 us a launch of 30 to 44).
 typedef f4 f4u __attribute__((aligned(4)));
 constexpr int T = 2;                                // 16 x 16 tiles of a wave, either way
 constexpr int TM = 32 * T;                          // rows and columns of a workgroup's tile
@@ -490,10 +490,11 @@ __global__ __launch_bounds__(NT) void k_gemm_s3(const float* __restrict__ A, con
   constexpr uint32_t kLeast = (127u - 100u) << 24;
   if (__builtin_expect(__any((low < kLeast - 1u) | (neg >= 0xff800000u) | (pos >= 0x7f800000)), 0)) {      // (the wave by itself, straight from memory)
     const int m = m0 + wm + lc, n = n0 + wn + lc;
+    f4 again[T][T];
 #pragma unroll
     for (int i = 0; i < T; ++i)
 #pragma unroll
-      for (int j = 0; j < T; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < T; ++j) again[i][j] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 2
     for (int k = kbeg + lg; k - lg < kend; k += 4) {
       const int kc = min(k, kend - 1);
@@ -516,8 +517,18 @@ __global__ __launch_bounds__(NT) void k_gemm_s3(const float* __restrict__ A, con
 #pragma unroll
       for (int i = 0; i < T; ++i)
 #pragma unroll
-        for (int j = 0; j < T; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < T; ++j) again[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], again[i][j], 0, 0, 0);
     }
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+      for (int j = 0; j < T; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float v = acc[i][j][r], w = again[i][j][r];
+          const uint32_t u = __builtin_bit_cast(uint32_t, v) << 1;
+          acc[i][j][r] = u - 1u < kLeast - 1u || u >= 0xff000000u ? w : v;
+        }
     store();
   }
 }

@@ -118,6 +118,27 @@ def test_forward_has_no_offset(k, Cin):
     assert err[0] <= 1.02 * err[1], err
 
 
+def test_sums_beside_one_the_parts_do_not_hold():
+    """... stay bit for bit what they are without it."""
+    rng = np.random.default_rng(6)
+    N, Cin, Cout, P = 1, 40, 30, 50
+    x, w = rng.standard_normal((N, Cin, 1, P)).astype(np.float32), rng.standard_normal((Cout, Cin)).astype(np.float32)
+
+    def run(x):
+        y = torch.full((N, Cout, 1, P), float("nan"), device="cuda")
+        rc.glue_conv1x1_fwd(pu.dev(x), pu.dev(w), y)
+        return y.cpu().numpy()
+
+    clean = run(x)
+    for bad in (np.inf, np.nan, 3.4e38, 0.0):
+        b = x.copy()
+        b[0, 7, 0, 20] = bad
+        if bad == 0.0:
+            b[0, :, 0, 20] *= 2.0 ** -118
+        y = run(b)
+        assert np.array_equal(np.delete(y, 20, 3), np.delete(clean, 20, 3)) and not np.array_equal(y[..., 20], clean[..., 20])
+
+
 def _same(got, ref):
     """Infinities where the reference has them, of its sign, and its values elsewhere."""
     got = np.asarray(got, np.float64)
