@@ -140,16 +140,16 @@ __global__ __launch_bounds__(256) void k_gs_place_tile(const float* __restrict__
 #pragma unroll
       for (int t = 0; t < TP; ++t) {                     // a tap beyond the last one reads zeros
         const int u = min(u0 + t, g.kk - 1);
-        const float sign = tap_sign(u0 + t);
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
           const float* src = cur + t * ext2 + off[s * g.kk + u] + lane_at;
 #pragma unroll
-          for (int m = 0; m < 4; ++m) acc[s][m] = fmaf(sign, src[m * row8], acc[s][m]);
+          for (int m = 0; m < 4; ++m) acc[s][m] = src[m * row8] - acc[s][m];      // the taps' signs in turn
         }
       }
     }
     __syncthreads();
+    const float sign = tap_sign((g.kk + TP - 1) / TP * TP - 1);      // of the last one
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const int r = rot[s];
@@ -157,12 +157,12 @@ __global__ __launch_bounds__(256) void k_gs_place_tile(const float* __restrict__
       for (int m = 0; m < 4; ++m) {
         const int oy = oy0 + ly + 8 * m, ox = ox0 + lx;
         if (FUSED) {                                     // ties go to the smallest orientation
-          const float v = acc[s][m];
+          const float v = fmaf(sign, acc[s][m], 0.f);      // (no negative zeros)
           const bool take = (r >= 0) & ((best_r[m] < 0) | (v > best[m]) | ((v == best[m]) & (r < best_r[m])));
           best[m] = take ? v : best[m];
           best_r[m] = take ? r : best_r[m];
         } else if (r >= 0 && oy < g.Ho && ox < g.Wo) {
-          yout[(((size_t)n * g.Cout + co) * g.R + r) * Po + oy * g.Wo + ox] = acc[s][m];
+          yout[(((size_t)n * g.Cout + co) * g.R + r) * Po + oy * g.Wo + ox] = fmaf(sign, acc[s][m], 0.f);
         }
       }
     }
