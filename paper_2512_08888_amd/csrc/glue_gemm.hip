@@ -306,7 +306,8 @@ __global__ __launch_bounds__(NT) void k_gemm16(const uint16_t* __restrict__ A, c
 // The parts of an infinity, of a NaN and of a magnitude from 3.396e38 on make NaN of the sums they enter, and a magnitude below
 // 2^-110 is held to 2^-134 only, which a sum of 2^-100 and more does not show beside factors of up to 2^10.  So a wave with a sum
 // that is not finite, or below 2^-100 and not zero, multiplies its tile again on the fp32 instruction, as k_gemm does it, and
-// such sums, but no others, are replaced (looking for them after they are stored: 0.2 to 0.5 us a launch of 30 to 44).
+// such sums, but no others, are replaced (looking for them after they are stored: 0.1 to 0.8 us a launch of 30 to 44; stores in a
+// function shared by both places: 0.8 more).
 typedef f4 f4u __attribute__((aligned(4)));
 constexpr int T = 2;                                // 16 x 16 tiles of a wave, either way
 constexpr int TM = 32 * T;                          // rows and columns of a workgroup's tile
@@ -326,12 +327,13 @@ __global__ __launch_bounds__(NT) void k_gemm_s3(const float* __restrict__ A, con
   const size_t Cbase = (size_t)z * p.strideC;
   constexpr bool AKM = TA, BKM = !TB;               // operand stored k-major
   // the thread's piece of eight k of an operand: its row and first k inside the tile
-  static_assert(NT == 4 * TM, "four pieces of eight k per row");
+  constexpr int NP = 4 * TM / NT;                   // four such pieces a row
+  static_assert(NP == 1, "one piece per thread");   // (loops over one: without them 30.5 -> 31.2 us, the split sums' product below)
   auto prow = [&](bool km) { return km ? tid % TM : tid / 4; };
   auto pk = [&](bool km) { return 8 * (km ? tid / TM : tid % 4); };
 
   // A K-step's compute is short beside a load's way, so SETS - 1 K-steps are on their way in registers.
-  float ra[SETS][8], rb[SETS][8];
+  float ra[SETS][NP][8], rb[SETS][NP][8];
   // eight values of a row from k on; outside the matrix zero (every address is one of the operand's)
   auto fetch = [&](auto full_c, float (&r)[8], const float* base, bool km, int ld, int row, int rows, int k, bool shuf) {
     constexpr bool full = decltype(full_c)::value;  // the K-step lies inside the chunk
@@ -373,8 +375,11 @@ __global__ __launch_bounds__(NT) void k_gemm_s3(const float* __restrict__ A, con
   };
   auto gload = [&](int set, int k0) {
     auto all = [&](auto full_c) {
-      fetch(full_c, ra[set], Ap, AKM, p.lda, m0 + prow(AKM), p.M, k0 + pk(AKM), false);
-      fetch(full_c, rb[set], Bp, BKM, p.ldb, n0 + prow(BKM), p.N, k0 + pk(BKM), p.shufB);
+#pragma unroll
+      for (int j = 0; j < NP; ++j) {
+        fetch(full_c, ra[set][j], Ap, AKM, p.lda, m0 + prow(AKM), p.M, k0 + pk(AKM), false);
+        fetch(full_c, rb[set][j], Bp, BKM, p.ldb, n0 + prow(BKM), p.N, k0 + pk(BKM), p.shufB);
+      }
     };
     if (k0 + 32 <= kend) all(std::true_type{}); else all(std::false_type{});
   };
@@ -391,8 +396,11 @@ __global__ __launch_bounds__(NT) void k_gemm_s3(const float* __restrict__ A, con
   };
   auto sstore = [&](int buf, int set, bool neg) {
     uint16_t* a = sm16 + buf * 2 * OPW;
-    put(a, ra[set], prow(AKM), pk(AKM), neg);
-    put(a + OPW, rb[set], prow(BKM), pk(BKM), false);
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+      put(a, ra[set][j], prow(AKM), pk(AKM), neg);
+      put(a + OPW, rb[set][j], prow(BKM), pk(BKM), false);
+    }
   };
 
   f4 acc[T][T];
@@ -455,26 +463,25 @@ __global__ __launch_bounds__(NT) void k_gemm_s3(const float* __restrict__ A, con
     }
   }
   // accumulator tile (i, j): rows m = wm + 16 i + 4 lg + r, column n = wn + 16 j + lc
-  auto store = [&]() {
 #pragma unroll
-    for (int j = 0; j < T; ++j) {
-      const int gn = n0 + wn + 16 * j + lc;
-      if (gn >= p.N) continue;
-      const size_t coff = Cbase + (p.shufC ? shuf_pix(gn, p.shufW) : (size_t)gn);
+  for (int j = 0; j < T; ++j) {
+    const int gn = n0 + wn + 16 * j + lc;
+    if (gn >= p.N) continue;
+    const size_t coff = Cbase + (p.shufC ? shuf_pix(gn, p.shufW) : (size_t)gn);
 #pragma unroll
-      for (int i = 0; i < T; ++i)
+    for (int i = 0; i < T; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int gm = m0 + wm + 16 * i + 4 * lg + r;
-          if (gm < p.M) C[coff + (p.shufC ? shuf_row(gm, p.shufH, p.shufW) : (size_t)gm * p.ldc)] = acc[i][j][r];
-        }
-    }
-  };
-  store();
-  // Sums that the parts may not hold.  As bits, the largest of the positive and of the negative ones, and the smallest
-  // magnitude (2 |bits| - 1 puts zero last).
-  uint32_t low = 0xffffffffu, neg = 0u;
-  int pos = 0;
+      for (int r = 0; r < 4; ++r) {
+        const int gm = m0 + wm + 16 * i + 4 * lg + r;
+        if (gm < p.M) C[coff + (p.shufC ? shuf_row(gm, p.shufH, p.shufW) : (size_t)gm * p.ldc)] = acc[i][j][r];
+      }
+  }
+  // Sums that the parts may not hold: from twice their bits, without the sign, those below 2^-100 wrap round behind all others,
+  // and zeros, which are none of them, with them.
+  constexpr uint32_t kLeast = (127u - 100u) << 24, kBeyond = (255u << 24) - kLeast;
+  auto rank = [&](float v) { return (__builtin_bit_cast(uint32_t, v) << 1) - kLeast; };
+  auto held = [&](float v) { return rank(v) < kBeyond || v == 0.f; };
+  uint32_t last = 0u;
 #pragma unroll
   for (int i = 0; i < T; ++i)
 #pragma unroll
@@ -482,13 +489,21 @@ __global__ __launch_bounds__(NT) void k_gemm_s3(const float* __restrict__ A, con
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const float v = acc[i][j][r];
-        const uint32_t u = __builtin_bit_cast(uint32_t, v);
-        low = min(low, (u << 1) - 1u);
-        neg = max(neg, u);
-        pos = max(pos, (int)u);
+        last = max(last, rank(v));
       }
-  constexpr uint32_t kLeast = (127u - 100u) << 24;
-  if (__builtin_expect(__any((low < kLeast - 1u) | (neg >= 0xff800000u) | (pos >= 0x7f800000)), 0)) {      // (the wave by itself, straight from memory)
+  if (__builtin_expect(__any(last >= kBeyond), 0)) {
+    bool all = true;
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+      for (int j = 0; j < T; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float v = acc[i][j][r];
+          all = all && held(v);
+        }
+    if (__all(all)) return;
+    // the wave by itself, straight from memory
     const int m = m0 + wm + lc, n = n0 + wn + lc;
     f4 again[T][T];
 #pragma unroll
@@ -520,16 +535,19 @@ __global__ __launch_bounds__(NT) void k_gemm_s3(const float* __restrict__ A, con
         for (int j = 0; j < T; ++j) again[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], again[i][j], 0, 0, 0);
     }
 #pragma unroll
-    for (int i = 0; i < T; ++i)
+    for (int j = 0; j < T; ++j) {
+      const int gn = n0 + wn + 16 * j + lc;
+      if (gn >= p.N) continue;
+      const size_t coff = Cbase + (p.shufC ? shuf_pix(gn, p.shufW) : (size_t)gn);
 #pragma unroll
-      for (int j = 0; j < T; ++j)
+      for (int i = 0; i < T; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const float v = acc[i][j][r], w = again[i][j][r];
-          const uint32_t u = __builtin_bit_cast(uint32_t, v) << 1;
-          acc[i][j][r] = u - 1u < kLeast - 1u || u >= 0xff000000u ? w : v;
+          const int gm = m0 + wm + 16 * i + 4 * lg + r;
+          const float v = acc[i][j][r];
+          if (gm < p.M && !held(v)) C[coff + (p.shufC ? shuf_row(gm, p.shufH, p.shufW) : (size_t)gm * p.ldc)] = again[i][j][r];
         }
-    store();
+    }
   }
 }
 
