@@ -233,8 +233,8 @@ int rotconv_pool_fwd(const rotconv_plan* plan, const void* x, const void* w, voi
                      size_t ws_bytes, void* stream);
 /* rotconv_pool_fwd for callers that cannot allocate device memory or bring a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and kernels as
- * rotconv_pool_fwd (banks that do not fit at once go through in slices of filters, bit for bit the same values), but
- * the scratch (the re-laid banks and, for some plans, per-bank candidates or channel-split parts) lives in a file-scope device array of ROTCONV_STATIC_SCRATCH_BYTES that each GPU the library runs on
+ * rotconv_pool_fwd (banks and channel-split parts that do not fit at once go through in slices of filters, bit for bit
+ * the same values), but the scratch (the re-laid banks and, for some plans, per-bank candidates or channel-split parts) lives in a file-scope device array of ROTCONV_STATIC_SCRATCH_BYTES that each GPU the library runs on
  * holds until the process ends.  The call makes no hipMalloc / hipFree and uploads nothing:
  *   - ROTCONV_ERR_UNSUPPORTED if the plan's tables are not on the current device yet (run any ordinary call
  *     of the plan there first; that first call is the one that allocates);
