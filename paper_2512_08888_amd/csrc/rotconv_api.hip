@@ -254,7 +254,7 @@ int rotconv_plan_create_opt(const rotconv_desc* desc, const rotconv_plan_options
     p->fwd_csplit[1] = 1;
     p->fwd_base_cls = p4_fwd_base_classify(p, &p->host.fwd_base_coef);
   }
-  if (direct_fwd_supported(p)) {     // first layers: the pooled forward on the vector ALU
+  if (direct_fwd_supported(p)) {     // first layers: kernels of their own for the pooled forward
     p->direct[0] = 1;
     p->ws_bytes = std::max(p->ws_bytes, direct_fwd_pack_floats(p) * sizeof(float));
   }
@@ -869,7 +869,7 @@ bool bf16_pool_fwd_is_native(const rotconv_plan* plan, const void* x, const void
          aligned(idx, 8);
 }
 
-// Does the pooled forward run the vector-ALU kernel of layers with at most four input channels for these pointers?
+// Does the pooled forward run the kernels of layers with at most four input channels for these pointers?
 bool pool_fwd_is_direct(const rotconv_plan* p, const void* x, const void* ypool, const void* ws) {
   const size_t es = is_bf16(p) ? 2 : 4;
   return p->direct[0] && aligned(x, es) && aligned(ypool, es) && aligned(ws, 16);
@@ -914,7 +914,7 @@ int pool_fwd_impl(const rotconv_plan* plan, const void* x, const void* w, void* 
     launch_repitch(c.idx, idx, c.rows_p, c.Wp, c.W, 1, 0, c.st);
     return finish();
   }
-  if (pool_fwd_is_direct(plan, x, ypool, ws)) {     // at most four input channels: the vector-ALU kernel
+  if (pool_fwd_is_direct(plan, x, ypool, ws)) {     // at most four input channels
     const size_t dneed = own_need ? pool_fwd_need(plan, x, w, ypool, idx, ws) : plan->ws_bytes;
     if (!ws || ws_bytes < dneed) return ROTCONV_ERR_WORKSPACE;
     if (no_upload && !tables_on_current_device(plan)) return ROTCONV_ERR_UNSUPPORTED;
