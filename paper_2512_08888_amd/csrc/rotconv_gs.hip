@@ -217,8 +217,9 @@ __global__ __launch_bounds__(256) void k_gs_place(const float* __restrict__ P, c
         const int yi = oy + ty[u], xi = ox + tx[u];
         const bool ok = (unsigned)yi < (unsigned)g.H && (unsigned)xi < (unsigned)g.W;
         const float v = Pq[(size_t)u * Pi + (ok ? yi * g.W + xi : 0)];
-        acc = fmaf(tap_sign(u), ok ? v : 0.f, acc);
+        acc = (ok ? v : 0.f) - acc;      // the taps' signs in turn
       }
+      acc = fmaf(tap_sign(g.kk - 1), acc, 0.f);      // (no negative zeros)
       if (FUSED) {
         if (best_r < 0 || acc > best) { best = acc; best_r = r; }
       } else {
