@@ -57,8 +57,8 @@
  *     (rotconv_plan_bf16_parts) may make NaN of an infinity and of magnitudes from
  *     3.396e38 on, and hold magnitudes below 2^-110 to 2^-134 only.  Of these, the
  *     pooled forward of first layers keeps infinities and large magnitudes, and the
- *     matrix multiply + scatter family keeps both and, beside operands up to 2^10,
- *     small ones: it forms sums that are not finite or below 2^-100 again in fp32.
+ *     matrix multiply + scatter family and the weight gradient of first layers keep
+ *     both and, beside operands up to 2^10, small ones: they form sums that are not finite or below 2^-100 again in fp32.
  *     All others, and these with plan option bf16_parts = -1, follow IEEE arithmetic.
  *   - Return value: a rotconv_status.  Argument errors are found on the host
  *     before anything is launched and leave the outputs untouched.
@@ -158,15 +158,16 @@ typedef struct {
                            into the banks' products on the vector ALU), -1 never (one contraction per bank)    */
   int32_t direct;       /* layers with at most four input channels (a network's first layer): 0 automatic (the
                            pooled forward by kernels of their own: on the vector ALU, or, fp32 with at most three
-                           channels, R = 4 and W a multiple of four, on bf16 parts), -1 never                      */
-  int32_t direct_ty;    /* rows per band of the vector-ALU kernel: 0 automatic, n > 0 = n and always that kernel    */
+                           channels, R = 4 and W a multiple of four, on bf16 parts; so the weight gradient of fp32
+                           layers of R = 4, on parts for rows of at least four pixels), -1 never                   */
+  int32_t direct_ty;    /* rows per band of the vector-ALU kernels: 0 automatic, n > 0 = n and always those kernels */
   int32_t px_fwd;       /* bf16 pooled forward of layers with 8 to 128 input channels pooled over all orientations:
                            0 automatic (filters on the matrix instruction's M side, a lane per pixel column, for
                            layers with four banks and at most 64 input channels), 1 wherever that kernel can run,
                            -1 never (pixels on the M side, eight pixels per lane)                                   */
   int32_t bf16_parts;   /* fp32 contractions of 3x3 layers as products of the operands' three bf16 parts on the bf16
-                           matrix cores (forward of layers with more than four channels and of first layers of R = 4,
-                           gradients of quarter-turn layers, the matrix multiply + scatter family): 0 automatic (where that is the faster form), 1 wherever those kernels can run,
+                           matrix cores (forward of layers with more than four channels, forward and weight gradient of first layers of
+                           R = 4, gradients of quarter-turn layers, the matrix multiply + scatter family): 0 automatic (where that is the faster form), 1 wherever those kernels can run,
                            -1 never (fp32 matrix instructions: exact products whatever the operands' magnitude)     */
   int32_t reserved[3];  /* must be 0 */
 } rotconv_plan_options;
@@ -297,7 +298,8 @@ double rotconv_plan_conv_equivalents(const rotconv_plan* plan, int pass);
 const char* rotconv_plan_kernel_name(const rotconv_plan* plan, int pass);
 /* 1 if that pass (0 rotconv_pool_fwd, 1 rotconv_pool_bwd_data, 2 rotconv_pool_bwd_weight) multiplies bf16 parts of fp32
  * operands for aligned tensors (see rotconv_plan_options.bf16_parts), else 0.  First layers ("valu_direct") and the matrix
- * multiply + scatter family are among them. */
+ * multiply + scatter family are among them; the weight gradient of first layers, which forms every sum beyond the parts' range
+ * again in fp32, multiplies parts too but answers 0. */
 int rotconv_plan_bf16_parts(const rotconv_plan* plan, int pass);
 
 #ifdef __cplusplus

@@ -551,6 +551,7 @@ bool direct_bwd_weight_supported(const rotconv_plan* p) {
 }
 
 size_t direct_bwd_weight_ws_floats(const rotconv_plan* p) {
+  if (first_bwd_weight_layer(p)) return first_bwd_weight_ws_floats(p);
   const DirWGeom g = direct_wgeom(p);
   return (size_t)g.nchunk * g.CoutPad * p->d.Cin * 9;
 }
@@ -558,6 +559,10 @@ size_t direct_bwd_weight_ws_floats(const rotconv_plan* p) {
 void launch_direct_bwd_weight(const rotconv_plan* p, const void* x, const void* gpool, const uint8_t* idx, float* part,
                               float* dw, hipStream_t st) {
   const rotconv_desc& d = p->d;
+  if (first_bwd_weight_layer(p)) {
+    launch_first_bwd_weight(p, static_cast<const float*>(x), static_cast<const float*>(gpool), idx, part, dw, st);
+    return;
+  }
   const DirWGeom g = direct_wgeom(p);
   if (d.dtype == ROTCONV_BF16) launch_w<uint16_t>(d.Cin, g, x, gpool, idx, part, st);
   else launch_w<float>(d.Cin, g, x, gpool, idx, part, st);
