@@ -8,15 +8,16 @@
 // A workgroup owns 32 filters of a bank x 32 CB input channels x nine taps and walks down the rows of its strips of
 // sixteen pixels, two rows (32 pixels) a step.  D and its parts cost several times the vector work of anything else here
 // and do not depend on the channel, so they are built once per workgroup and step and handed round through LDS: eight
-// waves build (a wave four filters, a lane one pixel column of one filter: column neighbours by lane shifts, the routed
-// gradients of two of the four rows it needs kept from the step before), four waves split X, and all twelve multiply,
+// waves build (a wave four filters, a lane one pixel column of one filter: column neighbours by lane shifts; what a pair of rows
+// gives to the next step's D is summed with it, so that a row is routed once), four waves split X, and all twelve multiply,
 // a wave three taps of 32 channels (48 accumulator registers, so that three waves fit a SIMD and one's vector
 // instructions run beside another's matrix instructions).  LDS is double-buffered, one barrier per step; half of the
 // builders multiply first and build afterwards.
 //
 // What bounds it: with 128 channels per workgroup the matrix cores (six products: 89 us of the 118 at 4x128 -> 128,
 // 128x128; fp32 matrix cores, which need 145 us for one product each, took 182), with 64 the vector work of building
-// (about 830 instructions per SIMD and step beside 54 matrix instructions; 8x64 -> 64, 256x256: 284 us, was 370).
+// (about 740 instructions per SIMD and step beside 54 matrix instructions; 8x64 -> 64, 256x256: 309 us with the pair before
+// routed again, 288 so; with 128 channels the same time either way).
 // 4x512 -> 512, 32x32: 126 us, was 188; 2x256 -> 256, 32x32: 39, was 47; 8x512 -> 512, 16x16: 79, was 196.
 // Precision: the parts' sum of each 16 pixels starts from zero and only its total meets the running sum.  The matrix
 // instruction cuts the low bits of what it adds up towards minus infinity; over the pixels of a batch that offset grows
@@ -159,33 +160,43 @@ __global__ __launch_bounds__(NTW, 3) void k_s3_bwd_weight(const float* __restric
   };
   // A wave keeps a ring of slots as loaded (a builder the pairs of rows, a wave that splits X its pixels) and loads one
   // slot before the use: a slot is 1 to 2 us of matrix work, enough to cover memory.  A longer ring does not fit the
-  // registers with 128 channels (a ring of 4: 38 spilled, 135 against 125 us at 4x128 -> 128, 128x128) and with 64
-  // unrolls the loops past what two CUs share of instruction cache (633 against 628 us for both gradients of
-  // 8x64 -> 64, 256x256; with 56 KB of code it was 690).
-  constexpr int NXP = CB == 4 ? 2 : 1, RING = 3, AHEAD = RING - 2;
+  // registers with 128 channels and unrolls the loops towards what two CUs share of instruction cache (with 56 KB of code
+  // both gradients of 8x64 -> 64, 256x256 took 690 us where 34 KB took 628).
+  constexpr int NXP = CB == 4 ? 2 : 1, RING = 2, AHEAD = RING - 1;
   struct XRaw { s3_f4 v[NXP][2]; };
   // the second lane half's filters are stored in another order, so that a wave's four filters x sixteen pixels meet each
   // of the 32 banks twice and not four times
   const int bh = bc % 8 / 4;
   uint32_t* dst0 = Dl + (bc / 8) * (27 * 256) + (bh * 32 + (bf ^ (bh * 4))) * 4 + bc % 4;
-  auto build = [&](const Pair& before, const Pair& now, int buf) {
-    float D0[9], D1[9];
+  // What the pair of rows gives to the D of its slot's two output rows, which C0 and C1 begin, and then, in their place, to
+  // those of the next slot: every row is routed once.
+  auto build = [&](float (&C0)[9], float (&C1)[9], const Pair& now, int buf, bool store) {
+    float N0[9], N1[9], m[NR];
 #pragma unroll
-    for (int u = 0; u < 9; ++u) D0[u] = D1[u] = 0.f;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      float m[NR];
-      route(raw_of(r < 2 ? before : now, r % 2), m);
-      if (r < 3) add_row(m, r, D0);
-      if (r > 0) add_row(m, r - 1, D1);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    for (int u = 0; u < 9; ++u) N0[u] = N1[u] = 0.f;
+    route(raw_of(now, 0), m);
+    add_row(m, 2, C0);
+    add_row(m, 1, C1);
+    add_row(m, 0, N0);
+    __builtin_amdgcn_sched_barrier(0);
+    route(raw_of(now, 1), m);
+    add_row(m, 2, C1);
+    add_row(m, 1, N0);
+    add_row(m, 0, N1);
+    __builtin_amdgcn_sched_barrier(0);
     uint32_t* dst = dst0 + buf * DW;
+    if (store) {
+#pragma unroll
+      for (int u = 0; u < 9; ++u) {
+        const S3Pair p = s3_split2<true>(C0[u], C1[u]);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) dst[(u * 3 + e) * 256] = p.p[e];
+      }
+    }
 #pragma unroll
     for (int u = 0; u < 9; ++u) {
-      const S3Pair p = s3_split2<true>(D0[u], D1[u]);
-#pragma unroll
-      for (int e = 0; e < 3; ++e) dst[(u * 3 + e) * 256] = p.p[e];
+      C0[u] = N0[u];
+      C1[u] = N1[u];
     }
   };
 
@@ -278,6 +289,9 @@ __global__ __launch_bounds__(NTW, 3) void k_s3_bwd_weight(const float* __restric
     constexpr bool BUILDS = decltype(builds_c)::value, LATE = decltype(late_c)::value, XS = !BUILDS;
     Slot sb = begin(split), sl = sb;
     Pair kp[BUILDS ? RING : 1];
+    float C0[9], C1[9];
+#pragma unroll
+    for (int u = 0; u < 9; ++u) C0[u] = C1[u] = 0.f;
     XRaw kx[XS ? RING : 1];
 #pragma unroll
     for (int i = 0; i < AHEAD; ++i) {
@@ -298,10 +312,8 @@ __global__ __launch_bounds__(NTW, 3) void k_s3_bwd_weight(const float* __restric
         advance(sl);
         __builtin_amdgcn_sched_barrier(0);
         if (LATE && have) multiply(buf);
-        if (now) {
-          if constexpr (BUILDS) build(kp[(at + RING - 1) % RING], kp[at], buf ^ 1);
-          else stage_x(kx[at], buf ^ 1);
-        }
+        if constexpr (BUILDS) build(C0, C1, kp[at], buf ^ 1, now);      // (a unit's first slot only begins its sums)
+        else if (now) stage_x(kx[at], buf ^ 1);
         if (!LATE && have) multiply(buf);
         have = now;
         if (done) break;
