@@ -58,7 +58,8 @@
  *     3.396e38 on, and hold magnitudes below 2^-110 to 2^-134 only.  Of these, the
  *     pooled forward of first layers keeps infinities and large magnitudes, and the
  *     matrix multiply + scatter family and the weight gradient of first layers keep
- *     both and, beside operands up to 2^10, small ones: they form sums that are not finite or below 2^-100 again in fp32.
+ *     both and, beside operands up to 2^10, small ones: they form sums that are not
+ *     finite or below 2^-100 again in fp32.
  *     All others, and these with plan option bf16_parts = -1, follow IEEE arithmetic.
  *   - Return value: a rotconv_status.  Argument errors are found on the host
  *     before anything is launched and leave the outputs untouched.
@@ -148,7 +149,9 @@ typedef struct {
   int32_t fwd_csplit;   /* channel split of the 3x3 forward on small maps with deep inputs: 0 automatic,
                            1 never (where an unsplit kernel exists), n >= 2: n parts                        */
   int32_t gs;           /* shapes outside the 3x3 / stride 1 / pad 1 kernels on the matrix multiply + scatter
-                           family: 0 automatic (from about a megaflop), 1 always, -1 never (generic kernels)   */
+                           family: 0 automatic (from about a megaflop; fp32 pooled forwards of R = 4 and single
+                           orientations as one contraction over channels and taps, nothing placed), 1 always
+                           (products placed), -1 never (generic kernels)                                       */
   int32_t gs_chunk_mb;  /* MiB of products that family keeps in the workspace at once: 0 = 512, n > 0 = n,
                            -1 = one image at a time (at least one image's worth is always taken)               */
   int32_t bwd_lut;      /* fp32 gradients of layers whose pool group spans several first-quadrant banks:
@@ -298,8 +301,9 @@ double rotconv_plan_conv_equivalents(const rotconv_plan* plan, int pass);
 const char* rotconv_plan_kernel_name(const rotconv_plan* plan, int pass);
 /* 1 if that pass (0 rotconv_pool_fwd, 1 rotconv_pool_bwd_data, 2 rotconv_pool_bwd_weight) multiplies bf16 parts of fp32
  * operands for aligned tensors (see rotconv_plan_options.bf16_parts), else 0.  First layers ("valu_direct") and the matrix
- * multiply + scatter family are among them; the weight gradient of first layers, which forms every sum beyond the parts' range
- * again in fp32, multiplies parts too but answers 0. */
+ * multiply + scatter family are among them (its pooled forward answers for the products that are placed: the one contraction that
+ * takes their place with R = 4 multiplies parts always); the weight gradient of first layers, which forms every sum beyond the
+ * parts' range again in fp32, multiplies parts too but answers 0. */
 int rotconv_plan_bf16_parts(const rotconv_plan* plan, int pass);
 
 #ifdef __cplusplus

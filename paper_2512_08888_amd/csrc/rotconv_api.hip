@@ -11,6 +11,7 @@
 #include "rotconv_bf16.h"
 #include "rotconv_p4.h"
 #include "rotconv_gs.h"
+#include "rotconv_ig.h"
 #include "rotconv_direct.h"
 #include "rotconv_px_fwd_bf16.h"
 
@@ -165,6 +166,45 @@ void choose_fwd(rotconv_plan* p) {
   p4_fwd_choose_launches(p);
 }
 
+// One contraction over channels and taps instead of products that are placed.  Filters of other sizes and strides with the four
+// quarter turns, pooled: always (60 layers of 12 to 64 channels and filters, k = 2, 5, 7, stride 1 and 2: 0.48 of the time in the
+// mean, 0.14 to 0.78).  Single orientations: where modelled at less than 0.85 of the time of the kernels that place (200 layers of 5
+// to 600 channels and filters: 0.93 in the mean of all with that rule, 0.23 to 1.05; taken everywhere up to 1.3 on large maps).
+size_t ig_part_bytes(const rotconv_plan* p, const IgShape& s) {
+  return s.parts() > 1 ? align256((size_t)s.parts() * p->d.N * p->d.Cout * p->d.R * p->Ho * p->Wo * 4) : 0;
+}
+void choose_ig(rotconv_plan* p) {
+  if (!ig_fwd_supported(p)) return;
+  if (p->gs && p->opt.gs == 0) {
+    // what rotconv_pool_fwd_static holds wherever it holds the products (behind widened copies that may be less than its array)
+    const size_t holds = p->d.dtype == ROTCONV_F32 ? std::max<size_t>(gs_ws_bytes(p), ROTCONV_STATIC_SCRATCH_BYTES) : gs_ws_bytes(p);
+    const IgShape s = ig_fwd_shape(p, holds);
+    if (s.mt && ig_fwd_block_bytes(p, s) <= holds) p->ig[1] = s;
+    if (p->d.R == 1) p->ig[0] = p->ig[1];
+  } else if (p->d.R == 1 && p->fast[0] && p->opt.fwd_csplit == 0) {
+    const IgShape s = ig_fwd_shape(p, (size_t)64 << 20);
+    const double other = p4_fwd_us(p);
+    if (s.mt && other > 12. && s.us < 0.85 * other) p->ig[0] = s;
+  }
+  for (const IgShape& s : p->ig)
+    if (s.mt) p->ws_bytes = std::max(p->ws_bytes, ig_part_bytes(p, s) + align256(ig_fwd_pack_bytes(p, s)));
+}
+// Either forward of such a plan.
+void run_ig(const rotconv_plan* p, bool pooled, const float* x, const float* w, float* y, uint8_t* idx, void* ws, size_t ws_bytes,
+            hipStream_t st) {
+  const IgShape& s = p->ig[pooled];
+  const size_t parts = ig_part_bytes(p, s);
+  char* pack = static_cast<char*>(ws) + parts;
+  if (!parts) {
+    launch_ig_fwd(p, s, pooled, x, w, y, idx, pack, ws_bytes, st);
+    return;
+  }
+  float* part = static_cast<float*>(ws);
+  launch_ig_fwd(p, s, false, x, w, part, nullptr, pack, ws_bytes - parts, st);
+  if (pooled) launch_p4_sum_pool(p, part, s.parts(), y, idx, 0, p->d.Cout, st);
+  else launch_p4_sum_parts(p, part, s.parts(), y, st);
+}
+
 // the fp32 path's own need (a bf16 plan adds its staging areas in front, see carve())
 int check_ws_inner(const rotconv_plan* p, const void* ws, size_t ws_bytes) {
   if (p->ws_inner == 0) return ROTCONV_OK;
@@ -289,6 +329,7 @@ int rotconv_plan_create_opt(const rotconv_desc* desc, const rotconv_plan_options
     p->gs_chunk_bytes = gs_chunk_budget(p);
     p->ws_bytes = std::max(p->ws_bytes, gs_ws_bytes(p));
   }
+  choose_ig(p);
   p->ws_inner = p->ws_bytes = align256(p->ws_bytes);
   const size_t hw_in = (size_t)p->d.H * p->d.W, hw_out = (size_t)p->Ho * p->Wo;
   p->n_x = (size_t)p->d.N * p->d.Cin * hw_in;
@@ -314,6 +355,7 @@ int rotconv_plan_create_opt(const rotconv_desc* desc, const rotconv_plan_options
       delete p;
       return crc;
     }
+    p->avg_child->ig[0] = IgShape();      // (the call without a workspace runs what the others run)
     const AvgLayout L = avg_layout(p);
     const size_t staging = p->ws_bytes - p->ws_inner;       // a bf16 plan's fp32 copies in front (0 for fp32 plans)
     p->ws_inner = std::max(p->ws_inner, L.total);
@@ -456,6 +498,10 @@ static int f32_rotconv_fwd(const rotconv_plan* plan, const void* x, const void* 
   rotconv_plan* p = const_cast<rotconv_plan*>(plan);
   if ((rc = ensure_device_tables(p))) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (p->ig[0].mt && aligned(x, 4) && aligned(y, 4) && aligned(ws, 256)) {
+    run_ig(p, false, static_cast<const float*>(x), static_cast<const float*>(w), static_cast<float*>(y), nullptr, ws, ws_bytes, st);
+    return finish();
+  }
   const int cs = p->fwd_csplit[0];
   if (f32_fwd_is_fast(p, x, y, ws)) {
     const size_t parts = fwd_part_bytes(p, cs);       // small map, deep input: the channels are split over workgroups
@@ -620,6 +666,10 @@ static int f32_rotconv_pool_fwd(const rotconv_plan* plan, const void* x, const v
       run(mode, fwd_extra_bytes(p), yu, nullptr, 1, 1);
       launch_maxpool_fwd(p, yu, yf, idx, st, true);
     }
+    return finish();
+  }
+  if (p->ig[1].mt && aligned(x, 4) && aligned(ypool, 4) && aligned(ws, 256)) {
+    run_ig(p, true, static_cast<const float*>(x), static_cast<const float*>(w), static_cast<float*>(ypool), idx, ws, ws_bytes, st);
     return finish();
   }
   if (p->gs) {
@@ -1129,7 +1179,7 @@ double rotconv_plan_conv_equivalents(const rotconv_plan* plan, int pass) {
     if (pass == 0) return plan->fwd_base ? B : Q;
     return plan->bwd_lut ? B : Q;
   }
-  if (plan->gs) return Q;
+  if (plan->gs) return pass == 0 && plan->ig[1].mt ? plan->d.R : Q;
   return plan->d.R;
 }
 

@@ -1,0 +1,19 @@
+// Forward of fp32 layers as one contraction over channels and taps, the quarter turns as rows of it (rotconv_ig_fwd.hip).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "rotconv_internal.h"
+
+namespace rotconv {
+
+bool ig_fwd_supported(const rotconv_plan* p);                  // the layer is one that the kernels take
+IgShape ig_fwd_shape(const rotconv_plan* p, size_t budget);     // budget: bytes for a block's weights and shares (0: no shares)
+size_t ig_fwd_block_bytes(const rotconv_plan* p, const IgShape& s);     // packed weights of a filter block
+size_t ig_fwd_pack_bytes(const rotconv_plan* p, const IgShape& s);      // ... of all
+// y: pooled values with idx (pooled, one share), else the responses of every orientation, the shares one after the other.  The packed
+// weights of as many filter blocks at a time as ws_bytes hold.
+void launch_ig_fwd(const rotconv_plan* p, const IgShape& s, bool pooled, const float* x, const float* w, float* y, uint8_t* idx,
+                   void* ws, size_t ws_bytes, hipStream_t st);
+
+}  // namespace rotconv

@@ -71,6 +71,10 @@ struct DeviceTables {
   float* fwd_base_coef = nullptr;   // HostTables::fwd_base_coef (one element if the plan has none)
 };
 
+// How the forward as one contraction over channels and taps runs (rotconv_ig.h): wc blocks of 16 mt filters and 64 nt pixels, a
+// tile of th x tw, per workgroup; nsplit shares of the channels, times osplit of the orbits of taps; us: as modelled.
+struct IgShape { int mt = 0, nt = 0, wc = 1, th = 0, tw = 0, nsplit = 1, osplit = 1; double us = 0; int parts() const { return nsplit * osplit; } };
+
 }  // namespace rotconv
 
 struct rotconv_plan {
@@ -104,6 +108,7 @@ struct rotconv_plan {
   int fwd_sliced = 0;           // the pooled split goes through small scratch in slices of filter blocks
   // ... and the launches of the two, modelled once: which kernel, its rows per band and waves per workgroup
   struct FwdLaunch { int out_mode = -1, csplit = 0, nq = 0, chain = 0, ty = 0, nw = 0; } fwd_launch[2];
+  rotconv::IgShape ig[2];       // unpooled / pooled forward as one contraction over channels and taps (mt = 0: not)
   // Average pooling (Eq. 9 / Eq. 11): the fused calls run one ordinary convolution (this R = 1 plan with
   // Cout * R/G filters) on the group-averaged bank.  Owned by the parent.
   rotconv_plan* avg_child = nullptr;

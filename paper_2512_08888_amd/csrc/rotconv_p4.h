@@ -62,6 +62,7 @@ int p4_fwd_geoms(const rotconv_plan* p, int out_mode, P4Geom* out, int max_out, 
 // parts the forward splits its channel contraction into for this plan (1: none); with a split the kernel runs in
 // the unpooled mode into `csplit` parts of N * Cout * R * H * W floats, added by one of the two kernels below
 int p4_fwd_csplit(const rotconv_plan* p, bool pooled);
+double p4_fwd_us(const rotconv_plan* p);
 bool p4_fwd_chain_whole(const rotconv_plan* p);
 void p4_fwd_choose_launches(rotconv_plan* p);   // fills fwd_launch, after the channel splits
 void launch_p4_sum_parts(const rotconv_plan* p, const float* part, int nparts, float* y, hipStream_t st);

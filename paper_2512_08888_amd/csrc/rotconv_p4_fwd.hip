@@ -805,6 +805,13 @@ int p4_fwd_csplit(const rotconv_plan* p, bool pooled) {
   return best_s;
 }
 
+// The unpooled forward's modelled time, us; negative where there is none.  (With a channel split 0.78 of the models' sum.)
+double p4_fwd_us(const rotconv_plan* p) {
+  const int cs = p->fwd_csplit[0];
+  const double c = plan_cost(p, kOutUnpooled, cs, 1), parts = 4.0 * cs * p->d.N * p->d.Cout * p->d.R * p->d.H * p->d.W;
+  return c < 0 ? c : cs > 1 ? 0.078 * (c + 80. + parts / 0.2e6) : 0.1 * c;
+}
+
 // Are the chained waves alone (rows that they overhang masked) no faster with a split, pooled?  In units of 0.3 us: four per
 // 32-channel chunk and row step of a wave and three for the placing; a split's parts at 4 TB/s and 8 us of launches.
 bool p4_fwd_chain_whole(const rotconv_plan* p) {
@@ -1016,14 +1023,14 @@ void launch_p4_fwd_parts(const rotconv_plan* p, int b0, int b1, const float* x, 
 }
 
 void launch_p4_sum_parts(const rotconv_plan* p, const float* part, int nparts, float* y, hipStream_t st) {
-  const size_t n_elem = (size_t)p->d.N * p->d.Cout * p->d.R * p->d.H * p->d.W;
+  const size_t n_elem = (size_t)p->d.N * p->d.Cout * p->d.R * p->Ho * p->Wo;
   const unsigned blocks = (unsigned)std::max<size_t>(1, std::min<size_t>((n_elem / 4 + 255) / 256, 4096));
   hipLaunchKernelGGL(k_p4_sum_parts, dim3(blocks), dim3(256), 0, st, part, y, n_elem, nparts);
 }
 
 void launch_p4_sum_pool(const rotconv_plan* p, const float* part, int nparts, float* ypool, uint8_t* idx, int c0, int nc,
                         hipStream_t st) {
-  const int HW = p->d.H * p->d.W;
+  const int HW = p->Ho * p->Wo;
   const size_t n_elem = (size_t)p->d.N * nc * p->d.R * HW;
   const size_t total = (size_t)p->d.N * nc * p->ng * HW;
   hipLaunchKernelGGL(k_p4_sum_pool, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, part, ypool, idx, n_elem,
