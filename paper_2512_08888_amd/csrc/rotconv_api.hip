@@ -181,6 +181,8 @@ void choose_ig(rotconv_plan* p) {
     const IgShape s = ig_fwd_shape(p, holds);
     if (s.mt && ig_fwd_block_bytes(p, s) <= holds) p->ig[1] = s;
     if (p->d.R == 1) p->ig[0] = p->ig[1];
+    if (ig_bwd_data_supported(p)) p->ig_dx = ig_bwd_data_shape(p, (size_t)256 << 20);
+    if (p->ig_dx.mt) p->ws_bytes = std::max(p->ws_bytes, ig_bwd_data_ws_bytes(p, p->ig_dx));
   } else if (p->d.R == 1 && p->fast[0] && p->opt.fwd_csplit == 0) {
     const IgShape s = ig_fwd_shape(p, (size_t)64 << 20);
     const double other = p4_fwd_us(p);
@@ -717,6 +719,10 @@ static int f32_rotconv_pool_bwd_data(const rotconv_plan* plan, const void* gpool
     }
     float* part = reinterpret_cast<float*>(static_cast<char*>(ws) + align256(p4_bwd_data_pack_floats(p) * sizeof(float)));
     launch_p4_bwd_data(p, static_cast<const float*>(gpool), idx, wd, static_cast<float*>(dx), part, st, raw);
+    return finish();
+  }
+  if (p->ig_dx.mt && aligned(gpool, 4) && aligned(dx, 4) && aligned(ws, 256)) {
+    launch_ig_bwd_data(p, p->ig_dx, static_cast<const float*>(gpool), idx, static_cast<const float*>(w), static_cast<float*>(dx), ws, st);
     return finish();
   }
   if (p->gs) {

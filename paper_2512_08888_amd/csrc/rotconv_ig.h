@@ -1,4 +1,4 @@
-// Forward of fp32 layers as one contraction over channels and taps, the quarter turns as rows of it (rotconv_ig_fwd.hip).
+// Passes of fp32 layers as one contraction with the four quarter turns apart (rotconv_ig_fwd.hip, rotconv_ig_bwd_data.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -15,5 +15,13 @@ size_t ig_fwd_pack_bytes(const rotconv_plan* p, const IgShape& s);      // ... o
 // weights of as many filter blocks at a time as ws_bytes hold.
 void launch_ig_fwd(const rotconv_plan* p, const IgShape& s, bool pooled, const float* x, const float* w, float* y, uint8_t* idx,
                    void* ws, size_t ws_bytes, hipStream_t st);
+
+
+// Input gradient of the same layers with four turns, pooled over them.  Shapes as above, `blocks` of input channels.
+bool ig_bwd_data_supported(const rotconv_plan* p);
+IgShape ig_bwd_data_shape(const rotconv_plan* p, size_t budget);
+size_t ig_bwd_data_ws_bytes(const rotconv_plan* p, const IgShape& s);       // packed weights and shares
+void launch_ig_bwd_data(const rotconv_plan* p, const IgShape& s, const float* gpool, const uint8_t* idx, const float* w, float* dx,
+                        void* ws, hipStream_t st);
 
 }  // namespace rotconv

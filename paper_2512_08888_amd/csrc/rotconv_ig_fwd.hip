@@ -35,6 +35,7 @@
 #include <type_traits>
 
 #include "rotconv_ig.h"
+#include "rotconv_ig_orbits.h"
 #include "rotconv_split3.h"
 
 namespace rotconv {
@@ -50,24 +51,7 @@ struct IgGeom {
   size_t part;                         // elements of a share's responses
 };
 
-// Position (i, j) of the k x k window after a quarter turn of the filter: (k - 1 - j, i).
-struct Orbit { int i, j; };
 constexpr int kPixel = 13;             // 16-byte units of a pixel in LDS
-__device__ __host__ __forceinline__ Orbit orbit_rep(int o, int k) { return Orbit{o / (k / 2), o % (k / 2)}; }
-__device__ __host__ __forceinline__ Orbit turn(Orbit t, int k) { return Orbit{k - 1 - t.j, t.i}; }
-
-// The tap that tile t of a block of turning filters holds: the orbits one after the other, then the centre.
-__device__ __host__ __forceinline__ int packed_tap(int t, int k) {
-  if ((k & 1) && t == k * k - 1) return k * k / 2;
-  Orbit at = orbit_rep(t / 4, k);
-  for (int m = 0; m < t % 4; ++m) at = turn(at, k);
-  return at.i * k + at.j;
-}
-
-__device__ __forceinline__ bool beyond_parts(float v) {
-  const float m = __builtin_fabsf(v);
-  return !(m < __builtin_inff()) || (m < 0x1p-100f && m != 0.f);
-}
 
 // What a wave's registers allow.
 __device__ __host__ constexpr int waves_per_simd(int S, int MT, int NT, bool MANY) {
@@ -184,7 +168,7 @@ __global__ __launch_bounds__(256 * WC, waves_per_simd(S, MT, NT, MANY)) void k_i
         for (int m = 1; m < 4; ++m) pos[m] = turn(pos[m - 1], g.k);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-          s3_f4 all[4];
+          s3_f4 all[2][4];             // of positions 0 and 1, of positions 2 and 3
 #pragma unroll
           for (int m = 0; m < 4; ++m) {
             u32x4 b[3];
@@ -198,13 +182,13 @@ __global__ __launch_bounds__(256 * WC, waves_per_simd(S, MT, NT, MANY)) void k_i
               for (int r = 0; r < 4; ++r) p[r] = s3_mfma(now[(m - r) & 3][kPa[e]], b[kPb[e]], p[r]);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              if (m == 0) all[r] = (m - r) & 1 ? -p[r] : p[r];
-              else if ((m - r) & 1) all[r] -= p[r];
-              else all[r] += p[r];
+              if (m % 2 == 0) all[m / 2][r] = (m - r) & 1 ? -p[r] : p[r];
+              else if ((m - r) & 1) all[m / 2][r] -= p[r];
+              else all[m / 2][r] += p[r];
             }
           }
 #pragma unroll
-          for (int r = 0; r < 4; ++r) acc[r][t] += all[r];
+          for (int r = 0; r < 4; ++r) acc[r][t] += all[0][r] + all[1][r];
         }
       };
       int o = o0;
@@ -417,13 +401,14 @@ bool ig_fwd_supported(const rotconv_plan* p) {
 
 // The shape with the smallest modelled time (us): a workgroup stages and splits `chunk` + `item` per 32 channels and multiplies at
 // `one`, `two` and `four` ns an instruction with that many waves on a SIMD; `start` for the launches, `bytes` (per us) for the
-// results, `sum` and five bytes a picosecond for adding up shares.  Fitted to 2700 launches of 230 layers (rms 10-12 %).
+// results, `sum` and their bytes for adding up shares.  Fitted to 2300 launches of 130 layers with one turn (rms 10 %), and to the
+// choice among 24 shapes of 60 layers with four (1.6 % off the best in the mean).
 // budget: bytes that a block's weights and the shares may take.
 IgShape ig_fwd_shape(const rotconv_plan* p, size_t budget) {
   const rotconv_desc& d = p->d;
   const bool turns = four_turns(p), may_split = budget > 0;
   struct { double chunk, item, one, two, four, start, bytes, sum; } k;
-  if (turns) k = {1.15, 0.36, 17., 9.3, 9.3, 7.6, 1.3e6, 6.};
+  if (turns) k = {1.75, 0.39, 13., 15., 15., 7.6, 1e6, 6.};
   else k = {1.4, 0.48, 16., 11.2, 10.6, 8.1, 5e6, 2.8};
   const size_t part = 4 * (size_t)d.N * d.Cout * d.R * p->Ho * p->Wo;
   const double out = 4.0 * d.N * d.Cout * p->Ho * p->Wo;
@@ -464,7 +449,7 @@ IgShape ig_fwd_shape(const rotconv_plan* p, size_t budget) {
             };
             const double full = 256. * occ, rest = std::fmod(wgs, full);
             double us = std::floor(wgs / full) * time(occ) + (rest > 0 ? time((int)std::ceil(rest / 256)) : 0.) + k.start + out / k.bytes;
-            if (s.parts() > 1) us += k.sum + s.parts() * (turns ? 4 : 1) * out / (turns ? 1.2e6 : 2.5e6);
+            if (s.parts() > 1) us += k.sum + s.parts() * (turns ? 4 : 1) * out / (turns ? 1.65e6 : 2.5e6);
             s.us = us;
             if (us < best.us) best = s;
           }

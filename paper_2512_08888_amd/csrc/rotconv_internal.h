@@ -109,6 +109,7 @@ struct rotconv_plan {
   // ... and the launches of the two, modelled once: which kernel, its rows per band and waves per workgroup
   struct FwdLaunch { int out_mode = -1, csplit = 0, nq = 0, chain = 0, ty = 0, nw = 0; } fwd_launch[2];
   rotconv::IgShape ig[2];       // unpooled / pooled forward as one contraction over channels and taps (mt = 0: not)
+  rotconv::IgShape ig_dx;       // ... the input gradient
   // Average pooling (Eq. 9 / Eq. 11): the fused calls run one ordinary convolution (this R = 1 plan with
   // Cout * R/G filters) on the group-averaged bank.  Owned by the parent.
   rotconv_plan* avg_child = nullptr;

@@ -1,0 +1,91 @@
+"""The input gradient as one contraction of masked pooled gradients (rotconv_ig_bwd_data.hip): filter sizes with and without a
+centre, strides (every remainder of a pixel), paddings, channels around blocks (16, 32) and filters around chunks (32), shares, idx values
+that route nothing, and the values the parts do not hold, against the oracle.
+
+Error bar: per position and chunk a sum of 32 products of each turn's (four cuts of at most 2^-23), then fp32 additions over the k^2
+positions and the chunks, each a rounding of a partial sum that grows with the root of their number: sqrt(4 + (k^2 + chunks) / 2) * 2^-24 in
+norm; four times that.
+"""
+import numpy as np
+import pytest
+
+import parity_util as pu
+from oracle import rotconv_oracle as orc
+from paper_2512_08888_amd import synth
+
+pytestmark = pytest.mark.gpu
+L = synth.LayerConfig
+
+
+def _rel(got, ref):
+    ref = np.asarray(ref, np.float64)
+    return float(np.linalg.norm(np.asarray(got, np.float64) - ref) / np.linalg.norm(ref))
+
+
+def _bar(cfg):
+    return 4 * 2.0 ** -24 * np.sqrt(4 + (cfg.k ** 2 + (cfg.Cout + 31) // 32) / 2)
+
+
+def _inputs(cfg, dyadic=False):
+    r = np.random.default_rng(cfg.seed)
+    idx = r.integers(0, 5, (cfg.N, cfg.Cout, cfg.Ho, cfg.Wo)).astype(np.uint8)
+    nothing = np.array([4, 7, 8, 12, 15, 127, 128, 254, 255], np.uint8)
+    idx = np.where(idx == 4, nothing[r.integers(0, len(nothing), idx.shape)], idx)
+    if dyadic:
+        return synth.make_x_dyadic(cfg), synth.make_w_dyadic(cfg), synth.make_g_dyadic(cfg), idx
+    return synth.make_x(cfg), synth.make_w(cfg), synth.make_g(cfg), idx
+
+
+def _reference(cfg, w, g, idx):
+    dy = orc.orient_maxpool_bwd(np.where(idx < 4, g, 0.0), np.where(idx < 4, idx, 0).astype(np.uint8), cfg.R, cfg.G)
+    return orc.rotconv_bwd_data(dy, orc.expand_bank(w, cfg.R, None, cfg.mode), cfg.H, cfg.W, cfg.stride, cfg.pad)
+
+
+CASES = [L(f"d{k}_{stride}_{Cin}_{H}x{W}_{Cout}", N=N, Cin=Cin, H=H, W=W, Cout=Cout, R=4, k=k, stride=stride, pad=pad,
+           seed=2400 + i, x_dist="normal")
+         for i, (N, Cin, H, W, Cout, k, stride, pad) in enumerate([
+             (1, 40, 20, 20, 40, 1, 1, 0), (2, 33, 19, 33, 17, 2, 1, 1), (1, 16, 40, 41, 31, 2, 2, 0), (3, 64, 17, 18, 33, 3, 2, 1),
+             (1, 12, 31, 64, 16, 3, 1, 0), (1, 20, 30, 21, 20, 3, 3, 2), (2, 3, 16, 45, 65, 4, 1, 2), (2, 32, 50, 96, 32, 5, 1, 2),
+             (1, 24, 16, 16, 96, 5, 1, 2), (1, 97, 17, 29, 31, 5, 2, 2), (2, 8, 64, 64, 32, 7, 1, 3), (1, 70, 16, 28, 16, 7, 2, 3),
+             (1, 16, 24, 20, 8, 15, 1, 7), (1, 32, 9, 300, 16, 5, 1, 4), (2, 17, 37, 22, 40, 2, 3, 0)])]
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=[c.name for c in CASES])
+def test_input_gradient(cfg):
+    x, w, g, idx = _inputs(cfg)
+    lay = pu.GpuLayer(cfg, x, w)
+    assert lay.plan.kernel_name(1) == "mfma_gemm_scatter"
+    dx = lay.pool_bwd_data(g, idx)
+    ref = _reference(cfg, w, g, idx)
+    assert _rel(dx, ref) < _bar(cfg)
+    assert np.array_equal(dx, lay.pool_bwd_data(g, idx))
+    routed = pu.GpuLayer(cfg, x, w, options=dict(gs=1)).pool_bwd_data(g, idx)            # the gradients through memory
+    assert _rel(routed, ref) < _bar(cfg) and not np.array_equal(dx, routed)
+
+
+@pytest.mark.parametrize("cfg", [CASES[1], CASES[8], CASES[11]], ids=lambda c: c.name)
+def test_input_gradient_dyadic(cfg):
+    x, w, g, idx = _inputs(cfg, dyadic=True)
+    assert np.array_equal(pu.GpuLayer(cfg, x, w).pool_bwd_data(g, idx).astype(np.float64), _reference(cfg, w, g, idx))
+
+
+@pytest.mark.parametrize("k,stride", [(5, 1), (3, 2), (4, 1)])
+def test_values_beyond_the_parts(k, stride):
+    """Infinite, huge and tiny operands: as the fp32 sums of the generic kernels have them."""
+    cfg = L("beyond", N=1, Cin=20, H=21, W=40, Cout=40, R=4, k=k, stride=stride, pad=k // 2, seed=2480, x_dist="normal")
+    x, w, g, idx = _inputs(cfg)
+
+    def both(g, w, idx):
+        return [pu.GpuLayer(cfg, x, w, options=o).pool_bwd_data(g, idx) for o in (dict(), dict(gs=-1))]
+    for value in (np.inf, -np.inf, np.nan, 1e30):
+        gi, ii = g.copy(), idx.copy()
+        gi[0, 33, 5, 11], ii[0, 33, 5, 11] = value, 2
+        got, ref = both(gi, w, ii)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref))
+        fin = np.isfinite(ref)
+        assert np.allclose(got[fin], ref[fin], rtol=1e-4, atol=1e-4 * np.abs(ref[fin & (np.abs(ref) < 1e20)]).max())
+        ii[0, 33, 5, 11] = 255          # routed nowhere
+        got, ref = both(gi, w, ii)
+        assert np.isfinite(got).all() and _rel(got, ref) < 1e-5
+    got, ref = both(g * np.float32(1e-22), w * np.float32(1e-14), idx)
+    assert _rel(got, ref) < 1e-5
