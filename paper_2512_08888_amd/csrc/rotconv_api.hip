@@ -166,10 +166,15 @@ void choose_fwd(rotconv_plan* p) {
   p4_fwd_choose_launches(p);
 }
 
-// One contraction over channels and taps instead of products that are placed.  Filters of other sizes and strides with the four
-// quarter turns, pooled: always (60 layers of 12 to 64 channels and filters, k = 2, 5, 7, stride 1 and 2: 0.48 of the time in the
-// mean, 0.14 to 0.78).  Single orientations: where modelled at less than 0.85 of the time of the kernels that place (200 layers of 5
-// to 600 channels and filters: 0.93 in the mean of all with that rule, 0.23 to 1.05; taken everywhere up to 1.3 on large maps).
+// One contraction over channels and taps instead of products that are placed, or of gradients routed through memory.
+// Filters of other sizes and strides with the four quarter turns, pooled, whose products it forms four times as often: 60 layers of
+// 12 to 64 channels and filters, k = 2, 5, 7, stride 1 and 2: forward 0.45, weight gradient 0.49, input gradient 0.31 of the time
+// in the mean, at most 0.78, 0.97 and 0.81.  With a stride always (4x128 -> 128, 128x128, stride 2 429 -> 102, 379 -> 160, 303 -> 144
+// us).  Without, 70 layers of 48 to 400 channels: the forward up to 96 (0.51 to 0.98; 161 and more 0.6 to 1.7), the weight gradient up
+// to 64 with up to 128 filters (0.43 to 0.97; beyond up to 2.0), the input gradient up to 64, and where the other's matrix
+// multiply has fewer tiles (64 x 64) than the chip has CUs (0.10 to 0.91; beyond up to 1.6).
+// Single orientations: where modelled at less than 0.85 of the time of the kernels that place (200 layers of 5 to 600 channels and
+// filters: 0.93 in the mean of all with that rule, 0.23 to 1.05; taken everywhere up to 1.3 on large maps).
 size_t ig_part_bytes(const rotconv_plan* p, const IgShape& s) {
   return s.parts() > 1 ? align256((size_t)s.parts() * p->d.N * p->d.Cout * p->d.R * p->Ho * p->Wo * 4) : 0;
 }
@@ -178,10 +183,17 @@ void choose_ig(rotconv_plan* p) {
   if (p->gs && p->opt.gs == 0) {
     // what rotconv_pool_fwd_static holds wherever it holds the products (behind widened copies that may be less than its array)
     const size_t holds = p->d.dtype == ROTCONV_F32 ? std::max<size_t>(gs_ws_bytes(p), ROTCONV_STATIC_SCRATCH_BYTES) : gs_ws_bytes(p);
-    const IgShape s = ig_fwd_shape(p, holds);
+    const rotconv_desc& d = p->d;
+    const bool strided = d.stride > 1;
+    const IgShape s = strided || d.R == 1 || d.Cin <= 96 ? ig_fwd_shape(p, holds) : IgShape();
     if (s.mt && ig_fwd_block_bytes(p, s) <= holds) p->ig[1] = s;
-    if (p->d.R == 1) p->ig[0] = p->ig[1];
-    if (ig_bwd_data_supported(p)) p->ig_dx = ig_bwd_data_shape(p, (size_t)256 << 20);
+    if (d.R == 1) p->ig[0] = p->ig[1];
+    if ((strided || (d.Cin <= 64 && d.Cout <= 128)) && ig_bwd_weight_supported(p)) {
+      p->ig_dw = 1;
+      p->ws_bytes = std::max(p->ws_bytes, ig_bwd_weight_ws_bytes(p));
+    }
+    const long tiles = (long)((d.Cin + 63) / 64) * ((d.H * d.W + 63) / 64) * d.N;
+    if ((strided || d.Cin <= 64 || tiles < 256) && ig_bwd_data_supported(p)) p->ig_dx = ig_bwd_data_shape(p, (size_t)256 << 20);
     if (p->ig_dx.mt) p->ws_bytes = std::max(p->ws_bytes, ig_bwd_data_ws_bytes(p, p->ig_dx));
   } else if (p->d.R == 1 && p->fast[0] && p->opt.fwd_csplit == 0) {
     const IgShape s = ig_fwd_shape(p, (size_t)64 << 20);
@@ -760,6 +772,10 @@ static int f32_rotconv_pool_bwd_weight(const rotconv_plan* plan, const void* x, 
   if (p->fast[2] && aligned(x, pixels ? 4 : 16) && aligned(gpool, pixels ? 4 : 16) && aligned(idx, pixels ? 1 : 4) && aligned(ws, 16)) {
     launch_p4_bwd_weight(p, static_cast<const float*>(x), static_cast<const float*>(gpool), idx,
                          static_cast<float*>(ws), dw, st);
+    return finish();
+  }
+  if (p->ig_dw && aligned(x, 4) && aligned(gpool, 4) && aligned(ws, 16)) {
+    launch_ig_bwd_weight(p, static_cast<const float*>(x), static_cast<const float*>(gpool), idx, dw, ws, st);
     return finish();
   }
   if (p->gs) {

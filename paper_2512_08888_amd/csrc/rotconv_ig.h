@@ -1,4 +1,5 @@
-// Passes of fp32 layers as one contraction with the four quarter turns apart (rotconv_ig_fwd.hip, rotconv_ig_bwd_data.hip).
+// Passes of fp32 layers as one contraction with the four quarter turns apart (rotconv_ig_fwd.hip, rotconv_ig_bwd_data.hip,
+// rotconv_ig_bwd_weight.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -23,5 +24,12 @@ IgShape ig_bwd_data_shape(const rotconv_plan* p, size_t budget);
 size_t ig_bwd_data_ws_bytes(const rotconv_plan* p, const IgShape& s);       // packed weights and shares
 void launch_ig_bwd_data(const rotconv_plan* p, const IgShape& s, const float* gpool, const uint8_t* idx, const float* w, float* dx,
                         void* ws, hipStream_t st);
+
+
+// Weight gradient of the same layers (k from 2, strides 1 and 2, rows of at least eight outputs).
+bool ig_bwd_weight_supported(const rotconv_plan* p);
+size_t ig_bwd_weight_ws_bytes(const rotconv_plan* p);
+void launch_ig_bwd_weight(const rotconv_plan* p, const float* x, const float* gpool, const uint8_t* idx, float* dw, void* ws,
+                          hipStream_t st);
 
 }  // namespace rotconv

@@ -110,6 +110,7 @@ struct rotconv_plan {
   struct FwdLaunch { int out_mode = -1, csplit = 0, nq = 0, chain = 0, ty = 0, nw = 0; } fwd_launch[2];
   rotconv::IgShape ig[2];       // unpooled / pooled forward as one contraction over channels and taps (mt = 0: not)
   rotconv::IgShape ig_dx;       // ... the input gradient
+  int ig_dw = 0;                // ... the weight gradient
   // Average pooling (Eq. 9 / Eq. 11): the fused calls run one ordinary convolution (this R = 1 plan with
   // Cout * R/G filters) on the group-averaged bank.  Owned by the parent.
   rotconv_plan* avg_child = nullptr;
