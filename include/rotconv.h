@@ -56,7 +56,8 @@
  *     of the others.  fp32 passes that multiply bf16 parts of the operands
  *     (rotconv_plan_bf16_parts) may make NaN of an infinity and of magnitudes from
  *     3.396e38 on, and hold magnitudes below 2^-110 to 2^-134 only.  Of these, the
- *     pooled forward of first layers keeps infinities and large magnitudes, and the
+ *     pooled forward of first layers keeps infinities and large magnitudes, as does
+ *     the forward on base products (options.fwd_base, not counted there), and the
  *     matrix multiply + scatter family and the weight gradient of first layers keep
  *     both and, beside operands up to 2^10, small ones: they form sums that are not
  *     finite or below 2^-100 again in fp32.
@@ -169,7 +170,7 @@ typedef struct {
                            layers with four banks and at most 64 input channels), 1 wherever that kernel can run,
                            -1 never (pixels on the M side, eight pixels per lane)                                   */
   int32_t bf16_parts;   /* fp32 contractions of 3x3 layers as products of the operands' three bf16 parts on the bf16
-                           matrix cores (forward of layers with more than four channels, forward and weight gradient of first layers of
+                           matrix cores (forward of layers with more than four channels, on base products too, forward and weight gradient of first layers of
                            R = 4, gradients of quarter-turn layers, the matrix multiply + scatter family): 0 automatic (where that is the faster form), 1 wherever those kernels can run,
                            -1 never (fp32 matrix instructions: exact products whatever the operands' magnitude)     */
   int32_t reserved[3];  /* must be 0 */
@@ -302,8 +303,8 @@ const char* rotconv_plan_kernel_name(const rotconv_plan* plan, int pass);
 /* 1 if that pass (0 rotconv_pool_fwd, 1 rotconv_pool_bwd_data, 2 rotconv_pool_bwd_weight) multiplies bf16 parts of fp32
  * operands for aligned tensors (see rotconv_plan_options.bf16_parts), else 0.  First layers ("valu_direct") and the matrix
  * multiply + scatter family are among them (its pooled forward answers for the products that are placed: the one contraction that
- * takes their place with R = 4 multiplies parts always); the weight gradient of first layers, which forms every sum beyond the
- * parts' range again in fp32, multiplies parts too but answers 0. */
+ * takes their place with R = 4 multiplies parts always); the weight gradient of first layers and the forward on base
+ * products ("mfma_p4_base"), which form sums beyond the parts' range again in fp32, multiply parts too but answer 0. */
 int rotconv_plan_bf16_parts(const rotconv_plan* plan, int pass);
 
 #ifdef __cplusplus

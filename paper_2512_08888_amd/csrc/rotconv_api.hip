@@ -661,8 +661,7 @@ static int f32_rotconv_pool_fwd(const rotconv_plan* plan, const void* x, const v
       return finish();
     }
     if (p->fwd_base) {     // the pool group spans all banks: products of the base bank, banks combined in the kernel
-      launch_p4_pack_base(p, wf, static_cast<float*>(ws), st);
-      launch_p4_fwd_base(p, xf, static_cast<float*>(ws), yf, idx, st);
+      launch_p4_fwd_base(p, xf, wf, static_cast<float*>(ws), yf, idx, st);
       return finish();
     }
     const int nq = mode == kOutPartial ? p4_fwd_fold(p) : 1;

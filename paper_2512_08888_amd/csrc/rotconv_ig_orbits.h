@@ -19,10 +19,4 @@ __device__ __host__ __forceinline__ int packed_tap(int t, int k) {
   return at.i * k + at.j;
 }
 
-// A sum that bf16 parts (rotconv_split3.h) do not hold: not finite, or below 2^-100 and not zero.
-__device__ __forceinline__ bool beyond_parts(float v) {
-  const float m = __builtin_fabsf(v);
-  return !(m < __builtin_inff()) || (m < 0x1p-100f && m != 0.f);
-}
-
 }  // namespace rotconv

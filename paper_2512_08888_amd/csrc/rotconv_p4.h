@@ -92,10 +92,11 @@ void launch_p4_combine(const rotconv_plan* p, const float* pv, const uint8_t* pi
 // pooled forward on base products (pool group spanning several banks): one conv-equivalent on the matrix cores
 int p4_fwd_base_classify(const rotconv_plan* p, std::vector<float>* coef);   // bank classes (-1: none) and coefficients
 bool p4_fwd_base_supported(const rotconv_plan* p);
-size_t p4_fwd_base_pack_floats(const rotconv_plan* p);
-void launch_p4_pack_base(const rotconv_plan* p, const float* w, float* wt, hipStream_t st);
-void launch_p4_fwd_base(const rotconv_plan* p, const float* x, const float* wt, float* ypool, uint8_t* idx,
+// (wt: room for the base bank's image, at most six bytes a weight padded to whole blocks and chunks)
+void launch_p4_fwd_base(const rotconv_plan* p, const float* x, const float* w, float* wt, float* ypool, uint8_t* idx,
                         hipStream_t st);
+void launch_p4_fwd_base_parts(const rotconv_plan* p, const P4Geom& g, bool stream, const float* x, const float* wt, const float* w,
+                              float* ypool, uint8_t* idx, hipStream_t st);
 
 // forward on bfloat16 tensors (bf16 matrix cores, fp32 accumulation); out_val is bf16 for the pooled and
 // unpooled modes and fp32 for the per-bank candidates

@@ -27,9 +27,34 @@ __global__ __launch_bounds__(256) void k_p4_pack_base(const float* __restrict__ 
   for (int u = 0; u < 9; ++u) dst[u * 16] = in ? src[u] : 0.f;
 }
 
-// LDS beside the filter block: the edge arrays, and with `park` banks' second rolling sums parked there 16 bytes per
-// bank, quarter turn and thread (eight waves)
-size_t base_lds_extra(int park) { return (size_t)2 * 2 * 8 * 144 * 4 + (size_t)park * 4 * 512 * 16; }
+// ... or as bf16 parts, [CB][chunk][tap][part][lane][8]: a thread per (filter, pair of channels) and three taps (blockIdx.y)
+__global__ __launch_bounds__(256) void k_p4_pack_base_parts(const float* __restrict__ w, uint32_t* __restrict__ wt, int CB,
+                                                            int CinPad, int Cin, int Cout) {
+  const int e = blockIdx.x * 256 + threadIdx.x, u0 = blockIdx.y * 3;
+  if (e >= CB * CinPad * 8) return;
+  const int cb = e / (CinPad * 8), i = e % (CinPad * 8);
+  const int co = cb * 16 + i / 4 % 16, ci = i / 64 * 8 + i % 4 * 2;
+  const bool in0 = co < Cout && ci < Cin, in1 = co < Cout && ci + 1 < Cin;
+  const float* s0 = w + ((size_t)(in0 ? co : 0) * Cin + (in0 ? ci : 0)) * 9 + u0;
+  const float* s1 = w + ((size_t)(in1 ? co : 0) * Cin + (in1 ? ci + 1 : 0)) * 9 + u0;
+  uint32_t* dst = wt + (size_t)(e / 256) * kS3FwdChunk + i % 256;
+  float a[3], b[3];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    a[j] = s0[j];
+    b[j] = s1[j];
+  }
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    uint16_t pa[3], pb[3];
+    s3_split_weight(in0 ? a[j] : 0.f, pa[0], pa[1], pa[2]);
+    s3_split_weight(in1 ? b[j] : 0.f, pb[0], pb[1], pb[2]);
+    const uint32_t turn = s3_tap_turned(u0 + j) ? 0x80008000u : 0u;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) dst[((u0 + j) * 3 + k) * 256] = ((uint32_t)pa[k] | (uint32_t)pb[k] << 16) ^ turn;
+  }
+}
+
 bool needs_stream_base(int Cin, int park = 0) { return (size_t)cin_pad_base(Cin) * 576 + base_lds_extra(park) > 160 * 1024; }
 // rows a streamed filter block takes: only those the wave chains cover exactly
 bool stream_rows_ok(int W) { return (W & 15) == 0 && (W > 128 || (W & (W - 1)) == 0); }
@@ -44,15 +69,27 @@ int base_park(const rotconv_plan* p) {
   return 3;
 }
 
+// Products of the operands' bf16 parts (six bytes a weight; up to two resident banks' sums parked: 128 channels of R = 16, 160
+// of R = 8 without streaming) instead of fp32 instructions?  More than four channels always: 34 layers of 13 to 512 channels,
+// 14 to 300 rows and columns, 0.77 of the time in the mean, 0.40 to 0.96, and 0.4 to 0.9 of the error.  Not where an image is
+// so large that the offset that stands for "outside" lies in it.
+bool parts_resident(const rotconv_plan* p) {
+  const int chunks = cin_pad_base(p->d.Cin) / 32;
+  return (size_t)chunks * kS3FwdChunk * 4 + base_lds_extra(parts_park(p->host.Q, chunks)) <= 160 * 1024;
+}
+bool base_on_parts(const rotconv_plan* p) {
+  return p->d.Cin > 4 && p->opt.bf16_parts >= 0 && (size_t)p->d.Cin * p->d.H * p->d.W * 4 <= kOutside;
+}
+
 template <int NWX, int NWY, bool FASTW, bool STREAM, int KC, int NQ, int CLS, int PARK>
 void launch_i(const P4Geom& g, const float* x, const float* wt, const float* coef, const int32_t* rot_of, float* ov,
               uint8_t* oi, hipStream_t st) {
   const size_t wfl = STREAM ? (size_t)2 * KC * 4 * 144 : (size_t)g.cper * KC * 4 * 144;
-  const size_t lds = (wfl + 4 * NWX * NWY * 144) * sizeof(float) + (size_t)PARK * 4 * 64 * NWX * NWY * 16;
+  const size_t lds = wfl * sizeof(float) + base_lds_extra(PARK);
   const int grid = (g.units + 7) / 8 * 8;
   auto kern = k_p4_fwd_base<NWX, NWY, FASTW, STREAM, KC, NQ, CLS, PARK>;
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * NWX * NWY), lds, st, x, wt, coef, rot_of, ov, oi, g);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * NWX * NWY), lds, st, x, wt, nullptr, coef, rot_of, ov, oi, g);
 }
 
 template <int NWX, int NWY, int NQ, int CLS, int PARK>
@@ -80,14 +117,6 @@ void launch_c(const P4Geom& g, bool fastw, bool stream, const float* x, const fl
     default: launch_t<8, 1, NQ, CLS, PARK>(g, fastw, stream, x, wt, coef, rot_of, ov, oi, st); break;
   }
 }
-
-constexpr int cls_pack(int a, int b = 0, int c = 0, int d = 0) { return a | (b << 2) | (c << 4) | (d << 6); }
-// the bank-class lists with a compiled instance
-// (a 45 degree bank falls into the lower class: in fp64 its corner taps' source column comes out just below the
-// cell boundary; other bank lists run the per-bank kernel)
-constexpr int kCls16 = cls_pack(kClsId, kClsLo, kClsLo, kClsHi);     // 0, 22.5, 45, 67.5 degrees (R = 16)
-constexpr int kCls8 = cls_pack(kClsId, kClsLo);                      // 0, 45 degrees (R = 8)
-constexpr int kClsP4m = cls_pack(kClsId, kClsMirror);                // the filter and its mirror image (p4m, R = 8)
 
 bool cls_compiled(int Q, int cls) {
   return (Q == 4 && cls == kCls16) || (Q == 2 && (cls == kCls8 || cls == kClsP4m));
@@ -206,7 +235,8 @@ bool p4_fwd_base_supported(const rotconv_plan* p) {
   if (p->ng != 1 || p->opt.fwd_base < 0) return false;
   if ((d.W & 1) || (d.W > 128 && (d.W & 15))) return false;
   if ((double)d.Cin * d.H * d.W >= 1073741824.0) return false;     // 32-bit element offsets inside an image
-  // a streamed filter block: only rows that the wave chains cover exactly
+  // a filter block that the fp32 instructions would stream: only rows that the wave chains cover exactly (on parts, masked, 0.69
+  // to 1.55 of the per-bank kernel's time: 4x256 -> 64, 48x48, R = 16 123 -> 85 us, 1x600 -> 40, 60x34, R = 8 68 -> 105)
   if (needs_stream_base(d.Cin) && !stream_rows_ok(d.W)) return false;
   const int Q = p->host.Q;
   for (int i = 0; i < Q * 4; ++i)
@@ -215,21 +245,19 @@ bool p4_fwd_base_supported(const rotconv_plan* p) {
   return cls >= 0 && cls_compiled(Q, cls);
 }
 
-size_t p4_fwd_base_pack_floats(const rotconv_plan* p) {
-  return (size_t)((p->d.Cout + 15) / 16) * cin_pad_base(p->d.Cin) * 144;
-}
-
-void launch_p4_pack_base(const rotconv_plan* p, const float* w, float* wt, hipStream_t st) {
-  const int CinPad = cin_pad_base(p->d.Cin), CB = (p->d.Cout + 15) / 16;
-  const int total = CB * CinPad * 16;
-  hipLaunchKernelGGL(k_p4_pack_base, dim3((total + 255) / 256), dim3(256), 0, st, w, wt, CB, CinPad, p->d.Cin,
-                     p->d.Cout);
-}
-
-void launch_p4_fwd_base(const rotconv_plan* p, const float* x, const float* wt, float* ypool, uint8_t* idx,
+void launch_p4_fwd_base(const rotconv_plan* p, const float* x, const float* w, float* wt, float* ypool, uint8_t* idx,
                         hipStream_t st) {
   P4Geom gs[8];
   const int ng = base_geoms(p, gs, 8);
+  const int CinPad = cin_pad_base(p->d.Cin), CB = (p->d.Cout + 15) / 16;
+  if (base_on_parts(p)) {
+    hipLaunchKernelGGL(k_p4_pack_base_parts, dim3((CB * CinPad * 8 + 255) / 256, 3), dim3(256), 0, st, w,
+                       reinterpret_cast<uint32_t*>(wt), CB, CinPad, p->d.Cin, p->d.Cout);
+    for (int i = 0; i < ng; ++i) launch_p4_fwd_base_parts(p, gs[i], !parts_resident(p), x, wt, w, ypool, idx, st);
+    return;
+  }
+  hipLaunchKernelGGL(k_p4_pack_base, dim3((CB * CinPad * 16 + 255) / 256), dim3(256), 0, st, w, wt, CB, CinPad, p->d.Cin,
+                     p->d.Cout);
   const int park = base_park(p);
   const bool stream = needs_stream_base(p->d.Cin, park);
   const int cls = p->fwd_base_cls;

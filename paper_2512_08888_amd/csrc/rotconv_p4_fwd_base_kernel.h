@@ -6,8 +6,8 @@
 // the bilinear table of this build; a tap permutation for the mirror image of the p4m group), so its per-tap
 // channel contractions are the same linear map of the base bank's nine:
 //     P^q_t[co, h, x] = sum_u E_q[t][u] P_u[co, h, x],      P_u = sum_ci w[co,ci,u] X[ci,h,x].
-// The matrix cores therefore run ONE conv-equivalent (v_mfma_f32_16x16x4_f32, M = 16 pixels, N = 16 filters,
-// K = 4 channels) whatever the number of orientations; the banks' products are formed from the base products on
+// The matrix cores therefore run ONE conv-equivalent (M = 16 pixels, N = 16 filters; six bf16 products of the operands'
+// parts, K = 32 channels, or v_mfma_f32_16x16x4_f32) whatever the number of orientations; the banks' products are formed from the base products on
 // the vector ALU (at most four multiply-adds per tap: 0 for the centre, 2 for a corner, 4 for an edge tap of a
 // bilinear bank) and placed at their four quarter-turn positions (Eq. 8) exactly as in the single-bank kernel:
 //     Y_(q,s)[co, y, x] = sum_t P^q_t[co, y + i_s(t) - 1, x + j_s(t) - 1].
@@ -15,6 +15,15 @@
 // partial sums of all R orientations (2 R registers per pixel) stay in registers beside the products; a wave covers
 // 16 pixels x 16 filters of a row and walks down its band.  The maximum over all R orientations and its arg-max
 // (Eq. 10) are taken in the lane; nothing R-fold, and no per-bank candidate, reaches memory.
+//
+// What bounds it: about 2100 vector instructions per 16 pixels and row at R = 16 (1.67 ns each, 131 of the 218 us of
+// 4x128 -> 128, 128x128).  The fp32 instructions leave no room for vector instructions beside them and took 138 us of 283; as
+// parts the products take 60, and the reads of the weights' parts (27 x 1 KB a chunk and wave) 100 of the LDS' time.  4x64 -> 64,
+// 128x128, R = 8: 78 -> 53 us.  A sum that is not finite, or a lane's largest below 2^-100, has its wave form the row again on
+// the fp32 instruction and replace such sums, so that infinities and large magnitudes come out as there; the look costs 36 of the
+// instructions.
+// Parked sums count: with two banks parked instead of one 2x64 -> 64, 256x256 199 -> 179 us, streamed 2x256 -> 256, 64x64
+// 162 -> 138; 128 channels resident with one bank parked 220, streamed with two 235.
 //
 // The nnz pattern of E_q is compiled in (a bank is an identity, a mirror image, or a bilinear turn by less /
 // more than 45 degrees: the 2 x 2 source cell of every tap is fixed inside each of these classes); the plan's
@@ -27,6 +36,7 @@
 
 #include "rotconv_p4.h"
 #include "rotconv_p4_taps.h"
+#include "rotconv_split3.h"
 
 namespace rotconv {
 namespace {
@@ -55,7 +65,22 @@ __host__ __device__ constexpr int pat_src(int cls, int t, int e) {
   return (rr >= 0 && rr < 3 && cc >= 0 && cc < 3) ? rr * 3 + cc : -1;
 }
 
-int cin_pad_base(int Cin) { return Cin <= 4 ? 4 : (Cin + 31) / 32 * 32; }
+inline int cin_pad_base(int Cin) { return Cin <= 4 ? 4 : (Cin + 31) / 32 * 32; }
+
+// LDS beside the filter block: the edge arrays and zeros, and with `park` banks' second rolling sums parked there 16 bytes per
+// bank, quarter turn and thread (eight waves)
+inline size_t base_lds_extra(int park) { return (size_t)(2 * 2 * 8 + 1) * 144 * 4 + (size_t)park * 4 * 512 * 16; }
+// ... on parts, with a resident block of `chunks` (0: streamed): as many of four banks as fit, up to two
+constexpr int parts_park(int Q, int chunks) { return Q != 4 ? 0 : chunks <= 2 ? 2 : 1; }
+
+constexpr int cls_pack(int a, int b = 0, int c = 0, int d = 0) { return a | (b << 2) | (c << 4) | (d << 6); }
+// the bank-class lists with a compiled instance
+// (a 45 degree bank falls into the lower class: in fp64 its corner taps' source column comes out just below the
+// cell boundary; other bank lists run the per-bank kernel)
+constexpr int kCls16 = cls_pack(kClsId, kClsLo, kClsLo, kClsHi);     // 0, 22.5, 45, 67.5 degrees (R = 16)
+constexpr int kCls8 = cls_pack(kClsId, kClsLo);                      // 0, 45 degrees (R = 8)
+constexpr int kClsP4m = cls_pack(kClsId, kClsMirror);                // the filter and its mirror image (p4m, R = 8)
+
 
 // FASTW:  W % 4 == 0 and no wave chain reaches beyond the row: no load masks, vector stores.
 // STREAM: the filter block does not fit LDS: streamed in 32-channel chunks (double buffered).
@@ -64,21 +89,24 @@ int cin_pad_base(int Cin) { return Cin <= 4 ? 4 : (Cin + 31) / 32 * 32; }
 // PARK:   banks (the last PARK of them) whose second rolling sum lives in LDS between the row that starts it and the
 //         row that continues it, a lane's own slots ([bank][quarter turn][thread] x four pixels): 16 PARK registers
 //         less to keep across the channel loop.
-template <int NWX, int NWY, bool FASTW, bool STREAM, int KC, int NQ, int CLS, int PARK>
+// S3:     products of the operands' bf16 parts (rotconv_split3.h; chunks of 32 channels, KC is 8), else fp32 instructions.
+template <int NWX, int NWY, bool FASTW, bool STREAM, int KC, int NQ, int CLS, int PARK, bool S3 = false>
 __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __restrict__ x,
                                                                 const float* __restrict__ wt,
+                                                                [[maybe_unused]] const float* __restrict__ wbase,
                                                                 const float* __restrict__ coef,
                                                                 const int32_t* __restrict__ rot_of,
                                                                 float* __restrict__ out_val,
                                                                 uint8_t* __restrict__ out_idx, P4Geom g) {
   constexpr int NW = NWX * NWY;
   constexpr int NT = 64 * NW;
-  constexpr int CHF = KC * 4 * 144;      // floats of one chunk of the filter block
+  constexpr int CHF = S3 ? kS3FwdChunk : KC * 4 * 144;      // words of one chunk of the filter block
   extern __shared__ float smem[];
-  float* Wl = smem;                      // resident: [CinPad][9][16]; streamed: [2][32][9][16]
+  float* Wl = smem;                      // resident: [CinPad][9][16]; streamed: [2][32][9][16]; S3: [chunk][9][part][lane][4]
   float* EL = smem + (STREAM ? 2 * CHF : g.cper * CHF);    // [2][NW][9][16] left-edge products of every wave
   float* ER = EL + 2 * NW * 144;         // [2][NW][9][16] right-edge products
-  f4* PK = reinterpret_cast<f4*>(ER + 2 * NW * 144) + threadIdx.x;   // [PARK][4][NT] parked sums, this thread's column
+  float* EZ = ER + 2 * NW * 144;         // [9][16] zeros: what lies beyond either end of a chain
+  f4* PK = reinterpret_cast<f4*>(EZ + 144) + threadIdx.x;   // [PARK][4][NT] parked sums, this thread's column
 
   // XCD-aware unit decode: consecutive units (same image rows, different filter blocks) share an XCD's L2.
   const int per_xcd = (g.units + 7) / 8;
@@ -91,7 +119,8 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
   const int n = v / g.nbg;
 
   const int tid = threadIdx.x;
-  const float* wsrc = wt + ((size_t)cb * g.CinPad) * 144;
+  if (tid < 144) EZ[tid] = 0.f;
+  const float* wsrc = wt + (size_t)cb * nchunk * CHF;
   constexpr int WPT = (CHF / 4 + NT - 1) / NT;   // float4 per thread and chunk when streaming
   f4 wreg[STREAM ? WPT : 1];
   // a staging load = wave-uniform base (filter block, chunk, slot: scalar arithmetic) + the thread's 32-bit byte offset
@@ -176,13 +205,35 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
   for (int r = 0; r < PARK * 4; ++r) PK[r * NT] = f4{0.f, 0.f, 0.f, 0.f};    // read back by this thread only
 
   float a_cur[KC];
-  {
+  // S3: lane (lc, lg) reads channels 32 c + 8 lg + j, j = 0 .. 7, of its pixel: a lane offset and a uniform one, which stays
+  // inside the image; lanes whose channel or pixel does not exist read zero.
+  const uint32_t HW4 = (uint32_t)HW * 4u;
+  const auto rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(xn), 0, (int)((uint32_t)g.Cin * HW4), 0x27000);
+  const uint32_t lane8 = px_ok ? (uint32_t)lg * 8u * HW4 + (uint32_t)pxa * 4u : kOutside;
+  [[maybe_unused]] auto load_chunk = [&](uint32_t rp, int c) {
+    c = __builtin_amdgcn_readfirstlane(c);
+    const uint32_t row4 = __builtin_amdgcn_readfirstlane(rp) * 4u;
+    if (c * 32 + 32 <= g.Cin) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        a_cur[j % KC] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rx, lane8, row4 + (uint32_t)(c * 32 + j) * HW4, 0));
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int ch = c * 32 + j;
+        a_cur[j % KC] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rx, ch + 8 * lg < g.Cin ? lane8 : kOutside, row4 + (uint32_t)min(ch, g.Cin - 1) * HW4, 0));
+      }
+    }
+  };
+  if constexpr (S3) {
+    load_chunk(row_ptr(0), 0);
+  } else {
     const uint32_t rp = row_ptr(0);
 #pragma unroll
     for (int ks = 0; ks < KC; ++ks) a_cur[ks] = load_a(rp, ks);
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
-  const float* wl_lane = Wl + lg * 144 + lc;
+  const float* wl_lane = S3 ? Wl + lane * 4 : Wl + lg * 144 + lc;
   int seq = 0;                           // chunk steps done (streaming: LDS buffer parity)
 
   for (int t = 0; t < nsteps; ++t) {
@@ -226,9 +277,68 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
       }
       ++seq;
     };
+    // The same on parts: the chunk's pixels are split, the next chunk's loads go out, then tap by tap six products from zero,
+    // the smallest first, whose sum meets the running one while the next tap multiplies.
+    [[maybe_unused]] auto chunk_parts = [&](int c, bool first) {
+      const bool last = c + 1 == nchunk;
+      if (STREAM) wload(last ? 0 : c + 1);
+      u32x4 ap[3];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const S3Pair s = s3_split2(a_cur[2 * i % KC], a_cur[(2 * i + 1) % KC]);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) ap[e][i] = s.p[e];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      load_chunk(last ? rp_nxt : rp_cur, last ? 0 : c + 1);
+      const u32x4* wc = reinterpret_cast<const u32x4*>(wl_lane + (size_t)(STREAM ? seq & 1 : c) * CHF);
+      u32x4 wv[2][3];
+#pragma unroll
+      for (int e = 0; e < 3; ++e) wv[0][e] = wc[e * 64];
+      f4 before;
+#pragma unroll
+      for (int u = 0; u < 9; ++u) {
+        if (u + 1 < 9) {
+#pragma unroll
+          for (int e = 0; e < 3; ++e) wv[(u + 1) & 1][e] = wc[((u + 1) * 3 + e) * 64];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const u32x4* w = wv[u & 1];
+        f4 t = s3_mfma(ap[2], w[0], f4{0.f, 0.f, 0.f, 0.f});
+        t = s3_mfma(ap[0], w[2], t);
+        t = s3_mfma(ap[1], w[1], t);
+        t = s3_mfma(ap[0], w[1], t);
+        t = s3_mfma(ap[1], w[0], t);
+        t = s3_mfma(ap[0], w[0], t);
+        if (first) {
+          P[u] = t;
+        } else {
+          if (u > 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) P[u - 1][i] += before[i];
+          }
+          before = t;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (!first) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) P[8][i] += before[i];
+      }
+      if (STREAM) {
+        wstore((seq + 1) & 1);
+        __syncthreads();
+      }
+      ++seq;
+    };
     if (live) {
-      chunk(0, true);
-      for (int c = 1; c < nchunk; ++c) chunk(c, false);
+      if constexpr (S3) {
+        chunk_parts(0, true);
+        for (int c = 1; c < nchunk; ++c) chunk_parts(c, false);
+      } else {
+        chunk(0, true);
+        for (int c = 1; c < nchunk; ++c) chunk(c, false);
+      }
     } else if (STREAM) {
       for (int c = 0; c < nchunk; ++c) {
         wload(c + 1 == nchunk ? 0 : c + 1);
@@ -241,6 +351,39 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
       asm volatile("" ::: "memory");       // keeps this a branch
 #pragma unroll
       for (int u = 0; u < 9; ++u) P[u] = f4{0.f, 0.f, 0.f, 0.f};
+    }
+    if constexpr (S3) {
+      // Sums that the parts do not hold: one of the lane's is not finite, or its largest is below 2^-100.  As integers floats
+      // of one sign are in order, so the largest signed and the largest unsigned number say both for two signs.
+      int top = INT32_MIN;
+      uint32_t utop = 0;
+#pragma unroll
+      for (int u = 0; u < 9; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float v = P[u][i];      // (a vector's element, cast as it stands, is its first)
+          top = max(top, __builtin_bit_cast(int, v));
+          utop = max(utop, __builtin_bit_cast(uint32_t, v));
+        }
+      const uint32_t mag = max((uint32_t)max(top, 0), utop >> 31 ? utop & 0x7fffffffu : 0u);
+      if (__any(mag >= 0x7f800000u || (mag != 0u && mag < 0x0d800000u))) {      // such sums of the row again on the fp32 instruction
+        const bool fil = cb * 16 + lc < g.Cout;
+        const float* wr = wbase + (size_t)(fil ? cb * 16 + lc : 0) * g.Cin * 9;
+#pragma unroll
+        for (int u = 0; u < 9; ++u) {
+          f4 t = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+          for (int k = 0; k < g.Cin; k += 4) {
+            const int ci = k + lg;
+            const bool in = ci < g.Cin;
+            const float av = in && px_ok ? xn[(size_t)ci * HW + rp_cur + lane_px] : 0.f;
+            const float wr1 = wr[(in ? ci : 0) * 9 + u], wv = in && fil ? wr1 : 0.f;
+            t = __builtin_amdgcn_mfma_f32_16x16x4f32(av, s3_tap_turned(u) ? -wv : wv, t, 0, 0, 0);
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) P[u][i] = beyond_parts(P[u][i]) ? t[i] : P[u][i];
+        }
+      }
     }
 
     // ---- base products of the neighbouring pixels (all nine taps: a bank's edge taps draw on the centre) ------
@@ -269,16 +412,21 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
     }
     __syncthreads();
     if (NWX > 1) {
-      const float* eln = EL + (par * NW + wave + 1) * 144 + lc;  // right neighbour's left edge
-      const float* erp = ER + (par * NW + wave - 1) * 144 + lc;  // left neighbour's right edge
+      // right neighbour's left edge, left neighbour's right edge; zeros at the ends of the chain.  (A choice of value instead of
+      // address becomes a branch per read that waits for it: eighteen LDS latencies a row.)
+      const float* eln = (wx + 1 < NWX ? EL + (par * NW + wave + 1) * 144 : EZ) + lc;
+      const float* erp = (wx > 0 ? ER + (par * NW + wave - 1) * 144 : EZ) + lc;
       const bool at_r = lg == 3, at_l = lg == 0;
-      const bool has_r = wx + 1 < NWX, has_l = wx > 0;
+      float vr[9], vl[9];
 #pragma unroll
       for (int u = 0; u < 9; ++u) {
-        const float vr = has_r ? eln[u * 16] : 0.f;
-        const float vl = has_l ? erp[u * 16] : 0.f;
-        nbR[u] = at_r ? vr : nbR[u];
-        nbL[u] = at_l ? vl : nbL[u];
+        vr[u] = eln[u * 16];
+        vl[u] = erp[u * 16];
+      }
+#pragma unroll
+      for (int u = 0; u < 9; ++u) {
+        nbR[u] = at_r ? vr[u] : nbR[u];
+        nbL[u] = at_l ? vl[u] : nbL[u];
       }
     } else {
 #pragma unroll
@@ -288,7 +436,10 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
       }
     }
     // base product of tap u at the lane's pixel jj in -1 .. 4
-    auto pe = [&](int u, int jj) -> float { return jj < 0 ? nbL[u] : jj > 3 ? nbR[u] : P[u][jj]; };
+    auto pe = [&](int u, int jj) -> float {
+      const float v = jj < 0 ? nbL[u] : jj > 3 ? nbR[u] : P[u][jj];
+      return S3 && s3_tap_turned(u) ? -v : v;
+    };
 
     // ---- per bank: its products from the base products, placed at the four quarter-turn positions (Eq. 8),
     //      maximum over its four orientations; then the maximum across the banks (Eq. 10) ------------------------
@@ -306,7 +457,6 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
       constexpr bool parked = q >= NKEEP;
       // a parked bank's second sums of the previous row: read at the head of the bank's section, used pixel by pixel
       f4 pB[4];
-      f4 nB[4];
       if constexpr (parked) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) pB[s] = PK[((q - NKEEP) * 4 + s) * NT];
@@ -363,7 +513,7 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
           const float yfin = accA[r][j] + tr[2];   // rows h-2, h-1, h are in: output row h-1 done
           if constexpr (parked) {
             accA[r][j] = pB[s][j] + tr[1];
-            nB[s][j] = tr[0];
+            pB[s][j] = tr[0];                        // (in their place: output row h+1's)
           } else {
             accA[r][j] = accB[r][j] + tr[1];       // output row h has rows h-1, h
             accB[r][j] = tr[0];                    // output row h+1 has row h
@@ -383,14 +533,17 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
           besti[j] = bi;
         } else {
           // across banks an equal value wins only with the smaller orientation index (ties: the smallest r)
-          const bool take = bv > best[j] || (bv == best[j] && bi < besti[j]);
+          // (four banks: in one run of instructions without this branch the compiler spills 175 registers instead of 59)
+          bool take;
+          if constexpr (NQ == 2) take = (bv > best[j]) | ((bv == best[j]) & (bi < besti[j]));
+          else take = bv > best[j] || (bv == best[j] && bi < besti[j]);
           best[j] = take ? bv : best[j];
           besti[j] = take ? bi : besti[j];
         }
       }
       if constexpr (parked) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) PK[((q - NKEEP) * 4 + s) * NT] = nB[s];
+        for (int s = 0; s < 4; ++s) PK[((q - NKEEP) * 4 + s) * NT] = pB[s];
       }
     };
     bank(std::integral_constant<int, 0>{});

@@ -108,6 +108,12 @@ __device__ __forceinline__ s3_f16 s3_mfma32(u32x4 a, u32x4 b, s3_f16 c) {
 // products are subtracted where they are placed: the offsets cancel (five taps against four).
 __device__ __host__ constexpr bool s3_tap_turned(int u) { return u & 1; }
 
+// A sum that the parts do not hold: not finite, or below 2^-100 and not zero.
+__device__ __forceinline__ bool beyond_parts(float v) {
+  const float m = __builtin_fabsf(v);
+  return !(m < __builtin_inff()) || (m < 0x1p-100f && m != 0.f);
+}
+
 // Byte offset of positions outside an image in loads through its buffer descriptor: beyond the descriptor's size (the
 // kernels' limits on an image see to that), so that they read as zero.
 constexpr uint32_t kOutside = 0xfffffff0u;
