@@ -16,14 +16,14 @@
 // 16 pixels x 16 filters of a row and walks down its band.  The maximum over all R orientations and its arg-max
 // (Eq. 10) are taken in the lane; nothing R-fold, and no per-bank candidate, reaches memory.
 //
-// What bounds it: about 2100 vector instructions per 16 pixels and row at R = 16 (1.67 ns each, 131 of the 218 us of
+// What bounds it: about 2100 vector instructions per 16 pixels and row at R = 16 (1.67 ns each, 131 of the 213 us of
 // 4x128 -> 128, 128x128).  The fp32 instructions leave no room for vector instructions beside them and took 138 us of 283; as
 // parts the products take 60, and the reads of the weights' parts (27 x 1 KB a chunk and wave) 100 of the LDS' time.  4x64 -> 64,
-// 128x128, R = 8: 78 -> 53 us.  A sum that is not finite, or a lane's largest below 2^-100, has its wave form the row again on
+// 128x128, R = 8: 77 -> 58 us.  A sum that is not finite, or a lane's largest below 2^-100, has its wave form the row again on
 // the fp32 instruction and replace such sums, so that infinities and large magnitudes come out as there; the look costs 36 of the
 // instructions.
-// Parked sums count: with two banks parked instead of one 2x64 -> 64, 256x256 199 -> 179 us, streamed 2x256 -> 256, 64x64
-// 162 -> 138; 128 channels resident with one bank parked 220, streamed with two 235.
+// Parked sums count: with two banks parked instead of one 2x64 -> 64, 256x256 took 0.90 of the time, streamed 2x256 -> 256, 64x64
+// 0.85; 128 channels streamed with two 1.07 of resident with one.
 //
 // The nnz pattern of E_q is compiled in (a bank is an identity, a mirror image, or a bilinear turn by less /
 // more than 45 degrees: the 2 x 2 source cell of every tap is fixed inside each of these classes); the plan's
@@ -87,7 +87,7 @@ constexpr int kClsP4m = cls_pack(kClsId, kClsMirror);                // the filt
 // KC:     K-steps (of 4 channels) per prefetch chunk: 8, or 1 for layers with at most 4 input channels.
 // NQ:     banks; CLS: their classes, two bits each.
 // PARK:   banks (the last PARK of them) whose second rolling sum lives in LDS between the row that starts it and the
-//         row that continues it, a lane's own slots ([bank][quarter turn][thread] x four pixels): 16 PARK registers
+//         row that continues it, a lane's own slots of four floats ([bank][quarter turn or pixel][thread]): 16 PARK registers
 //         less to keep across the channel loop.
 // S3:     products of the operands' bf16 parts (rotconv_split3.h; chunks of 32 channels, KC is 8), else fp32 instructions.
 template <int NWX, int NWY, bool FASTW, bool STREAM, int KC, int NQ, int CLS, int PARK, bool S3 = false>
@@ -100,6 +100,11 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
                                                                 uint8_t* __restrict__ out_idx, P4Geom g) {
   constexpr int NW = NWX * NWY;
   constexpr int NT = 64 * NW;
+  // Parked sums as [bank][pixel][thread] x four quarter turns, of which a pixel's are held at a time, or as
+  // [bank][quarter turn][thread] x four pixels, a bank's at a time.  By the pixel where registers are short: what is spilled goes
+  // through memory (4x128 -> 128, 128x128: 59 registers, 176 MB a launch), 226 -> 213 us, streamed 2x256 -> 256, 64x64
+  // 140 -> 134; with two banks parked and a resident block the reads' waits cost more (2x64 -> 64, 256x256 191 / 195).
+  constexpr bool BY_PIXEL = S3 && (STREAM || PARK == 1);
   constexpr int CHF = S3 ? kS3FwdChunk : KC * 4 * 144;      // words of one chunk of the filter block
   extern __shared__ float smem[];
   float* Wl = smem;                      // resident: [CinPad][9][16]; streamed: [2][32][9][16]; S3: [chunk][9][part][lane][4]
@@ -455,9 +460,8 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
       constexpr int c = cls_of(CLS, q);
       constexpr bool turned = c == kClsLo || c == kClsHi;
       constexpr bool parked = q >= NKEEP;
-      // a parked bank's second sums of the previous row: read at the head of the bank's section, used pixel by pixel
-      f4 pB[4];
-      if constexpr (parked) {
+      [[maybe_unused]] f4 pB[4];
+      if constexpr (parked && !BY_PIXEL) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) pB[s] = PK[((q - NKEEP) * 4 + s) * NT];
       }
@@ -489,6 +493,9 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
+        // a parked bank's second sums of the previous row at this pixel, one per quarter turn
+        [[maybe_unused]] f4 pJ;
+        if constexpr (parked && BY_PIXEL) pJ = PK[((q - NKEEP) * 4 + j) * NT];
         if constexpr (turned) column(j + 1, Wn[(j + 2) % 3]);
         auto val = [&](int tt, int jj) -> float {
           if constexpr (c == kClsId) return pe(tt, jj);
@@ -512,8 +519,13 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
           }
           const float yfin = accA[r][j] + tr[2];   // rows h-2, h-1, h are in: output row h-1 done
           if constexpr (parked) {
-            accA[r][j] = pB[s][j] + tr[1];
-            pB[s][j] = tr[0];                        // (in their place: output row h+1's)
+            if constexpr (BY_PIXEL) {
+              accA[r][j] = pJ[s] + tr[1];
+              pJ[s] = tr[0];                         // (in their place: output row h+1's)
+            } else {
+              accA[r][j] = pB[s][j] + tr[1];
+              pB[s][j] = tr[0];
+            }
           } else {
             accA[r][j] = accB[r][j] + tr[1];       // output row h has rows h-1, h
             accB[r][j] = tr[0];                    // output row h+1 has row h
@@ -528,6 +540,7 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
             bi = gt ? rot[r] : bi;
           }
         }
+        if constexpr (parked && BY_PIXEL) PK[((q - NKEEP) * 4 + j) * NT] = pJ;
         if (q == 0) {
           best[j] = bv;
           besti[j] = bi;
@@ -541,7 +554,7 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
           besti[j] = take ? bi : besti[j];
         }
       }
-      if constexpr (parked) {
+      if constexpr (parked && !BY_PIXEL) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) PK[((q - NKEEP) * 4 + s) * NT] = pB[s];
       }
