@@ -69,10 +69,10 @@ int base_park(const rotconv_plan* p) {
   return 3;
 }
 
-// Products of the operands' bf16 parts (six bytes a weight; up to two resident banks' sums parked: 128 channels of R = 16, 160
+// Products of the operands' bf16 parts (six bytes a weight; up to three banks' sums parked: 128 channels of R = 16, 160
 // of R = 8 without streaming) instead of fp32 instructions?  More than four channels always: 34 layers of 13 to 512 channels,
-// 14 to 300 rows and columns, 0.79 of the time in the mean, 0.27 to 1.02 (shallow layers, which the vector ALU bounds either way,
-// 0.91 to 1.02), and 0.37 to 0.86 of the error.  Not where an image is
+// 14 to 300 rows and columns, 0.78 of the time in the mean, 0.28 to 1.00 (shallow layers, which the vector ALU bounds either way,
+// 0.91 to 1.00), and 0.37 to 0.86 of the error.  Not where an image is
 // so large that the offset that stands for "outside" lies in it.
 bool parts_resident(const rotconv_plan* p) {
   const int chunks = cin_pad_base(p->d.Cin) / 32;

@@ -23,7 +23,7 @@
 // the fp32 instruction and replace such sums, so that infinities and large magnitudes come out as there; the look costs 36 of the
 // instructions.
 // Parked sums count: with two banks parked instead of one 2x64 -> 64, 256x256 took 0.90 of the time, streamed 2x256 -> 256, 64x64
-// 0.85; 128 channels streamed with two 1.07 of resident with one.
+// 0.85; with three 8x23 -> 87, 274x128 496 -> 476 us; 128 channels streamed with two 1.07 of resident with one.
 //
 // The nnz pattern of E_q is compiled in (a bank is an identity, a mirror image, or a bilinear turn by less /
 // more than 45 degrees: the 2 x 2 source cell of every tap is fixed inside each of these classes); the plan's
@@ -70,8 +70,8 @@ inline int cin_pad_base(int Cin) { return Cin <= 4 ? 4 : (Cin + 31) / 32 * 32; }
 // LDS beside the filter block: the edge arrays and zeros, and with `park` banks' second rolling sums parked there 16 bytes per
 // bank, quarter turn and thread (eight waves)
 inline size_t base_lds_extra(int park) { return (size_t)(2 * 2 * 8 + 1) * 144 * 4 + (size_t)park * 4 * 512 * 16; }
-// ... on parts, with a resident block of `chunks` (0: streamed): as many of four banks as fit, up to two
-constexpr int parts_park(int Q, int chunks) { return Q != 4 ? 0 : chunks <= 2 ? 2 : 1; }
+// ... on parts, with a resident block of `chunks` (0: streamed): as many of four banks as fit
+constexpr int parts_park(int Q, int chunks) { return Q != 4 ? 0 : chunks == 1 ? 3 : chunks <= 2 ? 2 : 1; }
 
 constexpr int cls_pack(int a, int b = 0, int c = 0, int d = 0) { return a | (b << 2) | (c << 4) | (d << 6); }
 // the bank-class lists with a compiled instance

@@ -26,13 +26,16 @@ void go(const P4Geom& g, const Args& a, hipStream_t st) {
 
 template <int NWX, int NWY, int NQ, int CLS>
 void go_rows(const P4Geom& g, bool whole, bool stream, const Args& a, hipStream_t st) {
-  constexpr int deep = parts_park(NQ, 4), flat = parts_park(NQ, 2);
+  constexpr int deep = parts_park(NQ, 4), flat = parts_park(NQ, 2), one = parts_park(NQ, 1);
   if (stream) {
     if (whole) go<NWX, NWY, true, true, NQ, CLS, parts_park(NQ, 0)>(g, a, st);
     else go<NWX, NWY, false, true, NQ, CLS, parts_park(NQ, 0)>(g, a, st);
   } else if (parts_park(NQ, g.cper) == deep) {
     if (whole) go<NWX, NWY, true, false, NQ, CLS, deep>(g, a, st);
     else go<NWX, NWY, false, false, NQ, CLS, deep>(g, a, st);
+  } else if (parts_park(NQ, g.cper) == one) {
+    if (whole) go<NWX, NWY, true, false, NQ, CLS, one>(g, a, st);
+    else go<NWX, NWY, false, false, NQ, CLS, one>(g, a, st);
   } else {
     if (whole) go<NWX, NWY, true, false, NQ, CLS, flat>(g, a, st);
     else go<NWX, NWY, false, false, NQ, CLS, flat>(g, a, st);

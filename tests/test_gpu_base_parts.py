@@ -1,5 +1,5 @@
 """The pooled forward on products of the base bank as bf16 parts (rotconv_p4_fwd_base_kernel.h): chunks of 32 channels, blocks of 16
-filters, resident (one or two banks' sums parked) and streamed, whole rows and rows with masks, every chain length, and the values
+filters, resident (one to three banks' sums parked) and streamed, whole rows and rows with masks, every chain length, and the values
 the parts do not hold, against the oracle and the fp32 instructions (plan option bf16_parts = -1).
 
 Error bar: a chunk's products are one cut sum, the chunks', the bank's (up to four base products) and the nine taps' sums are
