@@ -175,10 +175,14 @@ void choose_fwd(rotconv_plan* p) {
 // multiply has fewer tiles (64 x 64) than the chip has CUs (0.10 to 0.91; beyond up to 1.6).
 // Single orientations: where modelled at less than 0.85 of the time of the kernels that place (200 layers of 5 to 600 channels and
 // filters: 0.93 in the mean of all with that rule, 0.23 to 1.05; taken everywhere up to 1.3 on large maps).
+// averaged: the plan of an averaged bank (or its padded one), whose forward is the one that the call without a workspace runs: on the
+// kernels that place, whose scratch is small.
 size_t ig_part_bytes(const rotconv_plan* p, const IgShape& s) {
   return s.parts() > 1 ? align256((size_t)s.parts() * p->d.N * p->d.Cout * p->d.R * p->Ho * p->Wo * 4) : 0;
 }
-void choose_ig(rotconv_plan* p) {
+// ... and the least that either forward makes do with: the shares and one block's weights
+size_t ig_least_bytes(const rotconv_plan* p, const IgShape& s) { return ig_part_bytes(p, s) + ig_fwd_block_bytes(p, s); }
+void choose_ig(rotconv_plan* p, bool averaged) {
   if (!ig_fwd_supported(p)) return;
   if (p->gs && p->opt.gs == 0) {
     // what rotconv_pool_fwd_static holds wherever it holds the products (behind widened copies that may be less than its array)
@@ -187,7 +191,7 @@ void choose_ig(rotconv_plan* p) {
     const bool strided = d.stride > 1;
     const IgShape s = strided || d.R == 1 || d.Cin <= 96 ? ig_fwd_shape(p, holds) : IgShape();
     if (s.mt && ig_fwd_block_bytes(p, s) <= holds) p->ig[1] = s;
-    if (d.R == 1) p->ig[0] = p->ig[1];
+    if (d.R == 1 && !averaged) p->ig[0] = p->ig[1];
     if ((strided || (d.Cin <= 64 && d.Cout <= 128)) && ig_bwd_weight_supported(p)) {
       p->ig_dw = 1;
       p->ws_bytes = std::max(p->ws_bytes, ig_bwd_weight_ws_bytes(p));
@@ -195,7 +199,7 @@ void choose_ig(rotconv_plan* p) {
     const long tiles = (long)((d.Cin + 63) / 64) * ((d.H * d.W + 63) / 64) * d.N;
     if ((strided || d.Cin <= 64 || tiles < 256) && ig_bwd_data_supported(p)) p->ig_dx = ig_bwd_data_shape(p, (size_t)256 << 20);
     if (p->ig_dx.mt) p->ws_bytes = std::max(p->ws_bytes, ig_bwd_data_ws_bytes(p, p->ig_dx));
-  } else if (p->d.R == 1 && p->fast[0] && p->opt.fwd_csplit == 0) {
+  } else if (!averaged && p->d.R == 1 && p->fast[0] && p->opt.fwd_csplit == 0) {
     const IgShape s = ig_fwd_shape(p, (size_t)64 << 20);
     const double other = p4_fwd_us(p);
     if (s.mt && other > 12. && s.us < 0.85 * other) p->ig[0] = s;
@@ -204,19 +208,21 @@ void choose_ig(rotconv_plan* p) {
     if (s.mt) p->ws_bytes = std::max(p->ws_bytes, ig_part_bytes(p, s) + align256(ig_fwd_pack_bytes(p, s)));
 }
 // Either forward of such a plan.
-void run_ig(const rotconv_plan* p, bool pooled, const float* x, const float* w, float* y, uint8_t* idx, void* ws, size_t ws_bytes,
-            hipStream_t st) {
+int run_ig(const rotconv_plan* p, bool pooled, const float* x, const float* w, float* y, uint8_t* idx, void* ws, size_t ws_bytes,
+           hipStream_t st) {
   const IgShape& s = p->ig[pooled];
+  if (ws_bytes < ig_least_bytes(p, s)) return ROTCONV_ERR_WORKSPACE;
   const size_t parts = ig_part_bytes(p, s);
   char* pack = static_cast<char*>(ws) + parts;
   if (!parts) {
     launch_ig_fwd(p, s, pooled, x, w, y, idx, pack, ws_bytes, st);
-    return;
+    return finish();
   }
   float* part = static_cast<float*>(ws);
   launch_ig_fwd(p, s, false, x, w, part, nullptr, pack, ws_bytes - parts, st);
   if (pooled) launch_p4_sum_pool(p, part, s.parts(), y, idx, 0, p->d.Cout, st);
   else launch_p4_sum_parts(p, part, s.parts(), y, st);
+  return finish();
 }
 
 // the fp32 path's own need (a bf16 plan adds its staging areas in front, see carve())
@@ -289,7 +295,10 @@ int rotconv_plan_create(const rotconv_desc* desc, rotconv_plan** out) {
   return rotconv_plan_create_opt(desc, nullptr, out);
 }
 
-int rotconv_plan_create_opt(const rotconv_desc* desc, const rotconv_plan_options* opts, rotconv_plan** out) {
+namespace {
+
+// averaged: the plan is the one that an average-pooling plan runs its fused calls through, or that one's padded plan.
+int create_plan(const rotconv_desc* desc, const rotconv_plan_options* opts, bool averaged, rotconv_plan** out) {
   if (!desc || !out) return ROTCONV_ERR_NULL;
   if (opts && (opts->reserved[0] || opts->reserved[1] || opts->reserved[2])) return ROTCONV_ERR_UNSUPPORTED;
   rotconv_plan* p = nullptr;
@@ -343,7 +352,7 @@ int rotconv_plan_create_opt(const rotconv_desc* desc, const rotconv_plan_options
     p->gs_chunk_bytes = gs_chunk_budget(p);
     p->ws_bytes = std::max(p->ws_bytes, gs_ws_bytes(p));
   }
-  choose_ig(p);
+  choose_ig(p, averaged);
   p->ws_inner = p->ws_bytes = align256(p->ws_bytes);
   const size_t hw_in = (size_t)p->d.H * p->d.W, hw_out = (size_t)p->Ho * p->Wo;
   p->n_x = (size_t)p->d.N * p->d.Cin * hw_in;
@@ -364,12 +373,11 @@ int rotconv_plan_create_opt(const rotconv_desc* desc, const rotconv_plan_options
     cd.Cout = p->d.Cout * p->ng; cd.R = 1; cd.angles_deg = nullptr; cd.mode = ROTCONV_EXACT90; cd.pool_group = 0;
     cd.pool_op = ROTCONV_POOL_MAX;
     cd.dtype = ROTCONV_F32;       // a bf16 plan runs it on widened copies
-    const int crc = rotconv_plan_create_opt(&cd, &p->opt, &p->avg_child);
+    const int crc = create_plan(&cd, &p->opt, true, &p->avg_child);
     if (crc != ROTCONV_OK) {
       delete p;
       return crc;
     }
-    p->avg_child->ig[0] = IgShape();      // (the call without a workspace runs what the others run)
     const AvgLayout L = avg_layout(p);
     const size_t staging = p->ws_bytes - p->ws_inner;       // a bf16 plan's fp32 copies in front (0 for fp32 plans)
     p->ws_inner = std::max(p->ws_inner, L.total);
@@ -387,7 +395,7 @@ int rotconv_plan_create_opt(const rotconv_desc* desc, const rotconv_plan_options
       cd.W = Wp;
       if (cd.mode == ROTCONV_P4M) cd.angles_deg = nullptr;   // that mode takes no explicit angles
       rotconv_plan* ch = nullptr;
-      const int crc = rotconv_plan_create_opt(&cd, &p->opt, &ch);
+      const int crc = create_plan(&cd, &p->opt, averaged, &ch);
       if (crc != ROTCONV_OK) {
         delete p;
         return crc;
@@ -404,6 +412,12 @@ int rotconv_plan_create_opt(const rotconv_desc* desc, const rotconv_plan_options
   }
   *out = p;
   return ROTCONV_OK;
+}
+
+}  // namespace
+
+int rotconv_plan_create_opt(const rotconv_desc* desc, const rotconv_plan_options* opts, rotconv_plan** out) {
+  return create_plan(desc, opts, false, out);
 }
 
 int rotconv_plan_destroy(rotconv_plan* plan) {
@@ -489,12 +503,18 @@ static size_t f32_other_fwd_need(const rotconv_plan* p) {
   return p->gs ? gs_ws_bytes(p) : align256((size_t)p->d.R * p->d.Cout * p->d.Cin * p->kk * sizeof(float));
 }
 
+// Does a forward of an fp32 plan run as one contraction over channels and taps for these pointers?
+static bool f32_fwd_is_ig(const rotconv_plan* p, bool pooled, const void* x, const void* y, const void* ws) {
+  return p->ig[pooled].mt && aligned(x, 4) && aligned(y, 4) && aligned(ws, 256);
+}
+
 // Scratch the unpooled forward of an fp32 plan needs for these pointers, whatever the plan's other calls need.
 static size_t f32_fwd_need(const rotconv_plan* p, const void* x, const void* y, const char* ws) {
   if (p->pad_child && p->pad_use[0]) {
     const PadLayout L = pad_layout(p);
     return L.child + f32_fwd_need(p->pad_child, ws + L.in, ws + L.out, ws + L.child);
   }
+  if (f32_fwd_is_ig(p, false, x, y, ws)) return ig_least_bytes(p, p->ig[0]);
   const int cs = p->fwd_csplit[0];
   return f32_fwd_is_fast(p, x, y, ws) ? fwd_part_bytes(p, cs) + p4_fwd_least_pack_bytes(p, 1, cs) : f32_other_fwd_need(p);
 }
@@ -512,10 +532,8 @@ static int f32_rotconv_fwd(const rotconv_plan* plan, const void* x, const void* 
   rotconv_plan* p = const_cast<rotconv_plan*>(plan);
   if ((rc = ensure_device_tables(p))) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (p->ig[0].mt && aligned(x, 4) && aligned(y, 4) && aligned(ws, 256)) {
-    run_ig(p, false, static_cast<const float*>(x), static_cast<const float*>(w), static_cast<float*>(y), nullptr, ws, ws_bytes, st);
-    return finish();
-  }
+  if (f32_fwd_is_ig(p, false, x, y, ws))
+    return run_ig(p, false, static_cast<const float*>(x), static_cast<const float*>(w), static_cast<float*>(y), nullptr, ws, ws_bytes, st);
   const int cs = p->fwd_csplit[0];
   if (f32_fwd_is_fast(p, x, y, ws)) {
     const size_t parts = fwd_part_bytes(p, cs);       // small map, deep input: the channels are split over workgroups
@@ -608,7 +626,8 @@ static bool f32_pool_fwd_is_fast(const rotconv_plan* p, const void* x, const voi
 static size_t f32_pool_fwd_need(const rotconv_plan* p, const void* x, const void* ypool, const uint8_t* idx,
                                 const void* ws) {
   if (f32_pool_fwd_is_fast(p, x, ypool, idx, ws)) return std::min(p->ws_inner, fwd_fast_least_bytes(p));
-  if (!p->avg_child) return f32_other_fwd_need(p);
+  // (one contraction has to fit where the products, whose place it takes, would)
+  if (!p->avg_child) return std::max(f32_other_fwd_need(p), f32_fwd_is_ig(p, true, x, ypool, ws) ? ig_least_bytes(p, p->ig[1]) : (size_t)0);
   const AvgLayout L = avg_layout(p);
   return L.child + f32_fwd_need(p->avg_child, x, ypool, static_cast<const char*>(ws) + L.child);
 }
@@ -681,10 +700,8 @@ static int f32_rotconv_pool_fwd(const rotconv_plan* plan, const void* x, const v
     }
     return finish();
   }
-  if (p->ig[1].mt && aligned(x, 4) && aligned(ypool, 4) && aligned(ws, 256)) {
-    run_ig(p, true, static_cast<const float*>(x), static_cast<const float*>(w), static_cast<float*>(ypool), idx, ws, ws_bytes, st);
-    return finish();
-  }
+  if (f32_fwd_is_ig(p, true, x, ypool, ws))
+    return run_ig(p, true, static_cast<const float*>(x), static_cast<const float*>(w), static_cast<float*>(ypool), idx, ws, ws_bytes, st);
   if (p->gs) {
     launch_gs_pool_fwd(p, static_cast<const float*>(x), static_cast<const float*>(w), static_cast<float*>(ypool), idx,
                        ws, st);

@@ -477,7 +477,8 @@ void launch_ig_fwd(const rotconv_plan* p, const IgShape& s, bool pooled, const f
   g.part = (size_t)d.N * d.Cout * d.R * p->Ho * p->Wo;
   const size_t lds = lds_bytes(g.npix);
   const int blocks = filter_blocks(p, s);
-  int most = (int)std::max<size_t>(1, std::min<size_t>(blocks, ws_bytes / block_bytes(p, s)));
+  int most = (int)std::min<size_t>(blocks, ws_bytes / block_bytes(p, s));      // (the caller sees to one)
+  if (most < 1) return;
   if (most < blocks && most > 1) most -= most % s.wc;
   for (int b = 0; b < blocks; b += most) {
     g.cb0 = b; g.ncb = std::min(most, blocks - b);

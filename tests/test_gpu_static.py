@@ -67,3 +67,17 @@ WHOLE = [
 @pytest.mark.parametrize("cfg", WHOLE, ids=[c.name for c in WHOLE])
 def test_split_beyond_the_scratch(cfg):
     _both(cfg, dict(relu=cfg.name == "w_relu"), 0)
+
+
+# averaged plans of few channels on padded rows, up to the scratch's end
+AVG_ODD = [
+    (L("a_1_64", N=2, Cin=1, H=104, W=205, Cout=64, R=4, seed=2221), dict(pool_op="avg")),
+    (L("a_2_36", N=3, Cin=2, H=631, W=37, Cout=36, R=4, seed=2222), dict(pool_op="avg")),
+    (L("a_3_30", N=1, Cin=3, H=1230, W=65, Cout=30, R=4, seed=2223), dict(pool_op="avg")),
+    (L("a16_2_20", N=1, Cin=2, H=200, W=93, Cout=20, R=4, seed=2224), dict(pool_op="avg", dtype=rc.BF16)),
+]
+
+
+@pytest.mark.parametrize("cfg,over", AVG_ODD, ids=[c.name for c, _ in AVG_ODD])
+def test_average_pooling_on_padded_rows(cfg, over):
+    _both(cfg, over, 0)
