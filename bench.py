@@ -101,7 +101,7 @@ def pass_accounting(N, Cin, Cout, H, W, R, q_paper, c_pooled, k, plan, pass_ms, 
         f_exec = ce * plan.conv_equivalents(i) + adds
         f_alg = ce * q_paper + adds
         t_hbm = nbytes[i] / (PEAK_HBM_GBS * 1e9)
-        valu = plan.kernel_name(i) == "valu_direct" and not plan.bf16_parts(i)      # (a first layer's forward may run on parts)
+        valu = plan.kernel_name(i) == "valu_direct" and not plan.bf16_parts(i)      # (a first layer's passes may run on parts)
         if valu:       # multiply-adds and placement additions as vector instructions, two per lane and clock at the peak
             lane_ops = ce * plan.conv_equivalents(i) / 2.0 + adds
             t_cmp = lane_ops / (2.0 * PEAK_VALU_LANE_OPS)

@@ -57,7 +57,7 @@
  *     (rotconv_plan_bf16_parts) may make NaN of an infinity and of magnitudes from
  *     3.396e38 on, and hold magnitudes below 2^-110 to 2^-134 only.  Of these, the
  *     pooled forward of first layers keeps infinities and large magnitudes, as does
- *     the forward on base products (options.fwd_base, not counted there), and the
+ *     the forward on base products (options.fwd_base), and the
  *     matrix multiply + scatter family and the weight gradient of first layers keep
  *     both and, beside operands up to 2^10, small ones: they form sums that are not
  *     finite or below 2^-100 again in fp32.
@@ -301,10 +301,8 @@ double rotconv_plan_conv_equivalents(const rotconv_plan* plan, int pass);
  * rotconv_workspace_bytes_unfused of scratch (with less they run "generic"). */
 const char* rotconv_plan_kernel_name(const rotconv_plan* plan, int pass);
 /* 1 if that pass (0 rotconv_pool_fwd, 1 rotconv_pool_bwd_data, 2 rotconv_pool_bwd_weight) multiplies bf16 parts of fp32
- * operands for aligned tensors (see rotconv_plan_options.bf16_parts), else 0.  First layers ("valu_direct") and the matrix
- * multiply + scatter family are among them (its pooled forward answers for the products that are placed: the one contraction that
- * takes their place with R = 4 multiplies parts always); the weight gradient of first layers and the forward on base
- * products ("mfma_p4_base"), which form sums beyond the parts' range again in fp32, multiply parts too but answer 0. */
+ * operands for aligned tensors (see rotconv_plan_options.bf16_parts), else 0; whatever the kernel family.  Which of these
+ * passes form sums beyond the parts' range again in fp32 is said at the top of this file. */
 int rotconv_plan_bf16_parts(const rotconv_plan* plan, int pass);
 
 #ifdef __cplusplus

@@ -189,9 +189,9 @@ void choose_ig(rotconv_plan* p, bool averaged) {
     const size_t holds = p->d.dtype == ROTCONV_F32 ? std::max<size_t>(gs_ws_bytes(p), ROTCONV_STATIC_SCRATCH_BYTES) : gs_ws_bytes(p);
     const rotconv_desc& d = p->d;
     const bool strided = d.stride > 1;
-    const IgShape s = strided || d.R == 1 || d.Cin <= 96 ? ig_fwd_shape(p, holds) : IgShape();
+    const IgShape s = !averaged && (strided || d.R == 1 || d.Cin <= 96) ? ig_fwd_shape(p, holds) : IgShape();
     if (s.mt && ig_fwd_block_bytes(p, s) <= holds) p->ig[1] = s;
-    if (d.R == 1 && !averaged) p->ig[0] = p->ig[1];
+    if (d.R == 1) p->ig[0] = p->ig[1];
     if ((strided || (d.Cin <= 64 && d.Cout <= 128)) && ig_bwd_weight_supported(p)) {
       p->ig_dw = 1;
       p->ws_bytes = std::max(p->ws_bytes, ig_bwd_weight_ws_bytes(p));
@@ -1198,12 +1198,16 @@ const char* rotconv_status_string(int status) {
   }
 }
 
+// Does the pass of a plan of the matrix multiply + scatter family run as one contraction?
+static bool on_ig(const rotconv_plan* p, int pass) { return pass == 0 ? p->ig[1].mt : pass == 1 ? p->ig_dx.mt : p->ig_dw; }
+
 double rotconv_plan_conv_equivalents(const rotconv_plan* plan, int pass) {
   if (!plan || pass < 0 || pass > 2) return 0.0;
   if (plan->pad_child && plan->pad_use[pass]) return rotconv_plan_conv_equivalents(plan->pad_child, pass);
   const int Q = plan->host.Q, B = plan->B;
   if (plan->avg_child) return (double)plan->ng * rotconv_plan_conv_equivalents(plan->avg_child, pass);
-  if (pass == 0 && plan->direct[0] && first_fwd_layer(plan)) return plan->d.R;     // the turns are rows of one contraction
+  // the turns are rows of one contraction
+  if (plan->direct[pass] && (pass == 0 ? first_fwd_layer(plan) : first_bwd_weight_layer(plan))) return plan->d.R;
   if (plan->direct[pass]) return Q;     // one product set per first-quadrant bank, on the vector ALU
   if (plan->d.dtype == ROTCONV_BF16 && plan->native16[pass]) {
     int present = 0;      // orientations in the set: the bf16 gradient kernels multiply every quarter turn on its own
@@ -1217,7 +1221,7 @@ double rotconv_plan_conv_equivalents(const rotconv_plan* plan, int pass) {
     if (pass == 0) return plan->fwd_base ? B : Q;
     return plan->bwd_lut ? B : Q;
   }
-  if (plan->gs) return pass == 0 && plan->ig[1].mt ? plan->d.R : Q;
+  if (plan->gs) return on_ig(plan, pass) ? plan->d.R : Q;
   return plan->d.R;
 }
 
@@ -1237,10 +1241,11 @@ int rotconv_plan_bf16_parts(const rotconv_plan* plan, int pass) {
   if (!plan || pass < 0 || pass > 2) return 0;
   if (plan->avg_child) return rotconv_plan_bf16_parts(plan->avg_child, pass);
   if (plan->pad_child && plan->pad_use[pass]) return rotconv_plan_bf16_parts(plan->pad_child, pass);
-  if (plan->direct[pass]) return pass == 0 && first_fwd_layer(plan);
-  if (!plan->fast[pass] && plan->gs) return gs_on_parts(plan, pass);
-  if ((pass == 0 && (plan->px16 || plan->fwd_base)) || !plan->fast[pass]) return 0;
+  if (plan->direct[pass]) return pass == 0 ? first_fwd_layer(plan) : first_bwd_weight_layer(plan);
+  if (!plan->fast[pass] && plan->gs) return on_ig(plan, pass) || gs_on_parts(plan, pass);
+  if ((pass == 0 && plan->px16) || !plan->fast[pass]) return 0;
   if (is_bf16(plan) && plan->native16[pass]) return 0;
+  if (pass == 0 && plan->fwd_base) return p4_fwd_base_on_parts(plan);
   return pass == 0 ? plan->fwd_s3 : pass == 1 ? s3_bwd_data_supported(plan) : s3_bwd_weight_supported(plan);
 }
 

@@ -92,6 +92,7 @@ void launch_p4_combine(const rotconv_plan* p, const float* pv, const uint8_t* pi
 // pooled forward on base products (pool group spanning several banks): one conv-equivalent on the matrix cores
 int p4_fwd_base_classify(const rotconv_plan* p, std::vector<float>* coef);   // bank classes (-1: none) and coefficients
 bool p4_fwd_base_supported(const rotconv_plan* p);
+bool p4_fwd_base_on_parts(const rotconv_plan* p);      // products of bf16 parts (else fp32 instructions)
 // (wt: room for the base bank's image, at most six bytes a weight padded to whole blocks and chunks)
 void launch_p4_fwd_base(const rotconv_plan* p, const float* x, const float* w, float* wt, float* ypool, uint8_t* idx,
                         hipStream_t st);

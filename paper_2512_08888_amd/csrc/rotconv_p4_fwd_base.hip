@@ -78,9 +78,6 @@ bool parts_resident(const rotconv_plan* p) {
   const int chunks = cin_pad_base(p->d.Cin) / 32;
   return (size_t)chunks * kS3FwdChunk * 4 + base_lds_extra(parts_park(p->host.Q, chunks)) <= 160 * 1024;
 }
-bool base_on_parts(const rotconv_plan* p) {
-  return p->d.Cin > 4 && p->opt.bf16_parts >= 0 && (size_t)p->d.Cin * p->d.H * p->d.W * 4 <= kOutside;
-}
 
 template <int NWX, int NWY, bool FASTW, bool STREAM, int KC, int NQ, int CLS, int PARK>
 void launch_i(const P4Geom& g, const float* x, const float* wt, const float* coef, const int32_t* rot_of, float* ov,
@@ -230,6 +227,10 @@ int p4_fwd_base_classify(const rotconv_plan* p, std::vector<float>* coef) {
 // The pooled forward of this plan can run on base products: 3x3 / stride 1 / pad 1, fp32 tensors, ONE pool group
 // holding every orientation of a filter, two to four banks with all four quarter turns each and a compiled class
 // list, rows the wave chains take (even; multiples of 16 beyond 128 pixels).
+bool p4_fwd_base_on_parts(const rotconv_plan* p) {
+  return p->d.Cin > 4 && p->opt.bf16_parts >= 0 && (size_t)p->d.Cin * p->d.H * p->d.W * 4 <= kOutside;
+}
+
 bool p4_fwd_base_supported(const rotconv_plan* p) {
   const rotconv_desc& d = p->d;
   if (d.k != 3 || d.stride != 1 || d.pad != 1 || d.dtype != ROTCONV_F32 || d.pool_op != ROTCONV_POOL_MAX) return false;
@@ -251,7 +252,7 @@ void launch_p4_fwd_base(const rotconv_plan* p, const float* x, const float* w, f
   P4Geom gs[8];
   const int ng = base_geoms(p, gs, 8);
   const int CinPad = cin_pad_base(p->d.Cin), CB = (p->d.Cout + 15) / 16;
-  if (base_on_parts(p)) {
+  if (p4_fwd_base_on_parts(p)) {
     hipLaunchKernelGGL(k_p4_pack_base_parts, dim3((CB * CinPad * 8 + 255) / 256, 3), dim3(256), 0, st, w,
                        reinterpret_cast<uint32_t*>(wt), CB, CinPad, p->d.Cin, p->d.Cout);
     for (int i = 0; i < ng; ++i) launch_p4_fwd_base_parts(p, gs[i], !parts_resident(p), x, wt, w, ypool, idx, st);

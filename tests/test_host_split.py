@@ -18,20 +18,26 @@ def test_selection():
     assert parts(1, 40, 32, 32, 16) == [True, False, True]
     assert parts(1, 16, 32, 32, 16) == [True, False, False]
     assert parts(1, 16, 32, 32, 16, options=dict(bf16_parts=1)) == [True] * 3
-    # other turns: the forward on base products and the table gradients stay with fp32 instructions
-    assert parts(4, 128, 128, 128, 128, R=16, mode="bilinear") == [False] * 3
+    # other turns: the forward on base products, while the table gradients stay with fp32 instructions
+    assert parts(4, 128, 128, 128, 128, R=16, mode="bilinear") == [True, False, False]
+    assert parts(4, 128, 128, 128, 128, R=16, mode="bilinear", options=dict(bf16_parts=-1)) == [False] * 3
     assert parts(4, 128, 128, 128, 128, R=16, mode="bilinear", options=dict(fwd_base=-1)) == [True, False, False]
-    # a first layer: its forward alone, unless the vector ALU is asked for, by form, by band or by what it alone takes
-    assert parts(2, 3, 512, 512, 64)[::2] == [True, False]
+    # a first layer: unless the vector ALU is asked for, by form, by band or by what it alone takes
+    assert parts(2, 3, 512, 512, 64)[::2] == [True, True]
     for other in (dict(options=dict(bf16_parts=-1)), dict(options=dict(direct_ty=1)), dict(dtype=rc.BF16), dict(R=16, mode="bilinear")):
         assert parts(2, 3, 512, 512, 64, **other)[::2] == [False, False], other
-    assert not parts(2, 3, 512, 510, 64)[0] and not parts(2, 4, 512, 512, 64)[0]
+    assert parts(2, 3, 512, 510, 64)[::2] == [False, True] and parts(2, 4, 512, 512, 64)[::2] == [False, True]
+    assert not parts(2, 3, 512, 3, 64)[2]
     assert parts(8, 64, 256, 256, 64, dtype=rc.BF16) == [False] * 3
+    # other filters: one contraction always, in each pass that runs as one
+    assert parts(2, 32, 96, 96, 32, k=5, pad=2) == [True] * 3
+    assert parts(2, 32, 96, 96, 32, k=5, pad=2, options=dict(bf16_parts=-1)) == [False] * 3
+    assert parts(6, 53, 188, 58, 25, k=5, stride=2, pad=2) == [True] * 3
     # matrix multiply + scatter: products of fewer than 512 tiles of 128 x 128 (forward 7 x 72 an image, input gradient 72,
     # weight gradient 7 in 36 parts)
-    assert parts(2, 32, 96, 96, 32, k=5, pad=2) == [False, True, True]
-    assert parts(1, 32, 96, 96, 32, k=5, pad=2) == [True] * 3
-    assert parts(1, 32, 96, 96, 32, k=5, pad=2, options=dict(bf16_parts=-1)) == [False] * 3
+    placed = dict(k=5, pad=2, options=dict(gs=1))
+    assert parts(2, 32, 96, 96, 32, **placed) == [False, True, True]
+    assert parts(1, 32, 96, 96, 32, **placed) == [True] * 3
     assert parts(2, 32, 96, 96, 32, k=5, pad=2, options=dict(bf16_parts=1)) == [True] * 3
     assert parts(3, 40, 101, 75, 24, R=8, mode="steerable", pool_group=4)[0]            # odd rows: the padded plan's
     assert parts(8, 64, 256, 256, 64, pool_op="avg") == [True] * 3                      # the averaged bank's plan
@@ -58,3 +64,15 @@ def test_odd_rows_of_pool_groups_over_several_banks_are_padded():
             odd, even = (rc.Plan(2, 24, 40, W, 12, options=opt, **kw) for W in (39, 40))
             assert odd.kernel_name(0) == even.kernel_name(0)
             assert odd.workspace_bytes > even.workspace_bytes
+
+
+def test_executed_work_of_one_contraction():
+    """Four products where the turns are rows of one contraction, one where they share a tap's product."""
+    work = lambda *a, **k: [rc.Plan(*a, **k).conv_equivalents(i) for i in range(3)]
+    assert work(2, 32, 96, 96, 32, k=5, pad=2) == [4, 4, 4]
+    assert work(2, 32, 96, 96, 32, k=5, pad=2, options=dict(gs=1)) == [1, 1, 1]
+    assert work(4, 200, 96, 96, 200, k=5, pad=2) == [1, 1, 1]                # deep layers: products placed, gradients routed
+    assert work(6, 53, 188, 58, 25, k=5, stride=2, pad=2) == [4, 4, 4]
+    assert work(2, 3, 512, 512, 64)[::2] == [4, 4]
+    assert work(2, 3, 512, 512, 64, options=dict(bf16_parts=-1))[::2] == [1, 1]
+    assert work(2, 32, 96, 96, 32, R=1, k=5, pad=2)[0] == 1
