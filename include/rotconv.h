@@ -56,11 +56,11 @@
  *     of the others.  fp32 passes that multiply bf16 parts of the operands
  *     (rotconv_plan_bf16_parts) may make NaN of an infinity and of magnitudes from
  *     3.396e38 on, and hold magnitudes below 2^-110 to 2^-134 only.  Of these, the
- *     pooled forward of first layers keeps infinities and large magnitudes, as does
- *     the forward on base products (options.fwd_base), and the
- *     matrix multiply + scatter family and the weight gradient of first layers keep
- *     both and, beside operands up to 2^10, small ones: they form sums that are not
- *     finite or below 2^-100 again in fp32.
+ *     pooled forward of first layers keeps infinities and large magnitudes, and the
+ *     forward on base products (options.fwd_base), the matrix multiply + scatter
+ *     family and the weight gradient of first layers keep both and, beside operands
+ *     up to 2^10, small ones: they form sums that are not finite or below 2^-100
+ *     again in fp32.
  *     All others, and these with plan option bf16_parts = -1, follow IEEE arithmetic.
  *   - Return value: a rotconv_status.  Argument errors are found on the host
  *     before anything is launched and leave the outputs untouched.

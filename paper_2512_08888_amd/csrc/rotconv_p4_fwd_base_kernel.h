@@ -19,9 +19,8 @@
 // What bounds it: about 2100 vector instructions per 16 pixels and row at R = 16 (1.67 ns each, 131 of the 213 us of
 // 4x128 -> 128, 128x128).  The fp32 instructions leave no room for vector instructions beside them and took 138 us of 283; as
 // parts the products take 60, and the reads of the weights' parts (27 x 1 KB a chunk and wave) 100 of the LDS' time.  4x64 -> 64,
-// 128x128, R = 8: 77 -> 58 us.  A sum that is not finite, or a lane's largest below 2^-100, has its wave form the row again on
-// the fp32 instruction and replace such sums, so that infinities and large magnitudes come out as there; the look costs 36 of the
-// instructions.
+// 128x128, R = 8: 77 -> 58 us.  A sum that is not finite, or below 2^-100 and not zero, has its wave form the row again on
+// the fp32 instruction and replace such sums, so that they come out as there; the look costs 54 of the instructions.
 // Parked sums count: with two banks parked instead of one 2x64 -> 64, 256x256 took 0.90 of the time, streamed 2x256 -> 256, 64x64
 // 0.85; with three 8x23 -> 87, 274x128 496 -> 476 us; 128 channels streamed with two 1.07 of resident with one.
 //
@@ -358,10 +357,13 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
       for (int u = 0; u < 9; ++u) P[u] = f4{0.f, 0.f, 0.f, 0.f};
     }
     if constexpr (S3) {
-      // Sums that the parts do not hold: one of the lane's is not finite, or its largest is below 2^-100.  As integers floats
-      // of one sign are in order, so the largest signed and the largest unsigned number say both for two signs.
+      // Sums that the parts do not hold, each looked at for itself: is one of the lane's not finite (as integers floats of one sign
+      // are in order, so the largest signed and the largest unsigned number say so for two signs), or the smallest magnitude
+      // below 2^-100?  Zeros, which are no such sums, are told apart where there is one (rows and pixels outside the image), by
+      // arithmetic: 36 comparisons are 36 masks, whose spills cost the kernel of 4x128 -> 128, 128x128 26 of 240 us.
       int top = INT32_MIN;
       uint32_t utop = 0;
+      float lo = __builtin_inff();
 #pragma unroll
       for (int u = 0; u < 9; ++u)
 #pragma unroll
@@ -369,10 +371,22 @@ __global__ __launch_bounds__(64 * NWX * NWY) void k_p4_fwd_base(const float* __r
           const float v = P[u][i];      // (a vector's element, cast as it stands, is its first)
           top = max(top, __builtin_bit_cast(int, v));
           utop = max(utop, __builtin_bit_cast(uint32_t, v));
+          lo = __builtin_fminf(lo, __builtin_fabsf(v));
         }
-      const uint32_t mag = max((uint32_t)max(top, 0), utop >> 31 ? utop & 0x7fffffffu : 0u);
-      if (__any(mag >= 0x7f800000u || (mag != 0u && mag < 0x0d800000u))) {      // such sums of the row again on the fp32 instruction
-        const bool fil = cb * 16 + lc < g.Cout;
+      const bool fil = cb * 16 + lc < g.Cout;
+      bool odd = top >= 0x7f800000 || utop >= 0xff800000u;
+      if (__any(fil && row_ok && live && lo < 0x1p-100f)) {
+        uint32_t least = 0xffffffffu;    // of a magnitude twice as an integer, less one: zero is the largest
+#pragma unroll
+        for (int u = 0; u < 9; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float v = P[u][i];
+            least = min(least, (__builtin_bit_cast(uint32_t, v) << 1) - 1u);
+          }
+        odd |= least < (0x0d800000u << 1) - 1u;      // (2^-100)
+      }
+      if (__any(odd)) {                  // such sums of the row again on the fp32 instruction
         const float* wr = wbase + (size_t)(fil ? cb * 16 + lc : 0) * g.Cin * 9;
 #pragma unroll
         for (int u = 0; u < 9; ++u) {

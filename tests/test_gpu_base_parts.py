@@ -70,3 +70,18 @@ def test_values_the_parts_do_not_hold(cfg):
     for ex, ew in ((-75, -40), (-115, 0), (60, 40)):
         got, ref = both(np.ldexp(x, ex), np.ldexp(w, ew))
         assert _rel(np.ldexp(got.astype(np.float64), -ex - ew), np.ldexp(ref.astype(np.float64), -ex - ew)) < 1e-6
+
+
+@pytest.mark.parametrize("cfg", [LAYERS[1], LAYERS[4], LAYERS[8], LAYERS[13]], ids=lambda c: c.name)
+def test_small_values_beside_ordinary_ones(cfg):
+    """Pixels that the parts hold to a few bits only (2^-122 of a part that ends at 2^-134), three by three among ordinary ones at every
+    offset from a lane's four pixels: what draws on them alone is as on the fp32 instructions.  Both are within the bar at the
+    top of the same sum (128 channels, 7e-7)."""
+    x, w = synth.make_x(cfg), np.ldexp(synth.make_w(cfg), 8)
+    at = [(2, 4 * i + i % 4) for i in range(1, (cfg.W - 3) // 4)]
+    for y, c in at:
+        x[..., y:y + 3, c:c + 3] = np.ldexp(x[..., y:y + 3, c:c + 3], -122)
+    got, ref = (np.stack([pu.GpuLayer(cfg, x, w, options=o).pool_fwd()[0][..., y + 1, c + 1] for y, c in at])
+                for o in (None, dict(bf16_parts=-1)))
+    assert 0 < np.abs(ref).max() < 2.0 ** -100
+    assert _rel(np.ldexp(got.astype(np.float64), 120), np.ldexp(ref.astype(np.float64), 120)) < 1e-6
