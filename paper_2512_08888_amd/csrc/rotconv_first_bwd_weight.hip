@@ -311,30 +311,43 @@ __global__ __launch_bounds__(256) void k_first_dw_finish(const float* __restrict
 #pragma unroll
       for (int i = 0; i < n; ++i) a[i] = a[i] + a[i + n];
     tot[u] = (float)a[0];
-    const float m = __builtin_fabsf(tot[u]);
-    if (!(m < __builtin_inff()) || (m < 0x1p-100f && m != 0.f)) odd = 1;
+    if (beyond_parts(tot[u])) odd = 1;
   }
   __syncthreads();
-  if (odd) {                           // sums that the parts do not hold, in fp32
+  if (odd) {                           // sums that the parts do not hold, in fp32: a thread four pixels of a row at a time
+    // (gradients of NaN throughout, 2x3 -> 64, 512x512: 1.5 ms instead of 68 us; with 36 loads per pixel 13)
     float a[9];
 #pragma unroll
     for (int u = 0; u < 9; ++u) a[u] = 0.f;
-    const int HW = H * W;
-    for (int p = threadIdx.x; p < N * HW; p += 256) {
-      const int n = p / HW, y = p % HW / W, c = p % W;
-      const float xv = x[((size_t)n * Cin + ci) * HW + p % HW];
+    const int HW = H * W, qpr = (W + 3) / 4;
+#pragma unroll 1
+    for (int e = threadIdx.x; e < N * H * qpr; e += 256) {
+      const int n = e / (H * qpr), y = e / qpr - n * H, c = 4 * (e % qpr);
       const size_t plane = ((size_t)n * Cout + co) * HW;
+      const float* xr = x + ((size_t)n * Cin + ci) * HW + (size_t)y * W;
+      float g[3][6];                   // the gradients around them, and their turns
+      int t[3][6];
 #pragma unroll
-      for (int u = 0; u < 9; ++u) {
-        float d = 0.f;
+      for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const int yy = y + 1 - tap_i(s, u), xx = c + 1 - tap_j(s, u);
-          if (yy < 0 || yy >= H || xx < 0 || xx >= W) continue;
-          const size_t o = plane + (size_t)yy * W + xx;
-          if (idx[o] == s) d += gpool[o];
+        for (int j = 0; j < 6; ++j) {
+          const int yy = y + i - 1, xx = c + j - 1;
+          const bool in = (unsigned)yy < (unsigned)H && (unsigned)xx < (unsigned)W;
+          const size_t o = plane + (in ? yy * W + xx : 0);
+          g[i][j] = gpool[o];
+          t[i][j] = in ? idx[o] : 255;
         }
-        a[u] += d * xv;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        if (c + b >= W) continue;
+        const float xv = xr[c + b];
+#pragma unroll
+        for (int u = 0; u < 9; ++u) {
+          float d = 0.f;
+#pragma unroll
+          for (int s = 0; s < 4; ++s) d += t[2 - tap_i(s, u)][b + 2 - tap_j(s, u)] == s ? g[2 - tap_i(s, u)][b + 2 - tap_j(s, u)] : 0.f;
+          a[u] += d * xv;
+        }
       }
     }
 #pragma unroll
@@ -343,8 +356,7 @@ __global__ __launch_bounds__(256) void k_first_dw_finish(const float* __restrict
     if (threadIdx.x < 9) {
       double s = 0.;
       for (int i = 0; i < 256; ++i) s += red[i][threadIdx.x];
-      const float m = __builtin_fabsf(tot[threadIdx.x]);
-      if (!(m < __builtin_inff()) || (m < 0x1p-100f && m != 0.f)) tot[threadIdx.x] = (float)s;
+      if (beyond_parts(tot[threadIdx.x])) tot[threadIdx.x] = (float)s;
     }
     __syncthreads();
   }

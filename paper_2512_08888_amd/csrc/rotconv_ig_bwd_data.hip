@@ -125,6 +125,17 @@ __global__ __launch_bounds__(256 * WC, 2) void k_ig_bwd_data(const float* __rest
     }
   };
 
+  // does tap position (i, j) reach the tile's pixels, and how far into the region?
+  auto reach = [&](Orbit t, int& off) {
+    const int dy = py + g.pad - t.i, dxx = px + g.pad - t.j;
+    if (g.stride == 1) {
+      off = ((dy - first_y) * g.rw + dxx - first_x) * kPixel;
+      return true;
+    }
+    const int qy = ceil_div(dy, g.stride), qx = ceil_div(dxx, g.stride);
+    off = ((qy - first_y) * g.rw + qx - first_x) * kPixel;
+    return qy * g.stride == dy && qx * g.stride == dxx;
+  };
   constexpr int kPa[5] = {2, 0, 1, 1, 0}, kPb[5] = {0, 2, 1, 0, 1};          // the small products; then the parts' first ones
   const u32x4* wl = wp + (size_t)min(cb, g.ncb - 1) * g.nch * g.kk * MT * 192 + lane;
 #pragma unroll 1
@@ -139,17 +150,6 @@ __global__ __launch_bounds__(256 * WC, 2) void k_ig_bwd_data(const float* __rest
       for (int r = 0; r < MT; ++r)
 #pragma unroll
         for (int d = 0; d < 3; ++d) a[r][d] = wq[((tile * MT + r) * 3 + d) * 64];
-    };
-    // does tap position (i, j) reach the tile's pixels, and how far into the region?
-    auto reach = [&](Orbit t, int& off) {
-      const int dy = py + g.pad - t.i, dxx = px + g.pad - t.j;
-      if (g.stride == 1) {
-        off = ((dy - first_y) * g.rw + dxx - first_x) * kPixel;
-        return true;
-      }
-      const int qy = ceil_div(dy, g.stride), qx = ceil_div(dxx, g.stride);
-      off = ((qy - first_y) * g.rw + qx - first_x) * kPixel;
-      return qy * g.stride == dy && qx * g.stride == dxx;
     };
 #pragma unroll 1
     for (int o = o0; o < o1; ++o) {
@@ -262,46 +262,66 @@ __global__ __launch_bounds__(256 * WC, 2) void k_ig_bwd_data(const float* __rest
     for (int t = 0; t < NT; ++t)
 #pragma unroll
       for (int i = 0; i < 4; ++i) odd |= beyond_parts(acc[r][t][i]);
-  if (__any(odd)) {                    // sums that the parts do not hold, in fp32
+  if (__builtin_expect(__any(odd), 0)) {      // the wave's sums in fp32; those that the parts do not hold are replaced
+    s3_f4 fresh[MT][NT];
+    clear(fresh);
 #pragma unroll 1
-    for (int e = 0; e < MT * NT * 4; ++e) {
-      const int er = e / (NT * 4), et = e / 4 % NT, ei = e % 4;
-      float old = 0.f;
-      int yy = 0, xx = 0;
-      bool in = false;
+    for (int co = c0 * 32; co < min(g.Cout, c1 * 32); ++co) {
+      const float* wr[MT][4];
 #pragma unroll
       for (int r = 0; r < MT; ++r)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
+        for (int i = 0; i < 4; ++i) wr[r][i] = w + ((size_t)co * g.Cin + min(f0 + 16 * r + i, g.Cin - 1)) * g.kk;
+      // adds what the output at a position that the tile's pixels reach gives to tile t, by its turn's weights (0 to 3)
+      // (gradients of NaN throughout, 2x32 -> 32, 96x96, 5 x 5: 0.32 ms instead of 45 us; an element at a time 6.7)
+      auto output = [&](int t, Orbit at, auto weight) {
+        const int dy = y[t] + g.pad - at.i, dxx = x[t] + g.pad - at.j, oy = dy / g.stride, ox = dxx / g.stride;
+        const bool in = live[t] && dy >= 0 && dxx >= 0 && oy < g.Ho && ox < g.Wo;
+        const size_t o = in ? (size_t)co * HWo + (size_t)oy * g.Wo + ox : 0;
+        const float gv = gi[o];
+        const int s = in ? ii[o] : 255;
+        if (s < 4)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) old = e == (r * NT + t) * 4 + i ? acc[r][t][i] : old;
-          if (et == t) { yy = y[t]; xx = x[t]; in = live[t]; }
+          for (int r = 0; r < MT; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) fresh[r][t][i] += weight(s, r, i) * gv;
+      };
+#pragma unroll 1
+      for (int o = o0; o < o1; ++o) {
+        Orbit pos[4];
+        int off;
+        pos[0] = orbit_rep(o, g.k);
+#pragma unroll
+        for (int m = 1; m < 4; ++m) pos[m] = turn(pos[m - 1], g.k);
+        float wv[4][MT][4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+#pragma unroll
+          for (int r = 0; r < MT; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) wv[d][r][i] = wr[r][i][pos[d].i * g.k + pos[d].j];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          if (!reach(pos[m], off)) continue;
+#pragma unroll
+          for (int t = 0; t < NT; ++t)
+            output(t, pos[m], [&](int s, int r, int i) {
+              const float lo = s & 1 ? wv[(m - 1) & 3][r][i] : wv[m][r][i], hi = s & 1 ? wv[(m - 3) & 3][r][i] : wv[(m - 2) & 3][r][i];
+              return s & 2 ? hi : lo;
+            });
         }
-      const int ci = f0 + 16 * er + ei;
-      float fresh = old;
-      if (beyond_parts(old) && in && ci < fend) {
-        fresh = 0.f;
-        for (int co = c0 * 32; co < min(g.Cout, c1 * 32); ++co)
-          for (int u = 4 * o0; u < 4 * o1 + (centre ? 1 : 0); ++u) {
-            const int tap = packed_tap(u, g.k);
-            Orbit at{tap / g.k, tap % g.k};
-            for (int s = 0; s < 4; ++s) {
-              const int dy = yy + g.pad - at.i, dxx = xx + g.pad - at.j, oy = dy / g.stride, ox = dxx / g.stride;
-              if (dy >= 0 && dxx >= 0 && oy * g.stride == dy && ox * g.stride == dxx && oy < g.Ho && ox < g.Wo) {
-                const size_t o = (size_t)co * HWo + (size_t)oy * g.Wo + ox;
-                if (ii[o] == s) fresh += w[((size_t)co * g.Cin + ci) * g.kk + tap] * gi[o];
-              }
-              at = turn(at, g.k);
-            }
-          }
       }
+      int off;
+      if (centre && reach(Orbit{g.k / 2, g.k / 2}, off))
 #pragma unroll
-      for (int r = 0; r < MT; ++r)
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) acc[r][t][i] = e == (r * NT + t) * 4 + i ? fresh : acc[r][t][i];
+        for (int t = 0; t < NT; ++t) output(t, Orbit{g.k / 2, g.k / 2}, [&](int, int r, int i) { return wr[r][i][g.kk / 2]; });
     }
+#pragma unroll
+    for (int r = 0; r < MT; ++r)
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[r][t][i] = beyond_parts(acc[r][t][i]) ? fresh[r][t][i] : acc[r][t][i];
   }
 
   float* out = dx + (size_t)blockIdx.y * g.part;

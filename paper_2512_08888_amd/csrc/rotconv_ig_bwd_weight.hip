@@ -14,7 +14,7 @@
 // own.  The last eight outputs of a row start at Wo - 8, and those that they repeat are masked.  The eight waves of a workgroup
 // take shares of the outputs (every other one contracts -X, as the instruction cuts towards minus infinity) and meet in LDS.
 //
-// A sum that is not finite, or below 2^-100 and not zero, is formed again in fp32 on the vector ALU.
+// A workgroup's sums that are not finite, or below 2^-100 and not zero, are formed again in fp32 on the vector ALU.
 //
 // What bounds it: matrix instructions (24 a tap and step) and, beside them, about 330 vector instructions a step of five taps
 // (masks and splits, the same for every tap); small maps the start of a wave, which has a step or two.  2x32 -> 32, 96x96, 5 x 5: 54 us
@@ -71,8 +71,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_ig_bwd_weight(const float* _
   const int co = min(f0 + lc, g.Cout - 1);                         // (rows and columns beyond the last are read by nobody)
   const int ci = min(c0 + lc, g.Cin - 1);
 
-  int step = (split * kWaves + wave) * g.per;
-  const int stop = min(step + g.per, g.steps);
+  const int first = (split * kWaves + wave) * g.per, stop = min(first + g.per, g.steps);
+  int step = first;
   int v = step * 4 + lg, n, y, q;
   n = v / (g.Ho * g.opr);
   y = v / g.opr - n * g.Ho;
@@ -204,7 +204,10 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_ig_bwd_weight(const float* _
   }
 
   // the waves' sums, ascending
+  __shared__ int beyond;               // is one that the parts do not hold among them?
+  if (tid == 0) beyond = 0;
   float* out = part + ((size_t)split * nblk + blk) * 4 * TJ * 256;
+  bool odd = false;
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     if (s) __syncthreads();
@@ -221,14 +224,83 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_ig_bwd_weight(const float* _
 #pragma unroll
       for (int t = 0; t < kWaves; ++t) sum += red[((t * TJ + o / 256) * 16 + o / 16 % 16) * 17 + o % 16];
       out[s * TJ * 256 + o] = (float)sum;
+      odd |= beyond_parts((float)sum);
+    }
+  }
+  if (odd) beyond = 1;
+  __syncthreads();
+  if (!beyond) return;
+
+  // Such sums in fp32 on the vector ALU, a turn at a time.  A wave takes its share of the outputs, four at a time; a lane's filters are
+  // 4 lg + r, its channel c0 + lc.  Gradients of NaN throughout: 0.5 ms instead of 44 us (an element at a time, a wave each: 11.7).
+  // (Before the sums meet in LDS the contraction would keep registers for this: the kernel 29.5 -> 31.2 us, so 30.5.)
+#pragma unroll 1
+  for (int s = 0; s < 4; ++s) {
+    s3_f4 fresh[TJ];
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) fresh[j] = s3_f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int w = first * 4; w < min(stop * 4, g.nq); ++w) {        // eights of outputs
+      const int wn = w / (g.Ho * g.opr), wy = w / g.opr - wn * g.Ho, wq = w % g.opr;
+      const int ox = min(8 * wq, g.Wo - 8), rep = 8 * wq - ox, iy = wy * ST + row - g.pad;
+      if ((unsigned)iy >= (unsigned)g.H) continue;
+      const float* xr1 = x + ((size_t)wn * g.Cin + ci) * HW + (size_t)iy * g.W;
+      s3_f4 part8[TJ];
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) part8[j] = s3_f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int h = rep / 4; h < 2; ++h) {
+        constexpr int NCOL = 3 * ST + TJ;
+        const int left = (ox + 4 * h) * ST - g.pad + j0;
+        float xv[NCOL], gv[4][4];
+        uint32_t iv[4];
+#pragma unroll
+        for (int e = 0; e < NCOL; ++e) xv[e] = xr1[min(max(left + e, 0), g.W - 1)];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const size_t o = ((size_t)wn * g.Cout + min(f0 + 4 * lg + r, g.Cout - 1)) * HWo + (size_t)wy * g.Wo + ox + 4 * h;
+          __builtin_memcpy(gv[r], gpool + o, 16);
+          iv[r] = load4(idx + o);
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          if (4 * h + b < rep) continue;                           // the eight before has it
+          uint32_t mask[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) mask[r] = (iv[r] >> 8 * b & 0xffu) == (uint32_t)s ? 0xffffffffu : 0u;
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) {
+            if ((unsigned)(left + b * ST + j) >= (unsigned)g.W) continue;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {                          // (masked products, so that 0 times infinity adds nothing)
+              const float p = gv[r][b] * xv[b * ST + j];
+              part8[j][r] += __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, p) & mask[r]);
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) fresh[j] += part8[j];
+    }
+    if (s) __syncthreads();
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[((wave * TJ + j) * 16 + 4 * lg + r) * 17 + lc] = fresh[j][r];
+    __syncthreads();
+    for (int o = tid; o < TJ * 256; o += 64 * kWaves) {
+      double sum = 0.;
+#pragma unroll
+      for (int t = 0; t < kWaves; ++t) sum += red[((t * TJ + o / 256) * 16 + o / 16 % 16) * 17 + o % 16];
+      float& old = out[s * TJ * 256 + o];
+      if (beyond_parts(old)) old = (float)sum;
     }
   }
 }
 
 // dW of a tap, four filters and 16 channels: a wave per turn adds up the shares, ascending, then the turns.
-__global__ __launch_bounds__(256) void k_ig_dw_finish(const float* __restrict__ part, float* __restrict__ dw,
-                                                      const float* __restrict__ x, const float* __restrict__ gpool,
-                                                      const uint8_t* __restrict__ idx, IgDwGeom g, int tj, int stride, int nsplit) {
+__global__ __launch_bounds__(256) void k_ig_dw_finish(const float* __restrict__ part, float* __restrict__ dw, IgDwGeom g, int tj,
+                                                      int nsplit) {
   __shared__ double tot[4][64];
   const int k = g.k, lane = threadIdx.x % 64, s0 = threadIdx.x / 64;
   int v = blockIdx.x;
@@ -251,31 +323,7 @@ __global__ __launch_bounds__(256) void k_ig_dw_finish(const float* __restrict__ 
   __syncthreads();
   if (s0) return;
   sum = (tot[0][lane] + tot[1][lane]) + (tot[2][lane] + tot[3][lane]);
-  float r = (float)sum;
-  const bool in = co < g.Cout && ci < g.Cin;
-  // sums that the parts do not hold, in fp32: a wave for one element after the other
-  unsigned long long odd = __ballot(in && beyond_parts(r));
-  while (odd) {
-    const int who = __builtin_ctzll(odd);
-    odd &= odd - 1;
-    const int cw = __shfl(co, who), iw = __shfl(ci, who);
-    const int HW = g.H * g.W, HWo = g.Ho * g.Wo;
-    double t = 0.;
-    for (int p = lane; p < g.N * HWo; p += 64) {
-      const int n = p / HWo, o = p % HWo;
-      const size_t go = ((size_t)n * g.Cout + cw) * HWo + o;
-      Orbit a{u / k, u % k};
-      for (int s = 0; s < 4; ++s) {
-        const int iy = o / g.Wo * stride + a.i - g.pad, ix = o % g.Wo * stride + a.j - g.pad;
-        if (idx[go] == s && (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W)
-          t += gpool[go] * x[((size_t)n * g.Cin + iw) * HW + (size_t)iy * g.W + ix];
-        a = turn(a, k);
-      }
-    }
-    for (int d = 32; d; d /= 2) t += __shfl_xor(t, d);
-    if (lane == who) r = (float)t;
-  }
-  if (in) dw[((size_t)co * g.Cin + ci) * (k * k) + u] = r;
+  if (co < g.Cout && ci < g.Cin) dw[((size_t)co * g.Cin + ci) * (k * k) + u] = (float)sum;
 }
 
 struct Launch { IgDwGeom g; int tj, splits; };
@@ -335,8 +383,7 @@ void launch_ig_bwd_weight(const rotconv_plan* p, const float* x, const float* gp
     case 4: if (two) go(k_ig_bwd_weight<4, 2>); else go(k_ig_bwd_weight<4, 1>); break;
     default: if (two) go(k_ig_bwd_weight<5, 2>); else go(k_ig_bwd_weight<5, 1>); break;
   }
-  hipLaunchKernelGGL(k_ig_dw_finish, dim3((unsigned)(l.g.nco * l.g.nci * p->kk * 4)), dim3(256), 0, st, part, dw, x, gpool, idx, l.g, l.tj,
-                     d.stride, l.splits);
+  hipLaunchKernelGGL(k_ig_dw_finish, dim3((unsigned)(l.g.nco * l.g.nci * p->kk * 4)), dim3(256), 0, st, part, dw, l.g, l.tj, l.splits);
 }
 
 }  // namespace rotconv
