@@ -543,21 +543,26 @@ __global__ __launch_bounds__(256) void k_p4_combine(const float* __restrict__ pv
   idx[o] = dead ? (uint8_t)255 : (uint8_t)bi;
 }
 
-// Channel split: y = sum of the parts, ascending (four elements per thread, scalar tail).  The parts lie on 16 bytes only where
-// n_elem is a multiple of four, and y of odd rows anywhere.
+// Channel split: y = sum of the parts, ascending, in 64 bits (four elements per thread, scalar tail).  The parts lie on 16 bytes only
+// where n_elem is a multiple of four, and y of odd rows anywhere.  (1x512 -> 128, 16x16 in sixteen parts: the error 9.8e-8 in fp32,
+// 6.6e-8 so, at the same time.)
 __global__ __launch_bounds__(256) void k_p4_sum_parts(const float* __restrict__ part, float* __restrict__ y,
                                                       size_t n_elem, int nparts) {
   const size_t n4 = n_elem / 4;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 256) {
-    f4 a = reinterpret_cast<const f4u*>(part)[i];
+    double a[4] = {0., 0., 0., 0.};
 #pragma unroll 8
-    for (int k = 1; k < nparts; ++k) a += reinterpret_cast<const f4u*>(part + (size_t)k * n_elem)[i];
-    reinterpret_cast<f4u*>(y)[i] = a;
+    for (int k = 0; k < nparts; ++k) {
+      const f4 v = reinterpret_cast<const f4u*>(part + (size_t)k * n_elem)[i];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] += v[e];
+    }
+    reinterpret_cast<f4u*>(y)[i] = f4{(float)a[0], (float)a[1], (float)a[2], (float)a[3]};
   }
   for (size_t e = n4 * 4 + (size_t)blockIdx.x * 256 + threadIdx.x; e < n_elem; e += (size_t)gridDim.x * 256) {
-    float v = part[e];
-    for (int k = 1; k < nparts; ++k) v += part[(size_t)k * n_elem + e];
-    y[e] = v;
+    double v = 0.;
+    for (int k = 0; k < nparts; ++k) v += part[(size_t)k * n_elem + e];
+    y[e] = (float)v;
   }
 }
 
