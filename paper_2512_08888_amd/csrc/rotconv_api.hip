@@ -221,7 +221,7 @@ int run_ig(const rotconv_plan* p, bool pooled, const float* x, const float* w, f
   float* part = static_cast<float*>(ws);
   launch_ig_fwd(p, s, false, x, w, part, nullptr, pack, ws_bytes - parts, st);
   if (pooled) launch_p4_sum_pool(p, part, s.parts(), y, idx, 0, p->d.Cout, st);
-  else launch_p4_sum_parts(p, part, s.parts(), y, st);
+  else launch_p4_sum_parts(p, part, s.parts(), y, st, true);
   return finish();
 }
 

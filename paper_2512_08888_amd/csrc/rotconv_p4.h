@@ -65,7 +65,7 @@ int p4_fwd_csplit(const rotconv_plan* p, bool pooled);
 double p4_fwd_us(const rotconv_plan* p);
 bool p4_fwd_chain_whole(const rotconv_plan* p);
 void p4_fwd_choose_launches(rotconv_plan* p);   // fills fwd_launch, after the channel splits
-void launch_p4_sum_parts(const rotconv_plan* p, const float* part, int nparts, float* y, hipStream_t st);
+void launch_p4_sum_parts(const rotconv_plan* p, const float* part, int nparts, float* y, hipStream_t st, bool wide = false);
 // of filters [c0, c0 + nc), which the parts hold; applies the plan's fused activation
 void launch_p4_sum_pool(const rotconv_plan* p, const float* part, int nparts, float* ypool, uint8_t* idx, int c0, int nc,
                         hipStream_t st);

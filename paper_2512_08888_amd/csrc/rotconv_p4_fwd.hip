@@ -44,6 +44,7 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 #include "rotconv_bf16.h"
 #include "rotconv_expand.h"
@@ -543,16 +544,24 @@ __global__ __launch_bounds__(256) void k_p4_combine(const float* __restrict__ pv
   idx[o] = dead ? (uint8_t)255 : (uint8_t)bi;
 }
 
-// Channel split: y = sum of the parts, ascending, in 64 bits (four elements per thread, scalar tail).  The parts lie on 16 bytes only
-// where n_elem is a multiple of four, and y of odd rows anywhere.  (1x512 -> 128, 16x16 in sixteen parts: the error 9.8e-8 in fp32,
-// 6.6e-8 so, at the same time.)
+// Channel split: y = sum of the parts, ascending (four elements per thread, scalar tail), in fp32 or, for the shares of the one
+// contraction, in 64 bits (1x512 -> 128, 16x16 in sixteen shares: the error 9.8e-8 in fp32, 6.6e-8 so, in no more time).  The parts lie on
+// 16 bytes only where n_elem is a multiple of four, and y of odd rows anywhere.
+template <typename A>
 __global__ __launch_bounds__(256) void k_p4_sum_parts(const float* __restrict__ part, float* __restrict__ y,
                                                       size_t n_elem, int nparts) {
+  // (in 64 bits from zero: eight loads at a time of the first eight parts too, 15.1 -> 13.5 us; in fp32 that would lose a part's -0)
+  constexpr int K0 = std::is_same_v<A, float> ? 1 : 0;
   const size_t n4 = n_elem / 4;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 256) {
-    double a[4] = {0., 0., 0., 0.};
+    A a[4] = {0, 0, 0, 0};
+    if constexpr (K0) {
+      const f4 first = reinterpret_cast<const f4u*>(part)[i];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] = first[e];
+    }
 #pragma unroll 8
-    for (int k = 0; k < nparts; ++k) {
+    for (int k = K0; k < nparts; ++k) {
       const f4 v = reinterpret_cast<const f4u*>(part + (size_t)k * n_elem)[i];
 #pragma unroll
       for (int e = 0; e < 4; ++e) a[e] += v[e];
@@ -560,8 +569,8 @@ __global__ __launch_bounds__(256) void k_p4_sum_parts(const float* __restrict__ 
     reinterpret_cast<f4u*>(y)[i] = f4{(float)a[0], (float)a[1], (float)a[2], (float)a[3]};
   }
   for (size_t e = n4 * 4 + (size_t)blockIdx.x * 256 + threadIdx.x; e < n_elem; e += (size_t)gridDim.x * 256) {
-    double v = 0.;
-    for (int k = 0; k < nparts; ++k) v += part[(size_t)k * n_elem + e];
+    A v = part[e];
+    for (int k = 1; k < nparts; ++k) v += part[(size_t)k * n_elem + e];
     y[e] = (float)v;
   }
 }
@@ -1027,10 +1036,11 @@ void launch_p4_fwd_parts(const rotconv_plan* p, int b0, int b1, const float* x, 
   launch_blocks(p, b0, b1, kOutUnpooled, x, w, pack, pack_bytes, out_val, nullptr, st, 1, csplit);
 }
 
-void launch_p4_sum_parts(const rotconv_plan* p, const float* part, int nparts, float* y, hipStream_t st) {
+void launch_p4_sum_parts(const rotconv_plan* p, const float* part, int nparts, float* y, hipStream_t st, bool wide) {
   const size_t n_elem = (size_t)p->d.N * p->d.Cout * p->d.R * p->Ho * p->Wo;
   const unsigned blocks = (unsigned)std::max<size_t>(1, std::min<size_t>((n_elem / 4 + 255) / 256, 4096));
-  hipLaunchKernelGGL(k_p4_sum_parts, dim3(blocks), dim3(256), 0, st, part, y, n_elem, nparts);
+  if (wide) hipLaunchKernelGGL(k_p4_sum_parts<double>, dim3(blocks), dim3(256), 0, st, part, y, n_elem, nparts);
+  else hipLaunchKernelGGL(k_p4_sum_parts<float>, dim3(blocks), dim3(256), 0, st, part, y, n_elem, nparts);
 }
 
 void launch_p4_sum_pool(const rotconv_plan* p, const float* part, int nparts, float* ypool, uint8_t* idx, int c0, int nc,
