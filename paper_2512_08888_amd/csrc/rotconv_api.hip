@@ -169,8 +169,10 @@ void choose_fwd(rotconv_plan* p) {
 // One contraction over channels and taps instead of products that are placed, or of gradients routed through memory.
 // Filters of other sizes and strides with the four quarter turns, pooled, whose products it forms four times as often: 60 layers of
 // 12 to 64 channels and filters, k = 2, 5, 7, stride 1 and 2: forward 0.45, weight gradient 0.49, input gradient 0.31 of the time
-// in the mean, at most 0.78, 0.97 and 0.81.  With a stride always (4x128 -> 128, 128x128, stride 2 429 -> 102, 379 -> 160, 303 -> 144
-// us).  Without, 70 layers of 48 to 400 channels: the forward up to 96 (0.51 to 0.98; 161 and more 0.6 to 1.7), the weight gradient up
+// in the mean, at most 0.78, 0.97 and 0.81.  With a stride of up to 8 wherever a tile fits LDS (4x128 -> 128, 128x128, stride 2 429 -> 102, 379 -> 160,
+// 303 -> 144 us; 120 layers, k = 1 to 7, strides 3 to 8: input gradient 0.42 in the mean, 0.09 to 0.83; forward 0.61, 0.20 to 1.06, but
+// 1 x 1 with a stride from 5 on, which uses few of the pixels it stages, 0.41 to 1.25; the weight gradient has strides 1 and 2 only).
+// Without, 70 layers of 48 to 400 channels: the forward up to 96 (0.51 to 0.98; 161 and more 0.6 to 1.7), the weight gradient up
 // to 64 with up to 128 filters (0.43 to 0.97; beyond up to 2.0), the input gradient up to 64, and where the other's matrix
 // multiply has fewer tiles (64 x 64) than the chip has CUs (0.10 to 0.91; beyond up to 1.6).
 // Single orientations: where modelled at less than 0.85 of the time of the kernels that place (200 layers of 5 to 600 channels and
@@ -183,13 +185,14 @@ size_t ig_part_bytes(const rotconv_plan* p, const IgShape& s) {
 // ... and the least that either forward makes do with: the shares and one block's weights
 size_t ig_least_bytes(const rotconv_plan* p, const IgShape& s) { return ig_part_bytes(p, s) + ig_fwd_block_bytes(p, s); }
 void choose_ig(rotconv_plan* p, bool averaged) {
-  if (!ig_fwd_supported(p)) return;
+  if (!ig_fwd_supported(p) || p->d.stride > 8) return;
   if (p->gs && p->opt.gs == 0) {
     // what rotconv_pool_fwd_static holds wherever it holds the products (behind widened copies that may be less than its array)
     const size_t holds = p->d.dtype == ROTCONV_F32 ? std::max<size_t>(gs_ws_bytes(p), ROTCONV_STATIC_SCRATCH_BYTES) : gs_ws_bytes(p);
     const rotconv_desc& d = p->d;
     const bool strided = d.stride > 1;
-    const IgShape s = !averaged && (strided || d.R == 1 || d.Cin <= 96) ? ig_fwd_shape(p, holds) : IgShape();
+    const bool turns = strided ? d.stride <= 4 * d.k : d.Cin <= 96;
+    const IgShape s = !averaged && (d.R == 1 || turns) ? ig_fwd_shape(p, holds) : IgShape();
     if (s.mt && ig_fwd_block_bytes(p, s) <= holds) p->ig[1] = s;
     if (d.R == 1) p->ig[0] = p->ig[1];
     if ((strided || (d.Cin <= 64 && d.Cout <= 128)) && ig_bwd_weight_supported(p)) {

@@ -138,8 +138,10 @@ __global__ __launch_bounds__(256 * WC, 2) void k_ig_bwd_data(const float* __rest
   };
   constexpr int kPa[5] = {2, 0, 1, 1, 0}, kPb[5] = {0, 2, 1, 0, 1};          // the small products; then the parts' first ones
   const u32x4* wl = wp + (size_t)min(cb, g.ncb - 1) * g.nch * g.kk * MT * 192 + lane;
+  // with strides beyond k no tap reaches most kinds of pixels: their gradients are zero
+  const bool reached = (py + g.pad) % g.stride < g.k && (px + g.pad) % g.stride < g.k;
 #pragma unroll 1
-  for (int c = c0; c < c1; ++c) {
+  for (int c = c0; c < (reached ? c1 : c0); ++c) {
     const u32x4* wq = wl + (size_t)c * g.kk * MT * 192;
     if (c > c0) __syncthreads();
     stage(c);

@@ -89,3 +89,21 @@ def test_values_beyond_the_parts(k, stride):
         assert np.isfinite(got).all() and _rel(got, ref) < 1e-5
     got, ref = both(g * np.float32(1e-22), w * np.float32(1e-14), idx)
     assert _rel(got, ref) < 1e-5
+
+
+# strides around and beyond the filter (kinds of pixels that no tap reaches), the largest that one contraction takes, and beyond it
+STRIDES = [L(f"s{k}_{stride}_{pad}", N=1, Cin=20, H=H, W=W, Cout=40, R=4, k=k, stride=stride, pad=pad, seed=2450 + i, x_dist="normal")
+           for i, (H, W, k, stride, pad) in enumerate([(61, 67, 1, 4, 0), (64, 70, 2, 5, 1), (90, 85, 3, 8, 0), (97, 96, 5, 7, 3),
+                                                       (90, 99, 3, 9, 1), (800, 530, 3, 260, 1)])]
+
+
+@pytest.mark.parametrize("cfg", STRIDES, ids=[c.name for c in STRIDES])
+def test_strides(cfg):
+    x, w, g, idx = _inputs(cfg)
+    lay = pu.GpuLayer(cfg, x, w)
+    dx = lay.pool_bwd_data(g, idx)
+    ref = _reference(cfg, w, g, idx)
+    assert _rel(dx, ref) < _bar(cfg)
+    assert not np.asarray(dx)[np.asarray(ref) == 0].any()
+    _, yp, _, _ = orc.layer_fwd(x, w, cfg.R, None, cfg.mode, cfg.stride, cfg.pad, cfg.G)
+    assert _rel(lay.pool_fwd()[0], yp) < _bar(cfg)

@@ -76,3 +76,12 @@ def test_executed_work_of_one_contraction():
     assert work(2, 3, 512, 512, 64)[::2] == [4, 4]
     assert work(2, 3, 512, 512, 64, options=dict(bf16_parts=-1))[::2] == [1, 1]
     assert work(2, 32, 96, 96, 32, R=1, k=5, pad=2)[0] == 1
+
+
+def test_strides_that_one_contraction_takes():
+    """Strides up to 8 (each remainder of a pixel is a launch dimension), the forward up to four times the filter."""
+    taken = lambda k, stride: [rc.Plan(4, 64, 40 * stride, 30 * stride, 128, k=k, stride=stride, pad=k // 2).conv_equivalents(i) == 4 for i in (0, 1)]
+    assert taken(3, 6) == [True, True] and taken(2, 8) == [True, True] and taken(1, 4) == [True, True]
+    assert taken(3, 8) == [False, True]                     # no tile of 64 outputs whose pixels fit LDS
+    assert taken(1, 5) == [False, True] and taken(3, 9) == [False, False]
+    assert [rc.Plan(4, 64, 600, 600, 128, k=3, stride=300, pad=1).conv_equivalents(i) for i in range(3)] == [1, 1, 1]
