@@ -172,7 +172,8 @@ void choose_fwd(rotconv_plan* p) {
 // in the mean, at most 0.78, 0.97 and 0.81.  With a stride of up to 8 wherever a tile fits LDS (4x128 -> 128, 128x128, stride 2 429 -> 102, 379 -> 160,
 // 303 -> 144 us; 120 layers, k = 1 to 7, strides 3 to 8: input gradient 0.42 in the mean, 0.09 to 0.83; forward 0.61, 0.20 to 1.06, but
 // 1 x 1 with a stride from 5 on, which uses few of the pixels it stages, 0.41 to 1.25; the weight gradient has strides 1 and 2 only).
-// Without, 70 layers of 48 to 400 channels: the forward up to 96 (0.51 to 0.98; 161 and more 0.6 to 1.7), the weight gradient up
+// k = 8 to 15, 40 layers: forward 0.03 to 0.58, input gradient 0.03 to 0.97, weight gradient 0.09 to 1.02.
+// Without a stride, 70 layers of 48 to 400 channels: the forward up to 96 (0.51 to 0.98; 161 and more 0.6 to 1.7), the weight gradient up
 // to 64 with up to 128 filters (0.43 to 0.97; beyond up to 2.0), the input gradient up to 64, and where the other's matrix
 // multiply has fewer tiles (64 x 64) than the chip has CUs (0.10 to 0.91; beyond up to 1.6).
 // Single orientations: where modelled at less than 0.85 of the time of the kernels that place (200 layers of 5 to 600 channels and
@@ -205,7 +206,7 @@ void choose_ig(rotconv_plan* p, bool averaged) {
   } else if (!averaged && p->d.R == 1 && p->fast[0] && p->opt.fwd_csplit == 0) {
     const IgShape s = ig_fwd_shape(p, (size_t)64 << 20);
     const double other = p4_fwd_us(p);
-    if (s.mt && other > 12. && s.us < 0.85 * other) p->ig[0] = s;
+    if (s.mt && s.us < 0.85 * other) p->ig[0] = s;      // (other: negative where there is no such kernel)
   }
   for (const IgShape& s : p->ig)
     if (s.mt) p->ws_bytes = std::max(p->ws_bytes, ig_part_bytes(p, s) + align256(ig_fwd_pack_bytes(p, s)));
