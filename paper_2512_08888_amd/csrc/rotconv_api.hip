@@ -176,8 +176,9 @@ void choose_fwd(rotconv_plan* p) {
 // Without a stride, 70 layers of 48 to 400 channels: the forward up to 96 (0.51 to 0.98; 161 and more 0.6 to 1.7), the weight gradient up
 // to 64 with up to 128 filters (0.43 to 0.97; beyond up to 2.0), the input gradient up to 64, and where the other's matrix
 // multiply has fewer tiles (64 x 64) than the chip has CUs (0.10 to 0.91; beyond up to 1.6).
-// Single orientations: where modelled at less than 0.85 of the time of the kernels that place (200 layers of 5 to 600 channels and
-// filters: 0.93 in the mean of all with that rule, 0.23 to 1.05; taken everywhere up to 1.3 on large maps).
+// Single orientations: with other filters and strides always (120 layers of 5 to 400 channels and filters, k = 1 to 8, strides 1 to 8:
+// 0.38 in the mean, 0.02 to 0.93); 3 x 3 at stride 1 where modelled at less than 0.85 of the time of the kernels that place (200 layers
+// of 5 to 600 channels and filters: 0.93 in the mean of all with that rule, 0.23 to 1.05; taken everywhere up to 1.3 on large maps).
 // averaged: the plan of an averaged bank (or its padded one), whose forward is the one that the call without a workspace runs: on the
 // kernels that place, whose scratch is small.
 size_t ig_part_bytes(const rotconv_plan* p, const IgShape& s) {

@@ -104,3 +104,65 @@ def test_values_beyond_the_parts(k, stride):
         assert np.allclose(got[fin], ref[fin], rtol=1e-4, atol=1e-4 * np.abs(ref[fin & (np.abs(ref) < 1e20)]).max())
     got, ref = both(x * np.float32(1e-22), w * np.float32(1e-14))
     assert _rel(got, ref) < 1e-5
+
+
+# single orientations with filters of other sizes and strides: even and odd k, with and without centre and remainder of rows, whole and
+# with channel shares, channels and filters around a chunk (32) and one or two blocks (16)
+ONE_OTHER = [L(f"p{k}_{stride}_{Cin}_{H}x{W}_{Cout}", N=N, Cin=Cin, H=H, W=W, Cout=Cout, R=1, k=k, stride=stride, pad=pad,
+               seed=2700 + i, x_dist="normal")
+             for i, (N, Cin, H, W, Cout, k, stride, pad) in enumerate([
+                 (1, 32, 20, 30, 40, 1, 1, 0), (2, 33, 19, 33, 17, 2, 1, 1), (1, 31, 40, 61, 15, 2, 2, 0), (3, 64, 17, 18, 33, 3, 2, 1),
+                 (1, 65, 31, 64, 16, 3, 1, 0), (1, 20, 60, 72, 31, 3, 3, 2), (2, 64, 16, 15, 32, 4, 1, 2), (2, 32, 50, 96, 33, 5, 1, 2),
+                 (1, 300, 12, 12, 48, 5, 2, 2), (1, 9, 64, 64, 16, 7, 2, 3), (1, 512, 9, 9, 64, 1, 1, 0), (1, 400, 11, 13, 70, 7, 1, 3),
+                 (4, 40, 40, 41, 32, 4, 4, 0), (1, 24, 64, 90, 20, 2, 8, 0)])]
+
+
+@pytest.mark.parametrize("cfg", ONE_OTHER, ids=[c.name for c in ONE_OTHER])
+def test_single_orientation_of_other_filters(cfg):
+    x, w = synth.make_x(cfg), synth.make_w(cfg)
+    lay = pu.GpuLayer(cfg, x, w)
+    assert lay.plan.kernel_name(0) == "mfma_gemm_scatter"
+    got = lay.fwd().cpu().numpy()
+    ref = orc.rotconv_fwd(x, orc.expand_bank(w, 1, None, cfg.mode), cfg.stride, cfg.pad).reshape(got.shape)
+    assert _rel(got, ref) < _bar(cfg)
+    placed = pu.GpuLayer(cfg, x, w, options=dict(gs=1)).fwd().cpu().numpy()
+    assert cfg.k == 1 or not np.array_equal(got, placed)       # (1 x 1: the same sums of 32 channels in the same order)
+    sure = np.abs(ref) > 1e-5 * np.abs(ref).max()
+    for relu in (False, True):
+        yp, idx = pu.GpuLayer(cfg, x, w, relu=relu).pool_fwd()
+        dead = (ref <= 0) & relu
+        assert _rel(yp, np.where(dead, 0, ref)) < _bar(cfg)
+        assert np.array_equal(idx[sure], np.where(dead, 255, 0)[sure])
+
+
+@pytest.mark.parametrize("cfg", [ONE_OTHER[2], ONE_OTHER[6], ONE_OTHER[11]], ids=lambda c: c.name)
+def test_single_orientation_of_other_filters_dyadic(cfg):
+    x, w = synth.make_x_dyadic(cfg), synth.make_w_dyadic(cfg)
+    lay = pu.GpuLayer(cfg, x, w)
+    got = lay.fwd().cpu().numpy()
+    ref = orc.rotconv_fwd(x, orc.expand_bank(w, 1, None, cfg.mode), cfg.stride, cfg.pad).reshape(got.shape)
+    assert np.array_equal(got.astype(np.float64), ref) and np.array_equal(lay.pool_fwd()[0].astype(np.float64), ref)
+
+
+@pytest.mark.parametrize("k,stride", [(5, 2), (3, 1)])
+def test_bf16_tensors(k, stride):
+    """A bf16 plan of such a layer widens its tensors and rounds what the fp32 kernels give once: to half a bf16 ulp in the norm."""
+    cfg = L("b16", N=2, Cin=40, H=33, W=52, Cout=36, R=4, k=k, stride=stride, pad=0, seed=2750, x_dist="normal")
+    r = np.random.default_rng(cfg.seed)
+    x, w, g = (pu.round_bf16(a) for a in (synth.make_x(cfg), synth.make_w(cfg), synth.make_g(cfg)))
+    plan = rc.Plan.from_config(cfg, dtype=rc.BF16)
+    assert [plan.kernel_name(i) for i in range(3)] == ["mfma_gemm_scatter"] * 3 and [plan.conv_equivalents(i) for i in range(3)] == [4] * 3
+    xd, wd, gd = (pu.dev(a, torch.bfloat16) for a in (x, w, g))
+    yp = torch.full((cfg.N, plan.Cpooled, plan.Ho, plan.Wo), float("nan"), dtype=torch.bfloat16, device="cuda")
+    idx = torch.full(yp.shape, 254, dtype=torch.uint8, device="cuda")
+    dx, dw = torch.full_like(xd, float("nan")), torch.full(wd.shape, float("nan"), device="cuda")
+    y, ref, _, w_rot = orc.layer_fwd(x, w, cfg.R, None, cfg.mode, cfg.stride, cfg.pad, cfg.G)
+    rc.rotconv_pool_fwd(plan, xd, wd, yp, idx)
+    pu.check_idx(idx.cpu().numpy(), y, orc.rotconv_fwd(np.abs(x), np.abs(w_rot), cfg.stride, cfg.pad), cfg.G, cfg.name)
+    given = r.integers(0, 4, yp.shape).astype(np.uint8)
+    rc.rotconv_pool_bwd_data(plan, gd, pu.dev(given), wd, dx)
+    rc.rotconv_pool_bwd_weight(plan, xd, gd, pu.dev(given), dw)
+    torch.cuda.synchronize()
+    rdx, rdw = orc.layer_bwd(x, w, g, given, cfg.R, None, cfg.mode, cfg.stride, cfg.pad, cfg.G)
+    assert _rel(yp.float().cpu().numpy(), ref) < 2.0 ** -9 and _rel(dx.float().cpu().numpy(), rdx) < 2.0 ** -9
+    assert _rel(dw.cpu().numpy(), rdw) < 5e-7

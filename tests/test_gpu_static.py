@@ -81,3 +81,20 @@ AVG_ODD = [
 @pytest.mark.parametrize("cfg,over", AVG_ODD, ids=[c.name for c, _ in AVG_ODD])
 def test_average_pooling_on_padded_rows(cfg, over):
     _both(cfg, over, 0)
+
+
+# one contraction whose shares leave room for some of its packed weights only: slices of filter blocks, the last of them ragged, two
+# blocks a workgroup; with the workspace all at once
+SLICED = [
+    (L("s_20_of_71", N=1, Cin=814, H=24, W=19, Cout=1122, R=4, k=1, stride=2, pad=0, seed=2231), {}),
+    (L("s_relu_70_of_76", N=1, Cin=667, H=13, W=29, Cout=1212, R=4, k=1, stride=2, pad=0, seed=2232), dict(relu=True)),
+    (L("s_one_tile", N=2, Cin=458, H=59, W=3, Cout=1486, R=4, k=1, stride=2, pad=0, seed=2233), {}),
+    (L("s_one_turn", N=1, Cin=1026, H=11, W=22, Cout=737, R=1, k=1, pad=0, seed=2234), {}),
+]
+
+
+@pytest.mark.parametrize("cfg,over", SLICED, ids=[c.name for c, _ in SLICED])
+def test_one_contraction_in_slices(cfg, over):
+    plan = rc.Plan.from_config(cfg, **over)
+    assert plan.kernel_name(0) == "mfma_gemm_scatter" and plan.bf16_parts(0) and plan.workspace_bytes > 16 << 20
+    _both(cfg, over, 0)
