@@ -154,7 +154,8 @@ typedef struct {
                            orientations as one contraction over channels and taps, nothing placed), 1 always
                            (products placed), -1 never (generic kernels)                                       */
   int32_t gs_chunk_mb;  /* MiB of products that family keeps in the workspace at once: 0 = 512, n > 0 = n,
-                           -1 = one image at a time (at least one image's worth is always taken)               */
+                           -1 = one image at a time (at least one image's worth is always taken); the shares of
+                           one contraction are bounded by the same, beside its packed weights                  */
   int32_t bwd_lut;      /* fp32 gradients of layers whose pool group spans several first-quadrant banks:
                            0 automatic (routed gradients folded into the base taps, one contraction),
                            -1 never (one contraction per bank)                                                 */

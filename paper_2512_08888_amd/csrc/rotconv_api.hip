@@ -189,8 +189,10 @@ size_t ig_least_bytes(const rotconv_plan* p, const IgShape& s) { return ig_part_
 void choose_ig(rotconv_plan* p, bool averaged) {
   if (!ig_fwd_supported(p) || p->d.stride > 8) return;
   if (p->gs && p->opt.gs == 0) {
-    // what rotconv_pool_fwd_static holds wherever it holds the products (behind widened copies that may be less than its array)
-    const size_t holds = p->d.dtype == ROTCONV_F32 ? std::max<size_t>(gs_ws_bytes(p), ROTCONV_STATIC_SCRATCH_BYTES) : gs_ws_bytes(p);
+    // what rotconv_pool_fwd_static holds wherever it holds the products (behind widened copies that may be less than its array); no
+    // more than these where the caller bounds them (option gs_chunk_mb)
+    const bool bounded = p->opt.gs_chunk_mb != 0;
+    const size_t holds = p->d.dtype == ROTCONV_F32 && !bounded ? std::max<size_t>(gs_ws_bytes(p), ROTCONV_STATIC_SCRATCH_BYTES) : gs_ws_bytes(p);
     const rotconv_desc& d = p->d;
     const bool strided = d.stride > 1;
     const bool turns = strided ? d.stride <= 4 * d.k : d.Cin <= 96;
@@ -202,9 +204,10 @@ void choose_ig(rotconv_plan* p, bool averaged) {
       p->ws_bytes = std::max(p->ws_bytes, ig_bwd_weight_ws_bytes(p));
     }
     const long tiles = (long)((d.Cin + 63) / 64) * ((d.H * d.W + 63) / 64) * d.N;
-    if ((strided || d.Cin <= 64 || tiles < 256) && ig_bwd_data_supported(p)) p->ig_dx = ig_bwd_data_shape(p, (size_t)256 << 20);
+    if ((strided || d.Cin <= 64 || tiles < 256) && ig_bwd_data_supported(p))
+      p->ig_dx = ig_bwd_data_shape(p, bounded ? std::min(gs_chunk_budget(p), (size_t)256 << 20) : (size_t)256 << 20);
     if (p->ig_dx.mt) p->ws_bytes = std::max(p->ws_bytes, ig_bwd_data_ws_bytes(p, p->ig_dx));
-  } else if (!averaged && p->d.R == 1 && p->fast[0] && p->opt.fwd_csplit == 0) {
+  } else if (!averaged && p->d.dtype == ROTCONV_F32 && p->d.R == 1 && p->fast[0] && p->opt.fwd_csplit == 0) {
     const IgShape s = ig_fwd_shape(p, (size_t)64 << 20);
     const double other = p4_fwd_us(p);
     if (s.mt && s.us < 0.85 * other) p->ig[0] = s;      // (other: negative where there is no such kernel)

@@ -18,7 +18,8 @@ void launch_ig_fwd(const rotconv_plan* p, const IgShape& s, bool pooled, const f
                    void* ws, size_t ws_bytes, hipStream_t st);
 
 
-// Input gradient of the same layers with four turns, pooled over them.  Shapes as above, `blocks` of input channels.
+// Input gradient of the same layers with four turns, pooled over them.  Shapes as above, `blocks` of input channels; the budget is that
+// of shares, beside the weights.
 bool ig_bwd_data_supported(const rotconv_plan* p);
 IgShape ig_bwd_data_shape(const rotconv_plan* p, size_t budget);
 size_t ig_bwd_data_ws_bytes(const rotconv_plan* p, const IgShape& s);       // packed weights and shares

@@ -398,6 +398,7 @@ IgShape ig_bwd_data_shape(const rotconv_plan* p, size_t budget) {
         if (!tiles || cost < old) { th = h; tw = w; pix = px; tiles = n; }
       }
       if (!tiles) continue;
+      if (pack_bytes(p, mt) > (size_t)256 << 20) continue;
       const int blocks = channel_blocks(p, mt);
       for (int wc = 1; wc <= (blocks > 1 ? 2 : 1); ++wc)
         for (int ns = 1; ns <= (budget ? nch : 1); ++ns) {
@@ -407,7 +408,7 @@ IgShape ig_bwd_data_shape(const rotconv_plan* p, size_t budget) {
             const int oper = (p->kk / 4 + os - 1) / os;
             if (os > 1 && (p->kk / 4 + oper - 1) / oper != os) continue;
             IgShape s{mt, nt, wc, th, tw, ns, os, 0.};
-            if (pack_bytes(p, mt) + (s.parts() > 1 ? s.parts() * part : 0) + 512 > budget) continue;
+            if (s.parts() > 1 && pack_bytes(p, mt) + s.parts() * part + 512 > budget) continue;
             const double wgs = (double)tiles * d.N * ((blocks + wc - 1) / wc) * ns * os * st2;
             const double mfma = (os > 1 ? 16 * oper + 1 : 4 * p->kk) / (double)st2 * nt * mt * 6e-3;
             const double stage = per * (1.6 + 0.28 * pix * 4 / (256. * wc));

@@ -85,3 +85,12 @@ def test_strides_that_one_contraction_takes():
     assert taken(3, 8) == [False, True]                     # no tile of 64 outputs whose pixels fit LDS
     assert taken(1, 5) == [False, True] and taken(3, 9) == [False, False]
     assert [rc.Plan(4, 64, 600, 600, 128, k=3, stride=300, pad=1).conv_equivalents(i) for i in range(3)] == [1, 1, 1]
+
+
+def test_one_contraction_keeps_to_the_scratch_that_the_caller_bounds():
+    """gs_chunk_mb: beside what the placed products take, the packed weights (six bytes each, padded to 32) and a MiB for the weight
+    gradient's partial sums."""""
+    for N, Cin, H, W, Cout, k, stride in ((3, 8, 34, 12, 14, 7, 1), (4, 43, 9, 17, 20, 7, 2), (8, 60, 30, 40, 40, 7, 1), (6, 64, 24, 24, 300, 5, 1), (4, 64, 28, 28, 64, 5, 2)):
+        ws = [rc.Plan(N, Cin, H, W, Cout, k=k, stride=stride, pad=k // 2, options=dict(gs_chunk_mb=-1, gs=gs)).workspace_bytes for gs in (0, 1)]
+        pad32 = lambda v: (v + 31) // 32 * 32
+        assert ws[0] <= ws[1] + 6 * pad32(Cin) * pad32(Cout) * k * k + (1 << 20)
