@@ -167,36 +167,51 @@ void choose_fwd(rotconv_plan* p) {
 }
 
 // One contraction over channels and taps instead of products that are placed, or of gradients routed through memory.
-// Filters of other sizes and strides with the four quarter turns, pooled, whose products it forms four times as often: 60 layers of
-// 12 to 64 channels and filters, k = 2, 5, 7, stride 1 and 2: forward 0.45, weight gradient 0.49, input gradient 0.31 of the time
-// in the mean, at most 0.78, 0.97 and 0.81.  With a stride of up to 8 wherever a tile fits LDS (4x128 -> 128, 128x128, stride 2 429 -> 102, 379 -> 160,
-// 303 -> 144 us; 120 layers, k = 1 to 7, strides 3 to 8: input gradient 0.42 in the mean, 0.09 to 0.83; forward 0.61, 0.20 to 1.06, but
-// 1 x 1 with a stride from 5 on, which uses few of the pixels it stages, 0.41 to 1.25; the weight gradient has strides 1 and 2 only).
-// k = 8 to 15, 40 layers: forward 0.03 to 0.58, input gradient 0.03 to 0.97, weight gradient 0.09 to 1.02.
-// Without a stride, 70 layers of 48 to 400 channels: the forward up to 96 (0.51 to 0.98; 161 and more 0.6 to 1.7), the weight gradient up
-// to 64 with up to 128 filters (0.43 to 0.97; beyond up to 2.0), the input gradient up to 64, and where the other's matrix
-// multiply has fewer tiles (64 x 64) than the chip has CUs (0.10 to 0.91; beyond up to 1.6).
-// Single orientations: with other filters and strides always (120 layers of 5 to 400 channels and filters, k = 1 to 8, strides 1 to 8:
-// 0.38 in the mean, 0.02 to 0.93); 3 x 3 at stride 1 where modelled at less than 0.85 of the time of the kernels that place (200 layers
-// of 5 to 600 channels and filters: 0.93 in the mean of all with that rule, 0.23 to 1.05; taken everywhere up to 1.3 on large maps).
-// averaged: the plan of an averaged bank (or its padded one), whose forward is the one that the call without a workspace runs: on the
-// kernels that place, whose scratch is small.
+// Filters of other sizes and strides with the four quarter turns, pooled, whose products it forms four times as often: 60 layers
+// of 12 to 64 channels and filters, k = 2, 5, 7, stride 1 and 2: forward 0.45, weight gradient 0.49, input gradient 0.31 of the
+// time in the mean, at most 0.78, 0.97 and 0.81.  With a stride of up to 8 wherever a tile fits LDS (4x128 -> 128, 128x128, stride 2
+// 429 -> 102, 379 -> 160, 303 -> 144 us; 120 layers, k = 1 to 7, strides 3 to 8: input gradient 0.42 in the mean, 0.09 to 0.83;
+// forward 0.61, 0.20 to 1.06, but 1 x 1 with a stride from 5 on, which uses few of the pixels it stages, 0.41 to 1.25; the weight
+// gradient has strides 1 and 2 only).  k = 8 to 15, 40 layers: forward 0.03 to 0.58, input gradient 0.03 to 0.97, weight gradient
+// 0.09 to 1.02.
+// Without a stride, 70 layers of 48 to 400 channels: the forward up to 96 (0.51 to 0.98; 161 and more 0.6 to 1.7), the weight
+// gradient up to 64 with up to 128 filters (0.43 to 0.97; beyond up to 2.0), the input gradient up to 64, and where the other's
+// matrix multiply has fewer tiles (64 x 64) than the chip has CUs (0.10 to 0.91; beyond up to 1.6).
+// Single orientations: with other filters and strides always (120 layers of 5 to 400 channels and filters, k = 1 to 8, strides 1
+// to 8: 0.38 in the mean, 0.02 to 0.93); 3 x 3 at stride 1 where modelled at less than 0.85 of the time of the kernels that place
+// (200 layers of 5 to 600 channels and filters: 0.93 in the mean of all with that rule, 0.23 to 1.05; taken everywhere up to 1.3 on
+// large maps).
+// Not for few filters, of which a tile has 16: stride 1 and at most eight from 5e9 products of one turn on (padded, times the
+// padding: 7x66 -> 1, 238x240, 5 x 5 125 us and 417 so; 148 layers above the line 0.45 to 3.34, 1.21 in the mean), single orientations
+// from 20e9; nor for 1 x 1 to 2 x 2 filters with longer strides, more than 64 channels and 3 MB of images, of whose staged
+// pixels few are used (3x114 -> 50, 212x33, 1 x 1, stride 3 19 / 37; 0.6 to 2.0).
+// averaged: the plan of an averaged bank (or its padded one), whose forward is the one that the call without a workspace runs: on
+// the kernels that place, whose scratch is small.
 size_t ig_part_bytes(const rotconv_plan* p, const IgShape& s) {
   return s.parts() > 1 ? align256((size_t)s.parts() * p->d.N * p->d.Cout * p->d.R * p->Ho * p->Wo * 4) : 0;
 }
 // ... and the least that either forward makes do with: the shares and one block's weights
 size_t ig_least_bytes(const rotconv_plan* p, const IgShape& s) { return ig_part_bytes(p, s) + ig_fwd_block_bytes(p, s); }
+// rows or columns of whole tiles for each one there is
+double padding(int n, int tile) { return (double)((n + tile - 1) / tile * tile) / n; }
 void choose_ig(rotconv_plan* p, bool averaged) {
   if (!ig_fwd_supported(p) || p->d.stride > 8) return;
   if (p->gs && p->opt.gs == 0) {
     // what rotconv_pool_fwd_static holds wherever it holds the products (behind widened copies that may be less than its array); no
     // more than these where the caller bounds them (option gs_chunk_mb)
     const bool bounded = p->opt.gs_chunk_mb != 0;
-    const size_t holds = p->d.dtype == ROTCONV_F32 && !bounded ? std::max<size_t>(gs_ws_bytes(p), ROTCONV_STATIC_SCRATCH_BYTES) : gs_ws_bytes(p);
+    size_t holds = gs_ws_bytes(p);
+    if (p->d.dtype == ROTCONV_F32 && !bounded) holds = std::max<size_t>(holds, ROTCONV_STATIC_SCRATCH_BYTES);
     const rotconv_desc& d = p->d;
     const bool strided = d.stride > 1;
-    const bool turns = strided ? d.stride <= 4 * d.k : d.Cin <= 96;
-    const IgShape s = !averaged && (d.R == 1 || turns) ? ig_fwd_shape(p, holds) : IgShape();
+    const double image_bytes = 4.0 * d.N * d.Cin * d.H * d.W;      // of all images
+    // products of one turn, filters padded to a tile, times what the padding adds to each that is needed
+    const double outputs = (double)d.N * p->Ho * p->Wo, padded = padding(d.Cout, 16);
+    const double products = outputs * p->kk * d.Cin * d.Cout * padded * padded;
+    bool fwd = strided ? d.stride <= 4 * d.k && (d.k >= d.stride || d.stride < 3 || d.Cin <= 64 || image_bytes < 3e6) : d.Cin <= 96;
+    fwd = fwd || d.R == 1;
+    if (!strided && d.Cout <= 8 && products * padding(d.Cin, 32) > (d.R == 1 ? 20e9 : 5e9)) fwd = false;
+    const IgShape s = !averaged && fwd ? ig_fwd_shape(p, holds) : IgShape();
     if (s.mt && ig_fwd_block_bytes(p, s) <= holds) p->ig[1] = s;
     if (d.R == 1) p->ig[0] = p->ig[1];
     if ((strided || (d.Cin <= 64 && d.Cout <= 128)) && ig_bwd_weight_supported(p)) {

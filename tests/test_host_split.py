@@ -94,3 +94,21 @@ def test_one_contraction_keeps_to_the_scratch_that_the_caller_bounds():
         ws = [rc.Plan(N, Cin, H, W, Cout, k=k, stride=stride, pad=k // 2, options=dict(gs_chunk_mb=-1, gs=gs)).workspace_bytes for gs in (0, 1)]
         pad32 = lambda v: (v + 31) // 32 * 32
         assert ws[0] <= ws[1] + 6 * pad32(Cin) * pad32(Cout) * k * k + (1 << 20)
+
+
+def one_contraction(which):
+    """Does pass `which` of a pooled layer of four turns run as one contraction (which multiplies parts whatever the tiles)?"""
+    return lambda N, Cin, H, W, Cout, k, stride=1: rc.Plan(N, Cin, H, W, Cout, k=k, stride=stride, pad=k // 2 if k > 1 else 0).conv_equivalents(which) == 4
+
+
+def test_forward_of_few_filters_and_sparse_pixels():
+    """On both sides of its lines, which follow measured times."""
+    taken = one_contraction(0)
+    assert not taken(7, 66, 238, 240, 1, 5) and not taken(6, 94, 244, 257, 2, 4) and not taken(8, 84, 195, 106, 5, 5)
+    assert taken(7, 66, 40, 40, 1, 5) and taken(6, 94, 60, 60, 2, 4) and taken(8, 84, 195, 106, 9, 5)
+    assert taken(7, 66, 238, 240, 1, 5, stride=2)
+    assert not taken(3, 114, 212, 33, 50, 1, stride=3) and not taken(7, 192, 152, 90, 11, 2, stride=3)
+    assert taken(3, 64, 212, 33, 50, 1, stride=3) and taken(3, 114, 40, 33, 50, 1, stride=3) and taken(3, 114, 212, 33, 50, 1, stride=2)
+    # a single orientation: fewer tiles of products than 512 are on parts either way
+    one = lambda *a: rc.Plan(*a, R=1, k=7, pad=3).bf16_parts(0)
+    assert not one(7, 39, 179, 105, 1) and one(7, 39, 179, 105, 4) and one(4, 39, 90, 105, 1)
