@@ -185,6 +185,9 @@ void choose_fwd(rotconv_plan* p) {
 // padding: 7x66 -> 1, 238x240, 5 x 5 125 us and 417 so; 148 layers above the line 0.45 to 3.34, 1.21 in the mean), single orientations
 // from 20e9; nor for 1 x 1 to 2 x 2 filters with longer strides, more than 64 channels and 3 MB of images, of whose staged
 // pixels few are used (3x114 -> 50, 212x33, 1 x 1, stride 3 19 / 37; 0.6 to 2.0).
+// The input gradient from nine filters on: with fewer a sum of 32 is mostly padding (4x59 -> 3, 198x105, 5 x 5 62 us and 192 so) and
+// its cuts show (2 to 8 filters: error 0.8 to 1.23 of the routed form's, from 9 on 0.71 in the mean); and not for filters smaller than
+// their stride with up to 24 filters from 30 MB of images on (8x235 -> 14, 180x81, 1 x 1, stride 4 53 / 112).
 // averaged: the plan of an averaged bank (or its padded one), whose forward is the one that the call without a workspace runs: on
 // the kernels that place, whose scratch is small.
 size_t ig_part_bytes(const rotconv_plan* p, const IgShape& s) {
@@ -219,7 +222,8 @@ void choose_ig(rotconv_plan* p, bool averaged) {
       p->ws_bytes = std::max(p->ws_bytes, ig_bwd_weight_ws_bytes(p));
     }
     const long tiles = (long)((d.Cin + 63) / 64) * ((d.H * d.W + 63) / 64) * d.N;
-    if ((strided || d.Cin <= 64 || tiles < 256) && ig_bwd_data_supported(p))
+    const bool sparse = d.k < d.stride && d.Cout <= 24 && image_bytes > 3e7;
+    if ((strided || d.Cin <= 64 || tiles < 256) && d.Cout > 8 && !sparse && ig_bwd_data_supported(p))
       p->ig_dx = ig_bwd_data_shape(p, bounded ? std::min(gs_chunk_budget(p), (size_t)256 << 20) : (size_t)256 << 20);
     if (p->ig_dx.mt) p->ws_bytes = std::max(p->ws_bytes, ig_bwd_data_ws_bytes(p, p->ig_dx));
   } else if (!averaged && p->d.dtype == ROTCONV_F32 && p->d.R == 1 && p->fast[0] && p->opt.fwd_csplit == 0) {
