@@ -188,6 +188,9 @@ void choose_fwd(rotconv_plan* p) {
 // The input gradient from nine filters on: with fewer a sum of 32 is mostly padding (4x59 -> 3, 198x105, 5 x 5 62 us and 192 so) and
 // its cuts show (2 to 8 filters: error 0.8 to 1.23 of the routed form's, from 9 on 0.71 in the mean); and not for filters smaller than
 // their stride with up to 24 filters from 30 MB of images on (8x235 -> 14, 180x81, 1 x 1, stride 4 53 / 112).
+// The weight gradient not for at most eight filters from 4e9 such products on, strided 12e9 (4x112 -> 1, 292x170, 7 x 7, stride 2 70 us
+// and 268 so; above the line 1.15 in the mean), nor 2 x 2 taps where three of four products are padding and there are
+// more than 20000 outputs (8x3 -> 1, 50x146 24 / 43; 0.9 to 1.8).
 // averaged: the plan of an averaged bank (or its padded one), whose forward is the one that the call without a workspace runs: on
 // the kernels that place, whose scratch is small.
 size_t ig_part_bytes(const rotconv_plan* p, const IgShape& s) {
@@ -217,7 +220,10 @@ void choose_ig(rotconv_plan* p, bool averaged) {
     const IgShape s = !averaged && fwd ? ig_fwd_shape(p, holds) : IgShape();
     if (s.mt && ig_fwd_block_bytes(p, s) <= holds) p->ig[1] = s;
     if (d.R == 1) p->ig[0] = p->ig[1];
-    if ((strided || (d.Cin <= 64 && d.Cout <= 128)) && ig_bwd_weight_supported(p)) {
+    const double narrow = padding(d.Cin, 16);
+    const bool few = (d.Cout <= 8 && products * narrow > (strided ? 12e9 : 4e9)) ||
+                     (!strided && d.k == 2 && padded * narrow >= 4 && outputs > 2e4);
+    if ((strided || (d.Cin <= 64 && d.Cout <= 128)) && !few && ig_bwd_weight_supported(p)) {
       p->ig_dw = 1;
       p->ws_bytes = std::max(p->ws_bytes, ig_bwd_weight_ws_bytes(p));
     }

@@ -120,3 +120,10 @@ def test_input_gradient_of_few_filters_and_sparse_pixels():
     assert [taken(1, 30, 30, 30, c, 7, stride=2) for c in (4, 8, 9)] == [False, False, True]
     assert [taken(8, 235, 180, 81, c, 1, stride=4) for c in (14, 24, 25)] == [False, False, True]
     assert taken(1, 235, 180, 81, 14, 1, stride=4) and taken(8, 235, 180, 81, 14, 2, stride=2)
+
+
+def test_weight_gradient_of_few_filters():
+    taken = one_contraction(2)
+    assert not taken(4, 59, 198, 105, 3, 5) and not taken(4, 112, 292, 170, 1, 7, stride=2) and not taken(8, 3, 50, 146, 1, 2)
+    assert taken(4, 59, 40, 105, 3, 5) and taken(4, 59, 198, 105, 9, 5) and taken(4, 112, 100, 100, 1, 7, stride=2)
+    assert taken(1, 3, 50, 146, 1, 2) and taken(8, 16, 50, 146, 16, 2) and taken(8, 3, 50, 146, 1, 2, stride=2)
