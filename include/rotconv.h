@@ -150,9 +150,10 @@ typedef struct {
   int32_t fwd_csplit;   /* channel split of the 3x3 forward on small maps with deep inputs: 0 automatic,
                            1 never (where an unsplit kernel exists), n >= 2: n parts                        */
   int32_t gs;           /* shapes outside the 3x3 / stride 1 / pad 1 kernels on the matrix multiply + scatter
-                           family: 0 automatic (from about a megaflop; fp32 pooled forwards of R = 4 and single
-                           orientations as one contraction over channels and taps, nothing placed), 1 always
-                           (products placed), -1 never (generic kernels)                                       */
+                           family: 0 automatic (from about a megaflop; fp32 passes of R = 4 pooled over all turns
+                           and forwards of single orientations as one contraction, nothing placed or routed,
+                           where that is the faster form), 1 always (products placed, gradients routed),
+                           -1 never (generic kernels)                                                          */
   int32_t gs_chunk_mb;  /* MiB of products that family keeps in the workspace at once: 0 = 512, n > 0 = n,
                            -1 = one image at a time (at least one image's worth is always taken); the shares of
                            one contraction are bounded by the same, beside its packed weights                  */
@@ -171,9 +172,11 @@ typedef struct {
                            layers with four banks and at most 64 input channels), 1 wherever that kernel can run,
                            -1 never (pixels on the M side, eight pixels per lane)                                   */
   int32_t bf16_parts;   /* fp32 contractions of 3x3 layers as products of the operands' three bf16 parts on the bf16
-                           matrix cores (forward of layers with more than four channels, on base products too, forward and weight gradient of first layers of
-                           R = 4, gradients of quarter-turn layers, the matrix multiply + scatter family): 0 automatic (where that is the faster form), 1 wherever those kernels can run,
-                           -1 never (fp32 matrix instructions: exact products whatever the operands' magnitude)     */
+                           matrix cores (forward of layers with more than four channels, on base products too,
+                           forward and weight gradient of first layers of R = 4, gradients of quarter-turn layers,
+                           the matrix multiply + scatter family): 0 automatic (where that is the faster form),
+                           1 wherever those kernels can run, -1 never (fp32 matrix instructions: exact products
+                           whatever the operands' magnitude)                                                        */
   int32_t reserved[3];  /* must be 0 */
 } rotconv_plan_options;
 
@@ -240,8 +243,9 @@ int rotconv_pool_fwd(const rotconv_plan* plan, const void* x, const void* w, voi
 /* rotconv_pool_fwd for callers that cannot allocate device memory or bring a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and kernels as
  * rotconv_pool_fwd (banks and channel-split parts that do not fit at once go through in slices of filters, bit for bit
- * the same values), but the scratch (the re-laid banks and, for some plans, per-bank candidates or channel-split parts) lives in a file-scope device array of ROTCONV_STATIC_SCRATCH_BYTES that each GPU the library runs on
- * holds until the process ends.  The call makes no hipMalloc / hipFree and uploads nothing:
+ * the same values), but the scratch (the re-laid banks and, for some plans, per-bank candidates or channel-split parts)
+ * lives in a file-scope device array of ROTCONV_STATIC_SCRATCH_BYTES that each GPU the library runs on holds until the
+ * process ends.  The call makes no hipMalloc / hipFree and uploads nothing:
  *   - ROTCONV_ERR_UNSUPPORTED if the plan's tables are not on the current device yet (run any ordinary call
  *     of the plan there first; that first call is the one that allocates);
  *   - ROTCONV_ERR_WORKSPACE if this call's scratch need exceeds ROTCONV_STATIC_SCRATCH_BYTES (e.g. layers deeper
@@ -296,14 +300,14 @@ double rotconv_plan_conv_equivalents(const rotconv_plan* plan, int pass);
 /* Name of the kernel family a call of the given kind on this plan uses ("generic", "mfma_p4", "mfma_p4_base" (the
  * pooled forward on products of the base bank), "mfma_p4_bf16", "mfma_p4_bf16_lut" (a bf16 gradient whose routed
  * gradients are folded into the base taps in fp32 and rounded to bf16 once, the matrix operand), "mfma_gemm_scatter",
- * "valu_direct" (layers with at most four input channels: kernels of their own, see the plan option), "mfma_px_bf16" (the bf16 pooled forward with
- * a lane per pixel column)).  pass: 0 / 1 / 2 = the fused calls rotconv_pool_fwd / _bwd_data / _bwd_weight (and
- * rotconv_fwd); 3 / 4 = the unfused gradient calls rotconv_bwd_data / rotconv_bwd_weight when given
- * rotconv_workspace_bytes_unfused of scratch (with less they run "generic"). */
+ * "valu_direct" (layers with at most four input channels: kernels of their own, see the plan option), "mfma_px_bf16"
+ * (the bf16 pooled forward with a lane per pixel column)).  pass: 0 / 1 / 2 = the fused calls rotconv_pool_fwd /
+ * _bwd_data / _bwd_weight (and rotconv_fwd); 3 / 4 = the unfused gradient calls rotconv_bwd_data / rotconv_bwd_weight
+ * when given rotconv_workspace_bytes_unfused of scratch (with less they run "generic"). */
 const char* rotconv_plan_kernel_name(const rotconv_plan* plan, int pass);
-/* 1 if that pass (0 rotconv_pool_fwd, 1 rotconv_pool_bwd_data, 2 rotconv_pool_bwd_weight) multiplies bf16 parts of fp32
- * operands for aligned tensors (see rotconv_plan_options.bf16_parts), else 0; whatever the kernel family.  Which of these
- * passes form sums beyond the parts' range again in fp32 is said at the top of this file. */
+/* 1 if that pass (0 rotconv_pool_fwd, 1 rotconv_pool_bwd_data, 2 rotconv_pool_bwd_weight) multiplies bf16 parts of
+ * fp32 operands for aligned tensors (see rotconv_plan_options.bf16_parts), else 0; whatever the kernel family.  Which
+ * of these passes form sums beyond the parts' range again in fp32 is said at the top of this file. */
 int rotconv_plan_bf16_parts(const rotconv_plan* plan, int pass);
 
 #ifdef __cplusplus

@@ -46,12 +46,6 @@ struct FirstWGeom {
   uint32_t xbytes, gbytes;
 };
 
-__device__ __forceinline__ uint32_t load4(const uint8_t* p) {      // any alignment
-  uint32_t v;
-  __builtin_memcpy(&v, p, 4);
-  return v;
-}
-
 template <int CIN, int FB>
 __global__ __launch_bounds__(64 * kWaves, 2) void k_first_bwd_weight(const float* __restrict__ x, const float* __restrict__ gpool,
                                                                      const uint8_t* __restrict__ idx, float* __restrict__ part,

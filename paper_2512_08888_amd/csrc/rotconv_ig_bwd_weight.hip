@@ -42,12 +42,6 @@ struct IgDwGeom {
   uint32_t xbytes, gbytes;
 };
 
-__device__ __forceinline__ uint32_t load4(const uint8_t* p) {      // any alignment
-  uint32_t v;
-  __builtin_memcpy(&v, p, 4);
-  return v;
-}
-
 // TJ: taps of a row per wave (k in groups of TJ)
 template <int TJ, int ST>
 __global__ __launch_bounds__(64 * kWaves, 2) void k_ig_bwd_weight(const float* __restrict__ x, const float* __restrict__ gpool,

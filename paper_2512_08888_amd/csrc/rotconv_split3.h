@@ -114,6 +114,13 @@ __device__ __forceinline__ bool beyond_parts(float v) {
   return !(m < __builtin_inff()) || (m < 0x1p-100f && m != 0.f);
 }
 
+// Four indices (a byte each) at any alignment.
+__device__ __forceinline__ uint32_t load4(const uint8_t* p) {
+  uint32_t v;
+  __builtin_memcpy(&v, p, 4);
+  return v;
+}
+
 // Byte offset of positions outside an image in loads through its buffer descriptor: beyond the descriptor's size (the
 // kernels' limits on an image see to that), so that they read as zero.
 constexpr uint32_t kOutside = 0xfffffff0u;

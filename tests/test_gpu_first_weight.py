@@ -7,7 +7,6 @@ with the root of their number: sqrt(6 + 40) * 2^-24 in norm is 4e-7; 1e-6 leaves
 """
 import numpy as np
 import pytest
-import torch
 
 import parity_util as pu
 from oracle import rotconv_oracle as orc
