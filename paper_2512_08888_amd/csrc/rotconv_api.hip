@@ -185,7 +185,7 @@ void choose_fwd(rotconv_plan* p) {
 // padding: 7x66 -> 1, 238x240, 5 x 5 125 us and 417 so; 148 layers above the line 0.45 to 3.34, 1.21 in the mean), single orientations
 // from 20e9; nor for 1 x 1 to 2 x 2 filters with longer strides, more than 64 channels and 3 MB of images, of whose staged
 // pixels few are used (3x114 -> 50, 212x33, 1 x 1, stride 3 19 / 37; 0.6 to 2.0).
-// The input gradient from nine filters on: with fewer a sum of 32 is mostly padding (4x59 -> 3, 198x105, 5 x 5 62 us and 192 so) and
+// The input gradient from nine filters on: with fewer a sum of 32 is mostly padding (4x59 -> 3, 198x105, 5 x 5 49 us and 150 so) and
 // its cuts show (2 to 8 filters: error 0.8 to 1.23 of the routed form's, from 9 on 0.71 in the mean); and not for filters smaller than
 // their stride with up to 24 filters from 30 MB of images on (8x235 -> 14, 180x81, 1 x 1, stride 4 53 / 112).
 // The weight gradient not for at most eight filters from 4e9 such products on, strided 12e9 (4x112 -> 1, 292x170, 7 x 7, stride 2 70 us

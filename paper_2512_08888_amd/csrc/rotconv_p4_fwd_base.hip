@@ -70,10 +70,10 @@ int base_park(const rotconv_plan* p) {
 }
 
 // Products of the operands' bf16 parts (six bytes a weight; up to three banks' sums parked: 128 channels of R = 16, 160
-// of R = 8 without streaming) instead of fp32 instructions?  More than four channels always: 34 layers of 13 to 512 channels,
-// 14 to 300 rows and columns, 0.78 of the time in the mean, 0.28 to 1.00 (shallow layers, which the vector ALU bounds either way,
-// 0.91 to 1.00), and 0.37 to 0.86 of the error.  Not where an image is
-// so large that the offset that stands for "outside" lies in it.
+// of R = 8 without streaming) instead of fp32 instructions?  More than four channels always: 40 layers that run this kernel, of 5 to
+// 512 channels and 14 to 300 rows and columns, 0.85 of the time in the mean, 0.69 to 1.01 (up to 32 channels, where the vector ALU
+// bounds either form, 0.89 to 1.01), and 0.75 of the error in the mean of 471, at most 0.99.  Not where an image is so large that
+// the offset that stands for "outside" lies in it.
 bool parts_resident(const rotconv_plan* p) {
   const int chunks = cin_pad_base(p->d.Cin) / 32;
   return (size_t)chunks * kS3FwdChunk * 4 + base_lds_extra(parts_park(p->host.Q, chunks)) <= 160 * 1024;
