@@ -182,12 +182,12 @@ void choose_fwd(rotconv_plan* p) {
 // (200 layers of 5 to 600 channels and filters: 0.93 in the mean of all with that rule, 0.23 to 1.05; taken everywhere up to 1.3 on
 // large maps).
 // Not for few filters, of which a tile has 16: stride 1 and at most eight from 5e9 products of one turn on (padded, times the
-// padding: 7x66 -> 1, 238x240, 5 x 5 125 us and 417 so; 148 layers above the line 0.45 to 3.34, 1.21 in the mean), single orientations
-// from 20e9; nor for 1 x 1 to 2 x 2 filters with longer strides, more than 64 channels and 3 MB of images, of whose staged
+// padding: 7x66 -> 1, 238x240, 5 x 5 125 us and 417 so; 148 layers above the line 0.45 to 3.34, 1.21 in the mean), single
+// orientations from 20e9; nor for 1 x 1 to 2 x 2 filters with longer strides, more than 64 channels and 3 MB of images, of whose staged
 // pixels few are used (3x114 -> 50, 212x33, 1 x 1, stride 3 19 / 37; 0.6 to 2.0).
-// The input gradient from nine filters on: with fewer a sum of 32 is mostly padding (4x59 -> 3, 198x105, 5 x 5 49 us and 150 so) and
-// its cuts show (2 to 8 filters: error 0.8 to 1.23 of the routed form's, from 9 on 0.71 in the mean); and not for filters smaller than
-// their stride with up to 24 filters from 30 MB of images on (8x235 -> 14, 180x81, 1 x 1, stride 4 53 / 112).
+// The input gradient from nine filters on, eight from 5 x 5 taps on: with fewer a sum of 32 is mostly padding (4x59 -> 3, 198x105,
+// 5 x 5 49 us and 150 so) and its cuts show (error up to 1.23 of the routed form's, from there on 0.71 in the mean); and not for
+// filters smaller than their stride with up to 24 filters from 30 MB of images on (8x235 -> 14, 180x81, 1 x 1, stride 4 53 / 112).
 // The weight gradient not for at most eight filters from 4e9 such products on, strided 12e9 (4x112 -> 1, 292x170, 7 x 7, stride 2 70 us
 // and 268 so; above the line 1.15 in the mean), nor 2 x 2 taps where three of four products are padding and there are
 // more than 20000 outputs (8x3 -> 1, 50x146 24 / 43; 0.9 to 1.8).
@@ -229,7 +229,7 @@ void choose_ig(rotconv_plan* p, bool averaged) {
     }
     const long tiles = (long)((d.Cin + 63) / 64) * ((d.H * d.W + 63) / 64) * d.N;
     const bool sparse = d.k < d.stride && d.Cout <= 24 && image_bytes > 3e7;
-    if ((strided || d.Cin <= 64 || tiles < 256) && d.Cout > 8 && !sparse && ig_bwd_data_supported(p))
+    if ((strided || d.Cin <= 64 || tiles < 256) && d.Cout >= (d.k < 5 ? 9 : 8) && !sparse && ig_bwd_data_supported(p))
       p->ig_dx = ig_bwd_data_shape(p, bounded ? std::min(gs_chunk_budget(p), (size_t)256 << 20) : (size_t)256 << 20);
     if (p->ig_dx.mt) p->ws_bytes = std::max(p->ws_bytes, ig_bwd_data_ws_bytes(p, p->ig_dx));
   } else if (!averaged && p->d.dtype == ROTCONV_F32 && p->d.R == 1 && p->fast[0] && p->opt.fwd_csplit == 0) {

@@ -111,7 +111,7 @@ def test_strides(cfg):
 
 # the fewest filters that the contraction takes, and the largest window
 FEWEST = [L(f"f{k}_{Cout}", N=2, Cin=17, H=24, W=20, Cout=Cout, R=4, k=k, stride=1, pad=k // 2, seed=2490 + i, x_dist="normal")
-          for i, (k, Cout) in enumerate([(2, 9), (5, 9), (15, 12)])]
+          for i, (k, Cout) in enumerate([(2, 9), (5, 8), (15, 12)])]
 
 
 @pytest.mark.parametrize("cfg", FEWEST, ids=[c.name for c in FEWEST])

@@ -116,8 +116,9 @@ def test_forward_of_few_filters_and_sparse_pixels():
 
 def test_input_gradient_of_few_filters_and_sparse_pixels():
     taken = one_contraction(1)
-    assert [taken(4, 59, 198, 105, c, 5) for c in (1, 3, 8, 9, 16)] == [False, False, False, True, True]
-    assert [taken(1, 30, 30, 30, c, 7, stride=2) for c in (4, 8, 9)] == [False, False, True]
+    assert [taken(4, 59, 198, 105, c, 5) for c in (1, 3, 7, 8, 16)] == [False, False, False, True, True]
+    assert [taken(4, 59, 98, 105, c, 2) for c in (1, 8, 9)] == [False, False, True]
+    assert [taken(1, 30, 30, 30, c, 7, stride=2) for c in (4, 7, 8)] == [False, False, True]
     assert [taken(8, 235, 180, 81, c, 1, stride=4) for c in (14, 24, 25)] == [False, False, True]
     assert taken(1, 235, 180, 81, 14, 1, stride=4) and taken(8, 235, 180, 81, 14, 2, stride=2)
 
